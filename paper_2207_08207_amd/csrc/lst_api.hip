@@ -147,10 +147,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.md_hits = I2(md); t.md_mod = I(md); t.md_pos = F4(md); t.md_stub = F2(md); t.mod_disc = F4(M);
   t.ls_cnt = I(md + 1); t.ls_off = I(md + 1); t.ls_md = I2(ls); t.ls_beta = F2(ls); t.ls_opos = F4(ls); t.ls_oinf = I(ls);
   t.ls_cache = I(kLsCache * md);
-  t.ls_ovf_flag = I(md + 1); t.ls_ovf_off = I(md + 1); t.ls_ovf = I(md);
-  t.t3_cnt = I(ls + 1); t.t3_off = I(ls + 1); t.t3_md = I4(t3); t.t3_attr = F4(t3); t.t3_first = F2(t3);
+  t.ls_ovf = I(md);
+  t.t3_off = I(ls + 1); t.ws_t3 = I((ls >> 6) + 1); t.t3_md = I4(t3); t.t3_attr = F4(t3); t.t3_first = F2(t3);
   t.t3_cache = I(kT3Cache * ls); t.t5_cache = I(kT5Cache * t3);
-  t.t5_cnt = I(t3 + 1); t.t5_off = I(t3 + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
+  t.t5_off = I(t3 + 1); t.ws_t5 = I((t3 >> 6) + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
   t.t5_keep = I(t5); t.t5_first = F2(t5);
   t.inc_cnt = I(md + 1); t.inc_off = I(md + 1); t.inc_cur = I(md + 1); t.inc_list = I2(5 * t5);
   t.pls = F(8 * S); t.pls_keep = I(S); t.seed_order = I(S + 1);
@@ -177,6 +177,13 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.ext_n = I(tc); t.ext_t3 = I(tc); t.ext_cnt = I(tc + 1); t.ext_off = I(tc + 1); t.ext_hits = I(18 * tc);
   t.ext_attr = F4(tc);
   t.scan_tmp = I(4096);
+  // the tile sums, one after another (cleared together)
+  const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
+  const long n_ts = (nl + n3 + n5 + 2 * np) * kSumStride;
+  t.ts_ls = I(n_ts);
+  t.ts_t3 = t.ts_ls + nl * kSumStride; t.ts_t5 = t.ts_t3 + n3 * kSumStride;
+  t.ts_p3 = t.ts_t5 + n5 * kSumStride; t.ts_p5 = t.ts_p3 + np * kSumStride;
+  t.sh_ls = tile_shift(md); t.sh_t3 = tile_shift(ls); t.sh_t5 = tile_shift(t3); t.sh_pt = tile_shift(S);
 #undef I
 #undef F
 #undef I2
@@ -196,20 +203,14 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
     const long nt_cap = (long)n_coarse((int)M) * n_hit_tiles(n_hits_alloc >= 0 ? n_hits_alloc : n_hits);
     sj(SC_HITS, t.tile_hist, t.tile_off, nullptr, nt, nt_cap, ct + C_NOUTER, nullptr, 0);
     sj(SC_MD, t.md_cnt, t.md_off, nullptr, M, M, ct + C_RMD, ct + C_NMD, md);
-    sj(SC_LS, t.ls_cnt, t.ls_off, ct + C_NMD, 0, md, ct + C_RLS, ct + C_NLS, ls);
-    sj(SC_T3, t.t3_cnt, t.t3_off, ct + C_NLS, 0, ls, ct + C_RT3, ct + C_NT3, t3);
-    sj(SC_T5, t.t5_cnt, t.t5_off, ct + C_NT3, 0, t3, ct + C_RT5, ct + C_NT5, t5);
     sj(SC_INC, t.inc_cnt, t.inc_off, ct + C_NMD, 0, md, ct + C_NINC, nullptr, 0);
     sj(SC_PH, t.ph_cnt, t.ph_off, nullptr, N, N, ct + C_NPH, nullptr, 0);
-    sj(SC_PT3, t.pt3_cnt, t.pt3_off, nullptr, S, S, ct + C_RPT3, ct + C_NPT3, p3);
-    sj(SC_PT5, t.pt5_cnt, t.pt5_off, nullptr, S, S, ct + C_RPT5, ct + C_NPT5, p5);
     sj(SC_F5, t.f_pt5, t.p_pt5, ct + C_NPT5, 0, p5, ct + C_NTC0, nullptr, 0);
     sj(SC_F3, t.f_pt3, t.p_pt3, ct + C_NPT3, 0, p3, ct + C_NTC1, nullptr, 0);
     sj(SC_FT5, t.f_t5, t.p_t5, ct + C_NT5, 0, t5, ct + C_NTC2, nullptr, 0);
     sj(SC_FPLS, t.f_pls, t.p_pls, nullptr, S, S, ct + C_NTC3, nullptr, 0);
     sj(SC_B3, t.b3_cnt, t.b3_off, nullptr, nbins, nbins, ct + C_NB3, nullptr, 0);
     sj(SC_B5, t.b5_cnt, t.b5_off, nullptr, nbins, nbins, ct + C_NB5, nullptr, 0);
-    sj(SC_LSOVF, t.ls_ovf_flag, t.ls_ovf_off, ct + C_NMD, 0, md, ct + C_NLSOVF, nullptr, 0);
     sj(SC_EXT, t.ext_cnt, t.ext_off, ct + C_NTC, 0, p5 + p3 + t5 + S, ct + C_NEXTHITS, nullptr, 0);
     // arrays indexed by MDs, triplets or quintuplets are cleared up to the built count
     // (the clears run after it is known), not the capacity
@@ -217,12 +218,11 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
       t.fills[id] = FillJob{p, n, n_dev, mul};
     };
     fj(FL_CTR, ct, C_COUNT);
+    fj(FL_TS, t.ts_ls, n_ts);
     fj(FL_INC_CNT, t.inc_cnt, md + 1, ct + C_NMD);
     fj(FL_INC_CUR, t.inc_cur, md + 1, ct + C_NMD);
     fj(FL_PH_CNT, t.ph_cnt, N + 1);
     fj(FL_PH_CUR, t.ph_cur, N + 1);
-    fj(FL_O3_BEST, reinterpret_cast<int *>(t.o3_best), 2 * (t3 + 1), ct + C_NT3, 2);
-    fj(FL_O5_BEST, reinterpret_cast<int *>(t.o5_best), 2 * (t5 + 1), ct + C_NT5, 2);
     fj(FL_SEED_USED, t.seed_used, S + 1);
     fj(FL_T5_USED, t.t5_used, t5 + 1, ct + C_NT5);
     fj(FL_B3_CNT, t.b3_cnt, nbins + 1);

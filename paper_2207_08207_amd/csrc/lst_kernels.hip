@@ -170,7 +170,6 @@ __global__ void k_scan_apply(const Ws *__restrict__ wb, int job) {
   }
 }
 
-// blocks for one wave per item (capped; kernels stride)
 // Blocks for n items, one wave per item (grid_waves) or one thread per item
 // (grid_for), at `block` threads per block; kernels stride over the rest.
 static inline int grid_waves(long n, int block = kBlock) {
@@ -204,6 +203,66 @@ static void scan(const Ws *wb, int B, int job, long n_cap, hipStream_t st) {
   const int nb = (int)std::min<long>(std::min<long>((n_cap + kScanTile) / kScanTile, kMaxScanBlocks), share);
   k_scan_reduce<<<dim3(nb, B), kBlock, 0, st>>>(wb, job);
   k_scan_apply<<<dim3(nb, B), kBlock, 0, st>>>(wb, job);
+}
+
+// ------------------------------------------------- offsets inside a fill pass
+// A stage's objects are counted per parent, then written at the exclusive
+// prefix of the counts.  The prefix of a wave's first parent is the sum of the
+// tile sums before its tile (added by the count pass, one atomic per wave) plus
+// the counts inside the tile before it, so the fill finds its own offsets and
+// the chain has no scan launches there: each cost about 5 us on one event, which
+// is launch and drain time and not work (the two-launch scans of the segment,
+// triplet, quintuplet and pixel stages were 0.06 ms of a 1.0 ms event).
+
+// Sum over the wave, in a scalar register.
+__device__ __forceinline__ int wave_total(int v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return __builtin_amdgcn_readfirstlane(v);
+}
+// Inclusive prefix of v over the wave's lanes.
+__device__ __forceinline__ int wave_inclusive(int v) {
+  const int lane = lane_id();
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(v, o, 64);
+    if (lane >= o) v += y;
+  }
+  return v;
+}
+// Prefix of the wave's parent p0: tile sums ts (2^sh parents each) before its
+// tile, then the sums `part` of 2^psh parents each (psh = 0: the counts
+// themselves) from the tile's start to p0.
+__device__ __forceinline__ int wave_prefix(const int *ts, int sh, const int *part, int psh, int p0) {
+  const int lane = lane_id();
+  const int T = p0 >> sh;
+  int v = 0;
+  for (int j = lane; j < T; j += 64) v += gp(ts)[j * kSumStride];
+  const int w1 = p0 >> psh;
+  for (int j = (T << (sh - psh)) + lane; j < w1; j += 64) v += gp(part)[j];
+  return wave_total(v);
+}
+// The same for a block (all its threads call it; p0 the block's first parent):
+// one read of the sums for its waves.  (With one per wave the fills of a launch
+// of eight events took 0.11 ms longer.)
+__device__ __forceinline__ int block_prefix(const int *ts, int sh, const int *part, int psh, int p0, int *s_red) {
+  const int T = p0 >> sh;
+  int v = 0;
+  for (int j = threadIdx.x; j < T; j += blockDim.x) v += gp(ts)[j * kSumStride];
+  const int w1 = p0 >> psh;
+  for (int j = (T << (sh - psh)) + (int)threadIdx.x; j < w1; j += blockDim.x) v += gp(part)[j];
+  v = wave_total(v);
+  const int wpb = blockDim.x >> 6;
+  __syncthreads();  // s_red may still be read by the previous call
+  if (lane_id() == 0) s_red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int t = 0;
+  for (int q = 0; q < wpb; ++q) t += s_red[q];
+  return __builtin_amdgcn_readfirstlane(t);
+}
+// The stage's total: required and built counts, the capacity flag.
+__device__ __forceinline__ void put_total(const Ws &w, int tot, int cap, int req, int built) {
+  w.ctr[req] = tot;
+  w.ctr[built] = tot < cap ? tot : cap;
+  if (tot > cap) atomicOr(w.ctr + C_STATUS, (int)ST_CAPACITY);
 }
 
 // ------------------------------------------------------------- windows
@@ -907,164 +966,6 @@ __device__ __forceinline__ void queue_pop64(int *qa, int rest) {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Fill pass of the segment search for the inner MDs with more segments than
-// the count pass cached (k_ls_copy writes the others and lists these densely):
-// one wave per inner MD a.  Its candidates -- the MDs of every module linked
-// to a's module, edge by edge -- are flattened into one list that the 64
-// lanes stride over, so a wave stays full even though each linked module
-// holds few MDs; candidates past the pre-tests, then past the pair pre-test,
-// are compacted in list order with ballot and mbcnt into two LDS queues, and
-// the full selection runs on full waves of the second.
-// Eight waves per SIMD (64 VGPRs; a few spill): the segment search is bound by
-// the latency of its dependent gathers, and more resident waves hide more of
-// it (measured 9% faster than the 77-VGPR, six-wave build; the same for the
-// triplet and quintuplet searches made them slower).
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_ls_fill(const Ws *__restrict__ wb,
-                                                                                             DevGeom g) {
-  const Ws &w = wb[blockIdx.y];
-  __shared__ int s_pre[kWaves][kMaxEdges + 1];  // running MD count before each edge
-  __shared__ int s_first[kWaves][kMaxEdges];    // first MD of each linked module
-  __shared__ int s_info[kWaves][kMaxEdges];
-  __shared__ float s_wmax[kWaves][kMaxEdges];   // window bound of each linked module
-  // candidates in order, as partner | module info << 30: past the candidate pre-tests
-  // (s_q) and past the pair pre-test as well (s_r)
-  __shared__ int s_q[kWaves][128], s_r[kWaves][128];
-  const int n_md = uload(w.ctr + C_NMD);
-  const int wv = wave_id(), lane = lane_id();
-  const int wpb = blockDim.x >> 6;  // waves per block (a tuned launch may run fewer than kWaves)
-  const int waves_total = gridDim.x * wpb;
-  auto process = [&](const int a) {
-    const int ma = gp(w.md_mod)[a];
-    const float4 A = gload(w.md_pos, a);
-    const float2 sa = get_stub(w, g, a);
-    const ModInfo mia{gp(g.info)[ma]};
-    const int e0 = gp(g.map_off)[ma];
-    const int ne = gp(g.map_off)[ma + 1] - e0;  // <= kMaxEdges, checked when the geometry is loaded
-    // per-edge MD ranges and their exclusive prefix over the wave
-    int run = 0;
-    for (int k0 = 0; k0 < ne; k0 += 64) {
-      const int k = k0 + lane;
-      int first = 0, cnt = 0, info = 0;
-      float wm = 0.0f;
-      if (k < ne) {
-        const int mb = gp(g.map_tgt)[e0 + k];
-        first = gp(w.md_off)[mb];
-        const int last = min(w.md_off[mb + 1], n_md);
-        cnt = last > first ? last - first : 0;
-        info = gp(g.info)[mb];
-        if (cnt > 0) {
-          const float4 disc = gload(w.mod_disc, mb);
-          wm = ls_window_bound(A, mia, disc, ModInfo{info}, g.d0max);
-          if (!ls_module_may_pass(A, disc, wm)) cnt = 0;
-        }
-      }
-      int x = cnt;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-      }
-      if (k < ne) {
-        s_pre[wv][k] = run + x - cnt;
-        s_first[wv][k] = first;
-        s_info[wv][k] = info;
-        s_wmax[wv][k] = wm;
-      }
-      run += __shfl(x, 63, 64);
-    }
-    if (lane == 0) s_pre[wv][ne] = run;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const int total = run;
-    int out = gp(w.ls_off)[a];
-    // the pair pre-test on the first n candidates of s_q (n <= 64); the passing ones join s_r
-    int nr = 0;
-    auto sift = [&](int n) {
-      bool ok = false;
-      int e = 0;
-      if (lane < n) {
-        e = s_q[wv][lane];
-        const int b = e & 0x3fffffff;
-        ok = ls_pair_may_pass(A, gload(w.md_pos, b), get_stub(w, g, b), mia, ModInfo{(int)((unsigned)e >> 30)},
-                              g.d0max);
-      }
-      const unsigned long long m = __ballot(ok);
-      if (ok) s_r[wv][nr + lanes_below(m)] = e;
-      nr += __popcll(m);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    };
-    // the full selection on the first n candidates of s_r (n <= 64), in candidate order
-    auto select = [&](int n) {
-      bool pass = false;
-      int b = 0, info = 0;
-      float2 beta = make_float2(0.f, 0.f);
-      if (lane < n) {
-        const int e = s_r[wv][lane];
-        b = e & 0x3fffffff;
-        info = (int)((unsigned)e >> 30);
-        pass = ls_pass(A, gload(w.md_pos, b), sa, get_stub(w, g, b), mia, ModInfo{info}, &beta, g.d0max);
-      }
-      const unsigned long long m = __ballot(pass);
-      const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-      const int pos = out + pre;
-      if (pass && pos < w.cap_ls) {
-        gstore(w.ls_md, pos, make_int2(a, b));
-        gstore(w.ls_beta, pos, beta);
-        gstore(w.ls_opos, pos, gload(w.md_pos, b));
-        gp(w.ls_oinf)[pos] = info;
-      }
-      out += __popcll(m);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    };
-    // candidates past the azimuth pre-tests and the inner MD's own stub check (both
-    // necessary conditions of ls_pass) are queued in LDS, and the full selection runs
-    // on full waves of them
-    int nq = 0;
-    int e = 0;  // edge of this lane's candidate (candidates advance monotonically)
-    for (int c0 = 0; c0 < total; c0 += 64) {
-      const int c = c0 + lane;
-      bool keep = false;
-      int b = 0, info = 0;
-      if (c < total) {
-        while (s_pre[wv][e + 1] <= c) ++e;
-        b = s_first[wv][e] + (c - s_pre[wv][e]);
-        const float4 Bp = gload(w.md_pos, b);
-        info = s_info[wv][e];
-        keep = ls_window_may_pass(A, Bp, s_wmax[wv][e]) &&
-               ls_inner_stub_may_pass(A, Bp, sa, mia, ModInfo{info}, g.d0max);
-      }
-      const unsigned long long m = __ballot(keep);
-      const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-      if (keep) s_q[wv][nq + pre] = b | (info << 30);
-      nq += __popcll(m);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      // each queue holds < 64 entries before a round adds at most 64
-      if (nq >= 64) {
-        sift(64);
-        queue_pop64(s_q[wv], nq - 64);
-        nq -= 64;
-        if (nr >= 64) {
-          select(64);
-          queue_pop64(s_r[wv], nr - 64);
-          nr -= 64;
-        }
-      }
-    }
-    if (nq > 0) sift(nq);
-    while (nr > 0) {
-      const int n2 = nr < 64 ? nr : 64;
-      select(n2);
-      queue_pop64(s_r[wv], nr - n2);
-      nr -= n2;
-    }
-  };
-  const int n_ovf = uload(w.ctr + C_NLSOVF);
-  for (int k = blockIdx.x * wpb + wv; k < n_ovf; k += waves_total) process(w.ls_ovf[k]);
-}
-
-
 // Count pass of the segment search: one wave per group of up to kLsGroup
 // consecutive inner MDs, taken in chunks of MDs of one module whose (inner MD,
 // linked module) pairs are flattened over the lanes.  Each candidate goes
@@ -1307,13 +1208,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       }
       k0 = k1;
     }
-    if (lane < na) {
-      const int c = s_cnt[wv][lane];
-      gp(w.ls_cnt)[a0 + lane] = c;
-      gp(w.ls_ovf_flag)[a0 + lane] = c > keep ? 1 : 0;
-    }
+    if (lane < na) gp(w.ls_cnt)[a0 + lane] = s_cnt[wv][lane];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Segments per tile of MDs (2^sh_ls of them), for the offsets of the fill, and
+// the list of the MDs with more segments than the count pass caches (428 of
+// 138k on a PU200 event), which the fill searches again.  The count pass does
+// not do this itself: an atomic per group of MDs there delays the wave's next
+// gathers until it is done (the count 0.119 -> 0.130 ms for one event, 0.88 ->
+// 0.93 ms for eight), more than this launch takes.
+__global__ void k_ls_sums(const Ws *__restrict__ wb, int keep) {
+  __shared__ int s_red[kWaves];
+  const Ws &w = wb[blockIdx.y];
+  const int n = uload(w.ctr + C_NMD), sh = w.sh_ls;
+  for (int t = blockIdx.x; (t << sh) < n; t += gridDim.x) {
+    const int j1 = min((t + 1) << sh, n);
+    int v = 0;
+    for (int j = (t << sh) + (int)threadIdx.x; j < j1; j += kBlock) {
+      const int c = gp(w.ls_cnt)[j];
+      v += c;
+      if (c > keep) gp(w.ls_ovf)[atomicAdd(w.ctr + C_NLSOVF, 1)] = j;
+    }
+    v = block_sum(v, s_red);
+    if (threadIdx.x == 0) w.ts_ls[t * kSumStride] = v;
   }
 }
 
@@ -1370,34 +1290,214 @@ __device__ __forceinline__ int round_parent(int start, int n, int c0, int *mark,
   return e;
 }
 
-// Segments of the MDs whose partners the count pass cached: one thread per
-// (MD, cache slot), in candidate order, with the angles ls_pass reports.
-// kLsCopyLanes threads per MD take slots k, k + kLsCopyLanes, ... (most MDs
-// have few segments).
-constexpr int kLsCopyLanes = 8;
-__global__ void k_ls_copy(const Ws *__restrict__ wb, int keep) {
+// Fill pass of the segment search.  Blocks [0, n_copy) write the segments of
+// the inner MDs whose partners the count pass cached: a wave takes kLsCopyMds
+// consecutive MDs, finds their offsets (wave_prefix) and strides over their
+// segments flattened, in candidate order, with the angles ls_pass reports.
+// The other blocks search again for the MDs with more segments than the cache
+// holds (listed by the count pass), one wave per inner MD a.  Its candidates
+// -- the MDs of every module linked to a's module, edge by edge -- are
+// flattened into one list that the 64 lanes stride over, so a wave stays full
+// even though each linked module holds few MDs; candidates past the pre-tests,
+// then past the pair pre-test, are compacted in list order with ballot and
+// mbcnt into two LDS queues, and the full selection runs on full waves of the
+// second.
+// Eight waves per SIMD (64 VGPRs; a few spill): the segment search is bound by
+// the latency of its dependent gathers, and more resident waves hide more of
+// it (measured 9% faster than the 77-VGPR, six-wave build; the same for the
+// triplet and quintuplet searches made them slower).
+constexpr int kLsCopyMds = 32;
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_ls_fill(
+    const Ws *__restrict__ wb, DevGeom g, int n_copy) {
   const Ws &w = wb[blockIdx.y];
-  const long n = (long)uload(w.ctr + C_NMD) * kLsCopyLanes;
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const int a = (int)(i / kLsCopyLanes), k0 = (int)(i % kLsCopyLanes);
-    const int cnt = gp(w.ls_cnt)[a];
-    if (cnt > keep) {
-      if (k0 == 0) gp(w.ls_ovf)[gp(w.ls_ovf_off)[a]] = a;  // searched again by k_ls_fill
-      continue;
+  __shared__ int s_pre[kWaves][kMaxEdges + 1];  // running MD count before each edge
+  __shared__ int s_first[kWaves][kMaxEdges];    // first MD of each linked module
+  __shared__ int s_info[kWaves][kMaxEdges];
+  __shared__ float s_wmax[kWaves][kMaxEdges];   // window bound of each linked module
+  // candidates in order, as partner | module info << 30: past the candidate pre-tests
+  // (s_q) and past the pair pre-test as well (s_r)
+  __shared__ int s_q[kWaves][128], s_r[kWaves][128];
+  __shared__ int s_red[kWaves];
+  const int n_md = uload(w.ctr + C_NMD);
+  const int wv = wave_id(), lane = lane_id();
+  const int wpb = blockDim.x >> 6;  // waves per block (a tuned launch may run fewer than kWaves)
+  if ((int)blockIdx.x < n_copy) {
+    const int keep = g.tiles.ls_cache;
+    int *s_seg = s_pre[wv], *s_off = s_first[wv], *s_mark = s_q[wv];  // 65 / 64 / 64 entries
+    const int per = wpb * kLsCopyMds;  // the block's MDs (in one tile)
+    for (int b0 = (int)blockIdx.x * per; b0 < n_md; b0 += n_copy * per) {
+      const int a0 = b0 + wv * kLsCopyMds, a = a0 + lane;
+      const bool mine = lane < kLsCopyMds && a < n_md;
+      const int cnt = mine ? gp(w.ls_cnt)[a] : 0;
+      int before = 0;  // the block's MDs on earlier waves
+      for (int j = b0 + lane; j < min(a0, n_md); j += 64) before += gp(w.ls_cnt)[j];
+      const int off = block_prefix(w.ts_ls, w.sh_ls, w.ls_cnt, 0, b0, s_red) + wave_total(before) +
+                      wave_inclusive(cnt) - cnt;
+      if (mine) {
+        gp(w.ls_off)[a] = off;
+        if (a == n_md - 1) {
+          gp(w.ls_off)[n_md] = off + cnt;
+          put_total(w, off + cnt, w.cap_ls, C_RLS, C_NLS);
+        }
+      }
+      s_off[lane] = off;
+      const int n = cnt <= keep ? cnt : 0;  // the others are searched again below
+      const int total = wave_segments(n, s_seg);
+      const int start = s_seg[lane];
+      int carry = 0;
+      for (int c0 = 0; c0 < total; c0 += 64) {
+        const int c = c0 + lane;
+        const int e = round_parent(start, n, c0, s_mark, carry);
+        if (c < total) {
+          const int k = c - s_seg[e], pos = s_off[e] + k;
+          if (pos < w.cap_ls) {
+            const int v = gp(w.ls_cache)[(long)(a0 + e) * kLsCache + k];
+            const int b = v & 0x3fffffff;
+            const float4 B = gload(w.md_pos, b);
+            gstore(w.ls_md, pos, make_int2(a0 + e, b));
+            gstore(w.ls_beta, pos, ls_beta(gload(w.md_pos, a0 + e), B));
+            gstore(w.ls_opos, pos, B);
+            gp(w.ls_oinf)[pos] = (int)((unsigned)v >> 30);
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    for (int k = k0; k < cnt; k += kLsCopyLanes) {
-      const int pos = gp(w.ls_off)[a] + k;
-      if (pos >= w.cap_ls) break;
-      const int e = gp(w.ls_cache)[(long)a * kLsCache + k];
-      const int b = e & 0x3fffffff;
-      const float4 B = gload(w.md_pos, b);
-      gstore(w.ls_md, pos, make_int2(a, b));
-      gstore(w.ls_beta, pos, ls_beta(gload(w.md_pos, a), B));
-      gstore(w.ls_opos, pos, B);
-      gp(w.ls_oinf)[pos] = (int)((unsigned)e >> 30);
-    }
+    return;
   }
+  auto process = [&](const int a) {
+    const int ma = gp(w.md_mod)[a];
+    const float4 A = gload(w.md_pos, a);
+    const float2 sa = get_stub(w, g, a);
+    const ModInfo mia{gp(g.info)[ma]};
+    const int e0 = gp(g.map_off)[ma];
+    const int ne = gp(g.map_off)[ma + 1] - e0;  // <= kMaxEdges, checked when the geometry is loaded
+    // per-edge MD ranges and their exclusive prefix over the wave
+    int run = 0;
+    for (int k0 = 0; k0 < ne; k0 += 64) {
+      const int k = k0 + lane;
+      int first = 0, cnt = 0, info = 0;
+      float wm = 0.0f;
+      if (k < ne) {
+        const int mb = gp(g.map_tgt)[e0 + k];
+        first = gp(w.md_off)[mb];
+        const int last = min(w.md_off[mb + 1], n_md);
+        cnt = last > first ? last - first : 0;
+        info = gp(g.info)[mb];
+        if (cnt > 0) {
+          const float4 disc = gload(w.mod_disc, mb);
+          wm = ls_window_bound(A, mia, disc, ModInfo{info}, g.d0max);
+          if (!ls_module_may_pass(A, disc, wm)) cnt = 0;
+        }
+      }
+      int x = cnt;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (k < ne) {
+        s_pre[wv][k] = run + x - cnt;
+        s_first[wv][k] = first;
+        s_info[wv][k] = info;
+        s_wmax[wv][k] = wm;
+      }
+      run += __shfl(x, 63, 64);
+    }
+    if (lane == 0) s_pre[wv][ne] = run;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int total = run;
+    int out = wave_prefix(w.ts_ls, w.sh_ls, w.ls_cnt, 0, a);
+    // the pair pre-test on the first n candidates of s_q (n <= 64); the passing ones join s_r
+    int nr = 0;
+    auto sift = [&](int n) {
+      bool ok = false;
+      int e = 0;
+      if (lane < n) {
+        e = s_q[wv][lane];
+        const int b = e & 0x3fffffff;
+        ok = ls_pair_may_pass(A, gload(w.md_pos, b), get_stub(w, g, b), mia, ModInfo{(int)((unsigned)e >> 30)},
+                              g.d0max);
+      }
+      const unsigned long long m = __ballot(ok);
+      if (ok) s_r[wv][nr + lanes_below(m)] = e;
+      nr += __popcll(m);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    // the full selection on the first n candidates of s_r (n <= 64), in candidate order
+    auto select = [&](int n) {
+      bool pass = false;
+      int b = 0, info = 0;
+      float2 beta = make_float2(0.f, 0.f);
+      if (lane < n) {
+        const int e = s_r[wv][lane];
+        b = e & 0x3fffffff;
+        info = (int)((unsigned)e >> 30);
+        pass = ls_pass(A, gload(w.md_pos, b), sa, get_stub(w, g, b), mia, ModInfo{info}, &beta, g.d0max);
+      }
+      const unsigned long long m = __ballot(pass);
+      const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+      const int pos = out + pre;
+      if (pass && pos < w.cap_ls) {
+        gstore(w.ls_md, pos, make_int2(a, b));
+        gstore(w.ls_beta, pos, beta);
+        gstore(w.ls_opos, pos, gload(w.md_pos, b));
+        gp(w.ls_oinf)[pos] = info;
+      }
+      out += __popcll(m);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    // candidates past the azimuth pre-tests and the inner MD's own stub check (both
+    // necessary conditions of ls_pass) are queued in LDS, and the full selection runs
+    // on full waves of them
+    int nq = 0;
+    int e = 0;  // edge of this lane's candidate (candidates advance monotonically)
+    for (int c0 = 0; c0 < total; c0 += 64) {
+      const int c = c0 + lane;
+      bool keep = false;
+      int b = 0, info = 0;
+      if (c < total) {
+        while (s_pre[wv][e + 1] <= c) ++e;
+        b = s_first[wv][e] + (c - s_pre[wv][e]);
+        const float4 Bp = gload(w.md_pos, b);
+        info = s_info[wv][e];
+        keep = ls_window_may_pass(A, Bp, s_wmax[wv][e]) &&
+               ls_inner_stub_may_pass(A, Bp, sa, mia, ModInfo{info}, g.d0max);
+      }
+      const unsigned long long m = __ballot(keep);
+      const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+      if (keep) s_q[wv][nq + pre] = b | (info << 30);
+      nq += __popcll(m);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // each queue holds < 64 entries before a round adds at most 64
+      if (nq >= 64) {
+        sift(64);
+        queue_pop64(s_q[wv], nq - 64);
+        nq -= 64;
+        if (nr >= 64) {
+          select(64);
+          queue_pop64(s_r[wv], nr - 64);
+          nr -= 64;
+        }
+      }
+    }
+    if (nq > 0) sift(nq);
+    while (nr > 0) {
+      const int n2 = nr < 64 ? nr : 64;
+      select(n2);
+      queue_pop64(s_r[wv], nr - n2);
+      nr -= n2;
+    }
+  };
+  const int n_ovf = uload(w.ctr + C_NLSOVF);
+  const int stride = ((int)gridDim.x - n_copy) * wpb;
+  for (int k = ((int)blockIdx.x - n_copy) * wpb + wv; k < n_ovf; k += stride) process(uload(w.ls_ovf + k));
 }
+
 
 // ------------------------------------------------------------- a3: T3
 // Parents: segments (a, b); candidates: the segments whose inner MD is b.
@@ -1447,14 +1547,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
   __shared__ int s_mi[kWaves][64], s_lo[kWaves][64], s_cnt[kWaves][64], s_seg[kWaves][65], s_cached[kWaves][64];
   __shared__ int s_qe[kWaves][128], s_qc[kWaves][128];  // pairs past the pre-test, in pair order
   __shared__ int s_mark[kWaves][64];
+  __shared__ int s_off[FILL ? kWaves : 1][64], s_red[kWaves];  // the parents' offsets
   const int n_ls = uload(w.ctr + C_NLS);
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;
-  for (long p0 = ((long)blockIdx.x * wpb + wv) * 64; p0 < n_ls; p0 += (long)gridDim.x * wpb * 64) {
+  if (FILL && n_ls == 0 && blockIdx.x == 0 && threadIdx.x == 0) w.t3_off[0] = 0;
+  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_ls; b0 += (long)gridDim.x * wpb * 64) {
+    const long p0 = b0 + wv * 64;
+    if (!FILL && p0 >= n_ls) break;  // (the fill's waves share their block's prefix)
     const int l1 = (int)p0 + lane;
-    int n = 0, cached = 0;
+    int n = 0, cached = 0, n_mine = 0;
+    if (FILL) {  // the parents' offsets, in place of their counts
+      n_mine = l1 < n_ls ? gp(w.t3_off)[l1] : 0;
+      int off = block_prefix(w.ts_t3, w.sh_t3, w.ws_t3, 6, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
+      for (long q = b0; q < p0 && q < n_ls; q += 64) off += uload(w.ws_t3 + (q >> 6));
+      s_off[wv][lane] = off;
+      if (l1 < n_ls) gp(w.t3_off)[l1] = off;
+      if (l1 == n_ls - 1) {
+        gp(w.t3_off)[n_ls] = off + n_mine;
+        put_total(w, off + n_mine, w.cap_t3, C_RT3, C_NT3);
+      }
+    }
     // the fill reads a parent's data only if the count pass found a triplet on it
-    if (l1 < n_ls && (!FILL || gp(w.t3_cnt)[l1] > 0)) {
+    if (l1 < n_ls && (!FILL || n_mine > 0)) {
       const int2 ab = gload(w.ls_md, l1);
       s_a[wv][lane] = gload(w.md_pos, ab.x);
       s_b[wv][lane] = gload(w.ls_opos, l1);
@@ -1462,12 +1577,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
       const int lo = gp(w.ls_off)[ab.y], hi = min(gp(w.ls_off)[ab.y + 1], n_ls);
       s_lo[wv][lane] = lo;
       n = hi > lo ? hi - lo : 0;
-      if (FILL) {
-        const int cnt = gp(w.t3_cnt)[l1];
-        if (cnt <= g.tiles.t3_cache) {  // the count pass kept them all: only those are tested again
-          n = cnt;
-          cached = 1;
-        }
+      if (FILL && n_mine <= g.tiles.t3_cache) {  // the count pass kept them all: only those are tested again
+        n = n_mine;
+        cached = 1;
       }
     }
     s_cnt[wv][lane] = 0;
@@ -1494,12 +1606,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
         if (!FILL) {
           if (r < g.tiles.t3_cache) gp(w.t3_cache)[(long)((int)p0 + e) * kT3Cache + r] = cand;
         } else {
-          const int pos = gp(w.t3_off)[(int)p0 + e] + r;
+          const int pos = s_off[wv][e] + r;
           if (pos < w.cap_t3) {
             const int2 ab = gload(w.ls_md, (int)p0 + e);
             gstore(w.t3_md, pos, make_int4(ab.x, ab.y, cmd, (int)p0 + e));
             gstore(w.t3_attr, pos, attr);
             gstore(w.t3_first, pos, make_float2(s_a[wv][e].x, s_a[wv][e].y));
+            gstore(w.o3_best, pos, 0ull);
           }
         }
       }
@@ -1553,7 +1666,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
       }
     }
     if (nq > 0) select(nq);
-    if (!FILL && l1 < n_ls) gp(w.t3_cnt)[l1] = s_cnt[wv][lane];
+    if (!FILL) {
+      const int c = l1 < n_ls ? s_cnt[wv][lane] : 0;
+      if (l1 < n_ls) gp(w.t3_off)[l1] = c;
+      const int sum = wave_total(c);
+      if (lane == 0) {
+        gp(w.ws_t3)[p0 >> 6] = sum;
+        if (sum > 0) atomicAdd(w.ts_t3 + (p0 >> w.sh_t3) * kSumStride, sum);
+      }
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
@@ -1585,15 +1706,30 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
   __shared__ float4 s_p[kWaves][3][64], s_tin[kWaves][64];
   __shared__ int s_mi[kWaves][64], s_lo[kWaves][64], s_cnt[kWaves][64], s_seg[kWaves][65], s_cached[kWaves][64];
   __shared__ int s_qe[kWaves][128], s_qc[kWaves][128];  // pairs past the pre-test, in pair order
+  __shared__ int s_off[FILL ? kWaves : 1][64], s_red[kWaves];  // the parents' offsets
   const int n_t3 = uload(w.ctr + C_NT3);
   const int n_ls = uload(w.ctr + C_NLS);
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;
-  for (long p0 = ((long)blockIdx.x * wpb + wv) * 64; p0 < n_t3; p0 += (long)gridDim.x * wpb * 64) {
+  if (FILL && n_t3 == 0 && blockIdx.x == 0 && threadIdx.x == 0) w.t5_off[0] = 0;
+  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_t3; b0 += (long)gridDim.x * wpb * 64) {
+    const long p0 = b0 + wv * 64;
+    if (!FILL && p0 >= n_t3) break;
     const int t1 = (int)p0 + lane;
-    int n = 0, cached = 0;
+    int n = 0, cached = 0, n_mine = 0;
+    if (FILL) {  // the parents' offsets, in place of their counts
+      n_mine = t1 < n_t3 ? gp(w.t5_off)[t1] : 0;
+      int off = block_prefix(w.ts_t5, w.sh_t5, w.ws_t5, 6, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
+      for (long q = b0; q < p0 && q < n_t3; q += 64) off += uload(w.ws_t5 + (q >> 6));
+      s_off[wv][lane] = off;
+      if (t1 < n_t3) gp(w.t5_off)[t1] = off;
+      if (t1 == n_t3 - 1) {
+        gp(w.t5_off)[n_t3] = off + n_mine;
+        put_total(w, off + n_mine, w.cap_t5, C_RT5, C_NT5);
+      }
+    }
     // the fill reads a parent's data only if the count pass found a quintuplet on it
-    if (t1 < n_t3 && (!FILL || gp(w.t5_cnt)[t1] > 0)) {
+    if (t1 < n_t3 && (!FILL || n_mine > 0)) {
       const int4 abc = gload(w.t3_md, t1);
       s_p[wv][0][lane] = gload(w.md_pos, abc.x);
       s_p[wv][1][lane] = gload(w.md_pos, abc.y);
@@ -1605,12 +1741,9 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
       const int lo = gp(w.t3_off)[lsb], hi = min(w.t3_off[lse], n_t3);
       s_lo[wv][lane] = lo;
       n = hi > lo ? hi - lo : 0;
-      if (FILL) {
-        const int cnt = gp(w.t5_cnt)[t1];
-        if (cnt <= g.tiles.t5_cache) {  // the count pass kept them all: only those are tested again
-          n = cnt;
-          cached = 1;
-        }
+      if (FILL && n_mine <= g.tiles.t5_cache) {  // the count pass kept them all: only those are tested again
+        n = n_mine;
+        cached = 1;
       }
     }
     s_cnt[wv][lane] = 0;
@@ -1645,7 +1778,7 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
           if (r < g.tiles.t5_cache) gp(w.t5_cache)[(long)((int)p0 + e) * kT5Cache + r] = t2;
         } else {
           const int t1e = (int)p0 + e;
-          const int pos = gp(w.t5_off)[t1e] + r;
+          const int pos = s_off[wv][e] + r;
           if (pos < w.cap_t5) {
             const int4 abc = gload(w.t3_md, t1e);
             gstore(w.t5_t3, pos, make_int2(t1e, t2));
@@ -1655,6 +1788,7 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
 #pragma unroll
             for (int k = 0; k < 8; ++k) dst[k] = at[k];
             gp(w.t5_keep)[pos] = 1;  // until a better duplicate is found
+            gstore(w.o5_best, pos, 0ull);
           }
         }
       }
@@ -1713,7 +1847,15 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
       }
     }
     if (nq > 0) select(nq);
-    if (!FILL && t1 < n_t3) gp(w.t5_cnt)[t1] = s_cnt[wv][lane];
+    if (!FILL) {
+      const int c = t1 < n_t3 ? s_cnt[wv][lane] : 0;
+      if (t1 < n_t3) gp(w.t5_off)[t1] = c;
+      const int sum = wave_total(c);
+      if (lane == 0) {
+        gp(w.ws_t5)[p0 >> 6] = sum;
+        if (sum > 0) atomicAdd(w.ts_t5 + (p0 >> w.sh_t5) * kSumStride, sum);
+      }
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
@@ -2126,6 +2268,14 @@ __device__ __forceinline__ int2 seed_zbins(const Seed &sd, float lo, float hi) {
   return make_int2(zbin_of(fminf(za, zb) - zw), zbin_of(fmaxf(za, zb) + zw));
 }
 
+// The key that orders a pT entry for the same-object rule: smaller (score,
+// seed) is better, and since scores are >= 0 their bits order them as
+// integers; complemented so that the best is the largest, found with an
+// atomic maximum per outer object (a value, not a position: order-independent).
+__device__ __forceinline__ unsigned long long pt_obj_key(float score, int seed) {
+  return ~(((unsigned long long)__float_as_uint(score) << 32) | (unsigned long long)(unsigned)seed);
+}
+
 // One wave per seed over the objects of the bins its trajectory can reach.
 // COUNT: number of passing objects.  FILL: passing object indices gathered in
 // LDS, ranked by object index, written at the seed's offset in object order
@@ -2135,8 +2285,11 @@ __device__ __forceinline__ int2 seed_zbins(const Seed &sd, float lo, float hi) {
 // passing objects per seed with their attributes, which the fill then ranks
 // and copies; more than max_slices marked bins are searched bin by bin.
 // (Seven waves per SIMD for the count: at most 72 VGPRs, no spills.)
-template <int K, bool FILL, bool BOTH = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_pt_binned(const Ws *__restrict__ wb, DevGeom g) {
+// The count pass searches both kinds on one mask per seed; the fill's first
+// n3 blocks take the triplets, the others the quintuplets.
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_pt_binned(const Ws *__restrict__ wb,
+                                                                                              DevGeom g, int n3) {
   __shared__ unsigned s_mask[kWaves][kMaskWords];
   __shared__ int s_slo[kWaves][kRings], s_shi[kWaves][kRings];
   __shared__ int2 s_zb[kWaves][kRings];
@@ -2147,53 +2300,39 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
   __shared__ int s_mark[kWaves][64];  // a slice's candidates start here (this round)
   const Ws &w = wb[blockIdx.y];
   const int wv = wave_id(), lane = lane_id();
-  const int si = blockIdx.x * (int)(blockDim.x >> 6) + wv;
+  const bool five = FILL && (int)blockIdx.x >= n3;
+  const int si = ((int)blockIdx.x - (five ? n3 : 0)) * (int)(blockDim.x >> 6) + wv;
+  if (FILL && w.n_seeds == 0 && threadIdx.x == 0) (five ? w.pt5_off : w.pt3_off)[0] = 0;
+  int pre = 0;  // offset of the block's first seed in the fill, which takes the seeds in their order
+  if constexpr (FILL) {
+    __shared__ int s_red[kWaves];
+    pre = block_prefix(five ? w.ts_p5 : w.ts_p3, w.sh_pt, five ? w.pt5_cnt : w.pt3_cnt, 0,
+                       min(si - wv, w.n_seeds), s_red);
+  }
   if (si >= w.n_seeds) return;
-  const int s = uload(w.seed_order + si);  // seeds of one direction on neighbouring waves
+  // the count: seeds of one direction on neighbouring waves
+  const int s = FILL ? si : uload(w.seed_order + si);
   const Seed sd = load_seed(w, s);
-  constexpr int kCache = K == 3 ? kPt3Cache : kPt5Cache;
-  static_assert(kCache <= kPassList, "the fill ranks the cache in its LDS list");
-  const int keep = K == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;  // <= kCache
+  static_assert(kPt3Cache <= kPassList && kPt5Cache <= kPassList, "the fill ranks the cache in its LDS list");
   const int pass_list = g.tiles.pass_list;                            // <= kPassList
   const int max_slices = g.tiles.max_slices;                          // <= kMaxSlices
-  int *cache = (K == 3 ? w.pt3_cache : w.pt5_cache) + (long)s * kCache;
-  float4 *cattr = (K == 3 ? w.pt3_cattr : w.pt5_cattr) + (long)s * kCache;
-  if constexpr (FILL) {
-    // the count pass cached every passing object of this seed with its attributes:
-    // rank them by object index (in LDS) and copy, no search
-    const int expect = (K == 3 ? w.pt3_cnt : w.pt5_cnt)[s];
-    if (expect <= keep) {
-      for (int i = lane; i < expect; i += 64) s_list[wv][i] = cache[i];
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      for (int i = lane; i < expect; i += 64) {
-        const int t = s_list[wv][i];
-        int rank = 0;
-        for (int q = 0; q < expect; ++q) rank += s_list[wv][q] < t ? 1 : 0;
-        const int pos = (K == 3 ? w.pt3_off : w.pt5_off)[s] + rank;
-        if (pos < (K == 3 ? w.cap_pt3 : w.cap_pt5)) {
-          (K == 3 ? w.pt3_so : w.pt5_so)[pos] = make_int2(s, t);
-          (K == 3 ? w.pt3_attr : w.pt5_attr)[pos] = cattr[i];
-        }
-      }
-      return;
-    }
-  }
   unsigned *mask = s_mask[wv];
-  for (int i = lane; i < kMaskWords; i += 64) mask[i] = 0u;
-  if (lane < kRings) {
-    s_slo[wv][lane] = 0x7f7fffff;  // largest finite float
-    s_shi[wv][lane] = 0;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  mark_seed_bins(sd, mask, s_slo[wv], s_shi[wv]);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  if (lane < kRings)
-    s_zb[wv][lane] = seed_zbins(sd, __int_as_float(s_slo[wv][lane]), __int_as_float(s_shi[wv][lane]));
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  auto mark_bins = [&] {  // the seed's (ring, azimuth) mask and z ranges
+    for (int i = lane; i < kMaskWords; i += 64) mask[i] = 0u;
+    if (lane < kRings) {
+      s_slo[wv][lane] = 0x7f7fffff;  // largest finite float
+      s_shi[wv][lane] = 0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    mark_seed_bins(sd, mask, s_slo[wv], s_shi[wv]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < kRings)
+      s_zb[wv][lane] = seed_zbins(sd, __int_as_float(s_slo[wv][lane]), __int_as_float(s_shi[wv][lane]));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
   // the search over one object kind's bins (KO = 3: triplets, 5: quintuplets)
   auto search = [&](auto kind) {
     constexpr int KO = decltype(kind)::value;
@@ -2207,9 +2346,46 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
     const int *blst = KO == 3 ? w.b3_list : w.b5_list;
     const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
     int n_pass = 0;
-    int base = FILL ? (KO == 3 ? w.pt3_off : w.pt5_off)[s] : 0;
-    const int expect = FILL ? (KO == 3 ? w.pt3_cnt : w.pt5_cnt)[s] : 0;
+    int base = 0, expect = 0;
     const int cap = KO == 3 ? w.cap_pt3 : w.cap_pt5;
+    int2 *so = KO == 3 ? w.pt3_so : w.pt5_so;
+    float4 *at = KO == 3 ? w.pt3_attr : w.pt5_attr;
+    // one entry of the output, which also offers its key to its outer object
+    auto put = [&](int pos, int t, const float4 &attr) {
+      if (pos >= cap) return;
+      gstore(so, pos, make_int2(s, t));
+      gstore(at, pos, attr);
+      atomicMax((KO == 3 ? w.o3_best : w.o5_best) + t, pt_obj_key(attr.z, s));
+    };
+    if constexpr (FILL) {
+      const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
+      int *offs = KO == 3 ? w.pt3_off : w.pt5_off;
+      base = pre;
+      for (int q = si - wv; q < si; ++q) base += uload(cnts + q);
+      expect = uload(cnts + s);
+      if (lane == 0) {
+        offs[s] = base;
+        if (s == w.n_seeds - 1) {
+          offs[s + 1] = base + expect;
+          put_total(w, base + expect, cap, KO == 3 ? C_RPT3 : C_RPT5, KO == 3 ? C_NPT3 : C_NPT5);
+        }
+      }
+      if (expect <= keepO) {
+        // the count pass cached every passing object of this seed with its attributes:
+        // rank them by object index (in LDS) and copy, no search
+        for (int i = lane; i < expect; i += 64) s_list[wv][i] = gp(cache)[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < expect; i += 64) {
+          const int t = s_list[wv][i];
+          int rank = 0;
+          for (int q = 0; q < expect; ++q) rank += s_list[wv][q] < t ? 1 : 0;
+          put(base + rank, t, gload(cattr, i));
+        }
+        return;
+      }
+      mark_bins();
+    }
     const bool listed = !FILL || expect <= pass_list;
     const float4 *bpos = KO == 3 ? w.b3_pos : w.b5_pos;
     // the full selection on the first n (<= 64) queued objects; passing ones are counted
@@ -2367,7 +2543,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
     }
     if (listed && nq > 0) full(nq);
     if (!FILL) {
-      if (lane == 0) (KO == 3 ? w.pt3_cnt : w.pt5_cnt)[s] = n_pass;
+      if (lane == 0) {
+        (KO == 3 ? w.pt3_cnt : w.pt5_cnt)[s] = n_pass;
+        if (n_pass > 0) atomicAdd((KO == 3 ? w.ts_p3 : w.ts_p5) + (s >> w.sh_pt) * kSumStride, n_pass);
+      }
       return;
     }
     if (listed) {
@@ -2386,8 +2565,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
           float4 attr;
           load_object<KO>(w, g, t, P, M, &kT, &dkT);
           pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-          (KO == 3 ? w.pt3_so : w.pt5_so)[pos] = make_int2(s, t);
-          (KO == 3 ? w.pt3_attr : w.pt5_attr)[pos] = attr;
+          put(pos, t, attr);
         }
       }
       return;
@@ -2410,40 +2588,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
       }
       const unsigned long long m = __ballot(pass);
       const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-      if (pass && base + pre < cap) {
-        (KO == 3 ? w.pt3_so : w.pt5_so)[base + pre] = make_int2(s, t);
-        (KO == 3 ? w.pt3_attr : w.pt5_attr)[base + pre] = attr;
-      }
+      if (pass) put(base + pre, t, attr);
       base += __popcll(m);
     }
   };
-  if constexpr (BOTH) {  // count pass of both kinds on one trajectory mask
+  if constexpr (FILL) {
+    if (five) search(std::integral_constant<int, 5>{});
+    else search(std::integral_constant<int, 3>{});
+  } else {  // both kinds on one trajectory mask
+    mark_bins();
     search(std::integral_constant<int, 3>{});
     search(std::integral_constant<int, 5>{});
-  } else {
-    search(std::integral_constant<int, K>{});
   }
 }
 
-// The key that orders a pT entry for the same-object rule: smaller (score,
-// seed) is better, and since scores are >= 0 their bits order them as
-// integers; complemented so that the best is the largest, found with an
-// atomic maximum per outer object (a value, not a position: order-independent).
-template <int K>
-__device__ __forceinline__ unsigned long long pt_obj_key(const Ws &w, int i) {
-  const float4 *at = K == 3 ? w.pt3_attr : w.pt5_attr;
-  const int2 *so = K == 3 ? w.pt3_so : w.pt5_so;
-  return ~(((unsigned long long)__float_as_uint(at[i].z) << 32) | (unsigned long long)(unsigned)so[i].x);
-}
-template <int K>
-__global__ void k_pt_obj_best(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = K == 3 ? w.ctr[C_NPT3] : w.ctr[C_NPT5];
-  const int2 *so = K == 3 ? w.pt3_so : w.pt5_so;
-  unsigned long long *best = K == 3 ? w.o3_best : w.o5_best;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    atomicMax(&best[so[i].y], pt_obj_key<K>(w, i));
-}
 template <int K>
 __device__ __forceinline__ void obj_hits(const Ws &w, int t, int *h) {
   if constexpr (K == 3) {
@@ -2467,7 +2625,7 @@ __device__ __forceinline__ void obj_hits(const Ws &w, int t, int *h) {
 // it (a minimum over the seed's entries, the hit tuples compared only on an
 // exact tie of scores) and checks it alone against the entries sharing its
 // outer object, whose tuples differ from it in the seed only: it survives if
-// it has the object's smallest (score, seed) (k_pt_obj_best).
+// it has the object's smallest (score, seed) (offered to the object by the fill).
 template <int K>
 __global__ void k_pt_dedup(const Ws *__restrict__ wb) {
   const Ws &w = wb[blockIdx.y];
@@ -2513,7 +2671,7 @@ __global__ void k_pt_dedup(const Ws *__restrict__ wb) {
       continue;
     }
     // the winner survives the same-object rule if it is its object's best (score, seed)
-    const bool kp = obest[so[win].y] == pt_obj_key<K>(w, win);
+    const bool kp = obest[so[win].y] == pt_obj_key(at[win].z, so[win].x);
     for (int j = j0 + lane; j < j1; j += 64) keep[j] = (j == win && kp) ? 1 : 0;
   }
 }
@@ -3039,7 +3197,6 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
     return (unsigned)std::max(1L, std::min((long)blocks, 4 * ev_waves / (threads / 64)));
   };
   auto grid = [&](long n) { return dim3(share(grid_for(n), kBlock), B); };
-  auto gridt = [&](long n) { return dim3(share(grid_for(n, tb), tb), B); };    // tuned thread-per-item sites
   auto gridwt = [&](long n) { return dim3(share(grid_waves(n, tb), tb), B); }; // tuned wave-per-item sites
   auto gridwb = [&](long n) { return dim3(share_big(grid_waves(n, tb), tb), B); }; // the heavy searches
   // one wave per seed, every seed its own wave (the seed search does not stride)
@@ -3048,7 +3205,7 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   const bool whole = kt && kt->site == kChainSite;  // the timer brackets the whole chain
   if (whole) (void)hipEventRecord(kt->beg, st);
   // a0: buckets
-  run([&] { k_clear<<<grid(C_COUNT), kBlock, 0, st>>>(wb, FL_CTR, FL_CTR + 1); });
+  run([&] { k_clear<<<grid(32768), kBlock, 0, st>>>(wb, FL_CTR, FL_TS + 1); });
   const long n_tiles = n_hit_tiles(N), n_co = n_coarse(M);
   run([&] {  // one block per hit tile, and enough threads for the seeds' validation
     const long blocks = std::max(n_tiles, (S + kBlock - 1) / kBlock);
@@ -3073,19 +3230,19 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
     const int lg = ls_group_for(g.tiles, B, b.cap_md);
     k_ls_count<<<gridwb((b.cap_md + lg - 1) / lg), tb, 0, st>>>(wb, g, lg);
   });
-  run([&] { scan(wb, B, SC_LS, b.cap_md, st); });
+  run([&] { k_ls_sums<<<dim3((unsigned)std::min<long>(n_sum_tiles(b.cap_md), 256), B), kBlock, 0, st>>>(wb, g.tiles.ls_cache); });
   run([&] {
-    scan(wb, B, SC_LSOVF, b.cap_md, st);
-    k_ls_copy<<<gridt((long)b.cap_md * kLsCopyLanes), tb, 0, st>>>(wb, g.tiles.ls_cache);
-    k_ls_fill<<<gridwt(b.cap_md < 16384 ? b.cap_md : 16384), tb, 0, st>>>(wb, g);  // the overflow MDs
+    const unsigned n_copy = gridwt((b.cap_md + kLsCopyMds - 1) / kLsCopyMds).x;
+    const unsigned n_ovf = gridwt(std::min(b.cap_md, 4096)).x;  // the overflow MDs (428 on a PU200 event)
+    k_ls_fill<<<dim3(n_copy + n_ovf, B), tb, 0, st>>>(wb, g, (int)n_copy);
   });
   // a3: T3
   run([&] { k_t3<false><<<gridwb((b.cap_ls + 63) / 64), tb, 0, st>>>(wb, g); });
-  run([&] { scan(wb, B, SC_T3, b.cap_ls, st); });
+  run([&] {});  // t3_scan
   run([&] { k_t3<true><<<gridwb((b.cap_ls + 63) / 64), tb, 0, st>>>(wb, g); });
   // a4: T5
   run([&] { k_t5<false><<<gridwb((b.cap_t3 + 63) / 64), tb, 0, st>>>(wb, g); });
-  run([&] { scan(wb, B, SC_T5, b.cap_t3, st); });
+  run([&] {});  // t5_scan
   run([&] { k_t5<true><<<gridwb((b.cap_t3 + 63) / 64), tb, 0, st>>>(wb, g); });
   // a5: T5 duplicate removal through per-MD incidence lists
   run([&] {
@@ -3121,19 +3278,17 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
     scan(wb, B, SC_B5, kSeedBins, st);
     k_obj_bin_scatter<5><<<grid(b.cap_t5), kBlock, 0, st>>>(wb, g);
   });
-  // both counts on one trajectory mask per seed
-  run([&] { if (seeds) k_pt_binned<3, false, true><<<seedwaves(), tb, 0, st>>>(wb, g); });
-  run([&] { if (seeds) scan(wb, B, SC_PT3, S, st); });
-  run([&] { if (seeds) k_pt_binned<3, true><<<seedwaves(), tb, 0, st>>>(wb, g); });
-  run([&] { if (seeds) scan(wb, B, SC_PT5, S, st); });
-  run([&] { if (seeds) k_pt_binned<5, true><<<seedwaves(), tb, 0, st>>>(wb, g); });
+  // both counts on one trajectory mask per seed, both fills in one launch
+  run([&] { if (seeds) k_pt_binned<false><<<seedwaves(), tb, 0, st>>>(wb, g, 0); });
+  run([&] {});  // pt3_scan
   run([&] {
     if (!seeds) return;
-    const long n = 2L * ((b.cap_t3 > b.cap_t5 ? b.cap_t3 : b.cap_t5) + 1);
-    k_clear<<<grid(n), kBlock, 0, st>>>(wb, FL_O3_BEST, FL_O5_BEST + 1);
-    k_pt_obj_best<3><<<grid(b.cap_pt3), kBlock, 0, st>>>(wb);
-    k_pt_obj_best<5><<<grid(b.cap_pt5), kBlock, 0, st>>>(wb);
+    const unsigned n3 = seedwaves().x;
+    k_pt_binned<true><<<dim3(2 * n3, B), tb, 0, st>>>(wb, g, (int)n3);
   });
+  run([&] {});  // pt5_scan
+  run([&] {});  // pt5_fill: with pt3_fill
+  run([&] {});  // pt_obj_best: offered by the fill
   run([&] { if (seeds) k_pt_dedup<3><<<dim3(grid_waves(S), B), kBlock, 0, st>>>(wb); });
   run([&] { if (seeds) k_pt_dedup<5><<<dim3(grid_waves(S), B), kBlock, 0, st>>>(wb); });
   // a8: cleaning and track candidates
