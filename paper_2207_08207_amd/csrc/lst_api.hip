@@ -152,9 +152,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.t3_cache = I(kT3Cache * ls); t.t5_cache = I(kT5Cache * t3);
   t.t5_off = I(t3 + 1); t.ws_t5 = I((t3 >> 6) + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
   t.t5_keep = I(t5); t.t5_first = F2(t5);
-  t.inc_cnt = I(md + 1); t.inc_off = I(md + 1); t.inc_cur = I(md + 1); t.inc_list = I2(5 * t5);
+  t.inc_cnt = I(md); t.inc_off = I(md); t.inc_list = I2(5 * t5);
   t.pls = F(8 * S); t.pls_keep = I(S); t.seed_order = I(S + 1);
-  t.ph_cnt = I(N + 1); t.ph_off = I(N + 1); t.ph_cur = I(N + 1); t.ph_list = I(4 * S);
+  t.seed_cnt = I(kSeedKeys);
+  t.ph_head = I(N); t.ph_next = I(4 * S);
   t.pt3_cnt = I(S + 1); t.pt3_off = I(S + 1); t.pt5_cnt = I(S + 1); t.pt5_off = I(S + 1);
   t.pt3_cache = I(kPt3Cache * S); t.pt5_cache = I(kPt5Cache * S);
   t.pt3_cattr = F4(kPt3Cache * S); t.pt5_cattr = F4(kPt5Cache * S);
@@ -163,9 +164,7 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.o3_best = reinterpret_cast<unsigned long long *>(take(8 * (size_t)(t3 + 1)));
   t.o5_best = reinterpret_cast<unsigned long long *>(take(8 * (size_t)(t5 + 1)));
   const long nbins = kSeedBins;
-  t.b3_cnt = I(nbins + 1); t.b3_off = I(nbins + 1); t.b3_cur = I(nbins + 1); t.b3_list = I(t3);
-  t.b5_cnt = I(nbins + 1); t.b5_off = I(nbins + 1); t.b5_cur = I(nbins + 1); t.b5_list = I(t5);
-  t.b3_pos = F4(t3); t.b5_pos = F4(t5);
+  t.bin_cnt = I(nbins); t.bin_off = I(nbins);
   t.seed_used = I(S + 1); t.t5_used = I(t5 + 1);
   t.f_pt5 = I(p5 + 1); t.f_pt3 = I(p3 + 1); t.f_t5 = I(t5 + 1); t.f_pls = I(S + 1);
   t.p_pt5 = I(p5 + 1); t.p_pt3 = I(p3 + 1); t.p_t5 = I(t5 + 1); t.p_pls = I(S + 1);
@@ -177,6 +176,16 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.ext_n = I(tc); t.ext_t3 = I(tc); t.ext_cnt = I(tc + 1); t.ext_off = I(tc + 1); t.ext_hits = I(18 * tc);
   t.ext_attr = F4(tc);
   t.scan_tmp = I(4096);
+  // arrays in place of others: once the segments are written, their cache holds what the
+  // seed search and the duplicate removal keep per MD; the candidates' lists, written last,
+  // hold the places of the seeds and of the quintuplets in their lists
+  static_assert(kLsCache * sizeof(int) >= sizeof(float4) + sizeof(int4) + sizeof(int2) + sizeof(int), "per-MD arrays");
+  t.bin_pos = reinterpret_cast<float4 *>(t.ls_cache);
+  t.bin_rng = reinterpret_cast<int4 *>(t.bin_pos + md);
+  t.md_bin = reinterpret_cast<int2 *>(t.bin_rng + md);
+  t.inc_b0 = reinterpret_cast<int *>(t.md_bin + md);
+  t.t5_slot = t.tc_hits;                       // 4 t5 <= 14 tc
+  t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;  // 2 S <= 5 tc
   // the tile sums, one after another (cleared together)
   const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
   const long n_ts = (nl + n3 + n5 + 2 * np) * kSumStride;
@@ -195,7 +204,7 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.n_hits = n_hits; t.n_seeds = n_seeds;
   t.cap_tc = (int)(p5 + p3 + t5 + n_seeds);
   if (w && base) {
-    const long N = n_hits, S = n_seeds;  // the jobs follow the event's own sizes
+    const long S = n_seeds;  // the jobs follow the event's own sizes
     int *ct = t.ctr;
     auto sj = [&](int id, const int *in, int *out, const int *n_dev, long n_fix, long n_cap, int *req, int *clamped,
                   long cap) { t.scans[id] = ScanJob{in, out, n_dev, (int)n_fix, (int)n_cap, req, clamped, (int)cap}; };
@@ -203,32 +212,17 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
     const long nt_cap = (long)n_coarse((int)M) * n_hit_tiles(n_hits_alloc >= 0 ? n_hits_alloc : n_hits);
     sj(SC_HITS, t.tile_hist, t.tile_off, nullptr, nt, nt_cap, ct + C_NOUTER, nullptr, 0);
     sj(SC_MD, t.md_cnt, t.md_off, nullptr, M, M, ct + C_RMD, ct + C_NMD, md);
-    sj(SC_INC, t.inc_cnt, t.inc_off, ct + C_NMD, 0, md, ct + C_NINC, nullptr, 0);
-    sj(SC_PH, t.ph_cnt, t.ph_off, nullptr, N, N, ct + C_NPH, nullptr, 0);
     sj(SC_F5, t.f_pt5, t.p_pt5, ct + C_NPT5, 0, p5, ct + C_NTC0, nullptr, 0);
     sj(SC_F3, t.f_pt3, t.p_pt3, ct + C_NPT3, 0, p3, ct + C_NTC1, nullptr, 0);
     sj(SC_FT5, t.f_t5, t.p_t5, ct + C_NT5, 0, t5, ct + C_NTC2, nullptr, 0);
     sj(SC_FPLS, t.f_pls, t.p_pls, nullptr, S, S, ct + C_NTC3, nullptr, 0);
-    sj(SC_B3, t.b3_cnt, t.b3_off, nullptr, nbins, nbins, ct + C_NB3, nullptr, 0);
-    sj(SC_B5, t.b5_cnt, t.b5_off, nullptr, nbins, nbins, ct + C_NB5, nullptr, 0);
     sj(SC_EXT, t.ext_cnt, t.ext_off, ct + C_NTC, 0, p5 + p3 + t5 + S, ct + C_NEXTHITS, nullptr, 0);
-    // arrays indexed by MDs, triplets or quintuplets are cleared up to the built count
-    // (the clears run after it is known), not the capacity
-    auto fj = [&](int id, int *p, long n, const int *n_dev = nullptr, int mul = 1) {
-      t.fills[id] = FillJob{p, n, n_dev, mul};
-    };
+    const auto fj = [&](int id, int *p, long n, int stride = 1) { t.fills[id] = FillJob{p, (int)n, stride}; };
     fj(FL_CTR, ct, C_COUNT);
-    fj(FL_TS, t.ts_ls, n_ts);
-    fj(FL_INC_CNT, t.inc_cnt, md + 1, ct + C_NMD);
-    fj(FL_INC_CUR, t.inc_cur, md + 1, ct + C_NMD);
-    fj(FL_PH_CNT, t.ph_cnt, N + 1);
-    fj(FL_PH_CUR, t.ph_cur, N + 1);
-    fj(FL_SEED_USED, t.seed_used, S + 1);
-    fj(FL_T5_USED, t.t5_used, t5 + 1, ct + C_NT5);
-    fj(FL_B3_CNT, t.b3_cnt, nbins + 1);
-    fj(FL_B3_CUR, t.b3_cur, nbins + 1);
-    fj(FL_B5_CNT, t.b5_cnt, nbins + 1);
-    fj(FL_B5_CUR, t.b5_cur, nbins + 1);
+    fj(FL_TS, t.ts_ls, n_ts / kSumStride, kSumStride);
+    fj(FL_SEED_CNT, t.seed_cnt, S > 0 ? kSeedKeys : 0);
+    fj(FL_SEED_USED, t.seed_used, S);
+    fj(FL_BIN_CNT, t.bin_cnt, S > 0 ? nbins : 0);
   }
   if (w) *w = t;
   return (off + kAlign - 1) / kAlign * kAlign;

@@ -86,15 +86,22 @@ __device__ __forceinline__ int block_sum(int v, int *s_red) {
 
 __device__ __forceinline__ int dev_count(const int *p, int fallback) { return p ? *p : fallback; }
 
-// ------------------------------------------------------------------ fill
-// Clears the arrays of fill jobs [j0, j1) of every event of the batch.
-__global__ void k_clear(const Ws *__restrict__ wb, int j0, int j1) {
+// ------------------------------------------------------------------ start
+// The chain's first launch: clears what later kernels count into and empties
+// the lists of the pixel hits that seeds use (the rest of ph_head is never
+// read).  Arrays indexed by MDs or quintuplets are cleared where those are
+// written, so no other launch of the chain only clears.
+__global__ void k_start(const Ws *__restrict__ wb) {
   const Ws &w = wb[blockIdx.y];
-  for (int j = j0; j < j1; ++j) {
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  for (int j = 0; j < FL_COUNT; ++j) {
     int *p = w.fills[j].p;
-    long n = w.fills[j].n;
-    if (w.fills[j].n_dev) n = min(n, (long)w.fills[j].mul * ((long)uload(w.fills[j].n_dev) + 1));
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = 0;
+    const int n = w.fills[j].n, st = w.fills[j].stride;
+    for (long i = tid; i < n; i += nt) gp(p)[i * st] = 0;
+  }
+  for (long i = tid; i < 4L * w.n_seeds; i += nt) {
+    const int h = gp(w.hits4)[i];
+    if (h >= 0 && h < w.n_hits) gp(w.ph_head)[h] = -1;
   }
 }
 
@@ -314,6 +321,47 @@ void launch_tc_export(const Ws *d_ws, int max_tc, int max_hits, int *type, int *
   k_tc_export<<<256, 256, 0, st>>>(d_ws, max_tc, max_hits, type, off, hits, counts);
 }
 
+// ---- binned search: objects grouped by first anchor (radius ring, azimuth bin, z bin)
+constexpr int kRings = 10;
+constexpr float kRing0 = 20.0f, kRingW = 10.0f;      // rings [20, 30), ..., [110, 120) cm, ends clamped
+constexpr int kPhiBins = 256;
+constexpr int kObjBins = kRings * kPhiBins;          // (ring, azimuth) pairs: the bits of a seed's mask
+constexpr float kZHalf = 275.0f, kZW = 10.0f;        // z bins [-275, -265), ..., ends clamped
+static_assert(kObjBins == kBinRows && kPhiBins * 8 == kSeedKeys, "seed-search bins and direction groups");
+constexpr int kMaskWords = kObjBins / 32;
+constexpr float kSampleStep = 2.0f;                  // trajectory sampling step [cm]
+constexpr int kMaxSamples = 112;                     // 224 cm of arc
+
+__device__ __forceinline__ int ring_of(float r) {
+  const int k = (int)floorf((r - kRing0) / kRingW);
+  return k < 0 ? 0 : (k >= kRings ? kRings - 1 : k);
+}
+__device__ __forceinline__ int phibin_of(float ph) {
+  const int b = (int)floorf((ph + (float)M_PI) * (float)(kPhiBins / (2.0 * M_PI)));
+  return b < 0 ? 0 : (b >= kPhiBins ? kPhiBins - 1 : b);
+}
+__device__ __forceinline__ int zbin_of(float z) {
+  const int b = (int)floorf((z + kZHalf) / kZW);
+  return b < 0 ? 0 : (b >= kZBins ? kZBins - 1 : b);
+}
+// Bin of the objects whose first anchor is a.
+__device__ __forceinline__ int obj_bin(const float4 &a) {
+  const float ph = atan2f(a.y, a.x);
+  const int rp = ph == ph ? ring_of(a.w) * kPhiBins + phibin_of(ph) : 0;
+  return rp * kBinStride + zbin_of(a.z);
+}
+// Processing order of the seed search: seeds grouped by direction (azimuth of
+// the seed's direction in kPhiBins sectors x 8 bins of lambda).  Seeds of one
+// group scan nearly the same bins, so waves that run together (consecutive
+// blocks) reuse each other's object lists in cache.  Results do not depend on
+// the order (each seed writes only its own entries), so places within a group
+// come from atomics.
+__device__ __forceinline__ int seed_key(float cx, float cy, float lam) {
+  const float ph = atan2f(cy, cx);
+  const int lb = (int)floorf((lam + 6.0f) * (1.0f / 1.5f));
+  return (ph == ph ? phibin_of(ph) : 0) * 8 + (lb < 0 ? 0 : (lb > 7 ? 7 : lb));
+}
+
 // ------------------------------------------------------------- a0: hits
 // Hits are bucketed by key = 2 module + sensor, stably (input order within a
 // key), with no global atomic: an LSD-free two-level counting sort.
@@ -371,6 +419,39 @@ __device__ __forceinline__ int bits_for(int n) {  // bits of the values 0 .. n -
   return b;
 }
 
+// Pixel line segment of seed s (Section 2.4): validated (returns true if its
+// data are invalid), its parameters computed, entered in the lists of its pixel
+// hits and counted in its direction group.
+__device__ __forceinline__ bool seed_prepare(const Ws &w, int s) {
+  const float px = gp(w.px)[s], py = gp(w.py)[s], pz = gp(w.pz)[s];
+  const int q = gp(w.q)[s];
+  bool bad = !(q == 1 || q == -1) || !(isfinite(px) && isfinite(py) && isfinite(pz));
+  bad |= !(px * px + py * py > 0.0f);
+  int h0 = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int h = gp(w.hits4)[4 * (long)s + k];
+    const bool in = h >= 0 && h < w.n_hits;
+    bad |= !in;
+    if (in) {
+      bad |= gp(w.module)[h] != -1;
+      gp(w.ph_next)[4 * (long)s + k] = atomicExch(w.ph_head + h, 4 * s + k);
+      if (k == 0) h0 = h;
+    }
+  }
+  const float pt = sqrtf(px * px + py * py);
+  float *o = w.pls + 8 * (long)s;
+  const float cx = px / pt, cy = py / pt, lam = pz / pt;
+  gstore(reinterpret_cast<float4 *>(o), 0, make_float4(pt, cx, cy, lam));
+  const bool any = w.n_hits > 0;
+  gstore(reinterpret_cast<float4 *>(o), 1,
+         make_float4((-(float)q * kCurv) / pt, any ? gp(w.x)[h0] : 0.f, any ? gp(w.y)[h0] : 0.f, any ? gp(w.z)[h0] : 0.f));
+  const int key = seed_key(cx, cy, lam);
+  gp(w.seed_key)[s] = key;
+  gp(w.seed_slot)[s] = atomicAdd(w.seed_cnt + key, 1);
+  return bad;
+}
+
 // One block per tile of kHitTile hits, each of its four waves counting 1024
 // consecutive hits into its own LDS row; the tile's coarse counts are the rows'
 // sums (k_hits_scatter recounts the rows to rank its waves).
@@ -409,16 +490,8 @@ __global__ __launch_bounds__(kBlock) void k_hits_count(const Ws *__restrict__ wb
       gp(w.tile_hist)[(long)c * ntb + tb] = t;
     }
   }
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x) {
-    bool bad = !(w.q[s] == 1 || gp(w.q)[s] == -1) || !(isfinite(w.px[s]) && isfinite(w.py[s]) && isfinite(w.pz[s]));
-    bad |= !(w.px[s] * gp(w.px)[s] + gp(w.py)[s] * gp(w.py)[s] > 0.0f);
-    for (int k = 0; k < 4; ++k) {
-      const int h = gp(w.hits4)[4 * s + k];
-      bad |= (h < 0 || h >= w.n_hits);
-      if (h >= 0 && h < w.n_hits) bad |= (w.module[h] != -1);
-    }
-    if (bad) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
-  }
+  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x)
+    if (seed_prepare(w, s)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
 }
 
 // Stable scatter of a tile's hits into coarse-bucket order: each wave's first
@@ -640,6 +713,7 @@ __global__ __launch_bounds__(kBlock) void k_md(const Ws *__restrict__ wb, DevGeo
           const float4 hj = j < kMdStage ? s_up[wv][j] : gload(w.hpos, up0 + j);
           gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
           gp(w.md_mod)[pos] = m;
+          gp(w.inc_cnt)[pos] = 0;
           gstore(w.md_pos, pos, hi);
           put_stub(w, g, pos, md_stub(hi, hj, mi));
         }
@@ -664,6 +738,7 @@ __global__ __launch_bounds__(kBlock) void k_md(const Ws *__restrict__ wb, DevGeo
         if (pos < w.cap_md) {
           gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
           gp(w.md_mod)[pos] = m;
+          gp(w.inc_cnt)[pos] = 0;
           gstore(w.md_pos, pos, hi);
           put_stub(w, g, pos, md_stub(hi, hj, mi));
         }
@@ -753,6 +828,7 @@ __global__ __launch_bounds__(64 * kMdParts) void k_md_big(const Ws *__restrict__
         if (pos < w.cap_md) {
           gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
           gp(w.md_mod)[pos] = m;
+          gp(w.inc_cnt)[pos] = 0;
           gstore(w.md_pos, pos, hi);
           put_stub(w, g, pos, md_stub(hi, hj, mi));
         }
@@ -786,6 +862,7 @@ __global__ __launch_bounds__(64 * kMdParts) void k_md_big(const Ws *__restrict__
         if (pos < w.cap_md) {
           gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
           gp(w.md_mod)[pos] = m;
+          gp(w.inc_cnt)[pos] = 0;
           gstore(w.md_pos, pos, hi);
           put_stub(w, g, pos, md_stub(hi, hj, mi));
         }
@@ -1220,11 +1297,64 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 // not do this itself: an atomic per group of MDs there delays the wave's next
 // gathers until it is done (the count 0.119 -> 0.130 ms for one event, 0.88 ->
 // 0.93 ms for eight), more than this launch takes.
-__global__ void k_ls_sums(const Ws *__restrict__ wb, int keep) {
+//
+// Blocks from n_sum on do what the pixel stages need and nothing else waits for:
+// the seeds' processing order (every block scans the group counts for itself)
+// and the pLS duplicate removal (seeds sharing at least 3 pixel hits; the lower
+// seed index wins).
+__device__ __forceinline__ bool pls_survives(const Ws &w, int s) {
+  int hs[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) hs[k] = gp(w.hits4)[4 * (long)s + k];
+  for (int k = 0; k < 4; ++k) {
+    const int h = hs[k];
+    if (h < 0 || h >= w.n_hits) continue;
+    for (int q = gp(w.ph_head)[h]; q >= 0; q = gp(w.ph_next)[q]) {
+      const int t = q >> 2;
+      if (t >= s) continue;
+      int sh = 0;
+      for (int i = 0; i < 4; ++i) {
+        bool f = false;
+        for (int j = 0; j < 4; ++j) f |= (gp(w.hits4)[4 * (long)t + j] == hs[i]);
+        sh += f ? 1 : 0;
+      }
+      if (sh >= 3) return false;
+    }
+  }
+  return true;
+}
+
+__global__ __launch_bounds__(kBlock) void k_ls_sums(const Ws *__restrict__ wb, int keep, int n_sum) {
   __shared__ int s_red[kWaves];
+  __shared__ int s_off[kSeedKeys];
   const Ws &w = wb[blockIdx.y];
+  if ((int)blockIdx.x >= n_sum) {
+    const int S = w.n_seeds, t = threadIdx.x, lane = lane_id();
+    const int q0 = ((int)blockIdx.x - n_sum) * kBlock;
+    if (q0 >= S) return;  // the whole block
+    constexpr int kPer = kSeedKeys / kBlock;
+    int c[kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) sum += c[i] = gp(w.seed_cnt)[t * kPer + i];
+    const int x = wave_inclusive(sum);
+    if (lane == 63) s_red[t >> 6] = x;
+    __syncthreads();
+    int ex = x - sum;
+    for (int q = 0; q < (t >> 6); ++q) ex += s_red[q];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      s_off[t * kPer + i] = ex;
+      ex += c[i];
+    }
+    __syncthreads();
+    for (int s = q0 + t; s < S; s += ((int)gridDim.x - n_sum) * kBlock) {
+      gp(w.seed_order)[s_off[gp(w.seed_key)[s]] + gp(w.seed_slot)[s]] = s;
+      gp(w.pls_keep)[s] = pls_survives(w, s) ? 1 : 0;
+    }
+    return;
+  }
   const int n = uload(w.ctr + C_NMD), sh = w.sh_ls;
-  for (int t = blockIdx.x; (t << sh) < n; t += gridDim.x) {
+  for (int t = blockIdx.x; (t << sh) < n; t += n_sum) {
     const int j1 = min((t + 1) << sh, n);
     int v = 0;
     for (int j = (t << sh) + (int)threadIdx.x; j < j1; j += kBlock) {
@@ -1700,9 +1830,92 @@ __device__ __forceinline__ bool phiz_may_pass(const float4 &P, const float4 &Q, 
   return fabsf(t1 - t2) <= (tol * kMargin + kEps) * 1.00001f + 1e-5f * (fabsf(t1) + fabsf(t2));
 }
 
+// The triplets that start at MD m: (first, end).
+__device__ __forceinline__ int2 md_triplets(const Ws &w, int m, int n_ls, int n_t3) {
+  const int l0 = min(gp(w.ls_off)[m], n_ls), l1 = min(gp(w.ls_off)[m + 1], n_ls);
+  const int lo = gp(w.t3_off)[l0], hi = min(gp(w.t3_off)[l1], n_t3);
+  return make_int2(lo, hi > lo ? hi : lo);
+}
+// The quintuplets among the triplets [r.x, r.y).
+__device__ __forceinline__ int2 triplets_t5(const Ws &w, int2 r, int n_t5) {
+  const int lo = min(gp(w.t5_off)[r.x], n_t5), hi = min(gp(w.t5_off)[r.y], n_t5);
+  return make_int2(lo, hi > lo ? hi : lo);
+}
+
+// Seed-search bins: the search tests first anchors, and the triplets and
+// quintuplets of one first MD are consecutive, so the bins hold MDs (50k on a
+// PU200 event, where its 124k triplets and 29k quintuplets had an entry each)
+// and one test serves all of an MD's objects of both kinds.  Count, placement
+// of the rows and scatter ride in the quintuplet stage's launches as further
+// blocks, q = 0, 1, ... of nq.
+__device__ __forceinline__ void bin_count(const Ws &w, int q, int nq) {
+  if (w.n_seeds == 0) return;
+  const int n = uload(w.ctr + C_NMD), n_ls = uload(w.ctr + C_NLS), n_t3 = uload(w.ctr + C_NT3);
+  for (int m = q * blockDim.x + threadIdx.x; m < n; m += nq * blockDim.x) {
+    const int2 r = md_triplets(w, m, n_ls, n_t3);
+    int2 b = make_int2(-1, 0);
+    if (r.y > r.x) {
+      b.x = obj_bin(gload(w.md_pos, m));
+      b.y = atomicAdd(w.bin_cnt + b.x, 1);
+    }
+    gstore(w.md_bin, m, b);
+  }
+}
+// A row's place among the others does not matter (its bins are consecutive, z
+// ascending): each block takes one atomic on the total and scans its own counts.
+constexpr int kRowsPerWave = 8;
+__device__ __forceinline__ void bin_place(const Ws &w, int q, int *s_wave) {
+  if (w.n_seeds == 0) return;
+  static_assert(kBinStride <= 64, "a row's bins on one wave");
+  const int lane = lane_id(), wv = wave_id(), wpb = blockDim.x >> 6;
+  const int r0 = (q * wpb + wv) * kRowsPerWave;
+  int c[kRowsPerWave], sum = 0;
+#pragma unroll
+  for (int r = 0; r < kRowsPerWave; ++r)
+    sum += c[r] = (lane < kZBins && r0 + r < kBinRows) ? gp(w.bin_cnt)[(r0 + r) * kBinStride + lane] : 0;
+  sum = wave_total(sum);
+  if (lane == 0) s_wave[wv] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int tot = 0;
+    for (int i = 0; i < wpb; ++i) tot += s_wave[i];
+    s_wave[kWaves] = atomicAdd(w.ctr + C_NBIN, tot);
+  }
+  __syncthreads();
+  int run = s_wave[kWaves];
+  for (int i = 0; i < wv; ++i) run += s_wave[i];
+#pragma unroll
+  for (int r = 0; r < kRowsPerWave; ++r) {
+    const int x = wave_inclusive(c[r]);
+    if (lane < kBinStride && r0 + r < kBinRows) gp(w.bin_off)[(r0 + r) * kBinStride + lane] = run + x - c[r];
+    run += __shfl(x, 63, 64);
+  }
+}
+__device__ __forceinline__ void bin_scatter(const Ws &w, const DevGeom &g, int q, int nq) {
+  if (w.n_seeds == 0) return;
+  const int n = uload(w.ctr + C_NMD), n_ls = uload(w.ctr + C_NLS), n_t3 = uload(w.ctr + C_NT3);
+  const int n_t5 = uload(w.ctr + C_NT5);
+  for (int m = q * blockDim.x + threadIdx.x; m < n; m += nq * blockDim.x) {
+    const int2 b = gload(w.md_bin, m);
+    if (b.x < 0) continue;
+    const int j = gp(w.bin_off)[b.x] + b.y;
+    const int2 r = md_triplets(w, m, n_ls, n_t3), v = triplets_t5(w, r, n_t5);
+    const float4 a = gload(w.md_pos, m);
+    gstore(w.bin_pos, j, make_float4(a.x, a.y, a.z, __int_as_float(gp(g.info)[gp(w.md_mod)[m]])));
+    gstore(w.bin_rng, j, make_int4(r.x, r.y - r.x, v.x, v.y - v.x));
+  }
+}
+
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeom g) {
+__global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeom g, int n_main) {
   const Ws &w = wb[blockIdx.y];
+  if ((int)blockIdx.x >= n_main) {  // the seed search's bins
+    __shared__ int s_wave[kWaves + 1];
+    const int q = (int)blockIdx.x - n_main, nq = (int)gridDim.x - n_main;
+    if constexpr (FILL) bin_place(w, q, s_wave);
+    else bin_count(w, q, nq);
+    return;
+  }
   __shared__ float4 s_p[kWaves][3][64], s_tin[kWaves][64];
   __shared__ int s_mi[kWaves][64], s_lo[kWaves][64], s_cnt[kWaves][64], s_seg[kWaves][65], s_cached[kWaves][64];
   __shared__ int s_qe[kWaves][128], s_qc[kWaves][128];  // pairs past the pre-test, in pair order
@@ -1712,7 +1925,7 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;
   if (FILL && n_t3 == 0 && blockIdx.x == 0 && threadIdx.x == 0) w.t5_off[0] = 0;
-  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_t3; b0 += (long)gridDim.x * wpb * 64) {
+  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_t3; b0 += (long)n_main * wpb * 64) {
     const long p0 = b0 + wv * 64;
     if (!FILL && p0 >= n_t3) break;
     const int t1 = (int)p0 + lane;
@@ -1788,6 +2001,8 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
 #pragma unroll
             for (int k = 0; k < 8; ++k) dst[k] = at[k];
             gp(w.t5_keep)[pos] = 1;  // until a better duplicate is found
+            gp(w.t5_used)[pos] = 0;
+            gstore(w.t5_first, pos, make_float2(s_p[wv][0][e].x, s_p[wv][0][e].y));
             gstore(w.o5_best, pos, 0ull);
           }
         }
@@ -1862,21 +2077,82 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
 }
 
 // ------------------------------------------------------------- a5: T5 dedup
-__global__ void k_t5_inc_count(const Ws *__restrict__ wb) {
+// Lists of the T5s on each MD.  The T5s that start at an MD are consecutive, so
+// only the other four of a T5's MDs count it: one thread per (T5, MD) takes the
+// T5's place in the MD's list (blocks [0, n5); the others scatter the seed
+// search's bins).  Device atomics run at about 8 per ns whatever waits for them;
+// taken inside the quintuplet fill, with its fewer and longer waves, they cost it
+// 46 us against 17 here.
+__global__ __launch_bounds__(kBlock) void k_t5_inc(const Ws *__restrict__ wb, DevGeom g, int n5) {
   const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NT5);
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-    for (int k = 0; k < 5; ++k) atomicAdd(&w.inc_cnt[gp(w.t5_md)[5 * (long)t + k]], 1);
+  if ((int)blockIdx.x >= n5) {
+    bin_scatter(w, g, (int)blockIdx.x - n5, (int)gridDim.x - n5);
+    return;
+  }
+  const long n = 4L * uload(w.ctr + C_NT5);
+  for (long i = blockIdx.x * (long)kBlock + threadIdx.x; i < n; i += (long)n5 * kBlock) {
+    const int md = gp(w.t5_md)[5 * (i >> 2) + 1 + (i & 3)];
+    gp(w.t5_slot)[i] = atomicAdd(w.inc_cnt + md, 1);
+  }
 }
-__global__ void k_t5_inc_scatter(const Ws *__restrict__ wb) {
+// Places of the lists: a list's place among the others does not matter, so each
+// block takes one atomic on the total and scans its own counts.
+__global__ __launch_bounds__(kBlock) void k_list_place(const Ws *__restrict__ wb) {
+  __shared__ int s_wave[kWaves], s_base;
   const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NT5);
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-    const int score = __float_as_int(w.t5_attr[8 * (long)t + 1]);
-    for (int k = 0; k < 5; ++k) {
-      const int md = gp(w.t5_md)[5 * (long)t + k];
-      w.inc_list[gp(w.inc_off)[md] + atomicAdd(&w.inc_cur[md], 1)] = make_int2(t, score);
+  const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
+  const int n = uload(w.ctr + C_NMD), n_ls = uload(w.ctr + C_NLS), n_t3 = uload(w.ctr + C_NT3);
+  const int n_t5 = uload(w.ctr + C_NT5);
+  constexpr int kItems = 2;
+  for (long b0 = (long)blockIdx.x * kItems * kBlock; b0 < n; b0 += (long)gridDim.x * kItems * kBlock) {
+    int c[kItems], sum = 0;
+    int2 own[kItems];  // the T5s it is the first MD of
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const long m = b0 + k * kBlock + t;
+      own[k] = make_int2(0, 0);
+      c[k] = 0;
+      if (m < n) {
+        own[k] = triplets_t5(w, md_triplets(w, (int)m, n_ls, n_t3), n_t5);
+        c[k] = gp(w.inc_cnt)[m];
+      }
+      sum += c[k] + own[k].y - own[k].x;
     }
+    const int x = wave_inclusive(sum);
+    __syncthreads();  // the previous round's reads
+    if (lane == 63) s_wave[wv] = x;
+    __syncthreads();
+    if (t == 0) {
+      int tot = 0;
+      for (int q = 0; q < kWaves; ++q) tot += s_wave[q];
+      s_base = tot > 0 ? atomicAdd(w.ctr + C_NINC, tot) : 0;
+    }
+    __syncthreads();
+    int at = s_base + x - sum;
+    for (int q = 0; q < wv; ++q) at += s_wave[q];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const long m = b0 + k * kBlock + t;
+      if (m < n) {
+        const int n0 = own[k].y - own[k].x;
+        gp(w.inc_off)[m] = at;
+        gp(w.inc_cnt)[m] = c[k] + n0;
+        gp(w.inc_b0)[m] = at + c[k] - own[k].x;
+        at += c[k] + n0;
+      }
+    }
+  }
+}
+// The T5s into their MDs' lists, one thread per (T5, MD): every place is known.
+__global__ __launch_bounds__(kBlock) void k_t5_inc_scatter(const Ws *__restrict__ wb) {
+  const Ws &w = wb[blockIdx.y];
+  const long n = 5L * uload(w.ctr + C_NT5);
+  for (long i = blockIdx.x * (long)kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
+    const long t = i / 5;
+    const int k = (int)(i - 5 * t);
+    const int md = gp(w.t5_md)[i];
+    const int pos = k == 0 ? gp(w.inc_b0)[md] + (int)t : gp(w.inc_off)[md] + gp(w.t5_slot)[4 * t + k - 1];
+    gstore(w.inc_list, pos, make_int2((int)t, __float_as_int(gp(w.t5_attr)[8 * t + 1])));
   }
 }
 
@@ -1939,10 +2215,9 @@ __global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb, 
         mt[j] = gp(w.t5_md)[5 * (long)t + j];
         S.mt[j][lane] = mt[j];
       }
-      if (k == 0) gstore(w.t5_first, t, make_float2(w.md_pos[mt[0]].x, w.md_pos[mt[0]].y));
       const int lo = gp(w.inc_off)[mt[k]];
       S.lo[lane] = lo;
-      cnt = gp(w.inc_off)[mt[k] + 1] - lo;
+      cnt = gp(w.inc_cnt)[mt[k]];
       S.st[lane] = gp(w.t5_attr)[8 * (long)t + 1];
     }
     const int total = wave_segments(cnt, S.seg);
@@ -1994,63 +2269,6 @@ __device__ __forceinline__ Seed load_seed(const Ws &w, int s) {
   return sd;
 }
 
-__global__ void k_pls(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x) {
-    const float px = gp(w.px)[s], py = gp(w.py)[s], pz = gp(w.pz)[s];
-    const float pt = sqrtf(px * px + py * py);
-    float *o = w.pls + 8 * (long)s;
-    o[0] = pt;
-    o[1] = px / pt;
-    o[2] = py / pt;
-    o[3] = pz / pt;
-    o[4] = (-(float)gp(w.q)[s] * kCurv) / pt;
-    int h0 = gp(w.hits4)[4 * (long)s];
-    h0 = (h0 >= 0 && h0 < w.n_hits) ? h0 : 0;
-    o[5] = gp(w.x)[h0];
-    o[6] = gp(w.y)[h0];
-    o[7] = gp(w.z)[h0];
-    for (int k = 0; k < 4; ++k) {
-      const int h = gp(w.hits4)[4 * (long)s + k];
-      if (h >= 0 && h < w.n_hits) atomicAdd(&w.ph_cnt[h], 1);
-    }
-  }
-}
-__global__ void k_ph_scatter(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x)
-    for (int k = 0; k < 4; ++k) {
-      const int h = gp(w.hits4)[4 * (long)s + k];
-      if (h >= 0 && h < w.n_hits) gp(w.ph_list)[gp(w.ph_off)[h] + atomicAdd(&w.ph_cur[h], 1)] = s;
-    }
-}
-// pLS duplicate removal: seeds sharing at least 3 pixel hits; the lower seed index wins.
-__global__ void k_pls_dedup(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x) {
-    int hs[4];
-    for (int k = 0; k < 4; ++k) hs[k] = gp(w.hits4)[4 * (long)s + k];
-    bool keep = true;
-    for (int k = 0; k < 4 && keep; ++k) {
-      const int h = hs[k];
-      if (h < 0 || h >= w.n_hits) continue;
-      for (int q = gp(w.ph_off)[h]; q < gp(w.ph_off)[h + 1] && keep; ++q) {
-        const int t = gp(w.ph_list)[q];
-        if (t >= s) continue;
-        int sh = 0;
-        for (int i = 0; i < 4; ++i) {
-          const int hi = hs[i];
-          bool f = false;
-          for (int j = 0; j < 4; ++j) f |= (w.hits4[4 * (long)t + j] == hi);
-          sh += f ? 1 : 0;
-        }
-        if (sh >= 3) keep = false;
-      }
-    }
-    gp(w.pls_keep)[s] = keep ? 1 : 0;
-  }
-}
-
 // ------------------------------------------------------------- a7: pT3 / pT5
 template <int K>
 __device__ __forceinline__ void load_object(const Ws &w, const DevGeom &g, int t, float4 *P, ModInfo *M, float *kT,
@@ -2071,116 +2289,6 @@ __device__ __forceinline__ void load_object(const Ws &w, const DevGeom &g, int t
     }
     const float4 a3 = w.t3_attr[gload(w.t5_t3, t).y];
     *kT = a3.x; *dkT = a3.y;
-  }
-}
-
-// ---- binned search: objects grouped by first anchor (radius ring, azimuth bin, z bin)
-constexpr int kRings = 10;
-constexpr float kRing0 = 20.0f, kRingW = 10.0f;      // rings [20, 30), ..., [110, 120) cm, ends clamped
-constexpr int kPhiBins = 256;
-constexpr int kObjBins = kRings * kPhiBins;          // (ring, azimuth) pairs: the bits of a seed's mask
-constexpr int kZBins = 55;
-constexpr float kZHalf = 275.0f, kZW = 10.0f;        // z bins [-275, -265), ..., ends clamped
-static_assert(kObjBins * kZBins == kSeedBins, "seed-search bin count");
-constexpr int kMaskWords = kObjBins / 32;
-constexpr float kSampleStep = 2.0f;                  // trajectory sampling step [cm]
-constexpr int kMaxSamples = 112;                     // 224 cm of arc
-
-__device__ __forceinline__ int ring_of(float r) {
-  const int k = (int)floorf((r - kRing0) / kRingW);
-  return k < 0 ? 0 : (k >= kRings ? kRings - 1 : k);
-}
-__device__ __forceinline__ int phibin_of(float ph) {
-  const int b = (int)floorf((ph + (float)M_PI) * (float)(kPhiBins / (2.0 * M_PI)));
-  return b < 0 ? 0 : (b >= kPhiBins ? kPhiBins - 1 : b);
-}
-__device__ __forceinline__ int zbin_of(float z) {
-  const int b = (int)floorf((z + kZHalf) / kZW);
-  return b < 0 ? 0 : (b >= kZBins ? kZBins - 1 : b);
-}
-template <int K>
-__device__ __forceinline__ int obj_bin(const Ws &w, int t) {
-  const float4 a = w.md_pos[K == 3 ? gload(w.t3_md, t).x : gp(w.t5_md)[5 * (long)t]];
-  const float ph = atan2f(a.y, a.x);
-  const int rp = ph == ph ? ring_of(sqrtf(a.x * a.x + a.y * a.y)) * kPhiBins + phibin_of(ph) : 0;
-  return rp * kZBins + zbin_of(a.z);
-}
-
-template <int K>
-__global__ void k_obj_bin_count(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = K == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
-  int *cnt = K == 3 ? w.b3_cnt : w.b5_cnt;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-    if (K == 3 || gp(w.t5_keep)[t]) atomicAdd(&cnt[obj_bin<K>(w, t)], 1);
-}
-template <int K>
-__global__ void k_obj_bin_scatter(const Ws *__restrict__ wb, DevGeom g) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = K == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
-  const int *off = K == 3 ? w.b3_off : w.b5_off;
-  int *cur = K == 3 ? w.b3_cur : w.b5_cur;
-  int *lst = K == 3 ? w.b3_list : w.b5_list;
-  float4 *pos = K == 3 ? w.b3_pos : w.b5_pos;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-    if (K == 3 || gp(w.t5_keep)[t]) {
-      const int b = obj_bin<K>(w, t);
-      const int j = off[b] + atomicAdd(&cur[b], 1);
-      lst[j] = t;
-      const int md = K == 3 ? gload(w.t3_md, t).x : gp(w.t5_md)[5 * (long)t];
-      const float4 a = gload(w.md_pos, md);
-      pos[j] = make_float4(a.x, a.y, a.z, __int_as_float(g.info[gp(w.md_mod)[md]]));
-    }
-}
-
-// Processing order of the seed search: seeds grouped by direction (azimuth of
-// the seed's direction in kPhiBins sectors x 8 bins of lambda), one block of
-// 1024 threads per event.  Seeds of one group scan nearly the same bins, so
-// waves that run together (consecutive blocks) reuse each other's object
-// lists in cache.  Results do not depend on the order (each seed writes only
-// its own entries), so ranks within a group come from LDS atomics.
-constexpr int kSeedKeys = kPhiBins * 8;
-__device__ __forceinline__ int seed_key(const Ws &w, int s) {
-  const float *p = w.pls + 8 * (long)s;
-  const float ph = atan2f(p[2], p[1]);
-  const int lb = (int)floorf((p[3] + 6.0f) * (1.0f / 1.5f));
-  return (ph == ph ? phibin_of(ph) : 0) * 8 + (lb < 0 ? 0 : (lb > 7 ? 7 : lb));
-}
-constexpr int kSeedKeyLds = 10240;  // seeds whose key the ordering keeps in LDS (the rest recompute it)
-__global__ __launch_bounds__(1024) void k_seed_order(const Ws *__restrict__ wb) {
-  __shared__ int s_cnt[kSeedKeys];
-  __shared__ unsigned short s_key[kSeedKeyLds];
-  __shared__ int s_wave[16];
-  static_assert(kSeedKeys <= 65536, "a key fits 16 bits");
-  const Ws &w = wb[blockIdx.y];
-  const int S = w.n_seeds, t = threadIdx.x, lane = lane_id(), wv = t >> 6;
-  for (int k = t; k < kSeedKeys; k += 1024) s_cnt[k] = 0;
-  __syncthreads();
-  for (int s = t; s < S; s += 1024) {
-    const int key = seed_key(w, s);
-    if (s < kSeedKeyLds) s_key[s] = (unsigned short)key;
-    atomicAdd(&s_cnt[key], 1);  // LDS
-  }
-  __syncthreads();
-  // exclusive scan of the key counts: two keys per thread, then over the block
-  static_assert(kSeedKeys == 2 * 1024, "two keys per thread");
-  const int c0 = s_cnt[2 * t], c1 = s_cnt[2 * t + 1];
-  int x = c0 + c1;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) s_wave[wv] = x;
-  __syncthreads();
-  int before = 0;
-  for (int q = 0; q < wv; ++q) before += s_wave[q];
-  const int ex = before + x - (c0 + c1);
-  s_cnt[2 * t] = ex;
-  s_cnt[2 * t + 1] = ex + c0;
-  __syncthreads();
-  for (int s = t; s < S; s += 1024) {
-    const int key = s < kSeedKeyLds ? (int)s_key[s] : seed_key(w, s);
-    gp(w.seed_order)[atomicAdd(&s_cnt[key], 1)] = s;  // LDS rank
   }
 }
 
@@ -2288,7 +2396,7 @@ __device__ __forceinline__ unsigned long long pt_obj_key(float score, int seed) 
 // The count pass searches both kinds on one mask per seed; the fill's first
 // n3 blocks take the triplets, the others the quintuplets.
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_pt_binned(const Ws *__restrict__ wb,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4 : 6))) void k_pt_binned(const Ws *__restrict__ wb,
                                                                                               DevGeom g, int n3) {
   __shared__ unsigned s_mask[kWaves][kMaskWords];
   __shared__ int s_slo[kWaves][kRings], s_shi[kWaves][kRings];
@@ -2296,8 +2404,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
   __shared__ int s_sl_j0[kWaves][kMaxSlices];       // bin id of each slice, then first list entry of each slice with candidates
   __shared__ int s_sl_pre[kWaves][kMaxSlices];      // candidates before each slice with candidates
   __shared__ int s_list[FILL ? kWaves : 1][FILL ? kPassList : 1];
-  __shared__ int s_pq[kWaves][128];  // candidates past the first-anchor test, awaiting the full one
+  __shared__ int s_pq[kWaves][128];  // MDs past the first-anchor test, their objects awaiting the full one
   __shared__ int s_mark[kWaves][64];  // a slice's candidates start here (this round)
+  __shared__ int s_seg[kWaves][65], s_first[kWaves][64];  // the queued MDs' objects
   const Ws &w = wb[blockIdx.y];
   const int wv = wave_id(), lane = lane_id();
   const bool five = FILL && (int)blockIdx.x >= n3;
@@ -2317,7 +2426,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
   const int pass_list = g.tiles.pass_list;                            // <= kPassList
   const int max_slices = g.tiles.max_slices;                          // <= kMaxSlices
   unsigned *mask = s_mask[wv];
-  auto mark_bins = [&] {  // the seed's (ring, azimuth) mask and z ranges
+  auto mark_bins = [&]() __attribute__((always_inline)) {  // the seed's (ring, azimuth) mask and z ranges
     for (int i = lane; i < kMaskWords; i += 64) mask[i] = 0u;
     if (lane < kRings) {
       s_slo[wv][lane] = 0x7f7fffff;  // largest finite float
@@ -2333,177 +2442,130 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  // the search over one object kind's bins (KO = 3: triplets, 5: quintuplets)
-  auto search = [&](auto kind) {
+  // entries of one kind (KO = 3: triplets, 5: quintuplets) that passed so far
+  int n_pass3 = 0, n_pass5 = 0;
+  // one entry of the output, which also offers its key to its outer object
+  auto put = [&](auto kind, int pos, int t, const float4 &attr) __attribute__((always_inline)) {
     constexpr int KO = decltype(kind)::value;
-    constexpr int kCacheO = KO == 3 ? kPt3Cache : kPt5Cache;
-    const int keepO = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;
-    int *cache = (KO == 3 ? w.pt3_cache : w.pt5_cache) + (long)s * kCacheO;
-    float4 *cattr = (KO == 3 ? w.pt3_cattr : w.pt5_cattr) + (long)s * kCacheO;
+    if (pos >= (KO == 3 ? w.cap_pt3 : w.cap_pt5)) return;
+    gstore(KO == 3 ? w.pt3_so : w.pt5_so, pos, make_int2(s, t));
+    gstore(KO == 3 ? w.pt3_attr : w.pt5_attr, pos, attr);
+    atomicMax((KO == 3 ? w.o3_best : w.o5_best) + t, pt_obj_key(attr.z, s));
+  };
+  // the full selection on one object per active lane; passing ones are counted in ballot
+  // order and remembered (count: the cache with their attributes; fill: the LDS list)
+  auto full = [&](auto kind, bool active, int t, int n_pass) __attribute__((always_inline)) {
+    constexpr int KO = decltype(kind)::value;
+    bool pass = false;
+    float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
+    // (quintuplets: those that survive the duplicate removal)
+    if (active && (KO == 3 || gp(w.t5_keep)[t] != 0)) {
+      float4 P[KO];
+      ModInfo M[KO];
+      float kT, dkT;
+      load_object<KO>(w, g, t, P, M, &kT, &dkT);
+      pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+    }
+    const unsigned long long m = __ballot(pass);
+    if (pass) {
+      const int r = n_pass + lanes_below(m);
+      if (FILL) {
+        if (r < kPassList) s_list[wv][r] = t;
+      } else if (r < (KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache)) {
+        constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
+        gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + r] = t;
+        gstore(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)s * kCache + r, attr);
+      }
+    }
+    return n_pass + __popcll(m);
+  };
+  // the objects of the first n (<= 64) queued MDs, flattened over the lanes, one kind after the other
+  auto expand = [&](auto kind, int n, int n_pass) __attribute__((always_inline)) {
+    constexpr int KO = decltype(kind)::value;
+    int first = 0, cnt = 0;
+    if (lane < n) {
+      const int4 r = gload(w.bin_rng, s_pq[wv][lane]);
+      first = KO == 3 ? r.x : r.z;
+      cnt = KO == 3 ? r.y : r.w;
+    }
+    s_first[wv][lane] = first;
+    const int total = wave_segments(cnt, s_seg[wv]);
+    const int start = s_seg[wv][lane];
+    int carry = 0;
+    for (int c0 = 0; c0 < total; c0 += 64) {
+      const int c = c0 + lane;
+      const int e = round_parent(start, cnt, c0, s_mark[wv], carry);
+      n_pass = full(kind, c < total, c < total ? s_first[wv][e] + (c - s_seg[wv][e]) : 0, n_pass);
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const int *boff = KO == 3 ? w.b3_off : w.b5_off;
-    const int *blst = KO == 3 ? w.b3_list : w.b5_list;
-    const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
-    int n_pass = 0;
-    int base = 0, expect = 0;
-    const int cap = KO == 3 ? w.cap_pt3 : w.cap_pt5;
-    int2 *so = KO == 3 ? w.pt3_so : w.pt5_so;
-    float4 *at = KO == 3 ? w.pt3_attr : w.pt5_attr;
-    // one entry of the output, which also offers its key to its outer object
-    auto put = [&](int pos, int t, const float4 &attr) {
-      if (pos >= cap) return;
-      gstore(so, pos, make_int2(s, t));
-      gstore(at, pos, attr);
-      atomicMax((KO == 3 ? w.o3_best : w.o5_best) + t, pt_obj_key(attr.z, s));
-    };
-    if constexpr (FILL) {
-      const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
-      int *offs = KO == 3 ? w.pt3_off : w.pt5_off;
-      base = pre;
-      for (int q = si - wv; q < si; ++q) base += uload(cnts + q);
-      expect = uload(cnts + s);
-      if (lane == 0) {
-        offs[s] = base;
-        if (s == w.n_seeds - 1) {
-          offs[s + 1] = base + expect;
-          put_total(w, base + expect, cap, KO == 3 ? C_RPT3 : C_RPT5, KO == 3 ? C_NPT3 : C_NPT5);
-        }
+    return n_pass;
+  };
+  // every marked bin's MDs through the exact first-anchor part of the selection (from the
+  // packed anchor); MDs passing it are queued, and their objects of the wanted kinds get the
+  // full selection
+  auto search = [&](auto want3, auto want5) __attribute__((always_inline)) {
+    // every marked (ring, azimuth) bin becomes a slice of the MD list (its reachable
+    // z bins, possibly empty); bit ids first, ranked over the wave by a prefix of the
+    // mask words' popcounts, then converted in place, 64 at a time, to (first entry,
+    // candidates before it)
+    int n_bits = 0;
+    for (int w0 = 0; w0 < kMaskWords; w0 += 64) {
+      const unsigned bits = w0 + lane < kMaskWords ? s_mask[wv][w0 + lane] : 0u;
+      const int pc = __popc(bits);
+      const int x = wave_inclusive(pc);
+      const int tot = __shfl(x, 63, 64);
+      if (n_bits + tot <= max_slices) {
+        int k = n_bits + x - pc;
+        for (unsigned bb = bits; bb; bb &= bb - 1u) s_sl_j0[wv][k++] = (w0 + lane) * 32 + __builtin_ctz(bb);
       }
-      if (expect <= keepO) {
-        // the count pass cached every passing object of this seed with its attributes:
-        // rank them by object index (in LDS) and copy, no search
-        for (int i = lane; i < expect; i += 64) s_list[wv][i] = gp(cache)[i];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int i = lane; i < expect; i += 64) {
-          const int t = s_list[wv][i];
-          int rank = 0;
-          for (int q = 0; q < expect; ++q) rank += s_list[wv][q] < t ? 1 : 0;
-          put(base + rank, t, gload(cattr, i));
-        }
-        return;
-      }
-      mark_bins();
+      n_bits += tot;
     }
-    const bool listed = !FILL || expect <= pass_list;
-    const float4 *bpos = KO == 3 ? w.b3_pos : w.b5_pos;
-    // the full selection on the first n (<= 64) queued objects; passing ones are counted
-    // in ballot order and remembered (count: the cache; fill: the LDS list)
-    auto full = [&](int n) {
-      bool pass = false;
-      int t = 0;
-      float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (lane < n) {
-        t = s_pq[wv][lane];
-        float4 P[KO];
-        ModInfo M[KO];
-        float kT, dkT;
-        load_object<KO>(w, g, t, P, M, &kT, &dkT);
-        pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-      }
-      const unsigned long long m = __ballot(pass);
-      if (pass) {
-        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-        if (FILL) {
-          if (n_pass + pre < kPassList) s_list[wv][n_pass + pre] = t;
-        } else if (n_pass + pre < keepO) {
-          cache[n_pass + pre] = t;
-          cattr[n_pass + pre] = attr;
-        }
-      }
-      n_pass += __popcll(m);
-    };
-    // one candidate per lane (list entry j): the exact first-anchor part of the selection
-    // from the packed anchor; objects passing it are queued, and the full selection runs
-    // on full waves of them
-    int nq = 0;
-    auto test = [&](bool active, int j) {
-      bool keep = false;
-      int t = 0;
-      if (active) {
-        t = blst[j];
-        const float4 f = bpos[j];
-        keep = pt_first_anchor(sd, f, ModInfo{__float_as_int(f.w)});
-      }
-      const unsigned long long m = __ballot(keep);
-      if (keep)
-        s_pq[wv][nq + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = t;
-      nq += __popcll(m);
+    const bool flat = n_bits <= max_slices;
+    int run = 0, n_live = 0;
+    if (flat) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if (nq >= 64) {
-        full(64);
-        const int rest = nq - 64;  // < 64: move the queue's tail to its front
-        const int v = lane < rest ? s_pq[wv][64 + lane] : 0;
+      // slices with candidates only, compacted in place (an entry is read before any
+      // write of its round, and compacted positions never pass the round's own)
+      for (int c0 = 0; c0 < n_bits; c0 += 64) {
+        const int k = c0 + lane;
+        int j0 = 0, len = 0;
+        if (k < n_bits) {
+          const int bin = s_sl_j0[wv][k];
+          const int2 zb = s_zb[wv][bin / kPhiBins];
+          j0 = gp(w.bin_off)[bin * kBinStride + zb.x];
+          len = gp(w.bin_off)[bin * kBinStride + zb.y + 1] - j0;
+        }
+        const int x = wave_inclusive(len);
+        const unsigned long long live = __ballot(len > 0);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if (lane < rest) s_pq[wv][lane] = v;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        nq = rest;
-      }
-    };
-    bool flat = false;
-    if (listed) {
-      // every marked (ring, azimuth) bin becomes a slice of the object list (its reachable
-      // z bins, possibly empty); bit ids first, ranked over the wave by a prefix of the
-      // mask words' popcounts, then converted in place, 64 at a time, to (first entry,
-      // candidates before it)
-      int n_bits = 0;
-      for (int w0 = 0; w0 < kMaskWords; w0 += 64) {
-        const unsigned bits = w0 + lane < kMaskWords ? s_mask[wv][w0 + lane] : 0u;
-        const int pc = __popc(bits);
-        int x = pc;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int y = __shfl_up(x, o, 64);
-          if (lane >= o) x += y;
+        if (len > 0) {
+          const int q = n_live + lanes_below(live);
+          s_sl_j0[wv][q] = j0;
+          s_sl_pre[wv][q] = run + x - len;
         }
-        const int tot = __shfl(x, 63, 64);
-        if (n_bits + tot <= max_slices) {
-          int k = n_bits + x - pc;
-          for (unsigned bb = bits; bb; bb &= bb - 1u) s_sl_j0[wv][k++] = (w0 + lane) * 32 + __builtin_ctz(bb);
-        }
-        n_bits += tot;
+        n_live += __popcll(live);
+        run += __builtin_amdgcn_readfirstlane(__shfl(x, 63, 64));
       }
-      flat = n_bits <= max_slices;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    // Rounds of 64 MDs, from the slices laid end to end (flat), or, with more marked bins
+    // than the slice table holds, bin by bin; one place that drains the queue.
+    int c0 = 0, jlo = 0;                       // flat: round start, slices that start before it
+    int wd = -1, j_at = 0, j_end = 0;          // bin by bin: mask word, list entries left of a bin
+    unsigned bits = 0u;
+    int nq = 0;
+    for (bool last = false;;) {
+      bool active = false;
+      int j = 0;
       if (flat) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // slices with candidates only, compacted in place (an entry is read before any
-        // write of its round, and compacted positions never pass the round's own)
-        int run = 0, n_live = 0;
-        for (int c0 = 0; c0 < n_bits; c0 += 64) {
-          const int k = c0 + lane;
-          int j0 = 0, len = 0;
-          if (k < n_bits) {
-            const int bin = s_sl_j0[wv][k];
-            const int2 zb = s_zb[wv][bin / kPhiBins];
-            j0 = boff[bin * kZBins + zb.x];
-            len = boff[bin * kZBins + zb.y + 1] - j0;
-          }
-          int x = len;
-          for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-          }
-          const unsigned long long live = __ballot(len > 0);
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          if (len > 0) {
-            const int q = n_live + lanes_below(live);
-            s_sl_j0[wv][q] = j0;
-            s_sl_pre[wv][q] = run + x - len;
-          }
-          n_live += __popcll(live);
-          run += __builtin_amdgcn_readfirstlane(__shfl(x, 63, 64));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // the slice of each lane's candidate: the slices starting before the round (jlo)
-        // plus those starting at or below the lane in it (distinct starts, marked)
-        int jlo = 0;
-        for (int c0 = 0; c0 < run; c0 += 64) {
+        last = c0 >= run;
+        if (!last) {
+          // the slice of each lane's candidate: the slices starting before the round (jlo)
+          // plus those starting at or below the lane in it (distinct starts, marked)
           const int c = c0 + lane;
           s_mark[wv][lane] = 0;
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2515,91 +2577,136 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
           const unsigned long long starts = __ballot(s_mark[wv][lane] != 0);
-          int j = 0;
-          if (c < run) {
+          active = c < run;
+          if (active) {
             const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
             const int e = jlo - 1 + __popcll(starts & upto);
             j = s_sl_j0[wv][e] + (c - s_sl_pre[wv][e]);
           }
           jlo += __popcll(starts);
-          test(c < run, j);
+          c0 += 64;
         }
-      }
-    }
-    if (listed && !flat) {
-      n_pass = 0;
-      nq = 0;
-      for (int wd = 0; wd < kMaskWords; ++wd) {
-        unsigned bits = mask[wd];
-        while (bits) {
-          const int bit = __builtin_ctz(bits);
-          bits &= bits - 1u;
-          const int bin = wd * 32 + bit;
-          const int2 zb = s_zb[wv][bin / kPhiBins];
-          const int j0 = boff[bin * kZBins + zb.x], j1 = boff[bin * kZBins + zb.y + 1];
-          for (int j = j0 + lane; j - lane < j1; j += 64) test(j < j1, j);
+      } else {
+        while (j_at >= j_end && !last) {  // the next marked bin with MDs
+          while (bits == 0u && ++wd < kMaskWords) bits = mask[wd];
+          last = wd >= kMaskWords;
+          if (!last) {
+            const int bin = wd * 32 + __builtin_ctz(bits);
+            bits &= bits - 1u;
+            const int2 zb = s_zb[wv][bin / kPhiBins];
+            j_at = uload(w.bin_off + bin * kBinStride + zb.x);
+            j_end = uload(w.bin_off + bin * kBinStride + zb.y + 1);
+          }
         }
+        j = j_at + lane;
+        active = !last && j < j_end;
+        j_at += 64;
       }
-    }
-    if (listed && nq > 0) full(nq);
-    if (!FILL) {
-      if (lane == 0) {
-        (KO == 3 ? w.pt3_cnt : w.pt5_cnt)[s] = n_pass;
-        if (n_pass > 0) atomicAdd((KO == 3 ? w.ts_p3 : w.ts_p5) + (s >> w.sh_pt) * kSumStride, n_pass);
+      bool keep = false;
+      if (active) {
+        const float4 f = gload(w.bin_pos, j);
+        keep = pt_first_anchor(sd, f, ModInfo{__float_as_int(f.w)});
       }
-      return;
-    }
-    if (listed) {
+      const unsigned long long m = __ballot(keep);
+      if (keep) s_pq[wv][nq + lanes_below(m)] = j;
+      nq += __popcll(m);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      // rank by object index (indices are distinct) and write in object order
-      for (int i = lane; i < n_pass; i += 64) {
-        const int t = s_list[wv][i];
-        int rank = 0;
-        for (int q = 0; q < n_pass; ++q) rank += s_list[wv][q] < t ? 1 : 0;
-        const int pos = base + rank;
-        if (pos < cap) {
-          float4 P[KO];
-          ModInfo M[KO];
-          float kT, dkT;
-          float4 attr;
-          load_object<KO>(w, g, t, P, M, &kT, &dkT);
-          pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-          put(pos, t, attr);
+      if (nq >= 64 || (last && nq > 0)) {
+        const int n = nq < 64 ? nq : 64;
+        if constexpr (decltype(want3)::value) n_pass3 = expand(std::integral_constant<int, 3>{}, n, n_pass3);
+        if constexpr (decltype(want5)::value) n_pass5 = expand(std::integral_constant<int, 5>{}, n, n_pass5);
+        queue_pop64(s_pq[wv], nq - n);
+        nq -= n;
+      }
+      if (last && nq == 0) break;
+    }
+  };
+  if constexpr (!FILL) {  // both kinds in one search
+    mark_bins();
+    search(std::true_type{}, std::true_type{});
+    if (lane == 0) {
+      gp(w.pt3_cnt)[s] = n_pass3;
+      gp(w.pt5_cnt)[s] = n_pass5;
+      if (n_pass3 > 0) atomicAdd(w.ts_p3 + (s >> w.sh_pt) * kSumStride, n_pass3);
+      if (n_pass5 > 0) atomicAdd(w.ts_p5 + (s >> w.sh_pt) * kSumStride, n_pass5);
+    }
+    return;
+  }
+  auto fill = [&](auto kind) __attribute__((always_inline)) {
+    constexpr int KO = decltype(kind)::value;
+    constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
+    const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;  // <= kCache
+    const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
+    int *offs = KO == 3 ? w.pt3_off : w.pt5_off;
+    int base = pre;
+    for (int q = si - wv; q < si; ++q) base += uload(cnts + q);
+    const int expect = uload(cnts + s);
+    if (lane == 0) {
+      offs[s] = base;
+      if (s == w.n_seeds - 1) {
+        offs[s + 1] = base + expect;
+        put_total(w, base + expect, KO == 3 ? w.cap_pt3 : w.cap_pt5, KO == 3 ? C_RPT3 : C_RPT5,
+                  KO == 3 ? C_NPT3 : C_NPT5);
+      }
+    }
+    const bool cached = expect <= keep;
+    if (expect > pass_list && !cached) {
+      // rare: too many passing objects for the LDS list; ordered scan of all objects
+      const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
+      const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
+      for (int t0 = 0; t0 < n_obj; t0 += 64) {
+        const int t = t0 + lane;
+        bool pass = false;
+        float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
+          const float2 f = first[t];
+          if (seed_box(sd, f.x, f.y)) {
+            float4 P[KO];
+            ModInfo M[KO];
+            float kT, dkT;
+            load_object<KO>(w, g, t, P, M, &kT, &dkT);
+            pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+          }
         }
+        const unsigned long long m = __ballot(pass);
+        if (pass) put(kind, base + lanes_below(m), t, attr);
+        base += __popcll(m);
       }
       return;
     }
-    // rare: too many passing objects for the LDS list; ordered scan of all objects
-    const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
-    for (int t0 = 0; t0 < n_obj; t0 += 64) {
-      const int t = t0 + lane;
-      bool pass = false;
-      float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
-        const float2 f = first[t];
-        if (seed_box(sd, f.x, f.y)) {
-          float4 P[KO];
-          ModInfo M[KO];
-          float kT, dkT;
-          load_object<KO>(w, g, t, P, M, &kT, &dkT);
-          pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-        }
+    // the passing objects: what the count pass cached with their attributes, or searched again
+    int n = expect;
+    if (cached) {
+      for (int i = lane; i < expect; i += 64)
+        s_list[wv][i] = gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + i];
+    } else {
+      mark_bins();
+      search(std::integral_constant<bool, KO == 3>{}, std::integral_constant<bool, KO == 5>{});
+      n = KO == 3 ? n_pass3 : n_pass5;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // rank by object index (indices are distinct) and write in object order
+    for (int i = lane; i < n; i += 64) {
+      const int t = s_list[wv][i];
+      int rank = 0;
+      for (int q = 0; q < n; ++q) rank += s_list[wv][q] < t ? 1 : 0;
+      float4 attr;
+      if (cached) {
+        attr = gload(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)s * kCache + i);
+      } else {
+        float4 P[KO];
+        ModInfo M[KO];
+        float kT, dkT;
+        load_object<KO>(w, g, t, P, M, &kT, &dkT);
+        pt_pass<KO>(sd, P, M, kT, dkT, &attr);
       }
-      const unsigned long long m = __ballot(pass);
-      const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-      if (pass) put(base + pre, t, attr);
-      base += __popcll(m);
+      put(kind, base + rank, t, attr);
     }
   };
-  if constexpr (FILL) {
-    if (five) search(std::integral_constant<int, 5>{});
-    else search(std::integral_constant<int, 3>{});
-  } else {  // both kinds on one trajectory mask
-    mark_bins();
-    search(std::integral_constant<int, 3>{});
-    search(std::integral_constant<int, 5>{});
-  }
+  if (five) fill(std::integral_constant<int, 5>{});
+  else fill(std::integral_constant<int, 3>{});
 }
 
 template <int K>
@@ -3205,7 +3312,7 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   const bool whole = kt && kt->site == kChainSite;  // the timer brackets the whole chain
   if (whole) (void)hipEventRecord(kt->beg, st);
   // a0: buckets
-  run([&] { k_clear<<<grid(32768), kBlock, 0, st>>>(wb, FL_CTR, FL_TS + 1); });
+  run([&] { k_start<<<grid(seeds ? kSeedBins : 4096), kBlock, 0, st>>>(wb); });
   const long n_tiles = n_hit_tiles(N), n_co = n_coarse(M);
   run([&] {  // one block per hit tile, and enough threads for the seeds' validation
     const long blocks = std::max(n_tiles, (S + kBlock - 1) / kBlock);
@@ -3230,7 +3337,11 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
     const int lg = ls_group_for(g.tiles, B, b.cap_md);
     k_ls_count<<<gridwb((b.cap_md + lg - 1) / lg), tb, 0, st>>>(wb, g, lg);
   });
-  run([&] { k_ls_sums<<<dim3((unsigned)std::min<long>(n_sum_tiles(b.cap_md), 256), B), kBlock, 0, st>>>(wb, g.tiles.ls_cache); });
+  run([&] {
+    const unsigned n_sum = (unsigned)std::min<long>(n_sum_tiles(b.cap_md), 256);
+    const unsigned n_seed = seeds ? grid(S).x : 0;
+    k_ls_sums<<<dim3(n_sum + n_seed, B), kBlock, 0, st>>>(wb, g.tiles.ls_cache, (int)n_sum);
+  });
   run([&] {
     const unsigned n_copy = gridwt((b.cap_md + kLsCopyMds - 1) / kLsCopyMds).x;
     const unsigned n_ovf = gridwt(std::min(b.cap_md, 4096)).x;  // the overflow MDs (428 on a PU200 event)
@@ -3241,43 +3352,33 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   run([&] {});  // t3_scan
   run([&] { k_t3<true><<<gridwb((b.cap_ls + 63) / 64), tb, 0, st>>>(wb, g); });
   // a4: T5
-  run([&] { k_t5<false><<<gridwb((b.cap_t3 + 63) / 64), tb, 0, st>>>(wb, g); });
+  // (with the seed search's bins in further blocks)
+  run([&] {
+    const dim3 d = gridwb((b.cap_t3 + 63) / 64);
+    const unsigned nq = seeds ? share(grid_for(b.cap_md, tb), tb) : 0;
+    k_t5<false><<<dim3(d.x + nq, B), tb, 0, st>>>(wb, g, (int)d.x);
+  });
   run([&] {});  // t5_scan
-  run([&] { k_t5<true><<<gridwb((b.cap_t3 + 63) / 64), tb, 0, st>>>(wb, g); });
+  run([&] {
+    const dim3 d = gridwb((b.cap_t3 + 63) / 64);
+    const int rows = (tb / 64) * kRowsPerWave;
+    const unsigned nq = seeds ? (kBinRows + rows - 1) / rows : 0;
+    k_t5<true><<<dim3(d.x + nq, B), tb, 0, st>>>(wb, g, (int)d.x);
+  });
   // a5: T5 duplicate removal through per-MD incidence lists
   run([&] {
-    k_clear<<<grid((long)b.cap_md + 1), kBlock, 0, st>>>(wb, FL_INC_CNT, FL_INC_CUR + 1);
-    k_t5_inc_count<<<grid(b.cap_t5), kBlock, 0, st>>>(wb);
+    const unsigned n5 = grid(4L * b.cap_t5).x, nq = seeds ? grid(b.cap_md).x : 0;
+    k_t5_inc<<<dim3(n5 + nq, B), kBlock, 0, st>>>(wb, g, (int)n5);
   });
-  run([&] { scan(wb, B, SC_INC, b.cap_md, st); });
-  run([&] { k_t5_inc_scatter<<<grid(b.cap_t5), kBlock, 0, st>>>(wb); });
+  run([&] { k_list_place<<<grid((b.cap_md + 1) / 2), kBlock, 0, st>>>(wb); });
+  run([&] { k_t5_inc_scatter<<<grid(5L * b.cap_t5), kBlock, 0, st>>>(wb); });
   run([&] {
     const int ipw = B == 1 ? 16 : 64;
     k_t5_dedup<<<gridwb((4L * b.cap_t5 + ipw - 1) / ipw), tb, (tb / 64) * kT5DedupLds, st>>>(wb, ipw);
   });
-  // a6: pLS
-  run([&] {
-    k_clear<<<grid(N + 1), kBlock, 0, st>>>(wb, FL_PH_CNT, FL_PH_CUR + 1);
-    if (seeds) k_pls<<<grid(S), kBlock, 0, st>>>(wb);
-  });
-  run([&] { if (seeds) scan(wb, B, SC_PH, N, st); });
-  run([&] { if (seeds) k_ph_scatter<<<grid(S), kBlock, 0, st>>>(wb); });
-  run([&] { if (seeds) k_pls_dedup<<<grid(S), kBlock, 0, st>>>(wb); });
-  // a7: pT3, pT5: objects binned by first anchor, one wave per seed over its bins
-  run([&] {
-    if (!seeds) return;
-    k_clear<<<grid(kSeedBins + 1), kBlock, 0, st>>>(wb, FL_B3_CNT, FL_B5_CUR + 1);
-    k_seed_order<<<one, 1024, 0, st>>>(wb);
-    k_obj_bin_count<3><<<grid(b.cap_t3), kBlock, 0, st>>>(wb);
-    scan(wb, B, SC_B3, kSeedBins, st);
-    k_obj_bin_scatter<3><<<grid(b.cap_t3), kBlock, 0, st>>>(wb, g);
-  });
-  run([&] {
-    if (!seeds) return;
-    k_obj_bin_count<5><<<grid(b.cap_t5), kBlock, 0, st>>>(wb);
-    scan(wb, B, SC_B5, kSeedBins, st);
-    k_obj_bin_scatter<5><<<grid(b.cap_t5), kBlock, 0, st>>>(wb, g);
-  });
+  // a6: pLS (with the hit count and the segment sums); a7's bins (with the quintuplets)
+  for (int q = 0; q < 6; ++q) run([&] {});  // pls, its hit lists and duplicate removal, pt3_bin, pt5_bin
+  // a7: pT3, pT5: one wave per seed over its bins;
   // both counts on one trajectory mask per seed, both fills in one launch
   run([&] { if (seeds) k_pt_binned<false><<<seedwaves(), tb, 0, st>>>(wb, g, 0); });
   run([&] {});  // pt3_scan
@@ -3293,8 +3394,6 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   run([&] { if (seeds) k_pt_dedup<5><<<dim3(grid_waves(S), B), kBlock, 0, st>>>(wb); });
   // a8: cleaning and track candidates
   run([&] {
-    const long n = (long)(S > b.cap_t5 ? S : b.cap_t5) + 1;
-    k_clear<<<grid(n), kBlock, 0, st>>>(wb, FL_SEED_USED, FL_T5_USED + 1);
     k_tc_pt5<<<grid(b.cap_pt5), kBlock, 0, st>>>(wb);
   });
   run([&] { scan(wb, B, SC_F5, b.cap_pt5, st); });

@@ -13,7 +13,7 @@ enum Ctr : int {
   C_RMD = 9, C_RLS, C_RT3, C_RT5, C_RPT3, C_RPT5,                      // required counts
   C_NT5KEEP = 15, C_NTC0 = 16, C_NTC1, C_NTC2, C_NTC3,                 // survivors, TCs per type
   C_NOUTER = 20, C_NINC = 21, C_NPH = 22, C_NO3 = 23, C_NO5 = 24,      // scratch totals
-  C_NB3 = 25, C_NB5 = 26,
+  C_NBIN = 25,
   C_NLSOVF = 27,                 // MDs with more segments than the count pass caches
   C_NEXTHITS = 28,               // hits of the extended track-candidate collection
   C_EXT = 29,                    // 1 once the track extensions of the event are written
@@ -65,21 +65,14 @@ struct ScanJob {
   int cap;
 };
 enum ScanId : int {
-  SC_HITS, SC_MD, SC_INC, SC_PH, SC_F5, SC_F3, SC_FT5, SC_FPLS, SC_B3, SC_B5, SC_EXT, SC_COUNT
+  SC_HITS, SC_MD, SC_F5, SC_F3, SC_FT5, SC_FPLS, SC_EXT, SC_COUNT
 };
-// One array cleared to zero at the start of the chain.
-// n: the array's length; with n_dev, only its first mul * (*n_dev + 1)
-// entries (the device-side count of what it is indexed by, plus one) when
-// that is fewer.
+// One array cleared to zero at the start of the chain: n entries, `stride` ints apart.
 struct FillJob {
   int *p;
-  long n;
-  const int *n_dev;
-  int mul;
+  int n, stride;
 };
-enum FillId : int {
-  FL_CTR, FL_TS, FL_INC_CNT, FL_INC_CUR, FL_PH_CNT, FL_PH_CUR, FL_SEED_USED, FL_T5_USED, FL_B3_CNT, FL_B3_CUR, FL_B5_CNT, FL_B5_CUR, FL_COUNT
-};
+enum FillId : int { FL_CTR, FL_TS, FL_SEED_CNT, FL_SEED_USED, FL_BIN_CNT, FL_COUNT };
 
 // Sums a count pass keeps so that its fill pass finds its own output offsets
 // (no scan launches between them): one sum per tile of 2^tile_shift(capacity)
@@ -123,9 +116,11 @@ constexpr int kExtPerWaveMax = 16;
 constexpr Tiles kTilesDefault{kMdCache, kLsCache, kT3Cache, kT5Cache, kPt3Cache, kPt5Cache, kPassList, kMaxSlices, 8, 0};
 
 // First-anchor bins of the seed search: 10 radius rings x 256 azimuth bins x
-// 55 z bins (10 cm over |z| < 275 cm); bins of one (ring, azimuth) pair are
-// contiguous, z ascending.
-constexpr int kSeedBins = 10 * 256 * 55;
+// 55 z bins (10 cm over |z| < 275 cm); bins of one (ring, azimuth) pair, a row,
+// are contiguous, z ascending, with the row's end as a 56th offset.
+constexpr int kBinRows = 10 * 256, kZBins = 55, kBinStride = kZBins + 1;
+constexpr int kSeedBins = kBinRows * kBinStride;
+constexpr int kSeedKeys = 256 * 8;  // direction groups of the seeds' processing order
 
 // Device pointers of one event (all inside the workspace except the inputs).
 // Kernels of a batch read descriptor blockIdx.y of a device array of these.
@@ -175,13 +170,19 @@ struct Ws {
   int *t5_keep;
   float2 *t5_first;
   int *t5_cache;    // per triplet: up to kT5Cache passing candidate triplets of the count pass
-  int *inc_cnt, *inc_off, *inc_cur;
+  // T5s on each MD (until the lists are placed: those it is not the first MD of), where
+  // its list starts (lists in any order), and what its T5s as first MD add to their index
+  int *inc_cnt, *inc_off, *inc_b0;
+  int *t5_slot;     // 4 per T5: its place in the lists of its second to fifth MDs
   int2 *inc_list;   // T5s containing each MD: (T5, bits of its chi2_xy score)
   // pixel seeds
   float *pls;       // 8 per seed: pT, cx, cy, lambda, kappa, x0, y0, z0
   int *pls_keep;
   int *seed_order;  // seeds in the seed search's processing order (grouped by direction)
-  int *ph_cnt, *ph_off, *ph_cur, *ph_list;      // seeds using each pixel hit
+  int *seed_key, *seed_slot, *seed_cnt;  // each seed's direction group and place in it; seeds per group
+  // seeds using each pixel hit, as linked lists of (4 seed + hit number): the hit's
+  // first entry (-1: none; set for the seeds' hits only) and each entry's next one
+  int *ph_head, *ph_next;
   // pixel triplets / quintuplets
   int *pt3_cnt, *pt3_off, *pt5_cnt, *pt5_off;
   int *pt3_cache, *pt5_cache;  // per seed: up to kPt3Cache / kPt5Cache passing objects found by the count pass
@@ -192,9 +193,13 @@ struct Ws {
   // per T3 / T5: the largest ~(score bits << 32 | seed) of the pT3 / pT5 entries on it,
   // i.e. its entry with the smallest (score, seed) (scores are >= 0, so their bits order them)
   unsigned long long *o3_best, *o5_best;
-  int *b3_cnt, *b3_off, *b3_cur, *b3_list;      // T3s by first-anchor (ring, azimuth, z) bin
-  int *b5_cnt, *b5_off, *b5_cur, *b5_list;      // surviving T5s by the same bins
-  float4 *b3_pos, *b5_pos;  // per list entry: the object's first anchor x, y, z and module info bits
+  // MDs that start a triplet, by (ring, azimuth, z) bin of their anchor: counts and offsets
+  // per bin, each MD's bin (-1: none) and place in it, and per list entry the anchor x, y, z
+  // with the module info bits and the MD's triplets and quintuplets (first, count, first, count)
+  int *bin_cnt, *bin_off;
+  int2 *md_bin;
+  float4 *bin_pos;
+  int4 *bin_rng;
   // track candidates
   int *seed_used, *t5_used;
   int *f_pt5, *f_pt3, *f_t5, *f_pls;            // TC flags
