@@ -154,7 +154,7 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.t5_keep = I(t5); t.t5_first = F2(t5);
   t.inc_cnt = I(md); t.inc_off = I(md); t.inc_list = I2(5 * t5);
   t.pls = F(8 * S); t.pls_keep = I(S); t.seed_order = I(S + 1);
-  t.seed_cnt = I(kSeedKeys);
+  t.seed_cnt = I(kSeedKeys + kDirBins);
   t.ph_head = I(N); t.ph_next = I(4 * S);
   t.pt3_cnt = I(S + 1); t.pt3_off = I(S + 1); t.pt5_cnt = I(S + 1); t.pt5_off = I(S + 1);
   t.pt3_cache = I(kPt3Cache * S); t.pt5_cache = I(kPt5Cache * S);
@@ -165,12 +165,12 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.o5_best = reinterpret_cast<unsigned long long *>(take(8 * (size_t)(t5 + 1)));
   const long nbins = kSeedBins;
   t.bin_cnt = I(nbins); t.bin_off = I(nbins);
-  t.seed_used = I(S + 1); t.t5_used = I(t5 + 1);
-  t.f_pt5 = I(p5 + 1); t.f_pt3 = I(p3 + 1); t.f_t5 = I(t5 + 1); t.f_pls = I(S + 1);
-  t.p_pt5 = I(p5 + 1); t.p_pt3 = I(p3 + 1); t.p_t5 = I(t5 + 1); t.p_pls = I(S + 1);
-  t.dir_pt5 = F4(p5); t.dir_pt3 = F4(p3); t.dir_t5 = F4(t5);
-  t.bdir_pt5 = F4(p5); t.bdir_pt3 = F4(p3); t.bdir_t5 = F4(t5);
-  t.boff_pt5 = I(129); t.boff_pt3 = I(129); t.boff_t5 = I(129);
+  t.t5_used = I(t5 + 1);
+  t.sdir_tc = I(S); t.w_pt5 = I(S); t.w_pt3 = I(S); t.sdir_off = I(kDirBins + 1);
+  const long sw = (S >> 6) + 1, tw = (t5 >> 6) + 1;  // words of seed / quintuplet flags
+  t.m_pt5 = reinterpret_cast<unsigned long long *>(take(8 * (size_t)(3 * sw + tw)));
+  t.m_pt3 = t.m_pt5 + sw; t.m_pls = t.m_pt3 + sw; t.m_t5 = t.m_pls + sw;
+  t.pls_near = reinterpret_cast<unsigned *>(I(2 * sw));
   t.tc_type = I(tc); t.tc_off = I(tc + 1); t.tc_hits = I(14 * tc);
   t.tc_md = I(5 * tc); t.tc_kap = F2(tc);
   t.ext_n = I(tc); t.ext_t3 = I(tc); t.ext_cnt = I(tc + 1); t.ext_off = I(tc + 1); t.ext_hits = I(18 * tc);
@@ -185,7 +185,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.md_bin = reinterpret_cast<int2 *>(t.bin_rng + md);
   t.inc_b0 = reinterpret_cast<int *>(t.md_bin + md);
   t.t5_slot = t.tc_hits;                       // 4 t5 <= 14 tc
-  t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;  // 2 S <= 5 tc
+  t.sdir = reinterpret_cast<float4 *>(t.tc_hits + 4 * t5);  // and 4 S + S more
+  t.sdir_pos = t.tc_hits + 4 * t5 + 4 * S;
+  t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;          // 4 S <= 5 tc
+  t.dir_key = t.tc_md + 2 * S; t.dir_slot = t.tc_md + 3 * S;
   // the tile sums, one after another (cleared together)
   const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
   const long n_ts = (nl + n3 + n5 + 2 * np) * kSumStride;
@@ -212,16 +215,13 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
     const long nt_cap = (long)n_coarse((int)M) * n_hit_tiles(n_hits_alloc >= 0 ? n_hits_alloc : n_hits);
     sj(SC_HITS, t.tile_hist, t.tile_off, nullptr, nt, nt_cap, ct + C_NOUTER, nullptr, 0);
     sj(SC_MD, t.md_cnt, t.md_off, nullptr, M, M, ct + C_RMD, ct + C_NMD, md);
-    sj(SC_F5, t.f_pt5, t.p_pt5, ct + C_NPT5, 0, p5, ct + C_NTC0, nullptr, 0);
-    sj(SC_F3, t.f_pt3, t.p_pt3, ct + C_NPT3, 0, p3, ct + C_NTC1, nullptr, 0);
-    sj(SC_FT5, t.f_t5, t.p_t5, ct + C_NT5, 0, t5, ct + C_NTC2, nullptr, 0);
-    sj(SC_FPLS, t.f_pls, t.p_pls, nullptr, S, S, ct + C_NTC3, nullptr, 0);
     sj(SC_EXT, t.ext_cnt, t.ext_off, ct + C_NTC, 0, p5 + p3 + t5 + S, ct + C_NEXTHITS, nullptr, 0);
     const auto fj = [&](int id, int *p, long n, int stride = 1) { t.fills[id] = FillJob{p, (int)n, stride}; };
     fj(FL_CTR, ct, C_COUNT);
     fj(FL_TS, t.ts_ls, n_ts / kSumStride, kSumStride);
-    fj(FL_SEED_CNT, t.seed_cnt, S > 0 ? kSeedKeys : 0);
-    fj(FL_SEED_USED, t.seed_used, S);
+    fj(FL_SEED_CNT, t.seed_cnt, S > 0 ? kSeedKeys + kDirBins : 0);
+    fj(FL_SEED_TC, t.sdir_tc, S);
+    fj(FL_PLS_NEAR, reinterpret_cast<int *>(t.pls_near), S > 0 ? 2 * ((S >> 6) + 1) : 0);
     fj(FL_BIN_CNT, t.bin_cnt, S > 0 ? nbins : 0);
   }
   if (w) *w = t;

@@ -362,6 +362,23 @@ __device__ __forceinline__ int seed_key(float cx, float cy, float lam) {
   return (ph == ph ? phibin_of(ph) : 0) * 8 + (lb < 0 ? 0 : (lb > 7 ? 7 : lb));
 }
 
+// Proximity queries (near_dir) read the seeds' directions at the beam line,
+// binned by azimuth, so that a query reads only the bins that can hold a near
+// entry.  Near entries have |dphi| < asin(D) (the test requires sin^2 dphi < D^2
+// and a positive dot product), so with bins of width 2 pi / kDirBins the query
+// covers ceil(asin(D) / width) + 1 bins on each side, one more than needed to
+// absorb atan2f rounding.  The decision itself is near_dir, unchanged.
+__device__ __forceinline__ int dir_bin(float dx, float dy) {
+  const float ph = atan2f(dy, dx);
+  if (!(ph == ph)) return 0;
+  const int b = (int)floorf((ph + (float)M_PI) * (float)(kDirBins / (2.0 * M_PI)));
+  return b < 0 ? 0 : (b >= kDirBins ? kDirBins - 1 : b);
+}
+constexpr int bin_reach(double D) {
+  // ceil(asin(D) / (2 pi / kDirBins)) + 1 for the D values used (asin(D) < 1.0005 D for D <= 0.05)
+  return (int)(D * 1.0005 / (2.0 * 3.14159265358979 / kDirBins)) + 2;
+}
+
 // ------------------------------------------------------------- a0: hits
 // Hits are bucketed by key = 2 module + sensor, stably (input order within a
 // key), with no global atomic: an LSD-free two-level counting sort.
@@ -419,6 +436,14 @@ __device__ __forceinline__ int bits_for(int n) {  // bits of the values 0 .. n -
   return b;
 }
 
+// ------------------------------------------------------------- a6: pLS
+__device__ __forceinline__ Seed load_seed(const Ws &w, int s) {
+  const float *p = w.pls + 8 * (long)s;
+  Seed sd;
+  sd.pt = p[0]; sd.cx = p[1]; sd.cy = p[2]; sd.lam = p[3]; sd.ks = p[4]; sd.x0 = p[5]; sd.y0 = p[6]; sd.z0 = p[7];
+  return sd;
+}
+
 // Pixel line segment of seed s (Section 2.4): validated (returns true if its
 // data are invalid), its parameters computed, entered in the lists of its pixel
 // hits and counted in its direction group.
@@ -449,6 +474,10 @@ __device__ __forceinline__ bool seed_prepare(const Ws &w, int s) {
   const int key = seed_key(cx, cy, lam);
   gp(w.seed_key)[s] = key;
   gp(w.seed_slot)[s] = atomicAdd(w.seed_cnt + key, 1);
+  const Dir d = seed_dir(load_seed(w, s));  // (this thread's own stores)
+  const int db = dir_bin(d.dx, d.dy);
+  gp(w.dir_key)[s] = db;
+  gp(w.dir_slot)[s] = atomicAdd(w.seed_cnt + kSeedKeys + db, 1);
   return bad;
 }
 
@@ -1300,7 +1329,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 //
 // Blocks from n_sum on do what the pixel stages need and nothing else waits for:
 // the seeds' processing order (every block scans the group counts for itself)
-// and the pLS duplicate removal (seeds sharing at least 3 pixel hits; the lower
+// (and that of their directions) and the pLS duplicate removal (seeds sharing at least 3 pixel hits; the lower
 // seed index wins).
 __device__ __forceinline__ bool pls_survives(const Ws &w, int s) {
   int hs[4];
@@ -1326,29 +1355,41 @@ __device__ __forceinline__ bool pls_survives(const Ws &w, int s) {
 
 __global__ __launch_bounds__(kBlock) void k_ls_sums(const Ws *__restrict__ wb, int keep, int n_sum) {
   __shared__ int s_red[kWaves];
-  __shared__ int s_off[kSeedKeys];
+  __shared__ int s_off[kSeedKeys], s_dir[kDirBins];
   const Ws &w = wb[blockIdx.y];
   if ((int)blockIdx.x >= n_sum) {
     const int S = w.n_seeds, t = threadIdx.x, lane = lane_id();
     const int q0 = ((int)blockIdx.x - n_sum) * kBlock;
     if (q0 >= S) return;  // the whole block
-    constexpr int kPer = kSeedKeys / kBlock;
-    int c[kPer], sum = 0;
+    // exclusive prefixes of the group counts and of the azimuth bins' (each from 0)
+    auto prefix = [&](const int *cnt, int *off, auto per) {
+      constexpr int kPer = decltype(per)::value;
+      int c[kPer], sum = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) sum += c[i] = gp(w.seed_cnt)[t * kPer + i];
-    const int x = wave_inclusive(sum);
-    if (lane == 63) s_red[t >> 6] = x;
-    __syncthreads();
-    int ex = x - sum;
-    for (int q = 0; q < (t >> 6); ++q) ex += s_red[q];
+      for (int i = 0; i < kPer; ++i) sum += c[i] = gp(cnt)[t * kPer + i];
+      const int x = wave_inclusive(sum);
+      __syncthreads();
+      if (lane == 63) s_red[t >> 6] = x;
+      __syncthreads();
+      int ex = x - sum;
+      for (int q = 0; q < (t >> 6); ++q) ex += s_red[q];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      s_off[t * kPer + i] = ex;
-      ex += c[i];
-    }
+      for (int i = 0; i < kPer; ++i) {
+        off[t * kPer + i] = ex;
+        ex += c[i];
+      }
+    };
+    prefix(w.seed_cnt, s_off, std::integral_constant<int, kSeedKeys / kBlock>{});
+    prefix(w.seed_cnt + kSeedKeys, s_dir, std::integral_constant<int, kDirBins / kBlock>{});
     __syncthreads();
+    if (q0 == 0)
+      for (int b = t; b <= kDirBins; b += kBlock) gp(w.sdir_off)[b] = b < kDirBins ? s_dir[b] : S;
     for (int s = q0 + t; s < S; s += ((int)gridDim.x - n_sum) * kBlock) {
       gp(w.seed_order)[s_off[gp(w.seed_key)[s]] + gp(w.seed_slot)[s]] = s;
+      const Dir d = seed_dir(load_seed(w, s));
+      const int pos = s_dir[gp(w.dir_key)[s]] + gp(w.dir_slot)[s];
+      gstore(w.sdir, pos, make_float4(d.dx, d.dy, d.lam, __int_as_float(s)));
+      gp(w.sdir_pos)[s] = pos;
       gp(w.pls_keep)[s] = pls_survives(w, s) ? 1 : 0;
     }
     return;
@@ -2261,14 +2302,6 @@ __global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb, 
   }
 }
 
-// ------------------------------------------------------------- a6: pLS
-__device__ __forceinline__ Seed load_seed(const Ws &w, int s) {
-  const float *p = w.pls + 8 * (long)s;
-  Seed sd;
-  sd.pt = p[0]; sd.cx = p[1]; sd.cy = p[2]; sd.lam = p[3]; sd.ks = p[4]; sd.x0 = p[5]; sd.y0 = p[6]; sd.z0 = p[7];
-  return sd;
-}
-
 // ------------------------------------------------------------- a7: pT3 / pT5
 template <int K>
 __device__ __forceinline__ void load_object(const Ws &w, const DevGeom &g, int t, float4 *P, ModInfo *M, float *kT,
@@ -2728,224 +2761,214 @@ __device__ __forceinline__ void obj_hits(const Ws &w, int t, int *h) {
 // pT duplicate removal: dropped when another entry with the same seed or the
 // same outer object has a smaller (score, seed, hit tuple).  Entries of one
 // seed differ in their outer object, so of a seed's entries only the one
-// with the smallest (score, hit tuple) can survive; one wave per seed finds
+// with the smallest (score, hit tuple) can survive; G lanes per seed find
 // it (a minimum over the seed's entries, the hit tuples compared only on an
-// exact tie of scores) and checks it alone against the entries sharing its
+// exact tie of scores) and check it alone against the entries sharing its
 // outer object, whose tuples differ from it in the seed only: it survives if
-// it has the object's smallest (score, seed) (offered to the object by the fill).
-template <int K>
-__global__ void k_pt_dedup(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = K == 3 ? w.ctr[C_NPT3] : w.ctr[C_NPT5];
+// it has the object's smallest (score, seed) (offered to it by the fill).
+// G = 32 for pT3 (11 entries a seed on a PU200 event, up to 190), 8 for pT5 (0.8): a
+// wave per seed left most lanes idle (89 us for eight events).
+template <int K, int G>
+__device__ __forceinline__ void pt_dedup(const Ws &w, int q, int nq) {
+  const int n = uload(w.ctr + (K == 3 ? C_NPT3 : C_NPT5));
   const int2 *so = K == 3 ? w.pt3_so : w.pt5_so;
   const float4 *at = K == 3 ? w.pt3_attr : w.pt5_attr;
   const int *soff = K == 3 ? w.pt3_off : w.pt5_off;
   const unsigned long long *obest = K == 3 ? w.o3_best : w.o5_best;
   int *keep = K == 3 ? w.pt3_keep : w.pt5_keep;
+  int *won = K == 3 ? w.w_pt3 : w.w_pt5;
   constexpr int H = 2 * K + 1;
-  const int lane = lane_id();
-  const int wpb = blockDim.x >> 6;
-  for (int s = blockIdx.x * wpb + (threadIdx.x >> 6); s < w.n_seeds; s += gridDim.x * wpb) {
-    const int j0 = min(soff[s], n), j1 = min(soff[s + 1], n);
-    if (j0 >= j1) continue;
-    // the smallest score of the seed's entries (scores of accepted entries are finite)
+  const int per = (int)blockDim.x / G, sub = threadIdx.x & (G - 1);
+  // (whole groups: every lane of a group follows the same path)
+  for (int s = q * per + (int)threadIdx.x / G; s < w.n_seeds; s += nq * per) {
+    const int j0 = min(gp(soff)[s], n), j1 = min(gp(soff)[s + 1], n);
+    // the smallest score of the seed's entries (scores of accepted entries are finite), an
+    // entry that has it and how many do
     float best = 3.0e38f;
-    for (int j = j0 + lane; j < j1; j += 64) best = fminf(best, at[j].z);
-    for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));
-    // the entry of that score with the smallest hit tuple (every lane scans the ties in order)
-    int win = -1;
-    int tw[H];
-    for (int c0 = j0; c0 < j1; c0 += 64) {
-      const int j = c0 + lane;
-      const bool tie = j < j1 && !(best < at[j].z) && !(at[j].z < best);
-      unsigned long long m = __ballot(tie);
-      while (m) {
-        const int l = __builtin_ctzll(m);
-        m &= m - 1;
-        const int jt = c0 + l;
-        int tj[H];
-        tj[0] = s;
-        obj_hits<K>(w, so[jt].y, tj + 1);
-        if (win < 0 || better<H>(best, tj, best, tw)) {
-          win = jt;
+    int ties = 0, win = -1;
+    for (int j = j0 + sub; j < j1; j += G) {
+      const float z = gload(at, j).z;
+      ties = z < best ? 1 : ties + (z == best ? 1 : 0);
+      win = z <= best ? j : win;
+      best = fminf(best, z);
+    }
+    for (int o = G / 2; o > 0; o >>= 1) {
+      const float ob = __shfl_xor(best, o, G);
+      const int ot = __shfl_xor(ties, o, G), ow = __shfl_xor(win, o, G);
+      ties = ob < best ? ot : ties + (ob == best ? ot : 0);
+      win = ob < best ? ow : (ob == best ? max(win, ow) : win);
+      best = fminf(best, ob);
+    }
+    if (ties > 1) {  // (a tenth of a PU200 event's seeds)
+      win = -1;
+      int tw[H];
+      const int g0 = lane_id() & ~(G - 1);  // the group's first lane in its wave
+      for (int c0 = j0; c0 < j1; c0 += G) {
+        const int j = c0 + sub;
+        const unsigned long long m = __ballot(j < j1 && gload(at, min(j, j1 - 1)).z == best);
+        for (unsigned mine = (unsigned)((m >> g0) & ((1ull << G) - 1)); mine; mine &= mine - 1u) {
+          const int jt = c0 + __builtin_ctz(mine);
+          int tj[H];
+          tj[0] = s;
+          obj_hits<K>(w, gload(so, jt).y, tj + 1);
+          if (win < 0 || better<H>(best, tj, best, tw)) {
+            win = jt;
 #pragma unroll
-          for (int q = 0; q < H; ++q) tw[q] = tj[q];
+            for (int i = 0; i < H; ++i) tw[i] = tj[i];
+          }
         }
       }
     }
-    if (win < 0) {  // no finite score (not produced by the selection): keep none
-      for (int j = j0 + lane; j < j1; j += 64) keep[j] = 0;
-      continue;
-    }
     // the winner survives the same-object rule if it is its object's best (score, seed)
-    const bool kp = obest[so[win].y] == pt_obj_key(at[win].z, so[win].x);
-    for (int j = j0 + lane; j < j1; j += 64) keep[j] = (j == win && kp) ? 1 : 0;
+    int obj = 0;
+    bool kp = false;
+    if (win >= 0) {
+      obj = gload(so, win).y;
+      kp = gload(obest, obj) == pt_obj_key(gload(at, win).z, s);
+    }
+    for (int j = j0 + sub; j < j1; j += G) gp(keep)[j] = (j == win && kp) ? 1 : 0;
+    if (sub == 0) {
+      gp(won)[s] = kp ? win : -1;
+      if (K == 5 && kp) {  // every surviving pT5 is a candidate; its seed and T5 are used
+        gp(w.sdir_tc)[gp(w.sdir_pos)[s]] = 1;
+        gp(w.t5_used)[obj] = 1;
+      }
+    }
   }
+}
+// Quintuplet entries on blocks [0, n5), triplet entries on the others.
+__global__ __launch_bounds__(kBlock) void k_pt_dedup(const Ws *__restrict__ wb, int n5) {
+  const Ws &w = wb[blockIdx.y];
+  if ((int)blockIdx.x < n5) pt_dedup<5, 8>(w, blockIdx.x, n5);
+  else pt_dedup<3, 32>(w, (int)blockIdx.x - n5, (int)gridDim.x - n5);
 }
 
 // ------------------------------------------------------------- a8: TC
-__device__ __forceinline__ Dir dir_of_seed(const Ws &w, int s) { return seed_dir(load_seed(w, s)); }
 __device__ __forceinline__ Dir dir_of_t5(const Ws &w, int t) {
   const float *a = w.t5_attr + 8 * (long)t;
   Dir d;
-  d.dx = a[6]; d.dy = a[7]; d.lam = a[3];
+  d.dx = gp(a)[6]; d.dy = gp(a)[7]; d.lam = gp(a)[3];
+  return d;
+}
+__device__ __forceinline__ Dir dir_of(const float4 &e) {
+  Dir d;
+  d.dx = e.x; d.dy = e.y; d.lam = e.z;
   return d;
 }
 
-// pT5 TCs: every surviving pT5; marks its seed and T5 as used.
-__global__ void k_tc_pt5(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NPT5);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int k = w.pt5_keep[i];
-    w.f_pt5[i] = k;
-    if (k) {
-      w.seed_used[gload(w.pt5_so, i).x] = 1;
-      w.t5_used[gload(w.pt5_so, i).y] = 1;
-    }
-  }
-}
-__global__ void k_tc_dirs_pt5(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NPT5);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    if (w.f_pt5[i]) {
-      const Dir d = dir_of_seed(w, gload(w.pt5_so, i).x);
-      w.dir_pt5[w.p_pt5[i]] = make_float4(d.dx, d.dy, d.lam, 0.f);
-    }
-}
+// The candidates' cleaning keeps one flag per seed or quintuplet, as bits of
+// 64-bit words, so no launch counts or compacts between the steps and the
+// writer ranks the candidates from the words' popcounts (1,000 words on a PU200
+// event).  A wave takes the kCleanItems items of one byte: most have no
+// candidate left to query, and the queries of one wave follow each other (with
+// 16 items a wave the T5 step of a PU200 event took 28 us).
+constexpr int kCleanItems = 8;
+__device__ __forceinline__ int clean_waves(long n) { return (int)((n + 63) / 64) * 8; }  // bytes of whole words
 
-// Direction lists of track candidates are binned by azimuth so that a
-// proximity query reads only the bins that can hold a near entry.  Near
-// entries have |dphi| < asin(D) (the test requires sin^2 dphi < D^2 and a
-// positive dot product), so with bins of width 2 pi / kDirBins the query
-// covers ceil(asin(D) / width) + 1 bins on each side, one more than needed
-// to absorb atan2f rounding.  The decision itself is near_dir, unchanged.
-constexpr int kDirBins = 128;
-
-__device__ __forceinline__ int dir_bin(float dx, float dy) {
-  const float ph = atan2f(dy, dx);
-  if (!(ph == ph)) return 0;
-  const int b = (int)floorf((ph + (float)M_PI) * (float)(kDirBins / (2.0 * M_PI)));
-  return b < 0 ? 0 : (b >= kDirBins ? kDirBins - 1 : b);
-}
-
-constexpr int bin_reach(double D) {
-  // ceil(asin(D) / (2 pi / kDirBins)) + 1 for the D values used (asin(D) < 1.0001 D for D <= 0.05)
-  return (int)(D * 1.0001 / (2.0 * 3.14159265358979 / kDirBins)) + 2;
-}
-
-// One block: counting sort of n (on the device) directions into kDirBins bins.
-__global__ __launch_bounds__(1024) void k_bin_dirs(const Ws *__restrict__ wb, int which) {
-  __shared__ int s_cnt[kDirBins], s_off[kDirBins + 1], s_cur[kDirBins];
-  const Ws &w = wb[blockIdx.y];
-  const float4 *dirs = which == 0 ? w.dir_pt5 : (which == 1 ? w.dir_pt3 : w.dir_t5);
-  int *bin_off = which == 0 ? w.boff_pt5 : (which == 1 ? w.boff_pt3 : w.boff_t5);
-  float4 *out = which == 0 ? w.bdir_pt5 : (which == 1 ? w.bdir_pt3 : w.bdir_t5);
-  const int n = w.ctr[which == 0 ? C_NTC0 : (which == 1 ? C_NTC1 : C_NTC2)];
-  for (int b = threadIdx.x; b < kDirBins; b += blockDim.x) { s_cnt[b] = 0; s_cur[b] = 0; }
-  __syncthreads();
-  for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_cnt[dir_bin(dirs[i].x, dirs[i].y)], 1);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int r = 0;
-    for (int b = 0; b < kDirBins; ++b) { s_off[b] = r; r += s_cnt[b]; }
-    s_off[kDirBins] = r;
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b <= kDirBins; b += blockDim.x) bin_off[b] = s_off[b];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const float4 d = dirs[i];
-    const int b = dir_bin(d.x, d.y);
-    out[s_off[b] + atomicAdd(&s_cur[b], 1)] = d;
-  }
-}
-
-// Wave-cooperative query: the 64 lanes stride over the entries of the bins
-// around the query's azimuth; returns (to every lane) whether any is near.
-// `d` and `active` must be wave-uniform.
-__device__ __forceinline__ bool near_any_wave(const Dir &d, bool active, const float4 *lst, const int *bin_off, float D,
-                                              int reach) {
-  if (!active) return false;
+// Calls f(place, entry) for the entries of the seeds' direction table within
+// `reach` bins of direction d, 64 a round on the wave's lanes (on all lanes:
+// active or not), until a call of a round returns true on some lane; returns
+// whether one did.
+template <class F>
+__device__ __forceinline__ bool near_seeds(const Ws &w, const Dir &d, int reach, F &&f) {
   const int lane = lane_id();
-  const int b0 = dir_bin(d.dx, d.dy);
-  for (int k = -reach; k <= reach; ++k) {
-    const int b = (b0 + k + kDirBins) % kDirBins;
-    const int j0 = bin_off[b], j1 = bin_off[b + 1];
-    for (int j = j0 + lane; j - lane < j1; j += 64) {
-      bool nr = false;
-      if (j < j1) {
-        const float4 e = lst[j];
-        Dir o;
-        o.dx = e.x; o.dy = e.y; o.lam = e.z;
-        nr = near_dir(d, o, D);
-      }
-      if (__ballot(nr)) return true;
-    }
+  const int b = dir_bin(d.dx, d.dy), lo = b - reach, hi = b + reach + 1;  // bins [lo, hi), wrapping round
+  const int a0 = uload(w.sdir_off + max(lo, 0)), a1 = uload(w.sdir_off + min(hi, kDirBins));
+  int c0 = 0, c1 = 0;
+  if (lo < 0) {
+    c0 = uload(w.sdir_off + lo + kDirBins);
+    c1 = w.n_seeds;
+  } else if (hi > kDirBins) {
+    c1 = uload(w.sdir_off + hi - kDirBins);
+  }
+  const int n1 = a1 - a0, n = n1 + c1 - c0;
+  for (int r = 0; r < n; r += 64) {
+    const int i = r + lane;
+    const bool hit = i < n && f(i < n1 ? a0 + i : c0 + (i - n1));
+    if (__ballot(hit)) return true;
   }
   return false;
 }
+// Whether a seed that is in a candidate (of the kinds in `kinds`) is near d.
+__device__ __forceinline__ bool near_candidate(const Ws &w, const Dir &d, int kinds, float D, int reach) {
+  return near_seeds(w, d, reach, [&](int j) {
+    return (gp(w.sdir_tc)[j] & kinds) != 0 && near_dir(d, dir_of(gload(w.sdir, j)), D);
+  });
+}
+__device__ __forceinline__ void put_flags(unsigned long long m, unsigned long long *words, int byte) {
+  if (lane_id() == 0) reinterpret_cast<unsigned char *>(words)[byte] = (unsigned char)m;
+}
 
-// pT3 TCs: surviving pT3 whose seed no TC-pT5 uses and that is not near any TC-pT5.
-// One wave per candidate (the query loops over binned lists with its lanes).
-__global__ void k_tc_pt3(const Ws *__restrict__ wb) {
+// pT3 candidates: surviving pT3 whose seed no pT5 candidate uses and that is not
+// near any pT5 candidate.
+__global__ __launch_bounds__(kBlock) void k_tc_pt3(const Ws *__restrict__ wb) {
   const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NPT3);
-  const int wpb = blockDim.x >> 6;
-  const int nw = gridDim.x * wpb;
-  for (int i = blockIdx.x * wpb + (threadIdx.x >> 6); i < n; i += nw) {
-    const int s = gload(w.pt3_so, i).x;
-    const bool cand = w.pt3_keep[i] && !w.seed_used[s];
-    const bool nr = near_any_wave(dir_of_seed(w, s), cand, w.bdir_pt5, w.boff_pt5, kDpT3, bin_reach(0.02));
-    if (lane_id() == 0) w.f_pt3[i] = (cand && !nr) ? 1 : 0;
+  const int lane = lane_id(), wpb = blockDim.x >> 6, n = clean_waves(w.n_seeds);
+  for (int i = blockIdx.x * wpb + wave_id(); i < n; i += gridDim.x * wpb) {
+    const int s = i * kCleanItems + lane;
+    const bool mine = lane < kCleanItems && s < w.n_seeds;
+    const bool five = mine && gp(w.w_pt5)[s] >= 0;
+    const bool three = mine && !five && gp(w.w_pt3)[s] >= 0;
+    const int pos = three ? gp(w.sdir_pos)[s] : 0;
+    unsigned long long acc = 0;
+    for (unsigned long long m = __ballot(three); m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      const Dir d = dir_of(gload(w.sdir, __builtin_amdgcn_readlane(pos, q)));
+      if (!near_candidate(w, d, 1, kDpT3, bin_reach(0.02))) acc |= 1ull << q;
+    }
+    // (the other waves' queries ask for the pT5 bit alone)
+    if (three && (acc >> lane & 1)) gp(w.sdir_tc)[pos] = 2;
+    put_flags(__ballot(five), w.m_pt5, i);
+    put_flags(acc, w.m_pt3, i);
   }
 }
-__global__ void k_tc_dirs_pt3(const Ws *__restrict__ wb) {
+
+// T5 candidates (blocks [0, n5)): surviving T5 not used by a pT5 candidate and
+// not near any pT5 or pT3 candidate; each marks the unused seeds near it.  pLS
+// candidates (the others): surviving pLS used by no candidate and not near any
+// pT5 or pT3 candidate; those marked by a T5 are left out when they are written.
+__global__ __launch_bounds__(kBlock) void k_tc_t5(const Ws *__restrict__ wb, int n5) {
   const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NPT3);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    if (w.f_pt3[i]) {
-      const int s = gload(w.pt3_so, i).x;
-      const Dir d = dir_of_seed(w, s);
-      w.dir_pt3[w.p_pt3[i]] = make_float4(d.dx, d.dy, d.lam, 0.f);
-      w.seed_used[s] = 1;
+  const int lane = lane_id(), wpb = blockDim.x >> 6;
+  if ((int)blockIdx.x < n5) {
+    const int n_t5 = uload(w.ctr + C_NT5), n = clean_waves(n_t5);
+    for (int i = blockIdx.x * wpb + wave_id(); i < n; i += n5 * wpb) {
+      const int t = i * kCleanItems + lane;
+      const bool cand = lane < kCleanItems && t < n_t5 && gp(w.t5_keep)[t] && !gp(w.t5_used)[t];
+      unsigned long long acc = __ballot(cand);
+      if (w.n_seeds > 0)
+        for (unsigned long long m = acc; m; m &= m - 1) {
+          const int q = __builtin_ctzll(m);
+          const Dir d = dir_of_t5(w, __builtin_amdgcn_readlane(t, q));
+          if (near_candidate(w, d, 3, kDT5, bin_reach(0.02))) {
+            acc &= ~(1ull << q);
+            continue;
+          }
+          near_seeds(w, d, bin_reach(0.05), [&](int j) {
+            if (gp(w.sdir_tc)[j] == 0) {
+              const float4 e = gload(w.sdir, j);
+              const int s = __float_as_int(e.w);
+              if (near_dir(dir_of(e), d, kDpLS)) atomicOr(w.pls_near + (s >> 5), 1u << (s & 31));
+            }
+            return false;
+          });
+        }
+      put_flags(acc, w.m_t5, i);
     }
-}
-// T5 TCs: surviving T5 not used by a TC-pT5 and not near any TC-pT5 or TC-pT3.
-__global__ void k_tc_t5(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NT5);
-  const int wpb = blockDim.x >> 6;
-  const int nw = gridDim.x * wpb;
-  for (int t = blockIdx.x * wpb + (threadIdx.x >> 6); t < n; t += nw) {
-    const bool cand = gp(w.t5_keep)[t] && !w.t5_used[t];
-    const Dir d = dir_of_t5(w, t);
-    const bool nr = near_any_wave(d, cand, w.bdir_pt5, w.boff_pt5, kDT5, bin_reach(0.02)) ||
-                    near_any_wave(d, cand, w.bdir_pt3, w.boff_pt3, kDT5, bin_reach(0.02));
-    if (lane_id() == 0) w.f_t5[t] = (cand && !nr) ? 1 : 0;
+    return;
   }
-}
-__global__ void k_tc_dirs_t5(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NT5);
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-    if (w.f_t5[t]) {
-      const Dir d = dir_of_t5(w, t);
-      w.dir_t5[w.p_t5[t]] = make_float4(d.dx, d.dy, d.lam, 0.f);
+  const int n = clean_waves(w.n_seeds), nw = ((int)gridDim.x - n5) * wpb;
+  for (int i = ((int)blockIdx.x - n5) * wpb + wave_id(); i < n; i += nw) {
+    const int s = i * kCleanItems + lane;
+    const bool mine = lane < kCleanItems && s < w.n_seeds;
+    const int pos = mine ? gp(w.sdir_pos)[s] : 0;
+    unsigned long long acc = __ballot(mine && gp(w.pls_keep)[s] && gp(w.sdir_tc)[pos] == 0);
+    for (unsigned long long m = acc; m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      const Dir d = dir_of(gload(w.sdir, __builtin_amdgcn_readlane(pos, q)));
+      if (near_candidate(w, d, 3, kDpLS, bin_reach(0.05))) acc &= ~(1ull << q);
     }
-}
-// pLS TCs: surviving pLS used by no TC and not near any TC.
-__global__ void k_tc_pls(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
-  const int wpb = blockDim.x >> 6;
-  const int nw = gridDim.x * wpb;
-  for (int s = blockIdx.x * wpb + (threadIdx.x >> 6); s < w.n_seeds; s += nw) {
-    const bool cand = gp(w.pls_keep)[s] && !w.seed_used[s];
-    const Dir d = dir_of_seed(w, s);
-    const bool nr = near_any_wave(d, cand, w.bdir_pt5, w.boff_pt5, kDpLS, bin_reach(0.05)) ||
-                    near_any_wave(d, cand, w.bdir_pt3, w.boff_pt3, kDpLS, bin_reach(0.05)) ||
-                    near_any_wave(d, cand, w.bdir_t5, w.boff_t5, kDpLS, bin_reach(0.05));
-    if (lane_id() == 0) w.f_pls[s] = (cand && !nr) ? 1 : 0;
+    put_flags(acc, w.m_pls, i);
   }
 }
 
@@ -2961,61 +2984,106 @@ __device__ __forceinline__ void ext_record(const Ws &w, int k, const int *md, in
   gstore(w.tc_kap, k, kap);
 }
 
-// Output: type, offsets, hit lists (pixel hits first, then MD hits inner to outer).
-__global__ void k_tc_write(const Ws *__restrict__ wb) {
+// Output: type, offsets, hit lists (pixel hits first, then MD hits inner to
+// outer), in the order pT5, pT3, T5, pLS.  A wave takes one word of flags of one
+// kind; its candidates' ranks come from the popcounts of the words before it and
+// of the kinds before its own, which every block sums for itself.
+__global__ __launch_bounds__(kBlock) void k_tc_write(const Ws *__restrict__ wb, int n_seed_blocks) {
+  __shared__ int s_sum[kWaves][5];
   const Ws &w = wb[blockIdx.y];
-  const int n0 = uload(w.ctr + C_NTC0), n1 = uload(w.ctr + C_NTC1), n2 = uload(w.ctr + C_NTC2), n3 = uload(w.ctr + C_NTC3);
-  const int np5 = uload(w.ctr + C_NPT5), np3 = uload(w.ctr + C_NPT3), nt5 = uload(w.ctr + C_NT5);
+  const int S = w.n_seeds, n_t5 = uload(w.ctr + C_NT5);
+  const int sw = (S + 63) >> 6, tw = (n_t5 + 63) >> 6;
+  // kind 0 pT5, 1 pT3, 2 pLS: n_seed_blocks each; 3 T5: the rest
+  const int kind = min((int)blockIdx.x / n_seed_blocks, 3);
+  const int q = (int)blockIdx.x - kind * n_seed_blocks, nq = kind < 3 ? n_seed_blocks : (int)gridDim.x - 3 * n_seed_blocks;
+  const int words = kind < 3 ? sw : tw;
+  const int lane = lane_id(), wv = wave_id();
+  // the block's words: a consecutive share of the kind's
+  const int share = ((words + nq - 1) / nq + kWaves - 1) / kWaves * kWaves;
+  const long first = (long)q * share, last = min(first + share, (long)words);
+  const bool totals = blockIdx.x == 0;
+  if (first >= last && !totals) return;
+  auto pls_word = [&](int j) {
+    return gp(w.m_pls)[j] & ~gp(reinterpret_cast<const unsigned long long *>(w.pls_near))[j];
+  };
+  auto word = [&](int k, int j) {
+    return k == 0 ? gp(w.m_pt5)[j] : k == 1 ? gp(w.m_pt3)[j] : k == 2 ? pls_word(j) : gp(w.m_t5)[j];
+  };
+  int v[5] = {0, 0, 0, 0, 0};  // candidates of each kind, and of this kind before `first`
+  for (int j = threadIdx.x; j < sw; j += kBlock) {
+    v[0] += __popcll(word(0, j));
+    v[1] += __popcll(word(1, j));
+    if (totals) v[2] += __popcll(word(2, j));
+  }
+  for (int j = threadIdx.x; j < tw; j += kBlock) v[3] += __popcll(word(3, j));
+  for (int j = threadIdx.x; j < first; j += kBlock) v[4] += __popcll(word(kind, j));
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int x = wave_total(v[i]);
+    if (lane == 0) s_sum[wv][i] = x;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    int x = 0;
+    for (int p = 0; p < kWaves; ++p) x += s_sum[p][i];
+    v[i] = x;
+  }
+  const int n0 = v[0], n1 = v[1], n2 = v[3];
   const long h1 = 14L * n0, h2 = h1 + 10L * n1, h3 = h2 + 10L * n2;
-  const int stride = gridDim.x * blockDim.x;
-  const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid == 0) {
-    w.ctr[C_NTC] = n0 + n1 + n2 + n3;
+  if (totals && threadIdx.x == 0) {
+    const int n3 = v[2], n = n0 + n1 + n2 + n3;
+    w.ctr[C_NTC0] = n0;
+    w.ctr[C_NTC1] = n1;
+    w.ctr[C_NTC2] = n2;
+    w.ctr[C_NTC3] = n3;
+    w.ctr[C_NTC] = n;
     w.ctr[C_NTCHITS] = (int)(h3 + 4L * n3);
-    w.tc_off[n0 + n1 + n2 + n3] = (int)(h3 + 4L * n3);
+    w.tc_off[n] = (int)(h3 + 4L * n3);
   }
-  for (int i = tid; i < np5; i += stride) {
-    if (!w.f_pt5[i]) continue;
-    const int k = w.p_pt5[i];
-    const int2 so = gload(w.pt5_so, i);
-    int *h = w.tc_hits + 14L * k;
-    for (int q = 0; q < 4; ++q) h[q] = gp(w.hits4)[4 * (long)so.x + q];
-    t5_hits(w, so.y, h + 4);
-    w.tc_type[k] = 0;
-    ext_record(w, k, w.t5_md + 5 * (long)so.y, 5, seed_kappa(w, so.x));
-    w.tc_off[k] = 14 * k;
-  }
-  for (int i = tid; i < np3; i += stride) {
-    if (!w.f_pt3[i]) continue;
-    const int k = w.p_pt3[i];
-    const int2 so = gload(w.pt3_so, i);
-    int *h = w.tc_hits + h1 + 10L * k;
-    for (int q = 0; q < 4; ++q) h[q] = gp(w.hits4)[4 * (long)so.x + q];
-    obj_hits<3>(w, so.y, h + 4);
-    w.tc_type[n0 + k] = 1;
-    {
+  int run = v[4];  // this kind's candidates before the round
+  for (long r = first; r < last; r += kWaves) {
+    int k = run;
+    unsigned long long m = 0;
+    for (int p = 0; p < kWaves; ++p) {
+      const unsigned long long mp = r + p < last ? word(kind, (int)r + p) : 0ull;
+      if (p < wv) k += __popcll(mp);
+      if (p == wv) m = mp;
+      run += __popcll(mp);
+    }
+    if (!(m >> lane & 1)) continue;
+    k += lanes_below(m);
+    const int i = (int)(r + wv) * 64 + lane;  // the seed or the quintuplet
+    if (kind == 0) {
+      const int2 so = gload(w.pt5_so, gp(w.w_pt5)[i]);
+      int *h = w.tc_hits + 14L * k;
+      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
+      t5_hits(w, so.y, h + 4);
+      w.tc_type[k] = 0;
+      ext_record(w, k, w.t5_md + 5 * (long)so.y, 5, seed_kappa(w, i));
+      w.tc_off[k] = 14 * k;
+    } else if (kind == 1) {
+      const int2 so = gload(w.pt3_so, gp(w.w_pt3)[i]);
+      int *h = w.tc_hits + h1 + 10L * k;
+      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
+      obj_hits<3>(w, so.y, h + 4);
+      w.tc_type[n0 + k] = 1;
       const int4 abc = gload(w.t3_md, so.y);
       const int md[3] = {abc.x, abc.y, abc.z};
-      ext_record(w, n0 + k, md, 3, seed_kappa(w, so.x));
+      ext_record(w, n0 + k, md, 3, seed_kappa(w, i));
+      w.tc_off[n0 + k] = (int)(h1 + 10L * k);
+    } else if (kind == 2) {
+      int *h = w.tc_hits + h3 + 4L * k;
+      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
+      w.tc_type[n0 + n1 + n2 + k] = 3;
+      w.tc_off[n0 + n1 + n2 + k] = (int)(h3 + 4L * k);
+    } else {
+      t5_hits(w, i, w.tc_hits + h2 + 10L * k);
+      w.tc_type[n0 + n1 + k] = 2;
+      ext_record(w, n0 + n1 + k, w.t5_md + 5 * (long)i, 5,
+                 make_float2(w.t5_attr[8 * (long)i], w.t3_attr[gload(w.t5_t3, i).y].y));
+      w.tc_off[n0 + n1 + k] = (int)(h2 + 10L * k);
     }
-    w.tc_off[n0 + k] = (int)(h1 + 10L * k);
-  }
-  for (int t = tid; t < nt5; t += stride) {
-    if (!w.f_t5[t]) continue;
-    const int k = w.p_t5[t];
-    t5_hits(w, t, w.tc_hits + h2 + 10L * k);
-    w.tc_type[n0 + n1 + k] = 2;
-    ext_record(w, n0 + n1 + k, w.t5_md + 5 * (long)t, 5,
-               make_float2(w.t5_attr[8 * (long)t], w.t3_attr[gload(w.t5_t3, t).y].y));
-    w.tc_off[n0 + n1 + k] = (int)(h2 + 10L * k);
-  }
-  for (int s = tid; s < w.n_seeds; s += stride) {
-    if (!w.f_pls[s]) continue;
-    const int k = w.p_pls[s];
-    int *h = w.tc_hits + h3 + 4L * k;
-    for (int q = 0; q < 4; ++q) h[q] = gp(w.hits4)[4 * (long)s + q];
-    w.tc_type[n0 + n1 + n2 + k] = 3;
-    w.tc_off[n0 + n1 + n2 + k] = (int)(h3 + 4L * k);
   }
 }
 
@@ -3390,32 +3458,27 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   run([&] {});  // pt5_scan
   run([&] {});  // pt5_fill: with pt3_fill
   run([&] {});  // pt_obj_best: offered by the fill
-  run([&] { if (seeds) k_pt_dedup<3><<<dim3(grid_waves(S), B), kBlock, 0, st>>>(wb); });
-  run([&] { if (seeds) k_pt_dedup<5><<<dim3(grid_waves(S), B), kBlock, 0, st>>>(wb); });
+  run([&] {
+    if (!seeds) return;
+    const unsigned n5 = grid(8 * S).x, n3 = grid(32 * S).x;
+    k_pt_dedup<<<dim3(n5 + n3, B), kBlock, 0, st>>>(wb, (int)n5);
+  });
+  run([&] {});  // pt5_dedup: with pt3_dedup
   // a8: cleaning and track candidates
+  for (int q = 0; q < 3; ++q) run([&] {});  // tc_pt5, its scan and directions: with the duplicate removal
+  auto clean = [&](long n) { return gridwt((n + kCleanItems - 1) / kCleanItems).x; };
+  run([&] { if (seeds) k_tc_pt3<<<dim3(clean(S), B), tb, 0, st>>>(wb); });
+  for (int q = 0; q < 2; ++q) run([&] {});  // tc_pt3_scan, tc_pt3_dirs
   run([&] {
-    k_tc_pt5<<<grid(b.cap_pt5), kBlock, 0, st>>>(wb);
+    const unsigned n5 = clean(b.cap_t5), ns = seeds ? clean(S) : 0;
+    k_tc_t5<<<dim3(n5 + ns, B), tb, 0, st>>>(wb, (int)n5);
   });
-  run([&] { scan(wb, B, SC_F5, b.cap_pt5, st); });
+  for (int q = 0; q < 4; ++q) run([&] {});  // tc_t5_scan, tc_t5_dirs, tc_pls (with tc_t5), tc_pls_scan
   run([&] {
-    k_tc_dirs_pt5<<<grid(b.cap_pt5), kBlock, 0, st>>>(wb);
-    k_bin_dirs<<<one, 1024, 0, st>>>(wb, 0);
+    const unsigned ns = share((int)std::min(1024L, (S + 255) / 256), kBlock);
+    const unsigned n5 = share((int)std::min(1024L, ((long)b.cap_t5 + 255) / 256), kBlock);
+    k_tc_write<<<dim3(3 * ns + n5, B), kBlock, 0, st>>>(wb, (int)ns);
   });
-  run([&] { k_tc_pt3<<<gridwt(b.cap_pt3), tb, 0, st>>>(wb); });
-  run([&] { scan(wb, B, SC_F3, b.cap_pt3, st); });
-  run([&] {
-    k_tc_dirs_pt3<<<grid(b.cap_pt3), kBlock, 0, st>>>(wb);
-    k_bin_dirs<<<one, 1024, 0, st>>>(wb, 1);
-  });
-  run([&] { k_tc_t5<<<gridwt(b.cap_t5), tb, 0, st>>>(wb); });
-  run([&] { scan(wb, B, SC_FT5, b.cap_t5, st); });
-  run([&] {
-    k_tc_dirs_t5<<<grid(b.cap_t5), kBlock, 0, st>>>(wb);
-    k_bin_dirs<<<one, 1024, 0, st>>>(wb, 2);
-  });
-  run([&] { if (seeds) k_tc_pls<<<gridwt(S), tb, 0, st>>>(wb); });
-  run([&] { if (seeds) scan(wb, B, SC_FPLS, S, st); });
-  run([&] { k_tc_write<<<grid(b.cap_tc), kBlock, 0, st>>>(wb); });
   // track extensions (when the geometry enables them)
   run([&] {
     if (!g.ext) return;

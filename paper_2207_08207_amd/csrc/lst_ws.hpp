@@ -65,14 +65,14 @@ struct ScanJob {
   int cap;
 };
 enum ScanId : int {
-  SC_HITS, SC_MD, SC_F5, SC_F3, SC_FT5, SC_FPLS, SC_EXT, SC_COUNT
+  SC_HITS, SC_MD, SC_EXT, SC_COUNT
 };
 // One array cleared to zero at the start of the chain: n entries, `stride` ints apart.
 struct FillJob {
   int *p;
   int n, stride;
 };
-enum FillId : int { FL_CTR, FL_TS, FL_SEED_CNT, FL_SEED_USED, FL_BIN_CNT, FL_COUNT };
+enum FillId : int { FL_CTR, FL_TS, FL_SEED_CNT, FL_SEED_TC, FL_PLS_NEAR, FL_BIN_CNT, FL_COUNT };
 
 // Sums a count pass keeps so that its fill pass finds its own output offsets
 // (no scan launches between them): one sum per tile of 2^tile_shift(capacity)
@@ -121,6 +121,7 @@ constexpr Tiles kTilesDefault{kMdCache, kLsCache, kT3Cache, kT5Cache, kPt3Cache,
 constexpr int kBinRows = 10 * 256, kZBins = 55, kBinStride = kZBins + 1;
 constexpr int kSeedBins = kBinRows * kBinStride;
 constexpr int kSeedKeys = 256 * 8;  // direction groups of the seeds' processing order
+constexpr int kDirBins = 512;       // azimuth bins of the seeds' directions at the beam line
 
 // Device pointers of one event (all inside the workspace except the inputs).
 // Kernels of a batch read descriptor blockIdx.y of a device array of these.
@@ -179,7 +180,7 @@ struct Ws {
   float *pls;       // 8 per seed: pT, cx, cy, lambda, kappa, x0, y0, z0
   int *pls_keep;
   int *seed_order;  // seeds in the seed search's processing order (grouped by direction)
-  int *seed_key, *seed_slot, *seed_cnt;  // each seed's direction group and place in it; seeds per group
+  int *seed_key, *seed_slot, *seed_cnt;  // each seed's direction group and place in it; seeds per group (and per azimuth bin)
   // seeds using each pixel hit, as linked lists of (4 seed + hit number): the hit's
   // first entry (-1: none; set for the seeds' hits only) and each entry's next one
   int *ph_head, *ph_next;
@@ -201,12 +202,18 @@ struct Ws {
   float4 *bin_pos;
   int4 *bin_rng;
   // track candidates
-  int *seed_used, *t5_used;
-  int *f_pt5, *f_pt3, *f_t5, *f_pls;            // TC flags
-  int *p_pt5, *p_pt3, *p_t5, *p_pls;            // their exclusive scans
-  float4 *dir_pt5, *dir_pt3, *dir_t5;           // compact directions (dx, dy, lambda)
-  float4 *bdir_pt5, *bdir_pt3, *bdir_t5;        // the same, grouped by azimuth bin
-  int *boff_pt5, *boff_pt3, *boff_t5;           // bin offsets (kDirBins + 1)
+  int *t5_used;
+  // the seeds sorted by azimuth bin of their direction at the beam line: (dx, dy, lambda,
+  // seed bits), bin offsets, each seed's place, and per place the candidates the seed is in
+  // (1 pT5, 2 pT3)
+  float4 *sdir;
+  int *sdir_off, *sdir_pos, *sdir_tc;
+  int *dir_key, *dir_slot;      // each seed's azimuth bin and place in it (counted after seed_cnt)
+  int *w_pt5, *w_pt3;           // per seed: its surviving pT5 / pT3 entry, or -1
+  // track-candidate flags, one bit a seed (pT5, pT3, pLS) or quintuplet, 64 a word;
+  // pls_near: the seeds near a T5 candidate
+  unsigned long long *m_pt5, *m_pt3, *m_pls, *m_t5;
+  unsigned *pls_near;
   int *tc_type, *tc_off, *tc_hits;
   int *tc_md;                                   // its outer-tracker MDs, inner to outer (5 per TC)
   float2 *tc_kap;                               // its curvature and curvature tolerance
