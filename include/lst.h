@@ -377,9 +377,9 @@ lst_status lst_autotune(lst_geometry geom, int32_t B, const lst_event_desc *evs,
  * plans created afterwards; results do not depend on them).  Tile i in
  * [0, lst_tile_count()) is named by lst_tile_name(i):
  *   md_cache, ls_cache, t3_cache, t5_cache: passing partners per parent that
- *     the MD / segment / triplet / quintuplet count pass remembers (module,
- *     MD, segment, triplet), so that its fill copies them instead of
- *     searching again (a parent with more is searched again);
+ *     the MD / segment / triplet / quintuplet search remembers (lower hit --
+ *     at most 6 are kept --, MD, segment, triplet), so that its fill copies
+ *     them instead of searching again (a parent with more is searched again);
  *   pt3_cache, pt5_cache: pT3 / pT5 per seed the seed-search count keeps with
  *     their attributes (Section 2.4);
  *   pass_list: passing objects of one seed ranked in on-chip memory by the

@@ -139,11 +139,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
 #define F4(n) reinterpret_cast<float4 *>(take(sizeof(float4) * (size_t)(n)))
   Ws t{};
   t.ctr = ctr;
-  const long tiles = (long)n_coarse((int)M) * n_hit_tiles(N);
-  t.boff = I(2 * M + 1); t.tile_hist = I(tiles + 1); t.tile_off = I(tiles + 1);
+  const long nc = n_coarse((int)M);
+  t.boff = I(2 * M + 1); t.tile_hist = I(nc * n_hit_tiles(N, kHitTile)); t.coarse_cnt = I(nc); t.coarse_off = I(nc + 1);
   t.hcp = F4(N + 1); t.hidx = I(N + 1); t.hpos = F4(N + 1);
-  t.md_cnt = I(M + 1); t.md_off = I(M + 1); t.md_cache = I(kMdCache * M); t.md_part = I((long)kMdParts * M);
-  t.md_bcache = I((long)kMdParts * kMdQCache * M); t.md_dense = I(M + 1);
+  t.md_cnt = I(M + 1); t.md_off = I(M + 1); t.md_tot = I(nc);
   t.md_hits = I2(md); t.md_mod = I(md); t.md_pos = F4(md); t.md_stub = F2(md); t.mod_disc = F4(M);
   t.ls_cnt = I(md + 1); t.ls_off = I(md + 1); t.ls_md = I2(ls); t.ls_beta = F2(ls); t.ls_opos = F4(ls); t.ls_oinf = I(ls);
   t.ls_cache = I(kLsCache * md);
@@ -153,9 +152,9 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.t5_off = I(t3 + 1); t.ws_t5 = I((t3 >> 6) + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
   t.t5_keep = I(t5); t.t5_first = F2(t5);
   t.inc_cnt = I(md); t.inc_off = I(md); t.inc_list = I2(5 * t5);
-  t.pls = F(8 * S); t.pls_keep = I(S); t.seed_order = I(S + 1);
-  t.seed_cnt = I(kSeedKeys + kDirBins);
-  t.ph_head = I(N); t.ph_next = I(4 * S);
+  t.pls = F(8 * S); t.pls_keep = I(S);
+  t.seed_cnt = I(kSeedKeys);
+  t.ph_owner = I(N); t.ph_head = I(N); t.ph_next = I(4 * S);
   t.pt3_cnt = I(S + 1); t.pt3_off = I(S + 1); t.pt5_cnt = I(S + 1); t.pt5_off = I(S + 1);
   t.pt3_cache = I(kPt3Cache * S); t.pt5_cache = I(kPt5Cache * S);
   t.pt3_cattr = F4(kPt3Cache * S); t.pt5_cattr = F4(kPt5Cache * S);
@@ -187,8 +186,7 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.t5_slot = t.tc_hits;                       // 4 t5 <= 14 tc
   t.sdir = reinterpret_cast<float4 *>(t.tc_hits + 4 * t5);  // and 4 S + S more
   t.sdir_pos = t.tc_hits + 4 * t5 + 4 * S;
-  t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;          // 4 S <= 5 tc
-  t.dir_key = t.tc_md + 2 * S; t.dir_slot = t.tc_md + 3 * S;
+  t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;          // 2 S <= 5 tc
   // the tile sums, one after another (cleared together)
   const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
   const long n_ts = (nl + n3 + n5 + 2 * np) * kSumStride;
@@ -211,15 +209,11 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
     int *ct = t.ctr;
     auto sj = [&](int id, const int *in, int *out, const int *n_dev, long n_fix, long n_cap, int *req, int *clamped,
                   long cap) { t.scans[id] = ScanJob{in, out, n_dev, (int)n_fix, (int)n_cap, req, clamped, (int)cap}; };
-    const long nt = (long)n_coarse((int)M) * n_hit_tiles(n_hits);
-    const long nt_cap = (long)n_coarse((int)M) * n_hit_tiles(n_hits_alloc >= 0 ? n_hits_alloc : n_hits);
-    sj(SC_HITS, t.tile_hist, t.tile_off, nullptr, nt, nt_cap, ct + C_NOUTER, nullptr, 0);
-    sj(SC_MD, t.md_cnt, t.md_off, nullptr, M, M, ct + C_RMD, ct + C_NMD, md);
     sj(SC_EXT, t.ext_cnt, t.ext_off, ct + C_NTC, 0, p5 + p3 + t5 + S, ct + C_NEXTHITS, nullptr, 0);
     const auto fj = [&](int id, int *p, long n, int stride = 1) { t.fills[id] = FillJob{p, (int)n, stride}; };
     fj(FL_CTR, ct, C_COUNT);
     fj(FL_TS, t.ts_ls, n_ts / kSumStride, kSumStride);
-    fj(FL_SEED_CNT, t.seed_cnt, S > 0 ? kSeedKeys + kDirBins : 0);
+    fj(FL_SEED_CNT, t.seed_cnt, S > 0 ? kSeedKeys : 0);
     fj(FL_SEED_TC, t.sdir_tc, S);
     fj(FL_PLS_NEAR, reinterpret_cast<int *>(t.pls_near), S > 0 ? 2 * ((S >> 6) + 1) : 0);
     fj(FL_BIN_CNT, t.bin_cnt, S > 0 ? nbins : 0);
@@ -577,7 +571,7 @@ lst_status lst_workspace_bytes(lst_geometry g, int32_t n_hits, int32_t n_seeds, 
 // The hit bucketing scans one count per (coarse bucket, tile of input hits):
 // an event must keep that within one device scan on this geometry.
 static lst_status check_bucketing(lst_geometry g, int64_t n_hits) {
-  const int64_t items = (int64_t)lst::n_coarse(g->g.n_mod) * lst::n_hit_tiles(n_hits);
+  const int64_t items = (int64_t)lst::n_coarse(g->g.n_mod) * lst::n_hit_tiles(n_hits, lst::kScanTileHits);
   if (items > kMaxTc) {
     char msg[200];
     snprintf(msg, sizeof(msg), "%lld hits: above what the hit bucketing scans on a detector of %d modules",

@@ -72,6 +72,10 @@ __device__ __forceinline__ void gstore(T *p, long i, const T &v) {
   ((__attribute__((address_space(1))) N *)p)[i] = n;
 }
 
+// The hardware reciprocal and reciprocal square root (within 1 ulp), for pre-tests.
+__device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
+
 __device__ __forceinline__ int block_sum(int v, int *s_red) {
   // wave reduction by shuffles, then across waves in LDS
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -87,9 +91,9 @@ __device__ __forceinline__ int block_sum(int v, int *s_red) {
 __device__ __forceinline__ int dev_count(const int *p, int fallback) { return p ? *p : fallback; }
 
 // ------------------------------------------------------------------ start
-// The chain's first launch: clears what later kernels count into and empties
-// the lists of the pixel hits that seeds use (the rest of ph_head is never
-// read).  Arrays indexed by MDs or quintuplets are cleared where those are
+// The chain's first launch: clears what later kernels count into, empties the
+// lists of the pixel hits that seeds use and gives each such hit an owner, the
+// seed whose store came last (the rest of ph_head and ph_owner is never read).  Arrays indexed by MDs or quintuplets are cleared where those are
 // written, so no other launch of the chain only clears.
 __global__ void k_start(const Ws *__restrict__ wb) {
   const Ws &w = wb[blockIdx.y];
@@ -101,7 +105,10 @@ __global__ void k_start(const Ws *__restrict__ wb) {
   }
   for (long i = tid; i < 4L * w.n_seeds; i += nt) {
     const int h = gp(w.hits4)[i];
-    if (h >= 0 && h < w.n_hits) gp(w.ph_head)[h] = -1;
+    if (h >= 0 && h < w.n_hits) {
+      gp(w.ph_head)[h] = -1;
+      gp(w.ph_owner)[h] = (int)(i >> 2);
+    }
   }
 }
 
@@ -350,21 +357,12 @@ __device__ __forceinline__ int obj_bin(const float4 &a) {
   const int rp = ph == ph ? ring_of(a.w) * kPhiBins + phibin_of(ph) : 0;
   return rp * kBinStride + zbin_of(a.z);
 }
-// Processing order of the seed search: seeds grouped by direction (azimuth of
-// the seed's direction in kPhiBins sectors x 8 bins of lambda).  Seeds of one
-// group scan nearly the same bins, so waves that run together (consecutive
-// blocks) reuse each other's object lists in cache.  Results do not depend on
-// the order (each seed writes only its own entries), so places within a group
-// come from atomics.
-__device__ __forceinline__ int seed_key(float cx, float cy, float lam) {
-  const float ph = atan2f(cy, cx);
-  const int lb = (int)floorf((lam + 6.0f) * (1.0f / 1.5f));
-  return (ph == ph ? phibin_of(ph) : 0) * 8 + (lb < 0 ? 0 : (lb > 7 ? 7 : lb));
-}
-
 // Proximity queries (near_dir) read the seeds' directions at the beam line,
 // binned by azimuth, so that a query reads only the bins that can hold a near
-// entry.  Near entries have |dphi| < asin(D) (the test requires sin^2 dphi < D^2
+// entry.  The seed search takes the seeds in the table's order: each azimuth bin
+// in four groups of the slope, so that waves that run together scan nearly the
+// same object bins and reuse each other's lists in cache (results do not depend
+// on the order).  Near entries have |dphi| < asin(D) (the test requires sin^2 dphi < D^2
 // and a positive dot product), so with bins of width 2 pi / kDirBins the query
 // covers ceil(asin(D) / width) + 1 bins on each side, one more than needed to
 // absorb atan2f rounding.  The decision itself is near_dir, unchanged.
@@ -381,29 +379,28 @@ constexpr int bin_reach(double D) {
 
 // ------------------------------------------------------------- a0: hits
 // Hits are bucketed by key = 2 module + sensor, stably (input order within a
-// key), with no global atomic: an LSD-free two-level counting sort.
-//  1. k_hits_count: each block counts the hits of its tile of kHitTile input
-//     hits per coarse bucket (key >> kFineBits) in LDS and writes the counts,
-//     coarse-bucket major (and validates hits and seeds);
-//  2. an exclusive scan of those counts gives every (coarse bucket, tile) its
-//     first position;
-//  3. k_hits_scatter: each wave walks its quarter of the tile again in input
-//     order, 64 hits at a time, after the waves before it; hits of one coarse
-//     bucket in a round find each other with ballots and take consecutive
-//     positions after the bucket's running position (stable), writing one
-//     16-byte record (x, y, z, input index and key within the bucket);
-//  4. k_bucket_sort: one block per coarse bucket counts its keys, writes their
-//     offsets and moves every hit (input index; x, y, z, r) to its key's
-//     running position, again 64 hits at a time in order.
+// key), with no global atomic: a two-level counting sort.
+//  1. k_hits_count: each block counts the hits of its tile of input hits per
+//     coarse bucket (key >> kFineBits) in LDS (and validates hits and prepares
+//     seeds);
+//  2. k_hits_rows turns each bucket's counts into the hits of earlier tiles;
+//  3. k_hits_scatter: each wave places its 64 to 512 hits of the tile in input
+//     order, 64 at a time, after the waves before it; hits of one coarse bucket
+//     in a round find each other with ballots and take consecutive positions
+//     after the bucket's running position (stable), writing one 16-byte record
+//     (x, y, z, input index and key within the bucket);
+//  4. k_bucket_md: one block per coarse bucket counts its keys, writes their
+//     offsets, moves every hit (input index; x, y, z, r) to its key's running
+//     position, again 64 hits at a time in order, and searches the bucket's
+//     modules for mini-doublets.
 
 // The bucket key of hit i, or -1 for a pixel hit or invalid data (*bad).
 __device__ __forceinline__ int hit_key(const Ws &w, int i, int n_mod, bool *bad) {
-  const int m = gp(w.module)[i];
+  const int m = gp(w.module)[i], sn = gp(w.sensor)[i];  // (a pixel hit's sensor is read, not used)
   const float x = gp(w.x)[i], y = gp(w.y)[i], z = gp(w.z)[i];
   bool b = !(isfinite(x) && isfinite(y) && isfinite(z)) || m < -1 || m >= n_mod;
   int key = -1;
   if (m >= 0) {
-    const int sn = gp(w.sensor)[i];
     b |= (sn != 0 && sn != 1);
     if (!b) key = 2 * m + sn;
   }
@@ -460,198 +457,192 @@ __device__ __forceinline__ bool seed_prepare(const Ws &w, int s) {
     bad |= !in;
     if (in) {
       bad |= gp(w.module)[h] != -1;
-      gp(w.ph_next)[4 * (long)s + k] = atomicExch(w.ph_head + h, 4 * s + k);
+      // a hit that another seed owns (few): join its list
+      if (gp(w.ph_owner)[h] != s) gp(w.ph_next)[4 * (long)s + k] = atomicExch(w.ph_head + h, 4 * s + k);
       if (k == 0) h0 = h;
     }
   }
-  const float pt = sqrtf(px * px + py * py);
-  float *o = w.pls + 8 * (long)s;
-  const float cx = px / pt, cy = py / pt, lam = pz / pt;
-  gstore(reinterpret_cast<float4 *>(o), 0, make_float4(pt, cx, cy, lam));
   const bool any = w.n_hits > 0;
-  gstore(reinterpret_cast<float4 *>(o), 1,
-         make_float4((-(float)q * kCurv) / pt, any ? gp(w.x)[h0] : 0.f, any ? gp(w.y)[h0] : 0.f, any ? gp(w.z)[h0] : 0.f));
-  const int key = seed_key(cx, cy, lam);
+  Seed sd;
+  sd.pt = sqrtf(px * px + py * py);
+  sd.cx = px / sd.pt;
+  sd.cy = py / sd.pt;
+  sd.lam = pz / sd.pt;
+  sd.ks = (-(float)q * kCurv) / sd.pt;
+  sd.x0 = any ? gp(w.x)[h0] : 0.f;
+  sd.y0 = any ? gp(w.y)[h0] : 0.f;
+  sd.z0 = any ? gp(w.z)[h0] : 0.f;
+  float4 *o = reinterpret_cast<float4 *>(w.pls + 8 * (long)s);
+  gstore(o, 0, make_float4(sd.pt, sd.cx, sd.cy, sd.lam));
+  gstore(o, 1, make_float4(sd.ks, sd.x0, sd.y0, sd.z0));
+  const Dir d = seed_dir(sd);
+  const int key = 4 * dir_bin(d.dx, d.dy) + (d.lam < 0.0f ? 0 : 2) + (fabsf(d.lam) < 1.5f ? 0 : 1);
   gp(w.seed_key)[s] = key;
   gp(w.seed_slot)[s] = atomicAdd(w.seed_cnt + key, 1);
-  const Dir d = seed_dir(load_seed(w, s));  // (this thread's own stores)
-  const int db = dir_bin(d.dx, d.dy);
-  gp(w.dir_key)[s] = db;
-  gp(w.dir_slot)[s] = atomicAdd(w.seed_cnt + kSeedKeys + db, 1);
   return bad;
 }
 
-// One block per tile of kHitTile hits, each of its four waves counting 1024
-// consecutive hits into its own LDS row; the tile's coarse counts are the rows'
-// sums (k_hits_scatter recounts the rows to rank its waves).
-static_assert(kHitTile == kWaves * 1024, "a wave's part of a tile is 1024 hits");
-__device__ __forceinline__ bool wave_coarse_counts(const Ws &w, int tb, int n_mod, int *row) {
-  const int lane = lane_id(), wv = wave_id();
-  bool any_bad = false;
-  const int i0 = tb * kHitTile + wv * 1024, i1 = min(w.n_hits, i0 + 1024);
-  for (int i = i0 + lane; i < i1; i += 64) {
-    bool bad;
-    const int key = hit_key(w, i, n_mod, &bad);
-    any_bad |= bad;
-    if (key >= 0) atomicAdd(&row[key >> kFineBits], 1);  // LDS
+// A tile is NW waves x R rounds of 64 hits: sixteen waves where their rows of
+// 16-bit counts fit LDS (n_coarse up to 1,700), else eight.  (Four waves of 16
+// rounds, as one block took before, left a tile's hits to a serial chain: 28 +
+// 43 us for the count and the scatter of one PU200 event.)
+template <int NW, int R>
+__global__ __launch_bounds__(64 * NW) void k_hits_count(const Ws *__restrict__ wb, int n_mod, int n_tiles) {
+  extern __shared__ int s_hits[];  // nc counts
+  const Ws &w = wb[blockIdx.y];
+  if ((int)blockIdx.x >= n_tiles) {  // the seeds
+    const int nt = ((int)gridDim.x - n_tiles) * 64 * NW;
+    for (int s = ((int)blockIdx.x - n_tiles) * 64 * NW + threadIdx.x; s < w.n_seeds; s += nt)
+      if (seed_prepare(w, s)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
+    return;
   }
-  return any_bad;
+  const int nc = n_coarse(n_mod), tb = blockIdx.x;
+  const long i0 = (long)tb * (64 * NW * R);
+  if (i0 < w.n_hits) {
+    for (int c = threadIdx.x; c < nc; c += 64 * NW) s_hits[c] = 0;
+    int key[R];
+    bool any_bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = (int)i0 + r * 64 * NW + (int)threadIdx.x;
+      bool bad = false;
+      key[r] = i < w.n_hits ? hit_key(w, i, n_mod, &bad) : -1;
+      any_bad |= bad;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (key[r] >= 0) atomicAdd(&s_hits[key[r] >> kFineBits], 1);  // LDS
+    if (any_bad) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_HIT);
+    __syncthreads();
+    for (int c = threadIdx.x; c < nc; c += 64 * NW) gp(w.tile_hist)[(long)tb * nc + c] = s_hits[c];
+  }
 }
 
-// The four waves' rows of coarse counts live in dynamic LDS (kWaves x nc ints,
-// sized at launch from the geometry), so small geometries keep more blocks
-// resident.
-__global__ __launch_bounds__(kBlock) void k_hits_count(const Ws *__restrict__ wb, int n_mod) {
-  extern __shared__ int s_rows[];
+// Each coarse bucket's counts per tile, in place, into the bucket's hits in
+// earlier tiles, and its total: 32 buckets per block, the tiles in 32 segments.
+__global__ __launch_bounds__(1024) void k_hits_rows(const Ws *__restrict__ wb, int n_mod, int tile) {
+  __shared__ int s_seg[32][33];
   const Ws &w = wb[blockIdx.y];
-  const int wv = wave_id();
-  const int nc = n_coarse(n_mod), ntb = n_hit_tiles(w.n_hits);
-  const int tb = blockIdx.x;
-  if (tb < ntb) {
-    for (int c = threadIdx.x; c < kWaves * nc; c += blockDim.x) s_rows[c] = 0;
-    __syncthreads();
-    if (wave_coarse_counts(w, tb, n_mod, s_rows + wv * nc)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_HIT);
-    __syncthreads();
-    for (int c = threadIdx.x; c < nc; c += blockDim.x) {
-      int t = 0;
-#pragma unroll
-      for (int q = 0; q < kWaves; ++q) t += s_rows[q * nc + c];
-      gp(w.tile_hist)[(long)c * ntb + tb] = t;
-    }
+  const int nc = n_coarse(n_mod), nt = n_hit_tiles(w.n_hits, tile);
+  const int col = threadIdx.x & 31, seg = threadIdx.x >> 5, c = blockIdx.x * 32 + col;
+  const int t0 = (int)((long)nt * seg / 32), t1 = (int)((long)nt * (seg + 1) / 32);
+  int sum = 0;
+  if (c < nc)
+    for (int t = t0; t < t1; ++t) sum += gp(w.tile_hist)[(long)t * nc + c];
+  s_seg[seg][col] = sum;
+  __syncthreads();
+  int run = 0;
+  for (int q = 0; q < seg; ++q) run += s_seg[q][col];
+  if (c >= nc) return;
+  for (int t = t0; t < t1; ++t) {
+    const int v = gp(w.tile_hist)[(long)t * nc + c];
+    gp(w.tile_hist)[(long)t * nc + c] = run;
+    run += v;
   }
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < w.n_seeds; s += gridDim.x * blockDim.x)
-    if (seed_prepare(w, s)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
+  if (seg == 31) gp(w.coarse_cnt)[c] = run;
 }
 
 // Stable scatter of a tile's hits into coarse-bucket order: each wave's first
-// slot in bucket c is the tile's offset (the scan of the tile counts) plus the
-// rows of the waves before it; in each round of 64 hits, a hit's rank among
+// slot in bucket c is the bucket's start (every block scans the bucket counts
+// for itself; the first writes the starts), plus the hits of earlier tiles, plus
+// those of the waves before it; in each round of 64 hits, a hit's rank among
 // the round's hits of its bucket (match_value) places it.  The hit's
 // coordinates, input index and key within its bucket travel with it (one
 // 16-byte store), so the per-bucket sort reads them contiguously.
-__global__ __launch_bounds__(kBlock) void k_hits_scatter(const Ws *__restrict__ wb, int n_mod) {
-  extern __shared__ int s_rows[];  // kWaves x nc, as in k_hits_count
+template <int NW, int R>
+__global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__ wb, int n_mod) {
+  extern __shared__ int s_hits[];  // nc positions, then NW rows of 16-bit counts, two a word
+  __shared__ int s_wave[NW];
+  constexpr int T = 64 * NW;
   const Ws &w = wb[blockIdx.y];
-  const int wv = wave_id(), lane = lane_id();
-  const int nc = n_coarse(n_mod), ntb = n_hit_tiles(w.n_hits);
-  const int tb = blockIdx.x;
-  if (tb >= ntb) return;  // the whole block
-  for (int c = threadIdx.x; c < kWaves * nc; c += blockDim.x) s_rows[c] = 0;
-  __syncthreads();
-  (void)wave_coarse_counts(w, tb, n_mod, s_rows + wv * nc);
-  __syncthreads();
-  for (int c = threadIdx.x; c < nc; c += blockDim.x) {
-    int run = gp(w.tile_off)[(long)c * ntb + tb];
+  const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
+  const int nc = n_coarse(n_mod), row = (nc + 1) / 2, tb = blockIdx.x;
+  const long i0 = (long)tb * (T * R) + wv * (64 * R);
+  if ((long)tb * (T * R) >= w.n_hits && tb > 0) return;  // the whole block
+  int *s_base = s_hits;
+  unsigned *rows = reinterpret_cast<unsigned *>(s_hits + nc);
+  for (int i = t; i < NW * row; i += T) rows[i] = 0u;
+  // the wave's hits, kept in registers
+  int key[R];
+  float x[R], y[R], z[R];
 #pragma unroll
-    for (int q = 0; q < kWaves; ++q) {
-      const int v = s_rows[q * nc + c];
-      s_rows[q * nc + c] = run;
-      run += v;
+  for (int r = 0; r < R; ++r) {
+    const int i = (int)i0 + r * 64 + lane;
+    bool bad = true;
+    key[r] = i < w.n_hits ? hit_key(w, i, n_mod, &bad) : -1;
+    x[r] = y[r] = z[r] = 0.f;
+    if (key[r] >= 0) {
+      x[r] = gp(w.x)[i];
+      y[r] = gp(w.y)[i];
+      z[r] = gp(w.z)[i];
     }
   }
+  // bucket starts: an exclusive scan of the bucket counts, kPer consecutive ones a thread
+  constexpr int kPer = (kMaxCoarse + T - 1) / T;
+  int v[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) sum += v[i] = t * kPer + i < nc ? gp(w.coarse_cnt)[t * kPer + i] : 0;
+  const int inc = wave_inclusive(sum);
+  if (lane == 63) s_wave[wv] = inc;
   __syncthreads();
-  int *s_run = s_rows + wv * nc;
+  int ex = inc - sum;
+  for (int q = 0; q < wv; ++q) ex += s_wave[q];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int c = t * kPer + i;
+    if (c < nc) {
+      s_base[c] = ex;
+      if (tb == 0) {
+        gp(w.coarse_off)[c] = ex;
+        if (c == nc - 1) gp(w.coarse_off)[nc] = ex + v[i];
+      }
+    }
+    ex += v[i];
+  }
+  // each wave's hits per bucket (at most 64 R < 2^16)
+  unsigned *mine = rows + wv * row;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (key[r] >= 0) {
+      const int c = key[r] >> kFineBits;
+      atomicAdd(&mine[c >> 1], 1u << (16 * (c & 1)));  // LDS
+    }
+  __syncthreads();
+  // ... into the hits of the waves before it, both halves of a word at once
+  for (int i = t; i < row; i += T) {
+    unsigned run = 0u;
+    for (int q = 0; q < NW; ++q) {
+      const unsigned u = rows[q * row + i];
+      rows[q * row + i] = run;
+      run += u;
+    }
+  }
+  if ((long)tb * (T * R) < w.n_hits)
+    for (int c = t; c < nc; c += T) s_base[c] += gp(w.tile_hist)[(long)tb * nc + c];
+  __syncthreads();
+  unsigned short *s_run = reinterpret_cast<unsigned short *>(mine);
   const int nbits = bits_for(nc);
-  const int i0 = tb * kHitTile + wv * 1024, i1 = min(w.n_hits, i0 + 1024);
-  for (int r0 = i0; r0 < i1; r0 += 64) {
-    const int i = r0 + lane;
-    bool bad = true;
-    const int key = i < i1 ? hit_key(w, i, n_mod, &bad) : -1;
-    const bool act = key >= 0;
-    const int c = act ? key >> kFineBits : 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool act = key[r] >= 0;
+    const int c = act ? key[r] >> kFineBits : 0;
     const unsigned long long peers = match_value(c, nbits, act);
     int base = 0;
     if (act) {
       base = s_run[c];
-      const int pos = base + lanes_below(peers);
-      gstore(w.hcp, pos, make_float4(gp(w.x)[i], gp(w.y)[i], gp(w.z)[i], __int_as_float(hit_tag(i, key))));
+      const int pos = s_base[c] + base + lanes_below(peers);
+      gstore(w.hcp, pos, make_float4(x[r], y[r], z[r], __int_as_float(hit_tag((int)i0 + r * 64 + lane, key[r]))));
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (act && lanes_below(peers) == 0) s_run[c] = base + __popcll(peers);  // the bucket's first lane
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// One block of kSortWaves waves per coarse bucket: the bucket's hits (in input
-// order) are split into kSortWaves consecutive runs; each wave counts its
-// run's keys, the block turns the counts into each (wave, key)'s first
-// position (key order, then wave order: stable), writes the keys' offsets, and
-// every wave places its run's hits 64 at a time in order.
-constexpr int kSortWaves = 8;
-__global__ __launch_bounds__(64 * kSortWaves) void k_bucket_sort(const Ws *__restrict__ wb, int n_mod) {
-  __shared__ int s_cnt[kSortWaves][kFineKeys];
-  __shared__ int s_key0[kFineKeys];
-  const Ws &w = wb[blockIdx.y];
-  const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
-  const int nc = n_coarse(n_mod), ntb = n_hit_tiles(w.n_hits), nkeys = 2 * n_mod;
-  const int c = blockIdx.x;
-  if (c >= nc) return;  // the whole block
-  const int j0 = gp(w.tile_off)[(long)c * ntb], j1 = gp(w.tile_off)[(long)(c + 1) * ntb];
-  const long L = j1 - j0;
-  const int a = j0 + (int)(L * wv / kSortWaves), b = j0 + (int)(L * (wv + 1) / kSortWaves);
-  for (int f = lane; f < kFineKeys; f += 64) s_cnt[wv][f] = 0;
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  for (int j = a + lane; j < b; j += 64) atomicAdd(&s_cnt[wv][tag_fine(gload(w.hcp, j).w)], 1);  // LDS
-  __syncthreads();
-  // each key's total over the waves, then the keys' first positions (wave 0: one key per lane)
-  int tot = 0;
-  if (t < kFineKeys)
-    for (int q = 0; q < kSortWaves; ++q) tot += s_cnt[q][t];
-  if (t < kFineKeys) s_key0[t] = tot;
-  __syncthreads();
-  if (wv == 0) {
-    static_assert(kFineKeys <= 64, "one key per lane");
-    const int x0 = lane < kFineKeys ? s_key0[lane] : 0;
-    int x = x0;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    const int ex = j0 + x - x0;
-    const int k = c * kFineKeys + lane;
-    if (lane < kFineKeys) {
-      s_key0[lane] = ex;
-      if (k < nkeys) gp(w.boff)[k] = ex;
-    }
-    if (c == nc - 1 && lane == 0) gp(w.boff)[nkeys] = j1;
-  }
-  __syncthreads();
-  // first position of each (wave, key): the key's first position plus the earlier waves' counts
-  if (t < kFineKeys) {
-    int run = s_key0[t];
-    for (int q = 0; q < kSortWaves; ++q) {
-      const int v = s_cnt[q][t];
-      s_cnt[q][t] = run;
-      run += v;
-    }
-  }
-  __syncthreads();
-  for (int r0 = a; r0 < b; r0 += 64) {
-    const int j = r0 + lane;
-    const bool act = j < b;
-    const float4 h = act ? gload(w.hcp, j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int f = act ? tag_fine(h.w) : 0;
-    const unsigned long long peers = match_value(f, kFineBits, act);
-    int base = 0;
-    if (act) {
-      base = s_cnt[wv][f];
-      const int pos = base + lanes_below(peers);
-      gp(w.hidx)[pos] = tag_index(h.w);
-      gstore(w.hpos, pos, make_float4(h.x, h.y, h.z, sqrtf(h.x * h.x + h.y * h.y)));
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (act && lanes_below(peers) == 0) s_cnt[wv][f] = base + __popcll(peers);
+    if (act && lanes_below(peers) == 0) s_run[c] = (unsigned short)(base + __popcll(peers));  // the bucket's first lane
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
 }
 
 // ------------------------------------------------------------- a1: MD
-constexpr int kMdStage = 128;  // hits per sensor staged in LDS per wave (more: read from HBM)
 // MD stubs are stored as float2 or, with the geometry's 16-bit stub switch, as
 // a dense array of binary16 pairs (rounded to nearest even) read back as float.
 __device__ __forceinline__ void put_stub(const Ws &w, const DevGeom &g, int pos, float2 st) {
@@ -664,9 +655,6 @@ __device__ __forceinline__ float2 get_stub(const Ws &w, const DevGeom &g, int i)
   if (g.stub16) return __half22float2(gload(reinterpret_cast<const __half2 *>(w.md_stub), i));
   return gload(w.md_stub, i);
 }
-
-constexpr long kMdBig = 2048;  // modules with more pairs go to a whole block (k_md_big)
-constexpr int kMdStageBig = 512;
 
 // Anchor disc of a module for the segment stage's module-level azimuth
 // pre-test, from the lower hits' bounding box (min/max reduced by the caller).
@@ -698,236 +686,310 @@ __device__ __forceinline__ int2 divmod22(int t, int n, float rn) {
   return make_int2(q, r);
 }
 
-// One wave per module of at most kMdBig pairs; pairs (lower i, upper j) in
-// row-major order, 64 at a time, compacted in order by ballot.  The fill also
-// writes the module's anchor disc.
-template <bool FILL>
-__global__ __launch_bounds__(kBlock) void k_md(const Ws *__restrict__ wb, DevGeom g) {
+// Floats as ints of the same order (for LDS atomic minima and maxima).
+__device__ __forceinline__ int ordered(float f) {
+  const int b = __float_as_int(f);
+  return b ^ ((b >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((b >> 31) & 0x7fffffff)); }
+
+// One block of kSortWaves waves per coarse bucket: the bucket's hits (in input
+// order) are split into kSortWaves consecutive runs; each wave counts its
+// run's keys, the block turns the counts into each (wave, key)'s first
+// position (key order, then wave order: stable), writes the keys' offsets, and
+// every wave places its run's hits 64 at a time in order.
+//
+// Then the MD search of the bucket's kBucketMods modules.  A module's window
+// admits about a hundredth of its (lower, upper) pairs, so each upper hit joins,
+// as it is placed, the list in LDS of one of its module's kMdBins bins of u =
+// tan(azimuth from one of the module's lower hits), and each lower hit (one a
+// lane, the bucket's modules end to end) tests only the uppers of the two bins
+// that its window touches.  For |u| <= 1/2 a pair that passes md_pass has
+// |u_j - u_i| = |sin(azimuth change)| / (cos cos) <= 5/4 W, up to rounding (each
+// u within 4e-7, W's test within 1e-6); bins are a little wider than twice that
+// bound (so a window touches two, whatever u inv rounds to) and wrap round (the
+// exact test decides, so sharing a bin only costs a test).  A module
+// with a hit outside that range (or nearly on the beam line, where products may
+// underflow), or a bucket with more hits than the lists hold, has every pair
+// tested.  A lower hit keeps up to kMdKeep partners, in order, for the fill.
+// (Testing all pairs, 8.8M on a PU200 event for 138k MDs, took 25 + 27 us to
+// count and 24 + 14 us to fill for one event, 318 us for eight; the kernel is
+// bound by the chain of its steps in the densest bucket, hence few passes over
+// the hits.)
+constexpr int kSortWaves = 8, kSortThreads = 64 * kSortWaves;
+constexpr int kBucketMods = kFineKeys / 2;
+constexpr int kMdBins = 64;    // per module
+constexpr int kMdList = 8192;  // hits of a bucket that the lists can hold
+static_assert((kMdBins & (kMdBins - 1)) == 0, "bins wrap round by a mask");
+
+// The module of the bucket's q-th lower hit (modules' lower hits before: lpre[0..kBucketMods]).
+__device__ __forceinline__ int lower_module(const int *lpre, int q) {
+  int m = 0;
+#pragma unroll
+  for (int s = kBucketMods / 2; s > 0; s >>= 1)
+    if (lpre[m + s] <= q) m += s;
+  return m;
+}
+// lpre from key0, by the first wave.
+__device__ __forceinline__ void lower_prefix(const int *key0, int *lpre) {
+  const int lane = lane_id();
+  const int n = lane < kBucketMods ? key0[2 * lane + 1] - key0[2 * lane] : 0;
+  const int x = wave_inclusive(n);
+  if (lane <= kBucketMods) lpre[lane] = x - n;
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict__ wb, DevGeom g) {
+  __shared__ int s_cnt[kSortWaves][kFineKeys];
+  __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1];
+  __shared__ int s_head[kBucketMods * kMdBins];  // per (module, bin): its first upper (position in the bucket), -1: none
+  __shared__ unsigned short s_next[kMdList];     // per hit of the bucket: the next upper of its bin
+  __shared__ int s_ref[kBucketMods], s_odd[kBucketMods], s_nmd[kBucketMods];
+  __shared__ float4 s_mod[kBucketMods];          // per module: reference direction x, y, window in u, bins per unit of u
+  __shared__ int s_x0[kBucketMods], s_x1[kBucketMods], s_y0[kBucketMods], s_y1[kBucketMods];
   const Ws &w = wb[blockIdx.y];
-  __shared__ float4 s_lo[kWaves][kMdStage], s_up[kWaves][kMdStage];
-  const int wv = wave_id(), lane = lane_id();
-  const int wpb = blockDim.x >> 6;
-  for (int m = blockIdx.x * wpb + wv; m < g.n_mod; m += gridDim.x * wpb) {
-    const int lo0 = gp(w.boff)[2 * m], nlo = gp(w.boff)[2 * m + 1] - lo0;
-    const int up0 = gp(w.boff)[2 * m + 1], nup = gp(w.boff)[2 * m + 2] - up0;
-    const long npair = (long)nlo * nup;
-    if (npair > kMdBig) {  // k_md_big's, listed for it (the list's order does not matter)
-      if (!FILL && lane == 0) gp(w.md_dense)[atomicAdd(w.ctr + C_NDENSE, 1)] = m;
-      continue;
-    }
-    if (npair == 0) {
-      if (!FILL && lane == 0) gp(w.md_cnt)[m] = 0;
-      continue;
-    }
-    for (int k = lane; k < nlo && k < kMdStage; k += 64) s_lo[wv][k] = gload(w.hpos, lo0 + k);
-    for (int k = lane; k < nup && k < kMdStage; k += 64) s_up[wv][k] = gload(w.hpos, up0 + k);
+  const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
+  const int n_mod = g.n_mod, nc = n_coarse(n_mod), nkeys = 2 * n_mod;
+  const int c = blockIdx.x, m0 = c * kBucketMods;
+  if (c >= nc) return;  // the whole block
+  const int j0 = uload(w.coarse_off + c), j1 = uload(w.coarse_off + c + 1);
+  const long L = j1 - j0;
+  const int a = j0 + (int)(L * wv / kSortWaves), b = j0 + (int)(L * (wv + 1) / kSortWaves);
+  for (int f = lane; f < kFineKeys; f += 64) s_cnt[wv][f] = 0;
+  for (int i = t; i < kBucketMods * kMdBins; i += kSortThreads) s_head[i] = -1;
+  if (t < kBucketMods) {
+    s_ref[t] = -1;
+    s_x0[t] = s_y0[t] = 0x7fffffff;
+    s_x1[t] = s_y1[t] = (int)0x80000000;
+    s_odd[t] = s_nmd[t] = 0;
+  }
+  __syncthreads();
+  for (int j = a + lane; j < b; j += 64) {
+    const int f = tag_fine(gload(w.hcp, j).w);
+    atomicAdd(&s_cnt[wv][f], 1);  // LDS
+    if ((f & 1) == 0) s_ref[f >> 1] = j;  // any of the module's lower hits
+  }
+  __syncthreads();
+  // each key's total over the waves, the keys' first positions (wave 0: one key per lane)
+  // and the modules' lower hits; the modules' references and windows (wave 1: one module per lane)
+  if (wv == 0) {
+    static_assert(kFineKeys < 64, "one key per lane");
+    int tot = 0;
+    if (lane < kFineKeys)
+      for (int q = 0; q < kSortWaves; ++q) tot += s_cnt[q][lane];
+    const int ex = j0 + wave_inclusive(tot) - tot;
+    const int k = c * kFineKeys + lane;
+    if (lane <= kFineKeys) s_key0[lane] = ex;  // (the last one is j1)
+    if (lane < kFineKeys && k < nkeys) gp(w.boff)[k] = ex;
+    if (c == nc - 1 && lane == 0) gp(w.boff)[nkeys] = j1;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const float4 win = gload(g.win, m);
-    const ModInfo mi{gp(g.info)[m]};
-    int base = FILL ? gp(w.md_off)[m] : 0;
-    const int np = (int)npair;  // <= kMdBig here
-    const float rnup = 1.0f / (float)nup;
-    const int n_md = FILL ? gp(w.md_off)[m + 1] - base : 0;
-    auto cache = gp(w.md_cache) + (long)kMdCache * m;
-    const int md_keep = g.tiles.md_cache;
-    if (FILL && n_md <= md_keep) {
-      // the count pass kept this module's passing pairs (row-major order): copy them
-      if (lane < n_md) {
-        const int pk = cache[lane];
-        const int i = pk >> 16, j = pk & 0xffff;
-        const int pos = base + lane;
-        if (pos < w.cap_md) {
-          const float4 hi = i < kMdStage ? s_lo[wv][i] : gload(w.hpos, lo0 + i);
-          const float4 hj = j < kMdStage ? s_up[wv][j] : gload(w.hpos, up0 + j);
-          gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
-          gp(w.md_mod)[pos] = m;
-          gp(w.inc_cnt)[pos] = 0;
-          gstore(w.md_pos, pos, hi);
-          put_stub(w, g, pos, md_stub(hi, hj, mi));
+    lower_prefix(s_key0, s_lpre);
+    // first position of each (wave, key): the key's first position plus the earlier waves' counts
+    if (lane < kFineKeys) {
+      int run = ex;
+      for (int q = 0; q < kSortWaves; ++q) {
+        const int v = s_cnt[q][lane];
+        s_cnt[q][lane] = run;
+        run += v;
+      }
+    }
+  } else if (wv == 1 && lane < kBucketMods && s_ref[lane] >= 0) {
+    const float4 h = gload(w.hcp, s_ref[lane]);
+    const float d = gload(g.win, m0 + lane).x * 1.27f + 4e-6f;
+    s_mod[lane] = make_float4(h.x, h.y, d, 0.47f / d);
+    const float r = sqrtf(h.x * h.x + h.y * h.y);
+    if (!(r >= 1e-3f && r <= 1e6f && d < 0.25f)) s_odd[lane] = 1;
+  }
+  __syncthreads();
+  // u of a hit of module m; false outside the range that the bins cover
+  auto u_of = [&](const float4 &mod, const float4 &h, float *u) {
+    const float dot = mod.x * h.x + mod.y * h.y, cr = mod.x * h.y - mod.y * h.x;
+    *u = cr * frcp(dot);
+    return h.w >= 1e-3f && h.w <= 1e6f && dot > 0.0f && fabsf(cr) <= 0.5f * dot;
+  };
+  auto bin_of = [](float u, float inv) { return (int)floorf(u * inv) & (kMdBins - 1); };
+  for (int r0 = a; r0 < b; r0 += 64) {
+    const int j = r0 + lane;
+    const bool act = j < b;
+    const float4 h = act ? gload(w.hcp, j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const int f = act ? tag_fine(h.w) : 0;
+    const unsigned long long peers = match_value(f, kFineBits, act);
+    int base = 0;
+    if (act) {
+      base = s_cnt[wv][f];
+      const int pos = base + lanes_below(peers), m = f >> 1;
+      const float4 hr = make_float4(h.x, h.y, h.z, sqrtf(h.x * h.x + h.y * h.y));
+      gp(w.hidx)[pos] = tag_index(h.w);
+      gstore(w.hpos, pos, hr);
+      if (s_ref[m] >= 0) {  // the module has lower hits
+        const float4 mod = s_mod[m];
+        float u;
+        if (!u_of(mod, hr, &u)) {
+          s_odd[m] = 1;
+        } else if (f & 1) {
+          const int i = pos - j0;
+          if (i < kMdList) s_next[i] = (unsigned short)atomicExch(&s_head[m * kMdBins + bin_of(u, mod.w)], i);
+        }
+        if ((f & 1) == 0) {  // the module's anchors' bounding box
+          atomicMin(&s_x0[m], ordered(h.x));
+          atomicMax(&s_x1[m], ordered(h.x));
+          atomicMin(&s_y0[m], ordered(h.y));
+          atomicMax(&s_y1[m], ordered(h.y));
         }
       }
     }
-    for (int p0 = 0; p0 < np && !(FILL && n_md <= md_keep); p0 += 64) {
-      const int p = p0 + lane;
-      bool pass = false;
-      int i = 0, j = 0;
-      float4 hi, hj;
-      if (p < np) {
-        const int2 ij = divmod22(p, nup, rnup);
-        i = ij.x;
-        j = ij.y;
-        hi = i < kMdStage ? s_lo[wv][i] : gload(w.hpos, lo0 + i);
-        hj = j < kMdStage ? s_up[wv][j] : gload(w.hpos, up0 + j);
-        pass = md_pass(hi, hj, win, mi);
-      }
-      const unsigned long long bm = __ballot(pass);
-      if (FILL && pass) {
-        const int pos = base + lanes_below(bm);
-        if (pos < w.cap_md) {
-          gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
-          gp(w.md_mod)[pos] = m;
-          gp(w.inc_cnt)[pos] = 0;
-          gstore(w.md_pos, pos, hi);
-          put_stub(w, g, pos, md_stub(hi, hj, mi));
-        }
-      }
-      if (!FILL && pass) {
-        const int r = base + lanes_below(bm);
-        if (r < md_keep) cache[r] = (i << 16) | j;
-      }
-      base += __popcll(bm);
-    }
-    if (!FILL) {
-      if (lane == 0) gp(w.md_cnt)[m] = base;
-    } else {
-      // a disc in x-y around every anchor of this module (the lower hits' bounding box)
-      float x0 = 3.0e38f, x1 = -3.0e38f, y0 = 3.0e38f, y1 = -3.0e38f;
-      for (int k = lane; k < nlo; k += 64) {
-        const float4 h = k < kMdStage ? s_lo[wv][k] : gload(w.hpos, lo0 + k);
-        x0 = fminf(x0, h.x); x1 = fmaxf(x1, h.x);
-        y0 = fminf(y0, h.y); y1 = fmaxf(y1, h.y);
-      }
-      for (int o = 32; o > 0; o >>= 1) {
-        x0 = fminf(x0, __shfl_xor(x0, o, 64)); x1 = fmaxf(x1, __shfl_xor(x1, o, 64));
-        y0 = fminf(y0, __shfl_xor(y0, o, 64)); y1 = fmaxf(y1, __shfl_xor(y1, o, 64));
-      }
-      if (lane == 0) gstore(w.mod_disc, m, anchor_disc(x0, x1, y0, y1));
-    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (act && lanes_below(peers) == 0) s_cnt[wv][f] = base + __popcll(peers);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
+  __syncthreads();
+  // ---- the MD search
+  const bool fits = L <= kMdList;
+  const int n_lower = s_lpre[kBucketMods];
+  for (int q = t; q < n_lower; q += kSortThreads) {
+    const int m = lower_module(s_lpre, q);
+    const int p = s_key0[2 * m] + (q - s_lpre[m]), up0 = s_key0[2 * m + 1], nup = s_key0[2 * m + 2] - up0;
+    unsigned kept[kMdKeep];
+#pragma unroll
+    for (int i = 0; i < kMdKeep; ++i) kept[i] = 0xffffu;
+    int n = 0;
+    auto take = [&](int j) {  // into the kept ones, ascending
+      ++n;
+      unsigned v = (unsigned)min(j, 0xffff);
+#pragma unroll
+      for (int i = 0; i < kMdKeep; ++i) {
+        const unsigned lo = min(kept[i], v);
+        v = max(kept[i], v);
+        kept[i] = lo;
+      }
+    };
+    if (nup > 0) {
+      const float4 hi = gload(w.hpos, p), win = gload(g.win, m0 + m);
+      const ModInfo mi{gp(g.info)[m0 + m]};
+      if (fits && !s_odd[m]) {
+        const float4 mod = s_mod[m];
+        float u;
+        u_of(mod, hi, &u);
+        const int b0 = bin_of(u - mod.z, mod.w), b1 = bin_of(u + mod.z, mod.w);
+        const int *head = s_head + m * kMdBins;
+        // the two bins' lists one after the other
+        int k = head[b0], rest = b1 != b0 ? head[b1] : -1;
+        if (k < 0) {
+          k = rest;
+          rest = -1;
+        }
+        while (k >= 0) {
+          const float4 hj = gload(w.hpos, j0 + k);
+          const int j = j0 + k - up0;
+          k = (int)(short)s_next[k];  // -1 at the end
+          if (k < 0) {
+            k = rest;
+            rest = -1;
+          }
+          if (md_pass(hi, hj, win, mi)) take(j);
+        }
+      } else {
+        for (int j = 0; j < nup; ++j)
+          if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) take(j);
+      }
+    }
+    static_assert(kMdKeep == 6 && kMdList <= 0x8000, "packed in three words; list ends are negative");
+    gstore(reinterpret_cast<int4 *>(w.hcp), p,
+           make_int4((int)(kept[0] | kept[1] << 16), (int)(kept[2] | kept[3] << 16), (int)(kept[4] | kept[5] << 16), n));
+    if (n > 0) atomicAdd(&s_nmd[m], n);
+  }
+  __syncthreads();
+  if (t < kBucketMods && m0 + t < n_mod) {
+    gp(w.md_cnt)[m0 + t] = s_nmd[t];
+    if (s_nmd[t] > 0)
+      gstore(w.mod_disc, m0 + t, anchor_disc(unordered(s_x0[t]), unordered(s_x1[t]), unordered(s_y0[t]), unordered(s_y1[t])));
+  }
+  if (t == 0) {
+    int tot = 0;
+    for (int m = 0; m < kBucketMods; ++m) tot += s_nmd[m];
+    gp(w.md_tot)[c] = tot;
+  }
 }
 
-// The same for the modules with more than kMdBig pairs (listed by the count
-// pass of k_md), one block (kBlock threads) each, so that no single wave
-// carries a dense module and no block walks the modules that are not dense: the block
-// (one wave per part: `parts` = blockDim.x / 64 <= kMdParts) stages both
-// sensors' hits, and each of its waves takes one consecutive part of the
-// module's row-major pairs on its own (no block barrier per round).  Sixteen
-// parts keep the densest module (~24,000 pairs on PU200) from setting the
-// kernel's end when a launch holds one event; over many events four parts
-// run faster.  The count pass writes each part's count (md_part), from which
-// the fill starts each part at the module's offset plus the counts of the
-// parts before it, so the module's MDs stay in row-major order; it also keeps
-// each part's first kMdParts * kMdQCache / parts passing pairs, so the fill of
-// a part with no more than that copies them instead of testing every pair
-// again.
-template <bool FILL>
-__global__ __launch_bounds__(64 * kMdParts) void k_md_big(const Ws *__restrict__ wb, DevGeom g) {
+// The MDs of a coarse bucket, in row-major (lower, upper) order per module: the
+// offset of each of the bucket's lower hits is the MDs of the buckets before
+// (summed here) plus a scan over the lower hits before it.  Partners that the
+// search did not keep are searched again.
+__global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__ wb, DevGeom g) {
+  __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1], s_red[kSortWaves];
   const Ws &w = wb[blockIdx.y];
-  __shared__ float4 s_lo[kMdStageBig], s_up[kMdStageBig];
-  __shared__ int s_part[kMdParts];
-  __shared__ float4 s_box[kMdParts];
-  const int parts = blockDim.x >> 6, qcap = kMdParts * kMdQCache / parts;
-  const int wid = wave_id(), lane = lane_id();
-  const int n_dense = uload(w.ctr + C_NDENSE);
-  for (int kd = blockIdx.x; kd < n_dense; kd += gridDim.x) {
-    const int m = uload(w.md_dense + kd);
-    const int lo0 = gp(w.boff)[2 * m], nlo = gp(w.boff)[2 * m + 1] - lo0;
-    const int up0 = gp(w.boff)[2 * m + 1], nup = gp(w.boff)[2 * m + 2] - up0;
-    const long npair = (long)nlo * nup;
-    if (npair <= kMdBig) continue;
-    __syncthreads();  // the previous module's LDS reads are done
-    for (int k = threadIdx.x; k < nlo && k < kMdStageBig; k += blockDim.x) s_lo[k] = gload(w.hpos, lo0 + k);
-    for (int k = threadIdx.x; k < nup && k < kMdStageBig; k += blockDim.x) s_up[k] = gload(w.hpos, up0 + k);
+  const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
+  const int n_mod = g.n_mod, nc = n_coarse(n_mod), nkeys = 2 * n_mod, c = blockIdx.x;
+  if (c >= nc) return;  // the whole block
+  int v = 0;
+  for (int j = t; j < c; j += kSortThreads) v += gp(w.md_tot)[j];
+  v = wave_total(v);
+  if (lane == 0) s_red[wv] = v;
+  if (t <= kFineKeys) s_key0[t] = gp(w.boff)[min(c * kFineKeys + t, nkeys)];
+  __syncthreads();
+  int run = 0;
+#pragma unroll
+  for (int q = 0; q < kSortWaves; ++q) run += s_red[q];
+  const int m0 = c * kBucketMods;
+  if (wv == 0) {
+    lower_prefix(s_key0, s_lpre);
+    // the modules' offsets; after the last one, the totals
+    const int n = lane < kBucketMods && m0 + lane < n_mod ? gp(w.md_cnt)[m0 + lane] : 0;
+    const int at = run + wave_inclusive(n) - n;
+    if (lane < kBucketMods && m0 + lane < n_mod) {
+      gp(w.md_off)[m0 + lane] = at;
+      if (m0 + lane == n_mod - 1) {
+        gp(w.md_off)[n_mod] = at + n;
+        put_total(w, at + n, w.cap_md, C_RMD, C_NMD);
+      }
+    }
+  }
+  __syncthreads();
+  const int n_lower = s_lpre[kBucketMods], keep = min(g.tiles.md_cache, kMdKeep);
+  for (int q0 = 0; q0 < n_lower; q0 += kSortThreads) {
+    const int q = q0 + t;
+    int m = 0, p = 0;
+    int4 r = make_int4(0, 0, 0, 0);
+    if (q < n_lower) {
+      m = lower_module(s_lpre, q);
+      p = s_key0[2 * m] + (q - s_lpre[m]);
+      r = gload(reinterpret_cast<const int4 *>(w.hcp), p);
+    }
+    const int n = r.w, x = wave_inclusive(n);
+    __syncthreads();  // the previous reads of s_red
+    if (lane == 63) s_red[wv] = x;
     __syncthreads();
-    const float4 win = gload(g.win, m);
-    const ModInfo mi{gp(g.info)[m]};
-    const float rnup = 1.0f / (float)nup;
-    const bool small = npair < (1L << 22);  // divmod22's range (always, below 2,048 hits per sensor)
-    const long q0 = npair * wid / parts, q1 = npair * (wid + 1) / parts;  // this wave's part
-    // the count pass keeps a part's first qcap passing pairs (indices < 2^16)
-    const bool packable = nlo <= 0xffff && nup <= 0xffff;
-    unsigned *qcache = reinterpret_cast<unsigned *>(w.md_bcache) + (long)m * kMdParts * kMdQCache + wid * qcap;
-    int base = 0, qn = 0;
-    if (FILL) {
-      base = gp(w.md_off)[m];
-      for (int q = 0; q < wid; ++q) base += gp(w.md_part)[(long)kMdParts * m + q];
-      qn = gp(w.md_part)[(long)kMdParts * m + wid];
+    int pos = run + x - n;
+    for (int i = 0; i < kSortWaves; ++i) {
+      if (i < wv) pos += s_red[i];
+      run += s_red[i];
     }
-    const bool cached = FILL && packable && qn <= qcap;
-    if (cached) {  // the part's MDs from the count pass's pairs, in the same order
-      for (int k = lane; k < qn; k += 64) {
-        const unsigned e = gp(qcache)[k];
-        const int i = (int)(e >> 16), j = (int)(e & 0xffffu);
-        const float4 hi = i < kMdStageBig ? s_lo[i] : gload(w.hpos, lo0 + i);
-        const float4 hj = j < kMdStageBig ? s_up[j] : gload(w.hpos, up0 + j);
-        const int pos = base + k;
-        if (pos < w.cap_md) {
-          gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
-          gp(w.md_mod)[pos] = m;
-          gp(w.inc_cnt)[pos] = 0;
-          gstore(w.md_pos, pos, hi);
-          put_stub(w, g, pos, md_stub(hi, hj, mi));
-        }
-      }
-    }
-    for (long p0 = q0; p0 < (cached ? q0 : q1); p0 += 64) {
-      const long p = p0 + lane;
-      bool pass = false;
-      int i = 0, j = 0;
-      float4 hi, hj;
-      if (p < q1) {
-        if (small) {
-          const int2 ij = divmod22((int)p, nup, rnup);
-          i = ij.x;
-          j = ij.y;
-        } else {
-          i = (int)(p / nup);
-          j = (int)(p - (long)i * nup);
-        }
-        hi = i < kMdStageBig ? s_lo[i] : gload(w.hpos, lo0 + i);
-        hj = j < kMdStageBig ? s_up[j] : gload(w.hpos, up0 + j);
-        pass = md_pass(hi, hj, win, mi);
-      }
-      const unsigned long long bm = __ballot(pass);
-      if (!FILL && pass && packable) {
-        const int r = base + lanes_below(bm);
-        if (r < qcap) gp(qcache)[r] = ((unsigned)i << 16) | (unsigned)j;
-      }
-      if (FILL && pass) {
-        const int pos = base + lanes_below(bm);
-        if (pos < w.cap_md) {
-          gstore(w.md_hits, pos, make_int2(gp(w.hidx)[lo0 + i], gp(w.hidx)[up0 + j]));
-          gp(w.md_mod)[pos] = m;
-          gp(w.inc_cnt)[pos] = 0;
-          gstore(w.md_pos, pos, hi);
-          put_stub(w, g, pos, md_stub(hi, hj, mi));
-        }
-      }
-      base += __popcll(bm);
-    }
-    if (!FILL) {
-      if (lane == 0) {
-        gp(w.md_part)[(long)kMdParts * m + wid] = base;
-        s_part[wid] = base;
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        int c = 0;
-        for (int q = 0; q < parts; ++q) c += s_part[q];
-        gp(w.md_cnt)[m] = c;
+    if (n == 0) continue;
+    const int up0 = s_key0[2 * m + 1], nup = s_key0[2 * m + 2] - up0;
+    const ModInfo mi{gp(g.info)[m0 + m]};
+    const float4 hi = gload(w.hpos, p);
+    const int lower = gp(w.hidx)[p];
+    auto put = [&](int at, int j, const float4 &hj) {
+      if (at >= w.cap_md) return;
+      gstore(w.md_hits, at, make_int2(lower, gp(w.hidx)[up0 + j]));
+      gp(w.md_mod)[at] = m0 + m;
+      gp(w.inc_cnt)[at] = 0;
+      gstore(w.md_pos, at, hi);
+      put_stub(w, g, at, md_stub(hi, hj, mi));
+    };
+    if (n <= keep && nup <= 0xffff) {
+      for (int i = 0; i < n; ++i) {
+        const int word = i < 2 ? r.x : (i < 4 ? r.y : r.z);
+        const int j = (word >> (16 * (i & 1))) & 0xffff;
+        put(pos + i, j, gload(w.hpos, up0 + j));
       }
     } else {
-      float x0 = 3.0e38f, x1 = -3.0e38f, y0 = 3.0e38f, y1 = -3.0e38f;
-      for (int k = threadIdx.x; k < nlo; k += blockDim.x) {
-        const float4 h = k < kMdStageBig ? s_lo[k] : gload(w.hpos, lo0 + k);
-        x0 = fminf(x0, h.x); x1 = fmaxf(x1, h.x);
-        y0 = fminf(y0, h.y); y1 = fmaxf(y1, h.y);
-      }
-      for (int o = 32; o > 0; o >>= 1) {
-        x0 = fminf(x0, __shfl_xor(x0, o, 64)); x1 = fmaxf(x1, __shfl_xor(x1, o, 64));
-        y0 = fminf(y0, __shfl_xor(y0, o, 64)); y1 = fmaxf(y1, __shfl_xor(y1, o, 64));
-      }
-      if (lane == 0) s_box[wid] = make_float4(x0, x1, y0, y1);
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        for (int q = 1; q < parts; ++q) {
-          x0 = fminf(x0, s_box[q].x); x1 = fmaxf(x1, s_box[q].y);
-          y0 = fminf(y0, s_box[q].z); y1 = fmaxf(y1, s_box[q].w);
-        }
-        gstore(w.mod_disc, m, anchor_disc(x0, x1, y0, y1));
+      const float4 win = gload(g.win, m0 + m);
+      for (int j = 0; j < nup; ++j) {
+        const float4 hj = gload(w.hpos, up0 + j);
+        if (md_pass(hi, hj, win, mi)) put(pos++, j, hj);
       }
     }
   }
@@ -951,8 +1013,6 @@ __global__ __launch_bounds__(64 * kMdParts) void k_md_big(const Ws *__restrict__
 // correctly rounded division and square root; their results differ from the
 // exact values by a few parts in 1e7, far inside each pre-test's margin, so
 // the pre-tests stay supersets of the exact selection that decides.
-__device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
 __device__ __forceinline__ float ls_window_bound(const float4 &A, ModInfo ma, float4 disc, ModInfo mb, float d0) {
   const float ub = kHalfKmax * ((disc.w + disc.z) + mb.er());
@@ -1328,66 +1388,62 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 // 0.93 ms for eight), more than this launch takes.
 //
 // Blocks from n_sum on do what the pixel stages need and nothing else waits for:
-// the seeds' processing order (every block scans the group counts for itself)
-// (and that of their directions) and the pLS duplicate removal (seeds sharing at least 3 pixel hits; the lower
+// the seeds' direction table (every block scans the group counts for itself)
+// and the pLS duplicate removal (seeds sharing at least 3 pixel hits; the lower
 // seed index wins).
 __device__ __forceinline__ bool pls_survives(const Ws &w, int s) {
   int hs[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) hs[k] = gp(w.hits4)[4 * (long)s + k];
+  auto loses_to = [&](int t) {
+    int sh = 0;
+    for (int i = 0; i < 4; ++i) {
+      bool f = false;
+      for (int j = 0; j < 4; ++j) f |= (gp(w.hits4)[4 * (long)t + j] == hs[i]);
+      sh += f ? 1 : 0;
+    }
+    return sh >= 3;
+  };
   for (int k = 0; k < 4; ++k) {
     const int h = hs[k];
     if (h < 0 || h >= w.n_hits) continue;
-    for (int q = gp(w.ph_head)[h]; q >= 0; q = gp(w.ph_next)[q]) {
-      const int t = q >> 2;
-      if (t >= s) continue;
-      int sh = 0;
-      for (int i = 0; i < 4; ++i) {
-        bool f = false;
-        for (int j = 0; j < 4; ++j) f |= (gp(w.hits4)[4 * (long)t + j] == hs[i]);
-        sh += f ? 1 : 0;
-      }
-      if (sh >= 3) return false;
-    }
+    const int o = gp(w.ph_owner)[h];
+    if (o < s && loses_to(o)) return false;
+    for (int q = gp(w.ph_head)[h]; q >= 0; q = gp(w.ph_next)[q])
+      if ((q >> 2) < s && loses_to(q >> 2)) return false;
   }
   return true;
 }
 
 __global__ __launch_bounds__(kBlock) void k_ls_sums(const Ws *__restrict__ wb, int keep, int n_sum) {
   __shared__ int s_red[kWaves];
-  __shared__ int s_off[kSeedKeys], s_dir[kDirBins];
+  __shared__ int s_off[kSeedKeys];
   const Ws &w = wb[blockIdx.y];
   if ((int)blockIdx.x >= n_sum) {
     const int S = w.n_seeds, t = threadIdx.x, lane = lane_id();
     const int q0 = ((int)blockIdx.x - n_sum) * kBlock;
     if (q0 >= S) return;  // the whole block
-    // exclusive prefixes of the group counts and of the azimuth bins' (each from 0)
-    auto prefix = [&](const int *cnt, int *off, auto per) {
-      constexpr int kPer = decltype(per)::value;
-      int c[kPer], sum = 0;
+    // exclusive prefix of the group counts
+    constexpr int kPer = kSeedKeys / kBlock;
+    int c[kPer], sum = 0;
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) sum += c[i] = gp(cnt)[t * kPer + i];
-      const int x = wave_inclusive(sum);
-      __syncthreads();
-      if (lane == 63) s_red[t >> 6] = x;
-      __syncthreads();
-      int ex = x - sum;
-      for (int q = 0; q < (t >> 6); ++q) ex += s_red[q];
+    for (int i = 0; i < kPer; ++i) sum += c[i] = gp(w.seed_cnt)[t * kPer + i];
+    const int x = wave_inclusive(sum);
+    if (lane == 63) s_red[t >> 6] = x;
+    __syncthreads();
+    int ex = x - sum;
+    for (int q = 0; q < (t >> 6); ++q) ex += s_red[q];
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        off[t * kPer + i] = ex;
-        ex += c[i];
-      }
-    };
-    prefix(w.seed_cnt, s_off, std::integral_constant<int, kSeedKeys / kBlock>{});
-    prefix(w.seed_cnt + kSeedKeys, s_dir, std::integral_constant<int, kDirBins / kBlock>{});
+    for (int i = 0; i < kPer; ++i) {
+      s_off[t * kPer + i] = ex;
+      ex += c[i];
+    }
     __syncthreads();
     if (q0 == 0)
-      for (int b = t; b <= kDirBins; b += kBlock) gp(w.sdir_off)[b] = b < kDirBins ? s_dir[b] : S;
+      for (int b = t; b <= kDirBins; b += kBlock) gp(w.sdir_off)[b] = b < kDirBins ? s_off[4 * b] : S;
     for (int s = q0 + t; s < S; s += ((int)gridDim.x - n_sum) * kBlock) {
-      gp(w.seed_order)[s_off[gp(w.seed_key)[s]] + gp(w.seed_slot)[s]] = s;
       const Dir d = seed_dir(load_seed(w, s));
-      const int pos = s_dir[gp(w.dir_key)[s]] + gp(w.dir_slot)[s];
+      const int pos = s_off[gp(w.seed_key)[s]] + gp(w.seed_slot)[s];
       gstore(w.sdir, pos, make_float4(d.dx, d.dy, d.lam, __int_as_float(s)));
       gp(w.sdir_pos)[s] = pos;
       gp(w.pls_keep)[s] = pls_survives(w, s) ? 1 : 0;
@@ -2453,7 +2509,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
   }
   if (si >= w.n_seeds) return;
   // the count: seeds of one direction on neighbouring waves
-  const int s = FILL ? si : uload(w.seed_order + si);
+  const int s = FILL ? si : __float_as_int(gload(w.sdir, si).w);
   const Seed sd = load_seed(w, s);
   static_assert(kPt3Cache <= kPassList && kPt5Cache <= kPassList, "the fill ranks the cache in its LDS list");
   const int pass_list = g.tiles.pass_list;                            // <= kPassList
@@ -3381,25 +3437,43 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   if (whole) (void)hipEventRecord(kt->beg, st);
   // a0: buckets
   run([&] { k_start<<<grid(seeds ? kSeedBins : 4096), kBlock, 0, st>>>(wb); });
-  const long n_tiles = n_hit_tiles(N), n_co = n_coarse(M);
-  run([&] {  // one block per hit tile, and enough threads for the seeds' validation
-    const long blocks = std::max(n_tiles, (S + kBlock - 1) / kBlock);
-    k_hits_count<<<dim3((unsigned)std::max(1L, std::min(blocks, 65535L)), B), kBlock, kWaves * n_co * sizeof(int), st>>>(wb, M);
+  // hits: the tile (rounds of 64 hits a wave) grows with the launch's hits, so that a
+  // small event still fills blocks and a large launch amortises a block's tables
+  const long n_co = n_coarse(M);
+  const int rounds = N * B <= 262144 ? 1 : (N * B <= 1048576 ? 2 : 4);
+  const int tile = kHitTile * rounds;
+  const long n_tiles = n_hit_tiles(N, tile);
+  const bool wide = n_co <= 1700;  // sixteen waves' rows fit 64 KiB of LDS
+  const unsigned hit_blocks = (unsigned)std::max(1L, n_tiles);
+  const size_t lds_scatter = n_co * sizeof(int) + (wide ? 16 : 8) * ((n_co + 1) / 2) * sizeof(int);
+  auto by_tile = [&](auto &&f) {
+    using std::integral_constant;
+    if (wide) {
+      if (rounds == 1) f(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+      else if (rounds == 2) f(integral_constant<int, 16>{}, integral_constant<int, 2>{});
+      else f(integral_constant<int, 16>{}, integral_constant<int, 4>{});
+    } else {
+      if (rounds == 1) f(integral_constant<int, 8>{}, integral_constant<int, 2>{});
+      else if (rounds == 2) f(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+      else f(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+    }
+  };
+  run([&] {  // one block per hit tile, the seeds on further blocks
+    by_tile([&](auto nw, auto r) {
+      const unsigned n_seed = (unsigned)std::min((S + 64 * nw() - 1) / (64 * nw()), 4096L);
+      k_hits_count<nw(), r()><<<dim3(hit_blocks + n_seed, B), 64 * nw(), n_co * sizeof(int), st>>>(wb, M, (int)hit_blocks);
+    });
   });
-  run([&] { scan(wb, B, SC_HITS, n_co * n_tiles, st); });
-  run([&] { k_hits_scatter<<<dim3((unsigned)std::max(1L, n_tiles), B), kBlock, kWaves * n_co * sizeof(int), st>>>(wb, M); });
-  run([&] { k_bucket_sort<<<dim3((unsigned)n_co, B), 64 * kSortWaves, 0, st>>>(wb, M); });
-  // a1: MD (a dense module's block: kMdParts waves for a launch of one event, else 4)
-  const int md_big_threads = 64 * (B == 1 ? kMdParts : 4);
-  run([&] {  // the small modules' count lists the dense ones for k_md_big
-    k_md<false><<<gridwb(M), tb, 0, st>>>(wb, g);
-    k_md_big<false><<<dim3(share(1024, md_big_threads), B), md_big_threads, 0, st>>>(wb, g);
-  });
-  run([&] { scan(wb, B, SC_MD, M, st); });
+  run([&] { k_hits_rows<<<dim3((unsigned)((n_co + 31) / 32), B), 1024, 0, st>>>(wb, M, tile); });
   run([&] {
-    k_md_big<true><<<dim3(share(1024, md_big_threads), B), md_big_threads, 0, st>>>(wb, g);
-    k_md<true><<<gridwb(M), tb, 0, st>>>(wb, g);
+    by_tile([&](auto nw, auto r) {
+      k_hits_scatter<nw(), r()><<<dim3(hit_blocks, B), 64 * nw(), lds_scatter, st>>>(wb, M);
+    });
   });
+  // the bucket sort and a1: MD
+  run([&] { k_bucket_md<<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g); });
+  for (int q = 0; q < 2; ++q) run([&] {});  // md_count, md_scan: with bucket_sort, md_fill
+  run([&] { k_md_fill<<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g); });
   // a2: LS
   run([&] {
     const int lg = ls_group_for(g.tiles, B, b.cap_md);

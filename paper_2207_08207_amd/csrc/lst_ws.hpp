@@ -17,7 +17,6 @@ enum Ctr : int {
   C_NLSOVF = 27,                 // MDs with more segments than the count pass caches
   C_NEXTHITS = 28,               // hits of the extended track-candidate collection
   C_EXT = 29,                    // 1 once the track extensions of the event are written
-  C_NDENSE = 30,                 // modules with more than kMdBig hit pairs (listed in md_dense)
   C_COUNT = 64
 };
 enum : int { ST_BAD_HIT = 1, ST_BAD_SEED = 2, ST_CAPACITY = 4 };
@@ -29,7 +28,7 @@ enum : int { ST_BAD_HIT = 1, ST_BAD_SEED = 2, ST_CAPACITY = 4 };
 // Storage and LDS arrays are sized for the maxima (the kXxx constants below);
 // results never depend on the choice.
 struct Tiles {
-  int md_cache;      // MDs per module whose (lower, upper) pair the MD count pass keeps, 0..kMdCache
+  int md_cache;      // partners per lower hit the MD search keeps, 0..kMdCache (at most kMdKeep are kept)
   int ls_cache;      // segments per MD the segment count pass keeps, 0..kLsCache
   int t3_cache;      // triplets per segment the triplet count pass keeps, 0..kT3Cache
   int t5_cache;      // quintuplets per triplet the quintuplet count pass keeps, 0..kT5Cache
@@ -65,7 +64,7 @@ struct ScanJob {
   int cap;
 };
 enum ScanId : int {
-  SC_HITS, SC_MD, SC_EXT, SC_COUNT
+  SC_EXT, SC_COUNT
 };
 // One array cleared to zero at the start of the chain: n entries, `stride` ints apart.
 struct FillJob {
@@ -94,22 +93,22 @@ __host__ __device__ inline long n_sum_tiles(long cap) { return (cap >> tile_shif
 // than this: the fill searches again).
 constexpr int kLsCache = 32;
 constexpr int kLsGroup = 16;  // most inner MDs per wave of the segment count pass
-constexpr int kMdCache = 32;  // MDs per module whose (lower, upper) pair the MD count pass keeps
-constexpr int kMdParts = 16;   // waves of a dense module's block (k_md_big), one part of its pairs each
-constexpr int kMdQCache = 16;  // MDs per part of a dense module whose pair the MD count pass keeps
+constexpr int kMdCache = 32;  // largest md_cache tile
+constexpr int kMdKeep = 6;    // partners per lower hit the MD search keeps
 constexpr int kT3Cache = 2;   // triplets per parent segment whose candidate the T3 count pass keeps
 constexpr int kT5Cache = 2;   // quintuplets per parent triplet whose candidate the T5 count pass keeps
 constexpr int kPt3Cache = 256;  // pT3 per seed (PU200 maximum ~190)
 constexpr int kPt5Cache = 16;   // pT5 per seed
-// Hit bucketing: block tiles of kHitTile input hits (four waves of 1024);
-// (module, sensor) keys in coarse buckets of kFineKeys consecutive keys (at
-// most kMaxCoarse of them, so 2 n_mod <= kFineKeys * kMaxCoarse).
-constexpr int kHitTile = 4096;
+// Hit bucketing: block tiles of kHitTile to 4 kHitTile input hits; (module,
+// sensor) keys in coarse buckets of kFineKeys consecutive keys (at most
+// kMaxCoarse of them, so 2 n_mod <= kFineKeys * kMaxCoarse).  kScanTileHits: the
+// tile that bounds an event's hits on a detector.
+constexpr int kHitTile = 1024, kScanTileHits = 4096;
 constexpr int kFineBits = 5, kFineKeys = 1 << kFineBits;
 constexpr int kMaxCoarse = 2048;
 constexpr int kMaxModules = kFineKeys * kMaxCoarse / 2;
 __host__ __device__ inline int n_coarse(int n_mod) { return (2 * n_mod + kFineKeys - 1) / kFineKeys; }
-__host__ __device__ inline int n_hit_tiles(long n_hits) { return (int)((n_hits + kHitTile - 1) / kHitTile); }
+__host__ __device__ inline int n_hit_tiles(long n_hits, int tile) { return (int)((n_hits + tile - 1) / tile); }
 constexpr int kPassList = 1024;  // passing objects of one seed ranked in LDS by the seed-search fill
 constexpr int kMaxSlices = 512;  // marked bins of one seed gathered into a flat list in LDS
 constexpr int kExtPerWaveMax = 16;
@@ -120,8 +119,8 @@ constexpr Tiles kTilesDefault{kMdCache, kLsCache, kT3Cache, kT5Cache, kPt3Cache,
 // are contiguous, z ascending, with the row's end as a 56th offset.
 constexpr int kBinRows = 10 * 256, kZBins = 55, kBinStride = kZBins + 1;
 constexpr int kSeedBins = kBinRows * kBinStride;
-constexpr int kSeedKeys = 256 * 8;  // direction groups of the seeds' processing order
-constexpr int kDirBins = 512;       // azimuth bins of the seeds' directions at the beam line
+constexpr int kDirBins = 512;             // azimuth bins of the seeds' directions at the beam line
+constexpr int kSeedKeys = 4 * kDirBins;   // direction groups: each bin in four of the slope
 
 // Device pointers of one event (all inside the workspace except the inputs).
 // Kernels of a batch read descriptor blockIdx.y of a device array of these.
@@ -135,15 +134,16 @@ struct Ws {
   int *ctr;
   // hit buckets by (module, sensor)
   int *boff, *hidx;  // (module, sensor) buckets: offsets (2 n_mod + 1), input index per bucketed hit
-  int *tile_hist, *tile_off;  // hits per (coarse bucket, wave tile), coarse-bucket major, and their scan
-  float4 *hcp;  // hits in coarse-bucket order (stable): x, y, z, input index | key within the bucket << 23 (bits)
+  // hits per (tile, coarse bucket), then the bucket's hits in earlier tiles; hits per coarse
+  // bucket; where each bucket starts
+  int *tile_hist, *coarse_cnt, *coarse_off;
+  // hits in coarse-bucket order (stable): x, y, z, input index | key within the bucket << 23
+  // (bits); once sorted, per lower hit the partners the MD search found (6 x 16 bits, count)
+  float4 *hcp;
   float4 *hpos;
   // mini-doublets
   int *md_cnt, *md_off;
-  int *md_cache;     // per module: up to kMdCache passing pairs (lower << 16 | upper) of the count pass
-  int *md_part;      // per dense module: MDs of each wave's part of its pairs (count pass)
-  int *md_bcache;    // per dense module and part: up to kMdQCache passing pairs (lower << 16 | upper)
-  int *md_dense;     // the dense modules, listed (in any order) by the small-module MD count pass
+  int *md_tot;      // MDs per coarse bucket (kFineKeys / 2 modules)
   int2 *md_hits;    // input indices of the lower and upper hit
   int *md_mod;
   float4 *md_pos;   // anchor (lower hit) x, y, z, r
@@ -179,11 +179,11 @@ struct Ws {
   // pixel seeds
   float *pls;       // 8 per seed: pT, cx, cy, lambda, kappa, x0, y0, z0
   int *pls_keep;
-  int *seed_order;  // seeds in the seed search's processing order (grouped by direction)
-  int *seed_key, *seed_slot, *seed_cnt;  // each seed's direction group and place in it; seeds per group (and per azimuth bin)
-  // seeds using each pixel hit, as linked lists of (4 seed + hit number): the hit's
-  // first entry (-1: none; set for the seeds' hits only) and each entry's next one
-  int *ph_head, *ph_next;
+  int *seed_key, *seed_slot, *seed_cnt;  // each seed's direction group and place in it; seeds per group
+  // seeds using each pixel hit: one of them (the owner), and the others as a linked list of
+  // (4 seed + hit number): the hit's first entry (-1: none) and each entry's next one.  Set
+  // for the seeds' hits only.
+  int *ph_owner, *ph_head, *ph_next;
   // pixel triplets / quintuplets
   int *pt3_cnt, *pt3_off, *pt5_cnt, *pt5_off;
   int *pt3_cache, *pt5_cache;  // per seed: up to kPt3Cache / kPt5Cache passing objects found by the count pass
@@ -203,12 +203,11 @@ struct Ws {
   int4 *bin_rng;
   // track candidates
   int *t5_used;
-  // the seeds sorted by azimuth bin of their direction at the beam line: (dx, dy, lambda,
-  // seed bits), bin offsets, each seed's place, and per place the candidates the seed is in
-  // (1 pT5, 2 pT3)
+  // the seeds sorted by group of their direction at the beam line (the seed search's order
+  // too): (dx, dy, lambda, seed bits), azimuth bin offsets, each seed's place, and per place
+  // the candidates the seed is in (1 pT5, 2 pT3)
   float4 *sdir;
   int *sdir_off, *sdir_pos, *sdir_tc;
-  int *dir_key, *dir_slot;      // each seed's azimuth bin and place in it (counted after seed_cnt)
   int *w_pt5, *w_pt3;           // per seed: its surviving pT5 / pT3 entry, or -1
   // track-candidate flags, one bit a seed (pT5, pT3, pLS) or quintuplet, 64 a word;
   // pls_near: the seeds near a T5 candidate
