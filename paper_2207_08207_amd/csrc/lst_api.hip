@@ -40,6 +40,11 @@ lst_status fail(lst_status s, const std::string &msg) { return fail(s, msg.c_str
   } while (0)
 
 constexpr size_t kAlign = 256;
+// Candidates' ints per event of a batch of B that the chain writes straight to
+// host memory: up to 1 MiB an event (a PU200 event takes 0.55) and 4 MiB a batch,
+// for batches of up to 64 events.
+constexpr int tc_room(int B) { return B > 64 ? 0 : (B <= 4 ? 262144 : 1048576 / B); }
+constexpr size_t kStageMax = 16u << 20;  // largest result copied through pinned memory
 constexpr int kTupleW[7] = {2, 4, 6, 10, 1, 7, 11};
 constexpr int kAttrW[7] = {0, 2, 4, 8, 5, 3, 3};
 constexpr int64_t kMaxCap = 8000000;  // bounded by the two-level device scan (4096 x 2048)
@@ -96,7 +101,8 @@ struct lst_batch_s {
   hipStream_t stream = nullptr;
   hipEvent_t done = nullptr;
   lst::Ws *h_ws = nullptr;  // pinned: the descriptors uploaded to the header
-  int *h_ctr = nullptr;     // pinned: copy of the B x C_COUNT counters
+  int *h_ctr = nullptr;     // pinned: the B x C_COUNT counters, written by the chain
+  int *h_tc = nullptr;      // pinned, B x tc_room(B) ints (or NULL): candidates of the events whose lists fit
   std::atomic<int> refs{0};
   std::atomic<bool> synced{false};
   lst_server_s *server = nullptr;  // a server batch returns its workspace block here when freed
@@ -165,15 +171,14 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   const long nbins = kSeedBins;
   t.bin_cnt = I(nbins); t.bin_off = I(nbins);
   t.t5_used = I(t5 + 1);
-  t.sdir_tc = I(S); t.w_pt5 = I(S); t.w_pt3 = I(S); t.sdir_off = I(kDirBins + 1);
+  t.sdir_tc = I(S); t.sdir_off = I(kDirBins + 1);
   const long sw = (S >> 6) + 1, tw = (t5 >> 6) + 1;  // words of seed / quintuplet flags
   t.m_pt5 = reinterpret_cast<unsigned long long *>(take(8 * (size_t)(3 * sw + tw)));
   t.m_pt3 = t.m_pt5 + sw; t.m_pls = t.m_pt3 + sw; t.m_t5 = t.m_pls + sw;
   t.pls_near = reinterpret_cast<unsigned *>(I(2 * sw));
-  t.tc_type = I(tc); t.tc_off = I(tc + 1); t.tc_hits = I(14 * tc);
+  t.tc_out = I(16 * tc + 1);
   t.tc_md = I(5 * tc); t.tc_kap = F2(tc);
-  t.ext_n = I(tc); t.ext_t3 = I(tc); t.ext_cnt = I(tc + 1); t.ext_off = I(tc + 1); t.ext_hits = I(18 * tc);
-  t.ext_attr = F4(tc);
+  t.ext_cnt = I(tc + 1); t.ext_off = I(tc + 1); t.ext_out = I(26 * tc + 1);
   t.scan_tmp = I(4096);
   // arrays in place of others: once the segments are written, their cache holds what the
   // seed search and the duplicate removal keep per MD; the candidates' lists, written last,
@@ -183,9 +188,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.bin_rng = reinterpret_cast<int4 *>(t.bin_pos + md);
   t.md_bin = reinterpret_cast<int2 *>(t.bin_rng + md);
   t.inc_b0 = reinterpret_cast<int *>(t.md_bin + md);
-  t.t5_slot = t.tc_hits;                       // 4 t5 <= 14 tc
-  t.sdir = reinterpret_cast<float4 *>(t.tc_hits + 4 * t5);  // and 4 S + S more
-  t.sdir_pos = t.tc_hits + 4 * t5 + 4 * S;
+  t.t5_slot = t.tc_out;                        // 4 t5 <= 16 tc
+  t.sdir = reinterpret_cast<float4 *>(t.tc_out + 4 * t5);  // and 4 S + S more
+  t.sdir_pos = t.tc_out + 4 * t5 + 4 * S;
+  t.w_pt3 = t.pt3_cnt; t.w_pt5 = t.pt5_cnt;    // once the entries are written
   t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;          // 2 S <= 5 tc
   // the tile sums, one after another (cleared together)
   const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
@@ -477,7 +483,9 @@ static void *pinned_get(size_t n) {
     }
   }
   void *q = nullptr;
-  if (hipHostMalloc(&q, k < kPoolClasses ? (size_t)1 << k : n, hipHostMallocDefault) != hipSuccess) return nullptr;
+  // every GPU may write there, and the host sees it once the chain has ended
+  constexpr unsigned kFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+  if (hipHostMalloc(&q, k < kPoolClasses ? (size_t)1 << k : n, kFlags) != hipSuccess) return nullptr;
   return q;
 }
 static void pinned_put(void *q, size_t n) {
@@ -525,22 +533,33 @@ static bool batch_host_resources(lst_batch_s *b, int B) {
   if (hipGetDevice(&b->device) != hipSuccess) return false;
   b->h_ctr = static_cast<int *>(pinned_get(sizeof(int) * lst::C_COUNT * B));
   b->h_ws = static_cast<lst::Ws *>(pinned_get(sizeof(lst::Ws) * B));
+  if (tc_room(B) > 0) b->h_tc = static_cast<int *>(pinned_get(sizeof(int) * tc_room(B) * B));  // (optional)
   b->done = event_get(b->device, false);
   return b->h_ctr && b->h_ws && b->done;
 }
 
 static void server_release_batch(lst_server_s *s, lst_batch_s *b);
 
+// Where the chain of event i of the batch writes its results on the host.
+static void set_host_results(const lst_batch_s *b, int i, lst::Ws *w) {
+  w->h_ctr = b->h_ctr + (size_t)i * lst::C_COUNT;
+  w->h_tc = b->h_tc ? b->h_tc + (size_t)i * tc_room(b->B) : nullptr;
+  w->h_tc_cap = b->h_tc ? tc_room(b->B) : 0;
+}
+
 static void release_batch_ref(lst_batch_s *b) {
   if (--b->refs > 0) return;
   if (b->owner && *b->owner == b) *b->owner = nullptr;
   if (b->server) server_release_batch(b->server, b);
-  if (!b->synced && b->done) drop(hipEventSynchronize(b->done));
+  // the chain writes to the pinned buffers until it ends
+  if (b->failed) drop(hipStreamSynchronize(b->stream));
+  else if (!b->synced && b->done) drop(hipEventSynchronize(b->done));
   event_put(b->device, b->tbeg, true);
   event_put(b->device, b->tend, true);
   event_put(b->device, b->done, false);
   pinned_put(b->h_ctr, sizeof(int) * lst::C_COUNT * b->B);
   pinned_put(b->h_ws, sizeof(lst::Ws) * b->B);
+  pinned_put(b->h_tc, sizeof(int) * tc_room(b->B) * b->B);
   delete b;
 }
 
@@ -621,6 +640,7 @@ static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *
                                  d_ctr + (size_t)i * lst::C_COUNT);
     w.x = ev.x; w.y = ev.y; w.z = ev.z; w.module = ev.module; w.sensor = ev.sensor;
     w.px = ev.px; w.py = ev.py; w.pz = ev.pz; w.q = ev.q; w.hits4 = ev.hits4;
+    set_host_results(b, i, &w);
     bound.n_hits = std::max(bound.n_hits, w.n_hits);
     bound.n_seeds = std::max(bound.n_seeds, w.n_seeds);
     bound.cap_md = std::max(bound.cap_md, w.cap_md);
@@ -637,13 +657,14 @@ static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *
     kt = lst::KernelTimer{site, b->tbeg, b->tend};
     b->timed_site = site;
   }
-  hipError_t he = hipMemcpyAsync(d_ws, b->h_ws, sizeof(lst::Ws) * B, hipMemcpyHostToDevice, stream);
+  // one event: its descriptor goes with the first launch
+  hipError_t he = hipSuccess;
+  if (B > 1) he = hipMemcpyAsync(d_ws, b->h_ws, sizeof(lst::Ws) * B, hipMemcpyHostToDevice, stream);
   if (he == hipSuccess) {
-    lst::enqueue_chain(g->g, d_ws, B, bound, stream, b->timed_site >= 0 ? &kt : nullptr, g->site_block);
+    lst::enqueue_chain(g->g, d_ws, B, bound, stream, b->timed_site >= 0 ? &kt : nullptr, g->site_block,
+                       B == 1 ? b->h_ws : nullptr);
     he = hipGetLastError();
   }
-  if (he == hipSuccess)
-    he = hipMemcpyAsync(b->h_ctr, d_ctr, sizeof(int) * lst::C_COUNT * B, hipMemcpyDeviceToHost, stream);
   if (he == hipSuccess) he = hipEventRecord(b->done, stream);
   if (he != hipSuccess) b->failed = true;
   *out = b;
@@ -811,8 +832,7 @@ lst_status lst_build_event_static(lst_geometry g, const lst_event_desc *ev, cons
   w.x = ev->x; w.y = ev->y; w.z = ev->z; w.module = ev->module; w.sensor = ev->sensor;
   w.px = ev->px; w.py = ev->py; w.pz = ev->pz; w.q = ev->q; w.hits4 = ev->hits4;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  lst::launch_put_desc(w, d_ws, st);
-  lst::enqueue_chain(g->g, d_ws, 1, w, st, nullptr, g->site_block);
+  lst::enqueue_chain(g->g, d_ws, 1, w, st, nullptr, g->site_block, &w);
   lst::launch_tc_export(d_ws, max_tc, max_tc_hits, type, offsets, hits, counts, st);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip("lst_build_event_static: launch", e);
@@ -840,6 +860,26 @@ lst_status lst_get_stage_counts(lst_event e, int64_t *counts, int64_t *required)
   return LST_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// A device range in a pinned buffer of the pool.
+struct Staged {
+  void *buf = nullptr;
+  size_t bytes = 0;
+  ~Staged() { pinned_put(buf, bytes); }
+};
+lst_status stage_copy(const void *src, size_t bytes, Staged *s) {
+  s->bytes = bytes;
+  s->buf = pinned_get(bytes);
+  if (!s->buf) return fail(LST_E_NOMEM, "pinned buffer for the results");
+  HIP_TRY(hipMemcpy(s->buf, src, bytes, hipMemcpyDeviceToHost));
+  return LST_OK;
+}
+}  // namespace
+
+extern "C" {
+
 lst_status lst_get_track_candidates(lst_event e, int32_t *n_tc, int32_t *n_hits_total, int32_t *type,
                                     int32_t *offsets, int32_t *hits) {
   if (!e || !n_tc || !n_hits_total) return fail(LST_E_INVALID, "lst_get_track_candidates: NULL argument");
@@ -847,12 +887,30 @@ lst_status lst_get_track_candidates(lst_event e, int32_t *n_tc, int32_t *n_hits_
   const int st = e->ctr()[lst::C_STATUS];
   if (st != 0) return fail(LST_E_STATE, "event did not build (status flags " + std::to_string(st) + ")");
   const lst::Ws &w = e->ws();
-  const int n = e->ctr()[lst::C_NTC], nh = e->ctr()[lst::C_NTCHITS];
-  *n_tc = n;
-  *n_hits_total = nh;
-  if (type && n > 0) HIP_TRY(hipMemcpy(type, w.tc_type, sizeof(int) * n, hipMemcpyDeviceToHost));
-  if (offsets) HIP_TRY(hipMemcpy(offsets, w.tc_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
-  if (hits && nh > 0) HIP_TRY(hipMemcpy(hits, w.tc_hits, sizeof(int) * nh, hipMemcpyDeviceToHost));
+  const size_t n = e->ctr()[lst::C_NTC], nh = e->ctr()[lst::C_NTCHITS];
+  *n_tc = (int32_t)n;
+  *n_hits_total = (int32_t)nh;
+  if (!type && !offsets && !hits) return LST_OK;
+  // types, offsets and hit lists are consecutive: on the host already, or one copy away
+  const size_t ints = 2 * n + 1 + nh;
+  Staged s;
+  const int *src = nullptr;
+  if (e->ctr()[lst::C_EXT] != 1 && w.h_tc && ints <= (size_t)w.h_tc_cap) {
+    src = w.h_tc;
+  } else if (ints * sizeof(int) <= kStageMax) {
+    const lst_status cs = stage_copy(w.tc_out, ints * sizeof(int), &s);
+    if (cs != LST_OK) return cs;
+    src = static_cast<const int *>(s.buf);
+  }
+  if (src) {
+    if (type && n > 0) std::memcpy(type, src, sizeof(int) * n);
+    if (offsets) std::memcpy(offsets, src + n, sizeof(int) * (n + 1));
+    if (hits && nh > 0) std::memcpy(hits, src + 2 * n + 1, sizeof(int) * nh);
+    return LST_OK;
+  }
+  if (type && n > 0) HIP_TRY(hipMemcpy(type, w.tc_out, sizeof(int) * n, hipMemcpyDeviceToHost));
+  if (offsets) HIP_TRY(hipMemcpy(offsets, w.tc_out + n, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
+  if (hits && nh > 0) HIP_TRY(hipMemcpy(hits, w.tc_out + 2 * n + 1, sizeof(int) * nh, hipMemcpyDeviceToHost));
   return LST_OK;
 }
 
@@ -866,22 +924,38 @@ lst_status lst_get_extended_track_candidates(lst_event e, int32_t *n_tc, int32_t
   if (e->ctr()[lst::C_EXT] != 1)
     return fail(LST_E_STATE, "track extensions were not enabled on the geometry when the event was enqueued");
   const lst::Ws &w = e->ws();
-  const int n = e->ctr()[lst::C_NTC], nh = e->ctr()[lst::C_NEXTHITS];
-  *n_tc = n;
-  *n_hits_total = nh;
-  if (type && n > 0) HIP_TRY(hipMemcpy(type, w.tc_type, sizeof(int) * n, hipMemcpyDeviceToHost));
-  if (offsets) HIP_TRY(hipMemcpy(offsets, w.ext_off, sizeof(int) * (n + 1), hipMemcpyDeviceToHost));
-  if (hits && nh > 0) HIP_TRY(hipMemcpy(hits, w.ext_hits, sizeof(int) * nh, hipMemcpyDeviceToHost));
-  if (n_added && n > 0) HIP_TRY(hipMemcpy(n_added, w.ext_n, sizeof(int) * n, hipMemcpyDeviceToHost));
-  if (t3 && n > 0) HIP_TRY(hipMemcpy(t3, w.ext_t3, sizeof(int) * n, hipMemcpyDeviceToHost));
-  if (attrs && n > 0) {
-    std::vector<float4> a;
-    HIP_TRY(d2h(a, w.ext_attr, (size_t)n));
-    for (int i = 0; i < n; ++i) {
-      attrs[3 * (size_t)i] = a[i].x;
-      attrs[3 * (size_t)i + 1] = a[i].y;
-      attrs[3 * (size_t)i + 2] = a[i].z;
-    }
+  const size_t n = e->ctr()[lst::C_NTC], nh = e->ctr()[lst::C_NEXTHITS];
+  *n_tc = (int32_t)n;
+  *n_hits_total = (int32_t)nh;
+  if (!type && !offsets && !hits && !n_added && !t3 && !attrs) return LST_OK;
+  const size_t ints = lst::ExtOut::ints(n, nh);
+  Staged s;
+  int *src = nullptr;
+  if (w.h_tc && ints <= (size_t)w.h_tc_cap) {
+    src = w.h_tc;
+  } else if (ints * sizeof(int) <= kStageMax) {
+    const lst_status cs = stage_copy(w.ext_out, ints * sizeof(int), &s);
+    if (cs != LST_OK) return cs;
+    src = static_cast<int *>(s.buf);
+  }
+  const lst::ExtOut x(src ? src : w.ext_out, n);
+  auto get = [&](void *dst, const void *from, size_t bytes) {
+    if (!dst || bytes == 0) return hipSuccess;
+    if (!src) return hipMemcpy(dst, from, bytes, hipMemcpyDeviceToHost);
+    std::memcpy(dst, from, bytes);
+    return hipSuccess;
+  };
+  std::vector<float4> a(attrs ? n : 0);
+  HIP_TRY(get(type, x.type, sizeof(int) * n));
+  HIP_TRY(get(offsets, x.off, sizeof(int) * (n + 1)));
+  HIP_TRY(get(hits, x.hits, sizeof(int) * nh));
+  HIP_TRY(get(n_added, x.added, sizeof(int) * n));
+  HIP_TRY(get(t3, x.t3, sizeof(int) * n));
+  HIP_TRY(get(a.data(), x.attr, sizeof(float4) * a.size()));
+  for (size_t i = 0; i < a.size(); ++i) {
+    attrs[3 * i] = a[i].x;
+    attrs[3 * i + 1] = a[i].y;
+    attrs[3 * i + 2] = a[i].z;
   }
   return LST_OK;
 }
@@ -1043,12 +1117,12 @@ lst_status lst_plan_create(lst_geometry g, int32_t B, int32_t max_hits, int32_t 
   bound.n_hits = max_hits;
   bound.n_seeds = max_seeds;
   bound.cap_tc = (int)(c[0].pt5 + c[0].pt3 + c[0].t5 + max_seeds);
-  const lst::Ws *d_ws = reinterpret_cast<const lst::Ws *>(p->base);
+  lst::Ws *d_ws = reinterpret_cast<lst::Ws *>(p->base);
   hipStream_t cs = nullptr;
   hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    lst::enqueue_chain(g->g, d_ws, B, bound, cs, nullptr, g->site_block);
+    lst::enqueue_chain(g->g, d_ws, B, bound, cs, nullptr, g->site_block, nullptr);
     hipError_t le = hipGetLastError();
     e = hipStreamEndCapture(cs, &p->graph);
     if (e == hipSuccess) e = le;
@@ -1089,12 +1163,12 @@ lst_status lst_plan_run(lst_plan p, int32_t n_events, const lst_event_desc *evs,
     release_batch_ref(b);
     return fail(LST_E_DEVICE, "lst_plan_run: pinned buffers or event creation failed");
   }
-  for (int i = 0; i < p->B; ++i) plan_slot(p, i, i < n_events ? &evs[i] : nullptr, &b->h_ws[i]);
-  int *d_ctr = reinterpret_cast<int *>(p->base + ((sizeof(lst::Ws) * (size_t)p->B + kAlign - 1) / kAlign) * kAlign);
+  for (int i = 0; i < p->B; ++i) {
+    plan_slot(p, i, i < n_events ? &evs[i] : nullptr, &b->h_ws[i]);
+    set_host_results(b, i, &b->h_ws[i]);
+  }
   hipError_t he = hipMemcpyAsync(p->base, b->h_ws, sizeof(lst::Ws) * p->B, hipMemcpyHostToDevice, b->stream);
   if (he == hipSuccess) he = hipGraphLaunch(p->exec, b->stream);
-  if (he == hipSuccess)
-    he = hipMemcpyAsync(b->h_ctr, d_ctr, sizeof(int) * lst::C_COUNT * p->B, hipMemcpyDeviceToHost, b->stream);
   if (he == hipSuccess) he = hipEventRecord(b->done, b->stream);
   if (he != hipSuccess) b->failed = true;
   for (int i = 0; i < n_events; ++i) {

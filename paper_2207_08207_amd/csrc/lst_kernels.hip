@@ -94,9 +94,17 @@ __device__ __forceinline__ int dev_count(const int *p, int fallback) { return p 
 // The chain's first launch: clears what later kernels count into, empties the
 // lists of the pixel hits that seeds use and gives each such hit an owner, the
 // seed whose store came last (the rest of ph_head and ph_owner is never read).  Arrays indexed by MDs or quintuplets are cleared where those are
-// written, so no other launch of the chain only clears.
-__global__ void k_start(const Ws *__restrict__ wb) {
-  const Ws &w = wb[blockIdx.y];
+// written, so no other launch of the chain only clears.  For one event (VALUE)
+// the launch's arguments carry the descriptor, and its first block writes it
+// where the later launches read it, instead of a copy before the chain.
+template <bool VALUE>
+__global__ void k_start(Ws value, Ws *wb) {
+  const Ws &w = VALUE ? value : wb[blockIdx.y];
+  if (VALUE && blockIdx.x == 0) {
+    static_assert(sizeof(Ws) % 4 == 0 && sizeof(Ws) <= 3584, "the first launch argument, within the argument block");
+    const auto *src = (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+    for (int i = threadIdx.x; i < (int)(sizeof(Ws) / 4); i += blockDim.x) gp(reinterpret_cast<int *>(wb))[i] = src[i];
+  }
   const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   for (int j = 0; j < FL_COUNT; ++j) {
     int *p = w.fills[j].p;
@@ -296,12 +304,6 @@ void launch_module_windows(const int *info, const float *pos_lo, const float *po
 }
 
 // ------------------------------------------------- allocation-free forms
-// One event descriptor written into device memory by a kernel (its argument
-// block carries it), for callers that have no host staging buffer.
-__global__ void k_put_desc(Ws w, Ws *dst) { *dst = w; }
-
-void launch_put_desc(const Ws &w, Ws *dst, hipStream_t st) { k_put_desc<<<1, 1, 0, st>>>(w, dst); }
-
 // Copies an event's track candidates to caller device buffers: counts[0] =
 // candidates, counts[1] = their hits, counts[2] = the chain's status flags;
 // the arrays are written only when the chain succeeded and both fit.
@@ -317,10 +319,10 @@ __global__ void k_tc_export(const Ws *__restrict__ wb, int max_tc, int max_hits,
   }
   if (st != 0 || n > max_tc || nh > max_hits) return;
   for (int i = tid; i <= n; i += stride) {
-    if (i < n) type[i] = w.tc_type[i];
-    off[i] = w.tc_off[i];
+    if (i < n) type[i] = gp(w.tc_out)[i];
+    off[i] = gp(w.tc_out)[n + i];
   }
-  for (int i = tid; i < nh; i += stride) hits[i] = w.tc_hits[i];
+  for (int i = tid; i < nh; i += stride) hits[i] = gp(w.tc_out)[2L * n + 1 + i];
 }
 
 void launch_tc_export(const Ws *d_ws, int max_tc, int max_hits, int *type, int *off, int *hits, int *counts,
@@ -3043,9 +3045,13 @@ __device__ __forceinline__ void ext_record(const Ws &w, int k, const int *md, in
 // Output: type, offsets, hit lists (pixel hits first, then MD hits inner to
 // outer), in the order pT5, pT3, T5, pLS.  A wave takes one word of flags of one
 // kind; its candidates' ranks come from the popcounts of the words before it and
-// of the kinds before its own, which every block sums for itself.
-__global__ __launch_bounds__(kBlock) void k_tc_write(const Ws *__restrict__ wb, int n_seed_blocks) {
+// of the kinds before its own, which every block sums for itself; its hit lists
+// are consecutive, so they are put together in LDS and written as one run, to
+// host memory as well if all candidates fit there.  last_launch: this launch ends the
+// chain (no track extensions), so its results go to the host.
+__global__ __launch_bounds__(kBlock) void k_tc_write(const Ws *__restrict__ wb, int n_seed_blocks, int last_launch) {
   __shared__ int s_sum[kWaves][5];
+  __shared__ int s_hits[kWaves][64 * 14];
   const Ws &w = wb[blockIdx.y];
   const int S = w.n_seeds, n_t5 = uload(w.ctr + C_NT5);
   const int sw = (S + 63) >> 6, tw = (n_t5 + 63) >> 6;
@@ -3069,7 +3075,7 @@ __global__ __launch_bounds__(kBlock) void k_tc_write(const Ws *__restrict__ wb, 
   for (int j = threadIdx.x; j < sw; j += kBlock) {
     v[0] += __popcll(word(0, j));
     v[1] += __popcll(word(1, j));
-    if (totals) v[2] += __popcll(word(2, j));
+    v[2] += __popcll(word(2, j));
   }
   for (int j = threadIdx.x; j < tw; j += kBlock) v[3] += __popcll(word(3, j));
   for (int j = threadIdx.x; j < first; j += kBlock) v[4] += __popcll(word(kind, j));
@@ -3085,61 +3091,70 @@ __global__ __launch_bounds__(kBlock) void k_tc_write(const Ws *__restrict__ wb, 
     for (int p = 0; p < kWaves; ++p) x += s_sum[p][i];
     v[i] = x;
   }
-  const int n0 = v[0], n1 = v[1], n2 = v[3];
-  const long h1 = 14L * n0, h2 = h1 + 10L * n1, h3 = h2 + 10L * n2;
-  if (totals && threadIdx.x == 0) {
-    const int n3 = v[2], n = n0 + n1 + n2 + n3;
-    w.ctr[C_NTC0] = n0;
-    w.ctr[C_NTC1] = n1;
-    w.ctr[C_NTC2] = n2;
-    w.ctr[C_NTC3] = n3;
-    w.ctr[C_NTC] = n;
-    w.ctr[C_NTCHITS] = (int)(h3 + 4L * n3);
-    w.tc_off[n] = (int)(h3 + 4L * n3);
+  const int n0 = v[0], n1 = v[1], n2 = v[3], n3 = v[2], n = n0 + n1 + n2 + n3;
+  const long h1 = 14L * n0, h2 = h1 + 10L * n1, h3 = h2 + 10L * n2, nh = h3 + 4L * n3;
+  int *host = (last_launch && w.h_tc && 2L * n + 1 + nh <= w.h_tc_cap) ? w.h_tc : nullptr;
+  auto put = [&](long i, int x) {
+    gp(w.tc_out)[i] = x;
+    if (host) gp(host)[i] = x;
+  };
+  if (totals && wv == 0) {
+    const int mine[6] = {C_NTC0, C_NTC1, C_NTC2, C_NTC3, C_NTC, C_NTCHITS};
+    const int val[6] = {n0, n1, n2, n3, n, (int)nh};
+    int x = gp(w.ctr)[lane];
+    static_assert(C_COUNT == 64, "a counter per lane");
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+      if (lane == mine[i]) {
+        x = val[i];
+        gp(w.ctr)[lane] = x;
+      }
+    if (last_launch && w.h_ctr) gp(w.h_ctr)[lane] = x;
+    if (lane == 0) put(2L * n, (int)nh);  // the offsets' end
   }
+  const int width = kind == 0 ? 14 : (kind == 2 ? 4 : 10);
+  const int at = kind == 0 ? 0 : (kind == 1 ? n0 : (kind == 3 ? n0 + n1 : n0 + n1 + n2));  // the kind's first candidate
+  const long hat = kind == 0 ? 0 : (kind == 1 ? h1 : (kind == 3 ? h2 : h3));               // and its first hit
   int run = v[4];  // this kind's candidates before the round
   for (long r = first; r < last; r += kWaves) {
-    int k = run;
+    int k0 = run;
     unsigned long long m = 0;
     for (int p = 0; p < kWaves; ++p) {
       const unsigned long long mp = r + p < last ? word(kind, (int)r + p) : 0ull;
-      if (p < wv) k += __popcll(mp);
+      if (p < wv) k0 += __popcll(mp);
       if (p == wv) m = mp;
       run += __popcll(mp);
     }
-    if (!(m >> lane & 1)) continue;
-    k += lanes_below(m);
-    const int i = (int)(r + wv) * 64 + lane;  // the seed or the quintuplet
-    if (kind == 0) {
-      const int2 so = gload(w.pt5_so, gp(w.w_pt5)[i]);
-      int *h = w.tc_hits + 14L * k;
-      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
-      t5_hits(w, so.y, h + 4);
-      w.tc_type[k] = 0;
-      ext_record(w, k, w.t5_md + 5 * (long)so.y, 5, seed_kappa(w, i));
-      w.tc_off[k] = 14 * k;
-    } else if (kind == 1) {
-      const int2 so = gload(w.pt3_so, gp(w.w_pt3)[i]);
-      int *h = w.tc_hits + h1 + 10L * k;
-      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
-      obj_hits<3>(w, so.y, h + 4);
-      w.tc_type[n0 + k] = 1;
-      const int4 abc = gload(w.t3_md, so.y);
-      const int md[3] = {abc.x, abc.y, abc.z};
-      ext_record(w, n0 + k, md, 3, seed_kappa(w, i));
-      w.tc_off[n0 + k] = (int)(h1 + 10L * k);
-    } else if (kind == 2) {
-      int *h = w.tc_hits + h3 + 4L * k;
-      for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
-      w.tc_type[n0 + n1 + n2 + k] = 3;
-      w.tc_off[n0 + n1 + n2 + k] = (int)(h3 + 4L * k);
-    } else {
-      t5_hits(w, i, w.tc_hits + h2 + 10L * k);
-      w.tc_type[n0 + n1 + k] = 2;
-      ext_record(w, n0 + n1 + k, w.t5_md + 5 * (long)i, 5,
-                 make_float2(w.t5_attr[8 * (long)i], w.t3_attr[gload(w.t5_t3, i).y].y));
-      w.tc_off[n0 + n1 + k] = (int)(h2 + 10L * k);
+    if (m >> lane & 1) {
+      const int row = lanes_below(m), k = at + k0 + row;
+      const int i = (int)(r + wv) * 64 + lane;  // the seed or the quintuplet
+      int *h = &s_hits[wv][row * width];
+      if (kind != 3)
+        for (int p = 0; p < 4; ++p) h[p] = gp(w.hits4)[4 * (long)i + p];
+      if (kind == 0) {
+        const int2 so = gload(w.pt5_so, gp(w.w_pt5)[i]);
+        t5_hits(w, so.y, h + 4);
+        ext_record(w, k, w.t5_md + 5 * (long)so.y, 5, seed_kappa(w, i));
+      } else if (kind == 1) {
+        const int2 so = gload(w.pt3_so, gp(w.w_pt3)[i]);
+        obj_hits<3>(w, so.y, h + 4);
+        const int4 abc = gload(w.t3_md, so.y);
+        const int md[3] = {abc.x, abc.y, abc.z};
+        ext_record(w, k, md, 3, seed_kappa(w, i));
+      } else if (kind == 3) {
+        t5_hits(w, i, h);
+        ext_record(w, k, w.t5_md + 5 * (long)i, 5,
+                   make_float2(w.t5_attr[8 * (long)i], w.t3_attr[gload(w.t5_t3, i).y].y));
+      }
+      put(k, kind == 2 ? 3 : (kind == 3 ? 2 : kind));
+      put((long)n + k, (int)(hat + (long)width * (k0 + row)));
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int cnt = __popcll(m) * width;
+    for (int i = lane; i < cnt; i += 64) put(2L * n + 1 + hat + (long)width * k0 + i, s_hits[wv][i]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -3233,7 +3248,7 @@ __global__ __launch_bounds__(kBlock) void k_tc_ext(const Ws *__restrict__ wb, De
     const bool mine = lane < kExtPerWave && k < n;
     int cnt = 0;
     if (mine) {
-      const int type = w.tc_type[k];
+      const int type = gp(w.tc_out)[k];
       const int K = type == 3 ? 0 : (type == 1 ? 3 : 5);
       s_k[wv][lane] = K;
       if (K > 0) {
@@ -3323,38 +3338,82 @@ __global__ __launch_bounds__(kBlock) void k_tc_ext(const Ws *__restrict__ wb, De
       __builtin_amdgcn_wave_barrier();
     }
     if (mine) {
-      w.ext_n[k] = best_n;
-      w.ext_t3[k] = best_t;
-      gstore(w.ext_attr, k, best_a);
-      w.ext_cnt[k] = (w.tc_off[k + 1] - w.tc_off[k]) + 2 * best_n;
+      const ExtOut x(w.ext_out, n);
+      gp(x.added)[k] = best_n;
+      gp(x.t3)[k] = best_t;
+      const float at[4] = {best_a.x, best_a.y, best_a.z, best_a.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gp(x.attr)[4L * k + i] = __float_as_int(at[i]);
+      w.ext_cnt[k] = (gp(w.tc_out)[n + k + 1] - gp(w.tc_out)[n + k]) + 2 * best_n;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
 }
 
-// The extended collection: each candidate's hits, then those of its added MDs.
-__global__ void k_tc_ext_write(const Ws *__restrict__ wb) {
+// The extended collection: each candidate's hits, then those of its added MDs,
+// and the types and offsets beside what the search wrote.  A wave takes 64
+// candidates, whose hit lists are consecutive: put together in LDS and written
+// as one run, to host memory as well (with the rest of ext_out) if it fits there.
+__global__ __launch_bounds__(kBlock) void k_tc_ext_write(const Ws *__restrict__ wb) {
+  __shared__ int s_hits[kWaves][64 * 18];
   const Ws &w = wb[blockIdx.y];
-  const int n = uload(w.ctr + C_NTC);
-  const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid == 0) w.ctr[C_EXT] = 1;
-  for (int k = tid; k < n; k += gridDim.x * blockDim.x) {
-    int *dst = w.ext_hits + w.ext_off[k];
-    const int b1 = w.tc_off[k + 1];
-    for (int h = w.tc_off[k]; h < b1; ++h) *dst++ = w.tc_hits[h];
-    const int na = w.ext_n[k];
-    if (na > 0) {
-      const int4 abc = w.t3_md[w.ext_t3[k]];
-      int2 hh = gload(w.md_hits, na == 1 ? abc.z : abc.y);
-      dst[0] = hh.x;
-      dst[1] = hh.y;
-      if (na == 2) {
-        hh = gload(w.md_hits, abc.z);
-        dst[2] = hh.x;
-        dst[3] = hh.y;
+  const int n = uload(w.ctr + C_NTC), nh = uload(w.ctr + C_NEXTHITS);
+  const int lane = lane_id(), wv = wave_id();
+  if (blockIdx.x == 0 && wv == 0) {  // the chain's end: the counters to the host
+    static_assert(C_COUNT == 64, "a counter per lane");
+    int x = gp(w.ctr)[lane];
+    if (lane == C_EXT) {
+      x = 1;
+      gp(w.ctr)[lane] = x;
+    }
+    if (w.h_ctr) gp(w.h_ctr)[lane] = x;
+  }
+  int *host = (w.h_tc && ExtOut::ints(n, nh) <= w.h_tc_cap) ? w.h_tc : nullptr;
+  const ExtOut x(w.ext_out, n), y(host, n);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    x.off[n] = nh;
+    if (host) y.off[n] = nh;
+  }
+  for (long c0 = ((long)blockIdx.x * kWaves + wv) * 64; c0 < n; c0 += (long)gridDim.x * kWaves * 64) {
+    const int k = (int)c0 + lane;
+    const int first = uload(w.ext_off + c0);
+    const int end = uload(w.ext_off + min(c0 + 64, (long)n));
+    if (k < n) {
+      const int type = gp(w.tc_out)[k], b0 = gp(w.tc_out)[n + k], b1 = gp(w.tc_out)[n + k + 1];
+      const int off = gp(w.ext_off)[k], na = gp(x.added)[k], t3 = gp(x.t3)[k];
+      int *dst = &s_hits[wv][off - first];
+      for (int h = b0; h < b1; ++h) *dst++ = gp(w.tc_out)[2L * n + 1 + h];
+      if (na > 0) {
+        const int4 abc = gload(w.t3_md, t3);
+        int2 hh = gload(w.md_hits, na == 1 ? abc.z : abc.y);
+        dst[0] = hh.x;
+        dst[1] = hh.y;
+        if (na == 2) {
+          hh = gload(w.md_hits, abc.z);
+          dst[2] = hh.x;
+          dst[3] = hh.y;
+        }
+      }
+      gp(x.type)[k] = type;
+      gp(x.off)[k] = off;
+      if (host) {
+        gp(y.type)[k] = type;
+        gp(y.off)[k] = off;
+        gp(y.added)[k] = na;
+        gp(y.t3)[k] = t3;
+        for (int i = 0; i < 4; ++i) gp(y.attr)[4L * k + i] = gp(x.attr)[4L * k + i];
       }
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < end - first; i += 64) {
+      const int v = s_hits[wv][i];
+      gp(x.hits)[(long)first + i] = v;
+      if (host) gp(y.hits)[(long)first + i] = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -3400,8 +3459,8 @@ int ls_group_for(const Tiles &t, int B, long cap_md) {
   return (int)std::max(1L, std::min((long)kLsGroup, gsz));
 }
 
-void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream_t st, const KernelTimer *kt,
-                   const int *site_block) {
+void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st, const KernelTimer *kt,
+                   const int *site_block, const Ws *value) {
   int site = 0;
   int tb = kBlock;  // block size of the current site (tunable sites only)
   // Runs one launch site; the timed site is bracketed by the timer's events.
@@ -3436,7 +3495,11 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   const bool whole = kt && kt->site == kChainSite;  // the timer brackets the whole chain
   if (whole) (void)hipEventRecord(kt->beg, st);
   // a0: buckets
-  run([&] { k_start<<<grid(seeds ? kSeedBins : 4096), kBlock, 0, st>>>(wb); });
+  run([&] {
+    const dim3 d = grid(seeds ? kSeedBins : 4096);
+    if (value) k_start<true><<<d, kBlock, 0, st>>>(*value, wb);
+    else k_start<false><<<d, kBlock, 0, st>>>(Ws{}, wb);
+  });
   // hits: the tile (rounds of 64 hits a wave) grows with the launch's hits, so that a
   // small event still fills blocks and a large launch amortises a block's tables
   const long n_co = n_coarse(M);
@@ -3551,7 +3614,7 @@ void enqueue_chain(const DevGeom &g, const Ws *wb, int B, const Ws &b, hipStream
   run([&] {
     const unsigned ns = share((int)std::min(1024L, (S + 255) / 256), kBlock);
     const unsigned n5 = share((int)std::min(1024L, ((long)b.cap_t5 + 255) / 256), kBlock);
-    k_tc_write<<<dim3(3 * ns + n5, B), kBlock, 0, st>>>(wb, (int)ns);
+    k_tc_write<<<dim3(3 * ns + n5, B), kBlock, 0, st>>>(wb, (int)ns, g.ext ? 0 : 1);
   });
   // track extensions (when the geometry enables them)
   run([&] {

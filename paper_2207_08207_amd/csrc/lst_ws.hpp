@@ -213,13 +213,18 @@ struct Ws {
   // pls_near: the seeds near a T5 candidate
   unsigned long long *m_pt5, *m_pt3, *m_pls, *m_t5;
   unsigned *pls_near;
-  int *tc_type, *tc_off, *tc_hits;
+  // n types, n + 1 offsets, then the hit lists, end to end (n: C_NTC), so that one copy reads them
+  int *tc_out;
+  // host memory (pinned; may be NULL): the counters, written at the chain's end, and the
+  // same candidates (with track extensions: ext_out) when they take at most h_tc_cap ints
+  int *h_ctr, *h_tc;
+  int h_tc_cap;
   int *tc_md;                                   // its outer-tracker MDs, inner to outer (5 per TC)
   float2 *tc_kap;                               // its curvature and curvature tolerance
-  // track extensions, per TC: MDs added (0-2), triplet (-1: none), (chi2_xy, chi2_rz, kappa),
-  // hit count of the extended TC, its exclusive scan, the extended hit lists
-  int *ext_n, *ext_t3, *ext_cnt, *ext_off, *ext_hits;
-  float4 *ext_attr;
+  // track extensions, end to end for n candidates (ExtOut): types, MDs added (0-2), triplets
+  // (-1: none), (chi2_xy, chi2_rz, kappa, -), n + 1 offsets, the extended hit lists; and the
+  // hit count of each extended candidate with its exclusive scan
+  int *ext_out, *ext_cnt, *ext_off;
   // the count passes' sums per tile of parents (tile_shift) and, for triplets and
   // quintuplets, per wave of 64 parents
   int *ts_ls, *ts_t3, *ts_t5, *ts_p3, *ts_p5;
@@ -229,6 +234,14 @@ struct Ws {
   int *scan_tmp;
   ScanJob scans[SC_COUNT];
   FillJob fills[FL_COUNT];
+};
+
+// Parts of ext_out for n candidates.
+struct ExtOut {
+  int *type, *added, *t3, *attr, *off, *hits;
+  __host__ __device__ ExtOut(int *p, long n)
+      : type(p), added(p + n), t3(p + 2 * n), attr(p + 3 * n), off(p + 7 * n), hits(p + 8 * n + 1) {}
+  __host__ __device__ static long ints(long n, long n_hits) { return 8 * n + 1 + n_hits; }
 };
 
 // Capacities and sizes (host-side).
@@ -257,13 +270,14 @@ bool site_tunable(int site);
 // device memory; `bound` holds, field by field, the largest sizes and
 // capacities of the batch (it sets the launch grids).  site_block (kMaxSites
 // entries or NULL): threads per block of each tunable site, 0 = the default.
-void enqueue_chain(const DevGeom &g, const Ws *d_ws, int B, const Ws &bound, hipStream_t st, const KernelTimer *kt,
-                   const int *site_block);
+// value (one event only): the descriptor, which the first launch carries and
+// writes to d_ws; NULL: d_ws is there already.
+void enqueue_chain(const DevGeom &g, Ws *d_ws, int B, const Ws &bound, hipStream_t st, const KernelTimer *kt,
+                   const int *site_block, const Ws *value);
 void launch_module_windows(const int *info, const float *pos_lo, const float *pos_up, const float *lmin,
                            const float *lmax, int n_mod, double d0, float4 *win, hipStream_t st);
-// Allocation-free forms: an event descriptor written by a kernel, and the
-// track candidates copied to caller device buffers (counts: n, hits, status).
-void launch_put_desc(const Ws &w, Ws *dst, hipStream_t st);
+// Allocation-free form: the track candidates copied to caller device buffers
+// (counts: n, hits, status).
 void launch_tc_export(const Ws *d_ws, int max_tc, int max_hits, int *type, int *off, int *hits, int *counts,
                       hipStream_t st);
 
