@@ -2243,15 +2243,21 @@ __global__ __launch_bounds__(kBlock) void k_list_place(const Ws *__restrict__ wb
   }
 }
 // The T5s into their MDs' lists, one thread per (T5, MD): every place is known.
+// An entry holds the T5, its score and its four other MDs, so that the
+// duplicate removal reads lists and nothing else.
 __global__ __launch_bounds__(kBlock) void k_t5_inc_scatter(const Ws *__restrict__ wb) {
   const Ws &w = wb[blockIdx.y];
   const long n = 5L * uload(w.ctr + C_NT5);
   for (long i = blockIdx.x * (long)kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
     const long t = i / 5;
     const int k = (int)(i - 5 * t);
+    int m[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) m[j] = gp(w.t5_md)[5 * t + j];
     const int md = gp(w.t5_md)[i];
     const int pos = k == 0 ? gp(w.inc_b0)[md] + (int)t : gp(w.inc_off)[md] + gp(w.t5_slot)[4 * t + k - 1];
     gstore(w.inc_list, pos, make_int2((int)t, __float_as_int(gp(w.t5_attr)[8 * t + 1])));
+    gstore(w.inc_mds, pos, make_int4(k > 0 ? m[0] : m[1], k > 1 ? m[1] : m[2], k > 2 ? m[2] : m[3], k > 3 ? m[3] : m[4]));
   }
 }
 
@@ -2282,70 +2288,71 @@ __device__ __forceinline__ bool better(float su, const int *hu, float st, const 
 // MD, and u is judged there only if it shares at least two MDs with t and its
 // first MD in common with t's first four is that k-th one (so each pair is
 // judged once; a duplicate shares two of the five MDs, hence one of the first
-// four).  Flattened as in the T3/T5 searches: a wave takes ipw items (64, or
-// 16 when one event alone leaves too few waves to hide the gathers' latency),
-// stages their MDs in LDS and strides all (item, candidate) pairs with its
-// lanes.
+// four).  A block takes 16 T5s, spread over the event, stages their MDs in LDS
+// and strides all (item, candidate) pairs, flattened, with all its waves.  The
+// lists are uneven (hundreds of T5s at an MD of a dense core, few elsewhere)
+// and consecutive T5s have the same ones, so the longest chain bounds the
+// launch: with 16 consecutive items a wave a PU200 event took 58 us and with
+// 64 211 us; 64 consecutive items a block, 55 us; 64 of T5s n / 16 apart, 19 us
+// (eight events: 241, 104 and 110 us).  Candidates' MDs come with the list: eight
+// events took 256 us when they were gathered from t5_md.
 // t5_keep starts at 1 (written by the fill); a strictly better duplicate
 // clears it (every writer writes 0).
-// Its LDS is dynamic, kT5DedupLds bytes per wave of the block, so that a tuned
-// launch of one-wave blocks does not hold four waves' worth.
-struct T5DedupLds {
-  int mt[5][64], lo[64], seg[65], mark[64];
-  float st[64];
-};
-constexpr size_t kT5DedupLds = sizeof(T5DedupLds);
-
-__global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb, int ipw) {
-  extern __shared__ T5DedupLds s_dd[];
+__global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb) {
+  __shared__ int s_mt[5][64], s_lo[64], s_cnt[64], s_seg[kWaves][65], s_mark[kWaves][64];
+  __shared__ float s_st[64];
   const Ws &w = wb[blockIdx.y];
   const int n = uload(w.ctr + C_NT5);
   const int wv = wave_id(), lane = lane_id();
-  const int wpb = blockDim.x >> 6;
-  auto &S = s_dd[wv];
-  for (long p0 = ((long)blockIdx.x * wpb + wv) * ipw; p0 < 4L * n; p0 += (long)gridDim.x * wpb * ipw) {
-    const long item = p0 + lane;
-    int cnt = 0;
-    if (lane < ipw && item < 4L * n) {
-      const int t = (int)(item >> 2), k = (int)(item & 3);
-      int mt[5];
+  const int stride = blockDim.x;
+  const int n_grp = (n + 15) / 16;
+  for (int q = blockIdx.x; q < n_grp; q += gridDim.x) {
+    __syncthreads();  // the previous items' data is no longer read
+    if (wv == 0) {
+      const int t = q + (lane >> 2) * n_grp, k = lane & 3;
+      int cnt = 0;
+      if (t < n) {
+        int mt[5];
 #pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        mt[j] = gp(w.t5_md)[5 * (long)t + j];
-        S.mt[j][lane] = mt[j];
+        for (int j = 0; j < 5; ++j) {
+          mt[j] = gp(w.t5_md)[5 * (long)t + j];
+          s_mt[j][lane] = mt[j];
+        }
+        s_lo[lane] = gp(w.inc_off)[mt[k]];
+        cnt = gp(w.inc_cnt)[mt[k]];
+        s_st[lane] = gp(w.t5_attr)[8 * (long)t + 1];
       }
-      const int lo = gp(w.inc_off)[mt[k]];
-      S.lo[lane] = lo;
-      cnt = gp(w.inc_cnt)[mt[k]];
-      S.st[lane] = gp(w.t5_attr)[8 * (long)t + 1];
+      s_cnt[lane] = cnt;
     }
-    const int total = wave_segments(cnt, S.seg);
-    const int start = S.seg[lane];
-    int carry = 0;
-    for (int c0 = 0; c0 < total; c0 += 64) {
+    __syncthreads();
+    const int cnt = s_cnt[lane];
+    const int total = wave_segments(cnt, s_seg[wv]);
+    const int start = s_seg[wv][lane];
+    for (int c0 = wv * 64; c0 < total; c0 += stride) {
       const int c = c0 + lane;
-      const int e = round_parent(start, cnt, c0, S.mark, carry);  // item of this lane's pair
+      // the item whose pairs run into this round, then that of each lane's pair
+      const unsigned long long before = __ballot(cnt > 0 && start < c0);
+      int carry = before ? 63 - (int)__builtin_clzll(before) : 0;
+      const int e = round_parent(start, cnt, c0, s_mark[wv], carry);
       if (c >= total) continue;
-      const int t = (int)((p0 + e) >> 2), k = (int)((p0 + e) & 3);
-      const int2 ue = w.inc_list[S.lo[e] + (c - S.seg[e])];
+      const int t = q + (e >> 2) * n_grp, k = e & 3;
+      const int pos = s_lo[e] + (c - s_seg[wv][e]);
+      const int2 ue = gload(w.inc_list, pos);
       const int u = ue.x;
       if (u == t) continue;
       // only a u that is not worse can drop t: the score first (kept in the list entry),
       // then sharing, then on a tie of scores the hit tuples (the decision of better<10>)
-      const float su = __int_as_float(ue.y), st = S.st[e];
+      const float su = __int_as_float(ue.y), st = s_st[e];
       if (st < su) continue;
-      int mu[5];
-#pragma unroll
-      for (int j = 0; j < 5; ++j) mu[j] = gp(w.t5_md)[5 * (long)u + j];
-      int shared = 0, first = 5;
+      // u has t's k-th MD; its others are in the list (the MDs of a T5 are distinct)
+      const int4 mu = gload(w.inc_mds, pos);
+      unsigned in = 0u;
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
-        const int v = S.mt[j][e];
-        const bool in = v == mu[0] || v == mu[1] || v == mu[2] || v == mu[3] || v == mu[4];
-        shared += in ? 1 : 0;
-        first = (in && first == 5) ? j : first;
+        const int v = s_mt[j][e];
+        in |= (v == mu.x || v == mu.y || v == mu.z || v == mu.w) ? 1u << j : 0u;
       }
-      if (shared < 2 || first != k) continue;
+      if (in >> k == 0u || (in & ((1u << k) - 1u)) != 0u) continue;
       bool drop = su < st;
       if (!drop) {
         int ht[10], hu[10];
@@ -2355,8 +2362,6 @@ __global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb, 
       }
       if (drop) gp(w.t5_keep)[t] = 0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -3578,8 +3583,8 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
   run([&] { k_list_place<<<grid((b.cap_md + 1) / 2), kBlock, 0, st>>>(wb); });
   run([&] { k_t5_inc_scatter<<<grid(5L * b.cap_t5), kBlock, 0, st>>>(wb); });
   run([&] {
-    const int ipw = B == 1 ? 16 : 64;
-    k_t5_dedup<<<gridwb((4L * b.cap_t5 + ipw - 1) / ipw), tb, (tb / 64) * kT5DedupLds, st>>>(wb, ipw);
+    const long blocks = (4L * b.cap_t5 + 63) / 64;  // 64 items a block
+    k_t5_dedup<<<dim3(share_big((int)std::min(blocks, 1L << 24), tb), B), tb, 0, st>>>(wb);
   });
   // a6: pLS (with the hit count and the segment sums); a7's bins (with the quintuplets)
   for (int q = 0; q < 6; ++q) run([&] {});  // pls, its hit lists and duplicate removal, pt3_bin, pt5_bin

@@ -176,6 +176,7 @@ struct Ws {
   int *inc_cnt, *inc_off, *inc_b0;
   int *t5_slot;     // 4 per T5: its place in the lists of its second to fifth MDs
   int2 *inc_list;   // T5s containing each MD: (T5, bits of its chi2_xy score)
+  int4 *inc_mds;    // and, in step with inc_list, that T5's four other MDs
   // pixel seeds
   float *pls;       // 8 per seed: pT, cx, cy, lambda, kappa, x0, y0, z0
   int *pls_keep;
