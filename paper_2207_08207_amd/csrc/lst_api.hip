@@ -153,9 +153,9 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.ls_cnt = I(md + 1); t.ls_off = I(md + 1); t.ls_md = I2(ls); t.ls_beta = F2(ls); t.ls_opos = F4(ls); t.ls_oinf = I(ls);
   t.ls_cache = I(kLsCache * md);
   t.ls_ovf = I(md);
-  t.t3_off = I(ls + 1); t.ws_t3 = I((ls >> 6) + 1); t.t3_md = I4(t3); t.t3_attr = F4(t3); t.t3_first = F2(t3);
+  t.t3_off = I(ls + 1); t.ws_t3 = I(ls / kMinParents + 1); t.t3_md = I4(t3); t.t3_attr = F4(t3); t.t3_first = F2(t3);
   t.t3_cache = I(kT3Cache * ls); t.t5_cache = I(kT5Cache * t3);
-  t.t5_off = I(t3 + 1); t.ws_t5 = I((t3 >> 6) + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
+  t.t5_off = I(t3 + 1); t.ws_t5 = I(t3 / kMinParents + 1); t.t5_t3 = I2(t5); t.t5_md = I(5 * t5); t.t5_attr = F(8 * t5);
   t.t5_keep = I(t5); t.t5_first = F2(t5);
   t.inc_cnt = I(md); t.inc_off = I(md); t.inc_list = I2(5 * t5);
   t.pls = F(8 * S); t.pls_keep = I(S);

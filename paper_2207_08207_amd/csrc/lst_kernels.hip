@@ -1768,9 +1768,24 @@ __device__ __forceinline__ int run_first_lane(int v, int n) {
   return 63 - __builtin_clzll(starts & upto);
 }
 
-// Seven waves per SIMD (at most 72 VGPRs, no spills).
+// Parents of a wave (as a power of two) in the triplet and quintuplet passes,
+// from the launch's parents, about n in each of its events: 64 fill the lanes'
+// setup and share the block's prefix among most, but a few thousand waves
+// leave the chip waiting for the one with the most pairs.  Measured, count +
+// fill, with 64 / 32 / 16: triplets of a PU200 event (484k segments) 58 / 62 /
+// 87 us, of eight 372 / 483 / 722, of a PU50 event 22 / 17 / 18; quintuplets of
+// a PU200 event (123k triplets) 87 / 72 / 60, of eight 196 / 237 / 322, of a PU50
+// event 40 / 23 / 21.  So 64 from 256k parents on, 32 from 160k, else 16
+// (kMinParents: the wave sums' arrays hold one per 16).
+__device__ __forceinline__ int parent_shift(int n) {
+  const long all = (long)n * gridDim.y;
+  static_assert(kMinParents == 16, "the shift returned for the smallest groups");
+  return all >= 262144 ? 6 : all >= 163840 ? 5 : 4;
+}
+
+// Seven waves per SIMD for the count (at most 72 VGPRs, no spills).
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_t3(const Ws *__restrict__ wb, DevGeom g) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 6 : 7))) void k_t3(const Ws *__restrict__ wb, DevGeom g) {
   const Ws &w = wb[blockIdx.y];
   __shared__ float4 s_a[kWaves][64], s_b[kWaves][64];
   __shared__ int s_mi[kWaves][64], s_lo[kWaves][64], s_cnt[kWaves][64], s_seg[kWaves][65], s_cached[kWaves][64];
@@ -1781,15 +1796,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;
   if (FILL && n_ls == 0 && blockIdx.x == 0 && threadIdx.x == 0) w.t3_off[0] = 0;
-  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_ls; b0 += (long)gridDim.x * wpb * 64) {
-    const long p0 = b0 + wv * 64;
+  const int lw = parent_shift(n_ls), nb = wpb << lw;  // log2 of a wave's parents, the block's parents
+  for (long b0 = (long)blockIdx.x * nb; b0 < n_ls; b0 += (long)gridDim.x * nb) {
+    const long p0 = b0 + (wv << lw);
     if (!FILL && p0 >= n_ls) break;  // (the fill's waves share their block's prefix)
-    const int l1 = (int)p0 + lane;
+    const int l1 = lane >> lw ? n_ls : (int)p0 + lane;
     int n = 0, cached = 0, n_mine = 0;
     if (FILL) {  // the parents' offsets, in place of their counts
       n_mine = l1 < n_ls ? gp(w.t3_off)[l1] : 0;
-      int off = block_prefix(w.ts_t3, w.sh_t3, w.ws_t3, 6, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
-      for (long q = b0; q < p0 && q < n_ls; q += 64) off += uload(w.ws_t3 + (q >> 6));
+      int off = block_prefix(w.ts_t3, w.sh_t3, w.ws_t3, lw, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
+      for (long q = b0; q < p0 && q < n_ls; q += 1 << lw) off += uload(w.ws_t3 + (q >> lw));
       s_off[wv][lane] = off;
       if (l1 < n_ls) gp(w.t3_off)[l1] = off;
       if (l1 == n_ls - 1) {
@@ -1900,7 +1916,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
       if (l1 < n_ls) gp(w.t3_off)[l1] = c;
       const int sum = wave_total(c);
       if (lane == 0) {
-        gp(w.ws_t3)[p0 >> 6] = sum;
+        gp(w.ws_t3)[p0 >> lw] = sum;
         if (sum > 0) atomicAdd(w.ts_t3 + (p0 >> w.sh_t3) * kSumStride, sum);
       }
     }
@@ -2024,15 +2040,16 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;
   if (FILL && n_t3 == 0 && blockIdx.x == 0 && threadIdx.x == 0) w.t5_off[0] = 0;
-  for (long b0 = (long)blockIdx.x * wpb * 64; b0 < n_t3; b0 += (long)n_main * wpb * 64) {
-    const long p0 = b0 + wv * 64;
+  const int lw = parent_shift(n_t3), nb = wpb << lw;
+  for (long b0 = (long)blockIdx.x * nb; b0 < n_t3; b0 += (long)n_main * nb) {
+    const long p0 = b0 + (wv << lw);
     if (!FILL && p0 >= n_t3) break;
-    const int t1 = (int)p0 + lane;
+    const int t1 = lane >> lw ? n_t3 : (int)p0 + lane;
     int n = 0, cached = 0, n_mine = 0;
     if (FILL) {  // the parents' offsets, in place of their counts
       n_mine = t1 < n_t3 ? gp(w.t5_off)[t1] : 0;
-      int off = block_prefix(w.ts_t5, w.sh_t5, w.ws_t5, 6, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
-      for (long q = b0; q < p0 && q < n_t3; q += 64) off += uload(w.ws_t5 + (q >> 6));
+      int off = block_prefix(w.ts_t5, w.sh_t5, w.ws_t5, lw, (int)b0, s_red) + wave_inclusive(n_mine) - n_mine;
+      for (long q = b0; q < p0 && q < n_t3; q += 1 << lw) off += uload(w.ws_t5 + (q >> lw));
       s_off[wv][lane] = off;
       if (t1 < n_t3) gp(w.t5_off)[t1] = off;
       if (t1 == n_t3 - 1) {
@@ -2166,7 +2183,7 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
       if (t1 < n_t3) gp(w.t5_off)[t1] = c;
       const int sum = wave_total(c);
       if (lane == 0) {
-        gp(w.ws_t5)[p0 >> 6] = sum;
+        gp(w.ws_t5)[p0 >> lw] = sum;
         if (sum > 0) atomicAdd(w.ts_t5 + (p0 >> w.sh_t5) * kSumStride, sum);
       }
     }
@@ -3558,19 +3575,19 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     k_ls_fill<<<dim3(n_copy + n_ovf, B), tb, 0, st>>>(wb, g, (int)n_copy);
   });
   // a3: T3
-  run([&] { k_t3<false><<<gridwb((b.cap_ls + 63) / 64), tb, 0, st>>>(wb, g); });
+  run([&] { k_t3<false><<<gridwt(b.cap_ls / kMinParents + 1), tb, 0, st>>>(wb, g); });
   run([&] {});  // t3_scan
-  run([&] { k_t3<true><<<gridwb((b.cap_ls + 63) / 64), tb, 0, st>>>(wb, g); });
+  run([&] { k_t3<true><<<gridwt(b.cap_ls / kMinParents + 1), tb, 0, st>>>(wb, g); });
   // a4: T5
   // (with the seed search's bins in further blocks)
   run([&] {
-    const dim3 d = gridwb((b.cap_t3 + 63) / 64);
+    const dim3 d = gridwt(b.cap_t3 / kMinParents + 1);
     const unsigned nq = seeds ? share(grid_for(b.cap_md, tb), tb) : 0;
     k_t5<false><<<dim3(d.x + nq, B), tb, 0, st>>>(wb, g, (int)d.x);
   });
   run([&] {});  // t5_scan
   run([&] {
-    const dim3 d = gridwb((b.cap_t3 + 63) / 64);
+    const dim3 d = gridwt(b.cap_t3 / kMinParents + 1);
     const int rows = (tb / 64) * kRowsPerWave;
     const unsigned nq = seeds ? (kBinRows + rows - 1) / rows : 0;
     k_t5<true><<<dim3(d.x + nq, B), tb, 0, st>>>(wb, g, (int)d.x);

@@ -93,6 +93,7 @@ __host__ __device__ inline long n_sum_tiles(long cap) { return (cap >> tile_shif
 // than this: the fill searches again).
 constexpr int kLsCache = 32;
 constexpr int kLsGroup = 16;  // most inner MDs per wave of the segment count pass
+constexpr int kMinParents = 16;  // fewest parents per wave of the triplet and quintuplet passes
 constexpr int kMdCache = 32;  // largest md_cache tile
 constexpr int kMdKeep = 6;    // partners per lower hit the MD search keeps
 constexpr int kT3Cache = 2;   // triplets per parent segment whose candidate the T3 count pass keeps
@@ -227,7 +228,7 @@ struct Ws {
   // hit count of each extended candidate with its exclusive scan
   int *ext_out, *ext_cnt, *ext_off;
   // the count passes' sums per tile of parents (tile_shift) and, for triplets and
-  // quintuplets, per wave of 64 parents
+  // quintuplets, per wave (parent_shift)
   int *ts_ls, *ts_t3, *ts_t5, *ts_p3, *ts_p5;
   int sh_ls, sh_t3, sh_t5, sh_pt;
   int *ws_t3, *ws_t5;
