@@ -149,7 +149,8 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.boff = I(2 * M + 1); t.tile_hist = I(nc * n_hit_tiles(N, kHitTile)); t.coarse_cnt = I(nc); t.coarse_off = I(nc + 1);
   t.hcp = F4(N + 1); t.hidx = I(N + 1); t.hpos = F4(N + 1);
   t.md_cnt = I(M + 1); t.md_off = I(M + 1); t.md_tot = I(nc);
-  t.md_hits = I2(md); t.md_mod = I(md); t.md_pos = F4(md); t.md_stub = F2(md); t.mod_disc = F4(M);
+  t.md_hits = I2(md); t.md_mod = I(md); t.md_pos = F4(md); t.md_stub = F2(md); t.mod_disc = F4(2 * M);
+  t.mod_az = reinterpret_cast<unsigned short *>(take(sizeof(short) * kAzBins * (size_t)M)); t.md_az = I(md);
   t.ls_cnt = I(md + 1); t.ls_off = I(md + 1); t.ls_md = I2(ls); t.ls_beta = F2(ls); t.ls_opos = F4(ls); t.ls_oinf = I(ls);
   t.ls_cache = I(kLsCache * md);
   t.ls_ovf = I(md);
@@ -338,6 +339,10 @@ lst_status lst_load_geometry(const lst_geometry_desc *d, lst_geometry *out) {
   }
   g->g.n_mod = M;
   g->g.n_edges = E;
+  g->g.map_asc = 1;
+  for (int m = 0; m < M; ++m)
+    for (int e = d->map_offsets[m] + 1; e < d->map_offsets[m + 1]; ++e)
+      if (d->map_targets[e] <= d->map_targets[e - 1]) g->g.map_asc = 0;
   g->g.map_off = g->d_off;
   g->g.map_tgt = g->d_tgt;
   g->g.win = g->d_win;

@@ -667,6 +667,14 @@ __device__ __forceinline__ float4 anchor_disc(float x0, float x1, float y0, floa
   return make_float4(cx, cy, rho, sqrtf(cx * cx + cy * cy));
 }
 
+// Bin of an azimuth in a module, from the sine of its angle from the disc's
+// centre: kAzBins equal steps over the disc's own |sine| <= radius / |c| = 1 / scale, the
+// values outside in the first and last.  Non-decreasing in the sine.
+__device__ __forceinline__ int azimuth_bin(float scale, float s) {
+  const float u = (s * scale + 1.0f) * (0.5f * kAzBins);
+  return (int)fminf(fmaxf(u, 0.0f), (float)(kAzBins - 1));  // (NaN: 0)
+}
+
 // Quotient and remainder of t / n for 0 <= t < 2^22 and n >= 1 from rn, the
 // float reciprocal of n: t is exact in float and the two roundings (of 1 / n
 // and of the product) are 2^-24 relative each, so the float quotient is within
@@ -906,7 +914,7 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
   if (t < kBucketMods && m0 + t < n_mod) {
     gp(w.md_cnt)[m0 + t] = s_nmd[t];
     if (s_nmd[t] > 0)
-      gstore(w.mod_disc, m0 + t, anchor_disc(unordered(s_x0[t]), unordered(s_x1[t]), unordered(s_y0[t]), unordered(s_y1[t])));
+      gstore(w.mod_disc, 2 * (m0 + t), anchor_disc(unordered(s_x0[t]), unordered(s_x1[t]), unordered(s_y0[t]), unordered(s_y1[t])));
   }
   if (t == 0) {
     int tot = 0;
@@ -921,6 +929,10 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
 // search did not keep are searched again.
 __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__ wb, DevGeom g) {
   __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1], s_red[kSortWaves];
+  __shared__ int s_at[kBucketMods + 1];  // the modules' first MDs, from the bucket's first
+  __shared__ int s_r0[kBucketMods], s_r1[kBucketMods], s_z0[kBucketMods], s_z1[kBucketMods];
+  __shared__ int s_az[kBucketMods * kAzBins];  // MDs per module and azimuth bin
+  static_assert(kBucketMods * kAzBins == kSortThreads, "one bin a thread");
   const Ws &w = wb[blockIdx.y];
   const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
   const int n_mod = g.n_mod, nc = n_coarse(n_mod), nkeys = 2 * n_mod, c = blockIdx.x;
@@ -930,6 +942,11 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
   v = wave_total(v);
   if (lane == 0) s_red[wv] = v;
   if (t <= kFineKeys) s_key0[t] = gp(w.boff)[min(c * kFineKeys + t, nkeys)];
+  s_az[t] = 0;
+  if (t < kBucketMods) {
+    s_r0[t] = s_z0[t] = 0x7fffffff;
+    s_r1[t] = s_z1[t] = (int)0x80000000;
+  }
   __syncthreads();
   int run = 0;
 #pragma unroll
@@ -940,6 +957,7 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
     // the modules' offsets; after the last one, the totals
     const int n = lane < kBucketMods && m0 + lane < n_mod ? gp(w.md_cnt)[m0 + lane] : 0;
     const int at = run + wave_inclusive(n) - n;
+    if (lane <= kBucketMods) s_at[lane] = at - run;  // (lanes past the modules count none)
     if (lane < kBucketMods && m0 + lane < n_mod) {
       gp(w.md_off)[m0 + lane] = at;
       if (m0 + lane == n_mod - 1) {
@@ -949,7 +967,7 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
     }
   }
   __syncthreads();
-  const int n_lower = s_lpre[kBucketMods], keep = min(g.tiles.md_cache, kMdKeep);
+  const int n_lower = s_lpre[kBucketMods], keep = min(g.tiles.md_cache, kMdKeep), first = run;
   for (int q0 = 0; q0 < n_lower; q0 += kSortThreads) {
     const int q = q0 + t;
     int m = 0, p = 0;
@@ -973,12 +991,19 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
     const ModInfo mi{gp(g.info)[m0 + m]};
     const float4 hi = gload(w.hpos, p);
     const int lower = gp(w.hidx)[p];
+    const float4 disc = gload(w.mod_disc, 2 * (m0 + m));
+    const int bin = m * kAzBins + azimuth_bin(disc.w * frcp(disc.z), (disc.x * hi.y - disc.y * hi.x) * (frcp(disc.w) * frcp(hi.w)));
+    atomicMin(&s_r0[m], ordered(hi.w));
+    atomicMax(&s_r1[m], ordered(hi.w));
+    atomicMin(&s_z0[m], ordered(hi.z));
+    atomicMax(&s_z1[m], ordered(hi.z));
     auto put = [&](int at, int j, const float4 &hj) {
       if (at >= w.cap_md) return;
       gstore(w.md_hits, at, make_int2(lower, gp(w.hidx)[up0 + j]));
       gp(w.md_mod)[at] = m0 + m;
       gp(w.inc_cnt)[at] = 0;
       gstore(w.md_pos, at, hi);
+      gp(w.inc_off)[at] = bin | atomicAdd(&s_az[bin], 1) << 9;
       put_stub(w, g, at, md_stub(hi, hj, mi));
     };
     if (n <= keep && nup <= 0xffff) {
@@ -995,6 +1020,26 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
       }
     }
   }
+  // each module's MDs grouped by azimuth, and its anchors' ranges of radius and z
+  __syncthreads();
+  int at = s_az[t];
+  for (int o = 1; o < kAzBins; o <<= 1) {
+    const int v = __shfl_up(at, o, kAzBins);
+    if ((t & (kAzBins - 1)) >= o) at += v;
+  }
+  at -= s_az[t];
+  if (m0 + t / kAzBins < n_mod) gp(w.mod_az)[(long)m0 * kAzBins + t] = (unsigned short)min(at, 0xffff);
+  __syncthreads();
+  s_az[t] = first + s_at[t / kAzBins] + at;
+  __syncthreads();
+  const int last = min(first + s_at[kBucketMods], w.cap_md);
+  for (int i = first + t; i < last; i += kSortThreads) {
+    const int v = gp(w.inc_off)[i], p = s_az[v & 511] + (v >> 9);
+    if (p < w.cap_md) gp(w.md_az)[p] = i;
+  }
+  if (t < kBucketMods && s_at[t + 1] > s_at[t])
+    gstore(w.mod_disc, 2 * (m0 + t) + 1,
+           make_float4(unordered(s_r0[t]), unordered(s_r1[t]), unordered(s_z0[t]), unordered(s_z1[t])));
 }
 
 // ------------------------------------------------------------- a2: LS
@@ -1027,6 +1072,89 @@ __device__ __forceinline__ float ls_window_bound(const float4 &A, ModInfo ma, fl
 __device__ __forceinline__ bool ls_module_may_pass(const float4 &A, float4 disc, float wmax) {
   const float dn = fabsf(A.x * disc.y - A.y * disc.x) * frcp(A.w);
   return dn - disc.z <= (wmax * (disc.w + disc.z)) * 1.001f + 1e-4f;
+}
+
+// What the pair loop of the count pass needs of a linked module: its centre's
+// direction, distance, radius (anchor_disc), ranges of r and z, the window
+// bound's two terms (ls_window_bound) and the scale of azimuth_bin.
+struct LsLink {
+  float nx, ny, c, rho;
+  float4 rng;
+  float ub, rs, bins;
+};
+__device__ __forceinline__ LsLink ls_link(const float4 &disc, const float4 &rng, ModInfo mb) {
+  LsLink l;
+  const float ic = frcp(disc.w);
+  l.nx = disc.x * ic; l.ny = disc.y * ic; l.c = disc.w; l.rho = disc.z;
+  l.rng = rng;
+  l.ub = kHalfKmax * ((disc.w + disc.z) + mb.er());
+  l.rs = l.ub < 0.99f ? frsq(1.0f - l.ub * l.ub) : -1.0f;
+  l.bins = disc.z < 0.5f * disc.w ? disc.w * frcp(disc.z) : -1.0f;
+  return l;
+}
+// And of an inner MD: 1 / r, 1 / separation (negative: none), the window
+// bound's terms and twice the pitch.
+__device__ __forceinline__ float4 ls_inner(const float4 &A, float2 st, ModInfo ma, float d0) {
+  const float ia = frcp(A.w);
+  return make_float4(ia, st.y > 0.0f ? frcp(st.y) : -1.0f, kHalfKmax * (A.w - ma.er()), (d0 + ma.hphi() + 0.005f) * ia);
+}
+
+// The bins of the linked module's kAzBins, first and end, that hold every MD B
+// past the window and the stub check of the inner MD A; false if there is none
+// (ls_window_bound and ls_module_may_pass included, on the link's constants).
+// With D the azimuth from A to B, |sin D| <= wmax (ls_window_may_pass; A.B > 0
+// and r_B > r_A are ls_pass's own).  A barrel A's stub check bounds t, the
+// tangent of the angle at B between the chord and the radial direction
+// (|st.x - st.y t| <= err, largest for the shortest chord), and t = r_A sin D /
+// (r_B - r_A cos D) with r_B in the module's range and cos D in
+// [sqrt(1 - wmax^2), 1]; where the window allows chords near the tangent, or r_B
+// cos D <= r_A, that bound is not taken.  An endcap A's check bounds st.y r_A
+// sin D / |dz|, with dz in the module's range.  The margins are those of
+// ls_stub_may_pass, and a further 1e-4 of the bound and 1e-5 in sine; rounding
+// stays below 1e-6 of both.  All bins for wide discs and windows, and for A far
+// from the module in azimuth.
+__device__ __forceinline__ bool ls_azimuth_bins(const float4 &A, float2 st, const float4 &in, ModInfo ma, const LsLink &l,
+                                                ModInfo mb, float d0, int *b0, int *b1) {
+  *b0 = 0;
+  *b1 = kAzBins;
+  // ls_window_bound and ls_module_may_pass, with the direction's products instead of the disc's
+  const float wmax = l.rs < 0.0f ? 3.0e38f : (((l.ub - in.z) * l.rs + in.w) * kMargin + kEps) * 1.01f + 1e-6f;
+  const float sd = (l.nx * A.y - l.ny * A.x) * in.x, cd = (l.nx * A.x + l.ny * A.y) * in.x;
+  if (!(l.c * fabsf(sd) - l.rho <= (wmax * (l.c + l.rho)) * 1.001f + 1e-4f)) return false;
+  if (!(l.bins > 0.0f && wmax < 0.69f && cd > 0.5f)) return true;
+  const float sw = wmax * 1.0001f + 1e-6f, cw = 0.9999f * __builtin_amdgcn_sqrtf(1.0f - sw * sw);
+  const float e2 = (ma.endcap() ? ma.hlong() : ma.hphi()) + (mb.endcap() ? mb.hlong() : mb.hphi());
+  float lo = -sw, hi = sw;
+  float near, far, err;  // sin D in [(x -+ err) * near or far] / (st.y r_A)
+  bool bound;
+  const float x = st.x;
+  if (!ma.endcap()) {
+    near = l.rng.x - A.w;
+    far = l.rng.y - A.w * cw;
+    bound = l.rng.x * cw > A.w * 1.0001f && A.w * sw <= 0.9f * near;
+    err = (2.0f * ma.hphi() + (2.0f * st.y) * (e2 * frcp(near) + d0 * in.x)) * (kMargin * 1.0005f) + kEps +
+          2e-4f * fabsf(x);
+  } else {
+    const float z0 = l.rng.z - A.z, z1 = l.rng.w - A.z;
+    near = fminf(fabsf(z0), fabsf(z1));
+    far = fmaxf(fabsf(z0), fabsf(z1));
+    bound = z0 > 0.0f || z1 < 0.0f;
+    const float chord = fmaxf(fabsf(l.rng.x - A.w), fabsf(l.rng.y - A.w)) + 1.1f * A.w * sw;
+    err = (2.0f * ma.hphi() + st.y * (e2 + chord * d0 * in.x) * frcp(near)) * (kMargin * 1.033f) + kEps +
+          0.0313f * fabsf(x);
+  }
+  if (bound && in.y > 0.0f) {
+    const float f = in.x * in.y, x0 = x - err, x1 = x + err;
+    const float p = x0 * (x0 >= 0.0f ? near : far) * f, q = x1 * (x1 >= 0.0f ? far : near) * f;
+    lo = fmaxf(lo, p - (1e-4f * fabsf(p) + 1e-5f));
+    hi = fminf(hi, q + (1e-4f * fabsf(q) + 1e-5f));
+    if (!(lo <= hi)) return false;
+  }
+  // sin(D + the azimuth from the disc's centre to A), within a right angle
+  const float cl = __builtin_amdgcn_sqrtf(1.0f - lo * lo), ch = __builtin_amdgcn_sqrtf(1.0f - hi * hi);
+  if (cl * cd - lo * sd > 0.0f) *b0 = azimuth_bin(l.bins, lo * cd + cl * sd - 1e-5f);
+  if (ch * cd - hi * sd > 0.0f) *b1 = azimuth_bin(l.bins, hi * cd + ch * sd + 1e-5f) + 1;
+  return true;
 }
 
 // One MD's stub check of ls_pass (ls_stub_ok) evaluated with the fast
@@ -1136,35 +1264,38 @@ __device__ __forceinline__ void queue_pop64(int *qa, int rest) {
 
 // Count pass of the segment search: one wave per group of up to kLsGroup
 // consecutive inner MDs, taken in chunks of MDs of one module whose (inner MD,
-// linked module) pairs are flattened over the lanes.  Each candidate goes
-// through the pre-tests as in k_ls_fill, but the queue of candidates past them
-// is shared by the group.  Full waves of queued pairs then go through a second,
-// pair-level pre-test (ls_pair_may_pass: about a third of them pass on PU200
-// events), and its survivors, queued the same way, through the full selection,
-// which thus runs on full waves of likely pairs rather than on the ~15 a single
-// MD queues.  The pairs of one inner MD are consecutive in both queues; a
-// passing pair's rank among its MD's passing pairs is the MD's count from
-// earlier flushes plus the passing lanes of its run below it.  Writes each MD's count and caches up to tiles.ls_cache
-// partners in candidate order.  The group size trades the fuller selection
-// waves against the number of waves in flight (tiles.ls_group; see
-// ls_group_for).
-constexpr int kLsPairs = kMaxEdges;  // (inner MD, linked module) pairs of a chunk in LDS
+// linked module) pairs are flattened over the lanes.  A pair's candidates are
+// the MDs in a run of the module's azimuth bins (ls_azimuth_bins; in MD order
+// and all of them if the module map does not ascend, since the fill then could
+// not put the partners in order).  They go 64 per round through the pair pre-test
+// (ls_pair_may_pass: a fifth of them pass on PU200 events), its survivors,
+// queued, through the full selection, which thus runs on full waves of likely
+// pairs.  The pairs of one inner MD are consecutive in the queue; a passing
+// pair's rank among its MD's passing pairs is the MD's count from earlier flushes
+// plus the passing lanes of its run below it.  Writes each MD's count and caches
+// up to tiles.ls_cache partners as found.
+//
+// Bound by the vector units: a PU200 event's 21.7M candidates of the modules
+// that the window reaches, each tested, took 72.5M wave instructions and 120 us
+// (eight events 872); the bins leave 4.9M, 53M instructions before the links'
+// constants were taken out of the pair loop, and 86-90 us (588), of which the
+// pairs (4.3M) take the most.  The bins cost the MD fill 13 -> 20 us (68 -> 109)
+// and their order the segment fill 24 -> 32 us (115 -> 136).
+constexpr int kLsPairs = 2 * kMaxEdges;  // (inner MD, linked module) pairs of a chunk in LDS
 
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_ls_count(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_ls_count(
     const Ws *__restrict__ wb, DevGeom g, int group) {
   const Ws &w = wb[blockIdx.y];
-  // (inner MD, linked module) pairs left with candidates, in (MD, map) order: first MD of
-  // the linked module, candidates before it, module info, window bound (bits); and the
-  // pair's inner MD (its slot in the group)
-  __shared__ int4 s_edge[kWaves][kLsPairs];
-  __shared__ int s_ek[kWaves][kLsPairs];
+  // (inner MD, linked module) pairs left with candidates, in (MD, map) order: first
+  // candidate less the candidates before it, those, and the pair's inner MD (its slot in
+  // the group) with the module's info
+  __shared__ int s_ej[kWaves][kLsPairs], s_ep[kWaves][kLsPairs], s_ek[kWaves][kLsPairs];
   __shared__ int s_mark[kWaves][64];            // a pair's candidates start here
-  // (inner MD, candidate) pairs in order, as partner | module info << 30 and the inner
-  // MD's slot in the group: past the candidate pre-tests (s_q) and past the pair
-  // pre-test as well (s_r)
-  __shared__ int s_q[kWaves][128], s_r[kWaves][128];
-  __shared__ unsigned char s_qg[kWaves][128], s_rg[kWaves][128];
-  __shared__ float4 s_A[kWaves][kLsGroup];      // the group's inner MDs
+  // (inner MD, candidate) pairs past the pair pre-test, in order, as partner | module info
+  // << 30 and the inner MD's slot in the group
+  __shared__ int s_r[kWaves][128];
+  __shared__ unsigned char s_rg[kWaves][128];
+  __shared__ float4 s_A[kWaves][kLsGroup], s_in[kWaves][kLsGroup];  // the group's inner MDs
   __shared__ float2 s_sa[kWaves][kLsGroup];
   __shared__ int s_mia[kWaves][kLsGroup], s_cnt[kWaves][kLsGroup], s_mm[kWaves][kLsGroup];
   const int n_md = uload(w.ctr + C_NMD);
@@ -1179,36 +1310,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     if (lane < na) {
       const int a = a0 + lane;
       const int ma = gp(w.md_mod)[a];
-      s_A[wv][lane] = gload(w.md_pos, a);
-      s_sa[wv][lane] = get_stub(w, g, a);
-      s_mia[wv][lane] = gp(g.info)[ma];
+      const float4 A = gload(w.md_pos, a);
+      const float2 sa = get_stub(w, g, a);
+      const ModInfo mia{gp(g.info)[ma]};
+      s_A[wv][lane] = A;
+      s_sa[wv][lane] = sa;
+      s_mia[wv][lane] = mia.bits;
+      s_in[wv][lane] = ls_inner(A, sa, mia, g.d0max);
       s_mm[wv][lane] = ma;
       s_cnt[wv][lane] = 0;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    // the pair pre-test on the first n pairs of s_q (n <= 64); the passing ones join s_r
     int nr = 0;
-    auto sift = [&](int n) {
-      bool ok = false;
-      int e = 0, q = 0;
-      if (lane < n) {
-        e = s_q[wv][lane];
-        q = s_qg[wv][lane];
-        const int b = e & 0x3fffffff;
-        ok = ls_pair_may_pass(s_A[wv][q], gload(w.md_pos, b), get_stub(w, g, b), ModInfo{s_mia[wv][q]},
-                              ModInfo{(int)((unsigned)e >> 30)}, g.d0max);
-      }
-      const unsigned long long m = __ballot(ok);
-      if (ok) {
-        const int pos = nr + lanes_below(m);
-        s_r[wv][pos] = e;
-        s_rg[wv][pos] = (unsigned char)q;
-      }
-      nr += __popcll(m);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    };
     // the full selection on the first n pairs of s_r (n <= 64)
     auto select = [&](int n) {
       bool pass = false;
@@ -1237,19 +1351,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     };
-    int nq = 0;
     // the linked modules' data of the current inner module (one per lane, when it has
     // at most 64 of them): consecutive inner MDs mostly share their module
     int cur_ma = -1, e0 = 0, ne = 0;
-    int r_first = 0, r_cnt = 0, r_info = 0;
-    float4 r_disc = make_float4(0.f, 0.f, 0.f, 0.f);
-    auto linked = [&](int kk, int &first, int &cnt, int &info, float4 &disc) {
-      const int mb = gp(g.map_tgt)[e0 + kk];
+    int r_mb = 0, r_first = 0, r_cnt = 0, r_info = 0;
+    LsLink r_l{};
+    auto linked = [&](int kk, int &mb, int &first, int &cnt, int &info, LsLink &l) {
+      mb = gp(g.map_tgt)[e0 + kk];
       first = gp(w.md_off)[mb];
       const int last = min(gp(w.md_off)[mb + 1], n_md);
       cnt = last > first ? last - first : 0;
       info = gp(g.info)[mb];
-      disc = gload(w.mod_disc, mb);
+      l = ls_link(gload(w.mod_disc, 2 * mb), gload(w.mod_disc, 2 * mb + 1), ModInfo{info});
     };
     // Chunks of consecutive inner MDs of one module, at most kLsPairs / ne of them, so
     // that every (inner MD, linked module) pair of the chunk fits the LDS list: the
@@ -1261,7 +1374,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         cur_ma = ma;
         e0 = uload(g.map_off + ma);
         ne = uload(g.map_off + ma + 1) - e0;  // <= kMaxEdges = kLsPairs, checked when the geometry is loaded
-        if (ne <= 64 && lane < ne) linked(lane, r_first, r_cnt, r_info, r_disc);
+        if (ne <= 64 && lane < ne) linked(lane, r_mb, r_first, r_cnt, r_info, r_l);
       }
       const int cap_k = ne > 0 ? kLsPairs / ne : na;
       int k1 = k0 + 1;
@@ -1272,24 +1385,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       for (int p0 = 0; p0 < npair; p0 += 64) {
         const int p = p0 + lane;
         const int2 ke = divmod22(p < npair ? p : 0, ne > 0 ? ne : 1, rne);  // (MD of the chunk, link)
-        int first = 0, cnt = 0, info = 0;
-        float4 disc = r_disc;
+        int mb = 0, first = 0, cnt = 0, info = 0;
+        LsLink l = r_l;
         if (ne <= 64) {  // the links' data from the lanes that hold them
-          first = __shfl(r_first, ke.y, 64);
-          cnt = __shfl(r_cnt, ke.y, 64);
-          info = __shfl(r_info, ke.y, 64);
-          disc = make_float4(__shfl(r_disc.x, ke.y, 64), __shfl(r_disc.y, ke.y, 64), __shfl(r_disc.z, ke.y, 64),
-                             __shfl(r_disc.w, ke.y, 64));
+          const auto from = [&](auto v) { return __shfl(v, ke.y, 64); };
+          mb = from(r_mb); first = from(r_first); cnt = from(r_cnt); info = from(r_info);
+          l = LsLink{from(r_l.nx), from(r_l.ny), from(r_l.c), from(r_l.rho),
+                     make_float4(from(r_l.rng.x), from(r_l.rng.y), from(r_l.rng.z), from(r_l.rng.w)),
+                     from(r_l.ub), from(r_l.rs), from(r_l.bins)};
         }
-        float wm = 0.0f;
         const int kk = k0 + ke.x;
         if (p < npair) {
-          if (ne > 64) linked(ke.y, first, cnt, info, disc);
+          if (ne > 64) linked(ke.y, mb, first, cnt, info, l);
           if (cnt > 0) {
-            const float4 A = s_A[wv][kk];
-            const ModInfo mia{s_mia[wv][kk]};
-            wm = ls_window_bound(A, mia, disc, ModInfo{info}, g.d0max);
-            if (!ls_module_may_pass(A, disc, wm)) cnt = 0;
+            int az0, az1;
+            if (!ls_azimuth_bins(s_A[wv][kk], s_sa[wv][kk], s_in[wv][kk], ModInfo{s_mia[wv][kk]}, l, ModInfo{info}, g.d0max,
+                                 &az0, &az1)) {
+              cnt = 0;
+            } else if (g.map_asc && cnt < 0xffff) {
+              const int l0 = gp(w.mod_az)[mb * kAzBins + az0];
+              const int l1 = az1 < kAzBins ? (int)gp(w.mod_az)[mb * kAzBins + az1] : cnt;
+              first += l0;
+              cnt = max(l1 - l0, 0);
+            }
           }
         } else {
           cnt = 0;
@@ -1302,8 +1420,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         const unsigned long long live = __ballot(cnt > 0);
         if (cnt > 0) {
           const int q = n_ne + lanes_below(live);
-          s_edge[wv][q] = make_int4(first, run + x - cnt, info, __float_as_int(wm));
-          s_ek[wv][q] = kk;
+          s_ep[wv][q] = run + x - cnt;
+          s_ej[wv][q] = first - (run + x - cnt);
+          s_ek[wv][q] = kk | info << 8;
         }
         n_ne += __popcll(live);
         run += __builtin_amdgcn_readfirstlane(__shfl(x, 63, 64));
@@ -1322,52 +1441,44 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (jlo + lane < n_ne) {
-          const int p = s_edge[wv][jlo + lane].y - c0;  // >= 0: it starts at or after c0
+          const int p = s_ep[wv][jlo + lane] - c0;  // >= 0: it starts at or after c0
           if (p < 64) s_mark[wv][p] = 1;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const unsigned long long starts = __ballot(s_mark[wv][lane] != 0);
         const int c = c0 + lane;
-        bool keep_c = false;
-        int b = 0, info = 0, kk = 0;
+        bool ok = false;
+        int e = 0, q = 0;
         if (c < total) {
           const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
           const int j = jlo - 1 + __popcll(starts & upto);
-          const int4 E = s_edge[wv][j];
-          kk = s_ek[wv][j];
-          const float4 A = s_A[wv][kk];
-          const float2 sa = s_sa[wv][kk];
-          const ModInfo mia{s_mia[wv][kk]};
-          b = E.x + (c - E.y);
-          const float4 Bp = gload(w.md_pos, b);
-          info = E.z;
-          keep_c = ls_window_may_pass(A, Bp, __int_as_float(E.w)) &&
-                   ls_inner_stub_may_pass(A, Bp, sa, mia, ModInfo{info}, g.d0max);
+          const int ki = s_ek[wv][j];
+          q = ki & 0xff;
+          int b = s_ej[wv][j] + c;
+          if (g.map_asc) b = gp(w.md_az)[b];
+          const float4 A = s_A[wv][q], B = gload(w.md_pos, b);
+          const ModInfo mia{s_mia[wv][q]}, mib{ki >> 8};
+          e = b | (ki >> 8) << 30;
+          ok = ls_pair_may_pass(A, B, get_stub(w, g, b), mia, mib, g.d0max);
         }
         jlo += __popcll(starts);
-        const unsigned long long m = __ballot(keep_c);
-        if (keep_c) {
-          const int pos = nq + lanes_below(m);
-          s_q[wv][pos] = b | (info << 30);
-          s_qg[wv][pos] = (unsigned char)kk;
+        const unsigned long long m = __ballot(ok);
+        if (ok) {
+          const int pos = nr + lanes_below(m);
+          s_r[wv][pos] = e;
+          s_rg[wv][pos] = (unsigned char)q;
         }
-        nq += __popcll(m);
+        nr += __popcll(m);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        // each queue holds < 64 entries before a round adds at most 64, and is drained
-        // 64 at a time; the group's last round drains both completely
+        // the queue holds < 64 entries before a round adds at most 64, and is drained 64 at
+        // a time; the group's last round drains it completely
         const bool fin = k1 == na && c0 + 64 >= total;
-        while (nq >= 64 || (fin && nq > 0)) {
-          const int n1 = nq < 64 ? nq : 64;
-          sift(n1);
-          queue_pop64(s_q[wv], s_qg[wv], nq - n1);
-          nq -= n1;
-          while (nr >= 64) {
-            select(64);
-            queue_pop64(s_r[wv], s_rg[wv], nr - 64);
-            nr -= 64;
-          }
+        while (nr >= 64) {
+          select(64);
+          queue_pop64(s_r[wv], s_rg[wv], nr - 64);
+          nr -= 64;
         }
         if (fin && nr > 0) {
           select(nr);
@@ -1535,7 +1646,7 @@ __device__ __forceinline__ int round_parent(int start, int n, int c0, int *mark,
 // the latency of its dependent gathers, and more resident waves hide more of
 // it (measured 9% faster than the 77-VGPR, six-wave build; the same for the
 // triplet and quintuplet searches made them slower).
-constexpr int kLsCopyMds = 32;
+constexpr int kLsCopyMds = 16;
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_ls_fill(
     const Ws *__restrict__ wb, DevGeom g, int n_copy) {
   const Ws &w = wb[blockIdx.y];
@@ -1546,6 +1657,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
   // candidates in order, as partner | module info << 30: past the candidate pre-tests
   // (s_q) and past the pair pre-test as well (s_r)
   __shared__ int s_q[kWaves][128], s_r[kWaves][128];
+  __shared__ int s_val[kWaves][256];  // the copied partners of three rounds
   __shared__ int s_red[kWaves];
   const int n_md = uload(w.ctr + C_NMD);
   const int wv = wave_id(), lane = lane_id();
@@ -1573,15 +1685,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       const int n = cnt <= keep ? cnt : 0;  // the others are searched again below
       const int total = wave_segments(n, s_seg);
       const int start = s_seg[lane];
-      int carry = 0;
-      for (int c0 = 0; c0 < total; c0 += 64) {
+      // A module's partners were found in azimuth order: with ascending module maps a
+      // partner's place is its rank.  The partners go through a ring in LDS, a round ahead,
+      // since an MD's (at most kLsCache) may lie in two rounds.
+      static_assert(kLsCache <= 64, "in at most two rounds");
+      int carry = 0, e_next = 0;
+      auto stage = [&](int c0) __attribute__((always_inline)) {
         const int c = c0 + lane;
-        const int e = round_parent(start, n, c0, s_mark, carry);
+        e_next = round_parent(start, n, c0, s_mark, carry);
+        s_val[wv][c & 255] = c < total ? gp(w.ls_cache)[(long)(a0 + e_next) * kLsCache + (c - s_seg[e_next])] : 0;
+      };
+      if (total > 0) stage(0);
+      for (int c0 = 0; c0 < total; c0 += 64) {
+        const int c = c0 + lane, e = e_next;
+        if (c0 + 64 < total) stage(c0 + 64);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         if (c < total) {
-          const int k = c - s_seg[e], pos = s_off[e] + k;
+          const int v = s_val[wv][c & 255], b = v & 0x3fffffff;
+          int k = c - s_seg[e];
+          if (g.map_asc) {
+            k = 0;
+            const int j1 = s_seg[e + 1];
+#pragma unroll 4
+            for (int j = s_seg[e]; j < j1; ++j) k += (s_val[wv][j & 255] & 0x3fffffff) < b ? 1 : 0;
+          }
+          const int pos = s_off[e] + k;
           if (pos < w.cap_ls) {
-            const int v = gp(w.ls_cache)[(long)(a0 + e) * kLsCache + k];
-            const int b = v & 0x3fffffff;
             const float4 B = gload(w.md_pos, b);
             gstore(w.ls_md, pos, make_int2(a0 + e, b));
             gstore(w.ls_beta, pos, ls_beta(gload(w.md_pos, a0 + e), B));
@@ -1615,7 +1745,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         cnt = last > first ? last - first : 0;
         info = gp(g.info)[mb];
         if (cnt > 0) {
-          const float4 disc = gload(w.mod_disc, mb);
+          const float4 disc = gload(w.mod_disc, 2 * mb);
           wm = ls_window_bound(A, mia, disc, ModInfo{info}, g.d0max);
           if (!ls_module_may_pass(A, disc, wm)) cnt = 0;
         }
@@ -3471,14 +3601,19 @@ bool site_tunable(int site) {
   return false;
 }
 
-// Inner MDs per wave of the segment count pass: the tile when set, else
-// enough groups for about 32k waves over the launch's events (MDs taken as a
-// quarter of the MD capacity, which defaults to the hit count): one event
-// alone gets groups of 4, launches of 16 or more PU200-size events groups of 16.
+// Inner MDs per wave of the segment count pass: the tile when set, else the
+// square root of the launch's expected MDs (a quarter of the MD capacity, which
+// defaults to the hit count) / 2048.  Large groups fill the lanes of the pair,
+// candidate and selection rounds; a launch with few MDs needs the waves more.
+// Measured with 1 / 2 / 4 / 6 / 8 MDs: tiny event (1.4k MDs) 9 / 14 / 21 / 27 / 33 us,
+// PU50 (37k) 40 / 32 / 28 / 34 / 40, PU140 (75k) - / 76 / 64 / 57 / 58, PU200 (138k)
+// - / 115 / 90 / 90 / 85; eight PU200 events with 4 / 8 / 12 708 / 631 / 622.
 int ls_group_for(const Tiles &t, int B, long cap_md) {
   if (t.ls_group > 0) return t.ls_group < kLsGroup ? t.ls_group : kLsGroup;
-  const long gsz = (long)B * (cap_md / 4) / 32768;
-  return (int)std::max(1L, std::min((long)kLsGroup, gsz));
+  const long n = (long)B * (cap_md / 4);
+  int q = 1;
+  while (q < kLsGroup && (q + 1) * (q + 1) * 2048L <= n) ++q;
+  return q;
 }
 
 void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st, const KernelTimer *kt,

@@ -42,6 +42,7 @@ struct Tiles {
 
 struct DevGeom {
   int n_mod, n_edges;
+  int map_asc;        // 1: every module's targets ascend
   const int *map_off, *map_tgt;
   const float4 *win;  // per module: W, A1, A2, A3
   const int *info;    // per module: bit 0 = 2S, bit 1 = endcap
@@ -93,6 +94,7 @@ __host__ __device__ inline long n_sum_tiles(long cap) { return (cap >> tile_shif
 // than this: the fill searches again).
 constexpr int kLsCache = 32;
 constexpr int kLsGroup = 16;  // most inner MDs per wave of the segment count pass
+constexpr int kAzBins = 32;    // azimuth bins of a module's MDs
 constexpr int kMinParents = 16;  // fewest parents per wave of the triplet and quintuplet passes
 constexpr int kMdCache = 32;  // largest md_cache tile
 constexpr int kMdKeep = 6;    // partners per lower hit the MD search keeps
@@ -149,7 +151,9 @@ struct Ws {
   int *md_mod;
   float4 *md_pos;   // anchor (lower hit) x, y, z, r
   float2 *md_stub;  // tangential displacement, sensor separation (dense half2 with DevGeom::stub16)
-  float4 *mod_disc;  // per module with MDs: x-y disc (cx, cy, radius, |c|) around its anchors
+  float4 *mod_disc;  // two per module with MDs: x-y disc (cx, cy, radius, |c|) around its anchors; r and z ranges
+  int *md_az;        // each module's MDs grouped by bins of azimuth (azimuth_bin)
+  unsigned short *mod_az;  // per module: the first place of each bin, from the module's first MD
   // segments
   int *ls_cnt, *ls_off;
   int *ls_cache;    // per MD: up to kLsCache passing partners found by the count pass (| info << 30)
