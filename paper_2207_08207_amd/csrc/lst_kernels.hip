@@ -91,21 +91,13 @@ __device__ __forceinline__ int block_sum(int v, int *s_red) {
 __device__ __forceinline__ int dev_count(const int *p, int fallback) { return p ? *p : fallback; }
 
 // ------------------------------------------------------------------ start
-// The chain's first launch: clears what later kernels count into, empties the
-// lists of the pixel hits that seeds use and gives each such hit an owner, the
-// seed whose store came last (the rest of ph_head and ph_owner is never read).  Arrays indexed by MDs or quintuplets are cleared where those are
-// written, so no other launch of the chain only clears.  For one event (VALUE)
-// the launch's arguments carry the descriptor, and its first block writes it
-// where the later launches read it, instead of a copy before the chain.
-template <bool VALUE>
-__global__ void k_start(Ws value, Ws *wb) {
-  const Ws &w = VALUE ? value : wb[blockIdx.y];
-  if (VALUE && blockIdx.x == 0) {
-    static_assert(sizeof(Ws) % 4 == 0 && sizeof(Ws) <= 3584, "the first launch argument, within the argument block");
-    const auto *src = (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
-    for (int i = threadIdx.x; i < (int)(sizeof(Ws) / 4); i += blockDim.x) gp(reinterpret_cast<int *>(wb))[i] = src[i];
-  }
-  const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+// On further blocks (q of nq) of the chain's first launch: clears what later
+// launches count into, empties the lists of the pixel hits that seeds use and
+// gives each such hit an owner, the seed whose store came last (the rest of
+// ph_head and ph_owner is never read).  Arrays indexed by MDs or quintuplets are
+// cleared where those are written, so no launch of the chain only clears.
+__device__ __forceinline__ void start_blocks(const Ws &w, int q, int nq) {
+  const int tid = q * blockDim.x + threadIdx.x, nt = nq * blockDim.x;
   for (int j = 0; j < FL_COUNT; ++j) {
     int *p = w.fills[j].p;
     const int n = w.fills[j].n, st = w.fills[j].stride;
@@ -383,8 +375,7 @@ constexpr int bin_reach(double D) {
 // Hits are bucketed by key = 2 module + sensor, stably (input order within a
 // key), with no global atomic: a two-level counting sort.
 //  1. k_hits_count: each block counts the hits of its tile of input hits per
-//     coarse bucket (key >> kFineBits) in LDS (and validates hits and prepares
-//     seeds);
+//     coarse bucket (key >> kFineBits) in LDS;
 //  2. k_hits_rows turns each bucket's counts into the hits of earlier tiles;
 //  3. k_hits_scatter: each wave places its 64 to 512 hits of the tile in input
 //     order, 64 at a time, after the waves before it; hits of one coarse bucket
@@ -488,14 +479,25 @@ __device__ __forceinline__ bool seed_prepare(const Ws &w, int s) {
 // 16-bit counts fit LDS (n_coarse up to 1,700), else eight.  (Four waves of 16
 // rounds, as one block took before, left a tile's hits to a serial chain: 28 +
 // 43 us for the count and the scatter of one PU200 event.)
-template <int NW, int R>
-__global__ __launch_bounds__(64 * NW) void k_hits_count(const Ws *__restrict__ wb, int n_mod, int n_tiles) {
+//
+// The chain's first launch, with start_blocks on the blocks from n_tiles on (a
+// launch of their own, 5 to 9 us, before).  Nothing of theirs is used here: the
+// hits' validity is reported by the scatter, the seeds are prepared beside the
+// bucket sort (with the count, their chain of gathers made it 20 us for a PU200
+// event).  For one event (VALUE) the launch's arguments carry the descriptor,
+// which the first of those blocks writes where the later launches read it,
+// instead of a copy before the chain.
+template <bool VALUE, int NW, int R>
+__global__ __launch_bounds__(64 * NW) void k_hits_count(Ws value, Ws *wb, int n_mod, int n_tiles) {
   extern __shared__ int s_hits[];  // nc counts
-  const Ws &w = wb[blockIdx.y];
-  if ((int)blockIdx.x >= n_tiles) {  // the seeds
-    const int nt = ((int)gridDim.x - n_tiles) * 64 * NW;
-    for (int s = ((int)blockIdx.x - n_tiles) * 64 * NW + threadIdx.x; s < w.n_seeds; s += nt)
-      if (seed_prepare(w, s)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
+  const Ws &w = VALUE ? value : wb[blockIdx.y];
+  if ((int)blockIdx.x >= n_tiles) {
+    if (VALUE && (int)blockIdx.x == n_tiles) {
+      static_assert(sizeof(Ws) % 4 == 0 && sizeof(Ws) <= 3584, "the first launch argument, within the argument block");
+      const auto *src = (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+      for (int i = threadIdx.x; i < (int)(sizeof(Ws) / 4); i += blockDim.x) gp(reinterpret_cast<int *>(wb))[i] = src[i];
+    }
+    start_blocks(w, (int)blockIdx.x - n_tiles, (int)gridDim.x - n_tiles);
     return;
   }
   const int nc = n_coarse(n_mod), tb = blockIdx.x;
@@ -503,19 +505,16 @@ __global__ __launch_bounds__(64 * NW) void k_hits_count(const Ws *__restrict__ w
   if (i0 < w.n_hits) {
     for (int c = threadIdx.x; c < nc; c += 64 * NW) s_hits[c] = 0;
     int key[R];
-    bool any_bad = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = (int)i0 + r * 64 * NW + (int)threadIdx.x;
-      bool bad = false;
+      bool bad;
       key[r] = i < w.n_hits ? hit_key(w, i, n_mod, &bad) : -1;
-      any_bad |= bad;
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (key[r] >= 0) atomicAdd(&s_hits[key[r] >> kFineBits], 1);  // LDS
-    if (any_bad) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_HIT);
     __syncthreads();
     for (int c = threadIdx.x; c < nc; c += 64 * NW) gp(w.tile_hist)[(long)tb * nc + c] = s_hits[c];
   }
@@ -568,11 +567,13 @@ __global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__
   // the wave's hits, kept in registers
   int key[R];
   float x[R], y[R], z[R];
+  bool any_bad = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = (int)i0 + r * 64 + lane;
-    bool bad = true;
+    bool bad = false;
     key[r] = i < w.n_hits ? hit_key(w, i, n_mod, &bad) : -1;
+    any_bad |= bad;
     x[r] = y[r] = z[r] = 0.f;
     if (key[r] >= 0) {
       x[r] = gp(w.x)[i];
@@ -580,6 +581,7 @@ __global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__
       z[r] = gp(w.z)[i];
     }
   }
+  if (any_bad) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_HIT);
   // bucket starts: an exclusive scan of the bucket counts, kPer consecutive ones a thread
   constexpr int kPer = (kMaxCoarse + T - 1) / T;
   int v[kPer], sum = 0;
@@ -760,7 +762,12 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
   const int wv = wave_id(), lane = lane_id(), t = threadIdx.x;
   const int n_mod = g.n_mod, nc = n_coarse(n_mod), nkeys = 2 * n_mod;
   const int c = blockIdx.x, m0 = c * kBucketMods;
-  if (c >= nc) return;  // the whole block
+  if (c >= nc) {  // the seeds
+    const int nt = ((int)gridDim.x - nc) * kSortThreads;
+    for (int s = (c - nc) * kSortThreads + t; s < w.n_seeds; s += nt)
+      if (seed_prepare(w, s)) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_SEED);
+    return;
+  }
   const int j0 = uload(w.coarse_off + c), j1 = uload(w.coarse_off + c + 1);
   const long L = j1 - j0;
   const int a = j0 + (int)(L * wv / kSortWaves), b = j0 + (int)(L * (wv + 1) / kSortWaves);
@@ -3652,11 +3659,7 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
   const bool whole = kt && kt->site == kChainSite;  // the timer brackets the whole chain
   if (whole) (void)hipEventRecord(kt->beg, st);
   // a0: buckets
-  run([&] {
-    const dim3 d = grid(seeds ? kSeedBins : 4096);
-    if (value) k_start<true><<<d, kBlock, 0, st>>>(*value, wb);
-    else k_start<false><<<d, kBlock, 0, st>>>(Ws{}, wb);
-  });
+  run([&] {});  // fill_counters: with hits_count
   // hits: the tile (rounds of 64 hits a wave) grows with the launch's hits, so that a
   // small event still fills blocks and a large launch amortises a block's tables
   const long n_co = n_coarse(M);
@@ -3678,10 +3681,12 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
       else f(integral_constant<int, 8>{}, integral_constant<int, 8>{});
     }
   };
-  run([&] {  // one block per hit tile, the seeds on further blocks
+  run([&] {  // one block per hit tile, the clears on further blocks
     by_tile([&](auto nw, auto r) {
-      const unsigned n_seed = (unsigned)std::min((S + 64 * nw() - 1) / (64 * nw()), 4096L);
-      k_hits_count<nw(), r()><<<dim3(hit_blocks + n_seed, B), 64 * nw(), n_co * sizeof(int), st>>>(wb, M, (int)hit_blocks);
+      constexpr int T = 64 * nw();
+      const dim3 d(hit_blocks + std::max(1u, grid(seeds ? kSeedBins : 4096).x * kBlock / T), B);
+      if (value) k_hits_count<true, nw(), r()><<<d, T, n_co * sizeof(int), st>>>(*value, wb, M, (int)hit_blocks);
+      else k_hits_count<false, nw(), r()><<<d, T, n_co * sizeof(int), st>>>(Ws{}, wb, M, (int)hit_blocks);
     });
   });
   run([&] { k_hits_rows<<<dim3((unsigned)((n_co + 31) / 32), B), 1024, 0, st>>>(wb, M, tile); });
@@ -3691,7 +3696,11 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     });
   });
   // the bucket sort and a1: MD
-  run([&] { k_bucket_md<<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g); });
+  // (with the seeds in further blocks)
+  run([&] {
+    const unsigned n_seed = (unsigned)std::min((S + kSortThreads - 1) / kSortThreads, 4096L);
+    k_bucket_md<<<dim3((unsigned)n_co + n_seed, B), kSortThreads, 0, st>>>(wb, g);
+  });
   for (int q = 0; q < 2; ++q) run([&] {});  // md_count, md_scan: with bucket_sort, md_fill
   run([&] { k_md_fill<<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g); });
   // a2: LS
