@@ -191,6 +191,8 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.inc_b0 = reinterpret_cast<int *>(t.md_bin + md);
   static_assert(5 * sizeof(int4) <= 26 * sizeof(int), "the other MDs of the lists' T5s, per quintuplet");
   t.inc_mds = reinterpret_cast<int4 *>(t.ext_out);  // 20 t5 <= 26 tc
+  t.pt_spill = reinterpret_cast<int *>(t.inc_list);  // read last by the T5 duplicate removal
+  t.n_spill = (int)(10 * t5 / kPassList);
   t.t5_slot = t.tc_out;                        // 4 t5 <= 16 tc
   t.sdir = reinterpret_cast<float4 *>(t.tc_out + 4 * t5);  // and 4 S + S more
   t.sdir_pos = t.tc_out + 4 * t5 + 4 * S;

@@ -2634,74 +2634,153 @@ __device__ __forceinline__ unsigned long long pt_obj_key(float score, int seed) 
   return ~(((unsigned long long)__float_as_uint(score) << 32) | (unsigned long long)(unsigned)seed);
 }
 
-// One wave per seed over the objects of the bins its trajectory can reach.
-// COUNT: number of passing objects.  FILL: passing object indices gathered in
-// LDS, ranked by object index, written at the seed's offset in object order
-// (the order of the full scan); a seed with more passing objects than the
-// list holds (tile pass_list <= kPassList) is filled by an ordered scan over
-// all objects instead.  The count pass keeps up to pt3_cache / pt5_cache
-// passing objects per seed with their attributes, which the fill then ranks
-// and copies; more than max_slices marked bins are searched bin by bin.
-// (Seven waves per SIMD for the count: at most 72 VGPRs, no spills.)
-// The count pass searches both kinds on one mask per seed; the fill's first
-// n3 blocks take the triplets, the others the quintuplets.
+// One entry of the output, which also offers its key to its outer object.
+template <int KO>
+__device__ __forceinline__ void put_pt(const Ws &w, int pos, int s, int t, const float4 &attr) {
+  if (pos >= (KO == 3 ? w.cap_pt3 : w.cap_pt5)) return;
+  gstore(KO == 3 ? w.pt3_so : w.pt5_so, pos, make_int2(s, t));
+  gstore(KO == 3 ? w.pt3_attr : w.pt5_attr, pos, attr);
+  atomicMax((KO == 3 ? w.o3_best : w.o5_best) + t, pt_obj_key(attr.z, s));
+}
+
+// Entries of the seeds whose passing objects the count pass kept (block q of nq):
+// a wave takes kPtSeeds seeds, finds their offsets and strides their entries,
+// flattened, through LDS, where an entry's place is its rank by object index
+// (indices are distinct): the order of the full scan.  A wave's time is its chain
+// of gathers (sums, counts, entries, attributes), which more seeds share, and the
+// ranks of its longest lists: with 1 / 4 / 16 seeds 22 / 21 / 28 us on a PU200
+// event (93k triplet entries), 140 / 83 / 75 on eight.
+constexpr int kPtSeeds = 4;
+constexpr int kPtStage = 512;  // entries of a wave in LDS at a time
+struct PtCopyLds {
+  int seg[65], off[64], mark[64], val[kPtStage];
+  unsigned char par[kPtStage];
+};
+template <int KO>
+__device__ __forceinline__ void pt_copy(const Ws &w, const DevGeom &g, int q, int nq, PtCopyLds &L, int *s_red) {
+  constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
+  static_assert(kCache <= kPtStage && kPtSeeds <= 64, "a seed's entries fit the stage");
+  const int wv = wave_id(), lane = lane_id(), wpb = blockDim.x >> 6, S = w.n_seeds;
+  const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;  // <= kCache
+  const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
+  int *offs = KO == 3 ? w.pt3_off : w.pt5_off;
+  if (S == 0 && q == 0 && threadIdx.x == 0) offs[0] = 0;
+  const int per = wpb * kPtSeeds;
+  for (int b0 = q * per; b0 < S; b0 += nq * per) {
+    const int s0 = b0 + wv * kPtSeeds, s = s0 + lane;
+    const bool mine = lane < kPtSeeds && s < S;
+    const int cnt = mine ? gp(cnts)[s] : 0;
+    int before = 0;  // the block's seeds on earlier waves
+    for (int j = b0 + lane; j < min(s0, S); j += 64) before += gp(cnts)[j];
+    const int off = block_prefix(KO == 3 ? w.ts_p3 : w.ts_p5, w.sh_pt, cnts, 0, b0, s_red) + wave_total(before) +
+                    wave_inclusive(cnt) - cnt;
+    if (mine) {
+      gp(offs)[s] = off;
+      if (s == S - 1) {
+        gp(offs)[S] = off + cnt;
+        put_total(w, off + cnt, KO == 3 ? w.cap_pt3 : w.cap_pt5, KO == 3 ? C_RPT3 : C_RPT5, KO == 3 ? C_NPT3 : C_NPT5);
+      }
+    }
+    L.off[lane] = off;
+    const int n = cnt <= keep ? cnt : 0;  // the others are searched again
+    wave_segments(n, L.seg);
+    const int start = L.seg[lane];
+    for (int e0 = 0; e0 < kPtSeeds;) {
+      // as many whole seeds as the stage holds
+      const int c0 = L.seg[e0];
+      const int e1 = e0 + __popcll(__ballot(lane >= e0 && lane < kPtSeeds && L.seg[lane + 1] - c0 <= kPtStage));
+      const int c1 = L.seg[e1];
+      int carry = e0;
+      for (int r = c0; r < c1; r += 64) {
+        const int c = r + lane, e = round_parent(start, n, r, L.mark, carry);
+        if (c < c1) {
+          L.val[c - c0] = gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)(s0 + e) * kCache + (c - L.seg[e])];
+          L.par[c - c0] = (unsigned char)e;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int c = c0 + lane; c < c1; c += 64) {
+        const int e = L.par[c - c0], t = L.val[c - c0], a = L.seg[e] - c0, b = L.seg[e + 1] - c0;
+        const float4 attr = gload(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)(s0 + e) * kCache + (c - c0 - a));
+        int rank = 0;
+#pragma unroll 8
+        for (int j = a; j < b; ++j) rank += L.val[j] < t ? 1 : 0;
+        put_pt<KO>(w, L.off[e] + rank, s0 + e, t, attr);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      e0 = e1;
+    }
+  }
+}
+
+// The seed search over the objects of the bins a seed's trajectory can reach.
+// The count: one wave per seed, both kinds on one mask; it counts the passing
+// objects and keeps up to pt3_cache / pt5_cache of them with their attributes.
+// A seed with more (up to 400 on dense events) writes the others' indices to one
+// of n_spill lists in global memory.
+// The fill copies the kept ones (blocks [0, nc) the triplets, [nc, 2 nc) the
+// quintuplets); the first wave of each other block takes the seeds of its group
+// of 64 with more: their objects, from cache and list, or from a second search if
+// no list was left, are ranked by object index in LDS and written at the seed's
+// offset; a seed with more of them than the LDS list holds (tile pass_list <=
+// kPassList) takes an ordered scan over all objects instead.  (Searching again for
+// the seven such seeds of eight PU200 events made the fill 193 us.)  More than
+// max_slices marked bins are searched bin by bin.
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4 : 6))) void k_pt_binned(const Ws *__restrict__ wb,
-                                                                                              DevGeom g, int n3) {
-  __shared__ unsigned s_mask[kWaves][kMaskWords];
-  __shared__ int s_slo[kWaves][kRings], s_shi[kWaves][kRings];
-  __shared__ int2 s_zb[kWaves][kRings];
-  __shared__ int s_sl_j0[kWaves][kMaxSlices];       // bin id of each slice, then first list entry of each slice with candidates
-  __shared__ int s_sl_pre[kWaves][kMaxSlices];      // candidates before each slice with candidates
-  __shared__ int s_list[FILL ? kWaves : 1][FILL ? kPassList : 1];
-  __shared__ int s_pq[kWaves][128];  // MDs past the first-anchor test, their objects awaiting the full one
-  __shared__ int s_mark[kWaves][64];  // a slice's candidates start here (this round)
-  __shared__ int s_seg[kWaves][65], s_first[kWaves][64];  // the queued MDs' objects
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_pt_binned(const Ws *__restrict__ wb,
+                                                                                              DevGeom g, int nc) {
+  constexpr int kSets = FILL ? 1 : kWaves;  // waves that search
+  __shared__ unsigned s_mask[kSets][kMaskWords];
+  __shared__ int s_slo[kSets][kRings], s_shi[kSets][kRings];
+  __shared__ int2 s_zb[kSets][kRings];
+  __shared__ int s_sl_j0[kSets][kMaxSlices];       // bin id of each slice, then first list entry of each slice with candidates
+  __shared__ int s_sl_pre[kSets][kMaxSlices];      // candidates before each slice with candidates
+  __shared__ int s_list[FILL ? kPassList : 1];
+  __shared__ int s_pq[kSets][128];  // MDs past the first-anchor test, their objects awaiting the full one
+  __shared__ int s_mark[kSets][64];  // a slice's candidates start here (this round)
+  __shared__ int s_seg[kSets][65], s_first[kSets][64];  // the queued MDs' objects
   const Ws &w = wb[blockIdx.y];
   const int wv = wave_id(), lane = lane_id();
-  const bool five = FILL && (int)blockIdx.x >= n3;
-  const int si = ((int)blockIdx.x - (five ? n3 : 0)) * (int)(blockDim.x >> 6) + wv;
-  if (FILL && w.n_seeds == 0 && threadIdx.x == 0) (five ? w.pt5_off : w.pt3_off)[0] = 0;
-  int pre = 0;  // offset of the block's first seed in the fill, which takes the seeds in their order
+  int s = 0;
   if constexpr (FILL) {
+    __shared__ PtCopyLds s_copy[kWaves];
     __shared__ int s_red[kWaves];
-    pre = block_prefix(five ? w.ts_p5 : w.ts_p3, w.sh_pt, five ? w.pt5_cnt : w.pt3_cnt, 0,
-                       min(si - wv, w.n_seeds), s_red);
+    if ((int)blockIdx.x < nc) return pt_copy<3>(w, g, blockIdx.x, nc, s_copy[wv], s_red);
+    if ((int)blockIdx.x < 2 * nc) return pt_copy<5>(w, g, (int)blockIdx.x - nc, nc, s_copy[wv], s_red);
+    if (wv > 0) return;
+  } else {
+    const int si = (int)blockIdx.x * (int)(blockDim.x >> 6) + wv;
+    if (si >= w.n_seeds) return;
+    s = __float_as_int(gload(w.sdir, si).w);  // seeds of one direction on neighbouring waves
   }
-  if (si >= w.n_seeds) return;
-  // the count: seeds of one direction on neighbouring waves
-  const int s = FILL ? si : __float_as_int(gload(w.sdir, si).w);
-  const Seed sd = load_seed(w, s);
-  static_assert(kPt3Cache <= kPassList && kPt5Cache <= kPassList, "the fill ranks the cache in its LDS list");
+  Seed sd{};
+  if (!FILL) sd = load_seed(w, s);
   const int pass_list = g.tiles.pass_list;                            // <= kPassList
   const int max_slices = g.tiles.max_slices;                          // <= kMaxSlices
-  unsigned *mask = s_mask[wv];
+  unsigned *mask = s_mask[FILL ? 0 : wv];
   auto mark_bins = [&]() __attribute__((always_inline)) {  // the seed's (ring, azimuth) mask and z ranges
     for (int i = lane; i < kMaskWords; i += 64) mask[i] = 0u;
     if (lane < kRings) {
-      s_slo[wv][lane] = 0x7f7fffff;  // largest finite float
-      s_shi[wv][lane] = 0;
+      s_slo[FILL ? 0 : wv][lane] = 0x7f7fffff;  // largest finite float
+      s_shi[FILL ? 0 : wv][lane] = 0;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    mark_seed_bins(sd, mask, s_slo[wv], s_shi[wv]);
+    mark_seed_bins(sd, mask, s_slo[FILL ? 0 : wv], s_shi[FILL ? 0 : wv]);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (lane < kRings)
-      s_zb[wv][lane] = seed_zbins(sd, __int_as_float(s_slo[wv][lane]), __int_as_float(s_shi[wv][lane]));
+      s_zb[FILL ? 0 : wv][lane] = seed_zbins(sd, __int_as_float(s_slo[FILL ? 0 : wv][lane]), __int_as_float(s_shi[FILL ? 0 : wv][lane]));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
   // entries of one kind (KO = 3: triplets, 5: quintuplets) that passed so far
   int n_pass3 = 0, n_pass5 = 0;
-  // one entry of the output, which also offers its key to its outer object
-  auto put = [&](auto kind, int pos, int t, const float4 &attr) __attribute__((always_inline)) {
-    constexpr int KO = decltype(kind)::value;
-    if (pos >= (KO == 3 ? w.cap_pt3 : w.cap_pt5)) return;
-    gstore(KO == 3 ? w.pt3_so : w.pt5_so, pos, make_int2(s, t));
-    gstore(KO == 3 ? w.pt3_attr : w.pt5_attr, pos, attr);
-    atomicMax((KO == 3 ? w.o3_best : w.o5_best) + t, pt_obj_key(attr.z, s));
-  };
+  // the list that takes the seed's entries past the cache (-1: none yet, -2: none left)
+  int spill3 = -1, spill5 = -1;
+  const int n_spill = w.n_spill;
   // the full selection on one object per active lane; passing ones are counted in ballot
   // order and remembered (count: the cache with their attributes; fill: the LDS list)
   auto full = [&](auto kind, bool active, int t, int n_pass) __attribute__((always_inline)) {
@@ -2717,14 +2796,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
       pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
     }
     const unsigned long long m = __ballot(pass);
+    const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;
+    int &spill = KO == 3 ? spill3 : spill5;
+    if (!FILL && n_pass + __popcll(m) > keep && spill == -1) {
+      int v = 0;
+      if (lane == 0) v = atomicAdd(w.ctr + C_NSPILL, 1);
+      v = __builtin_amdgcn_readfirstlane(v);
+      spill = v < n_spill ? v : -2;
+    }
     if (pass) {
       const int r = n_pass + lanes_below(m);
       if (FILL) {
-        if (r < kPassList) s_list[wv][r] = t;
-      } else if (r < (KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache)) {
+        if (r < kPassList) s_list[r] = t;
+      } else if (r < keep) {
         constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
         gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + r] = t;
         gstore(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)s * kCache + r, attr);
+      } else if (spill >= 0 && r < kPassList) {
+        gp(w.pt_spill)[(long)spill * kPassList + r] = t;
       }
     }
     return n_pass + __popcll(m);
@@ -2734,18 +2823,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
     constexpr int KO = decltype(kind)::value;
     int first = 0, cnt = 0;
     if (lane < n) {
-      const int4 r = gload(w.bin_rng, s_pq[wv][lane]);
+      const int4 r = gload(w.bin_rng, s_pq[FILL ? 0 : wv][lane]);
       first = KO == 3 ? r.x : r.z;
       cnt = KO == 3 ? r.y : r.w;
     }
-    s_first[wv][lane] = first;
-    const int total = wave_segments(cnt, s_seg[wv]);
-    const int start = s_seg[wv][lane];
+    s_first[FILL ? 0 : wv][lane] = first;
+    const int total = wave_segments(cnt, s_seg[FILL ? 0 : wv]);
+    const int start = s_seg[FILL ? 0 : wv][lane];
     int carry = 0;
     for (int c0 = 0; c0 < total; c0 += 64) {
       const int c = c0 + lane;
-      const int e = round_parent(start, cnt, c0, s_mark[wv], carry);
-      n_pass = full(kind, c < total, c < total ? s_first[wv][e] + (c - s_seg[wv][e]) : 0, n_pass);
+      const int e = round_parent(start, cnt, c0, s_mark[FILL ? 0 : wv], carry);
+      n_pass = full(kind, c < total, c < total ? s_first[FILL ? 0 : wv][e] + (c - s_seg[FILL ? 0 : wv][e]) : 0, n_pass);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -2761,13 +2850,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
     // candidates before it)
     int n_bits = 0;
     for (int w0 = 0; w0 < kMaskWords; w0 += 64) {
-      const unsigned bits = w0 + lane < kMaskWords ? s_mask[wv][w0 + lane] : 0u;
+      const unsigned bits = w0 + lane < kMaskWords ? s_mask[FILL ? 0 : wv][w0 + lane] : 0u;
       const int pc = __popc(bits);
       const int x = wave_inclusive(pc);
       const int tot = __shfl(x, 63, 64);
       if (n_bits + tot <= max_slices) {
         int k = n_bits + x - pc;
-        for (unsigned bb = bits; bb; bb &= bb - 1u) s_sl_j0[wv][k++] = (w0 + lane) * 32 + __builtin_ctz(bb);
+        for (unsigned bb = bits; bb; bb &= bb - 1u) s_sl_j0[FILL ? 0 : wv][k++] = (w0 + lane) * 32 + __builtin_ctz(bb);
       }
       n_bits += tot;
     }
@@ -2782,8 +2871,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
         const int k = c0 + lane;
         int j0 = 0, len = 0;
         if (k < n_bits) {
-          const int bin = s_sl_j0[wv][k];
-          const int2 zb = s_zb[wv][bin / kPhiBins];
+          const int bin = s_sl_j0[FILL ? 0 : wv][k];
+          const int2 zb = s_zb[FILL ? 0 : wv][bin / kPhiBins];
           j0 = gp(w.bin_off)[bin * kBinStride + zb.x];
           len = gp(w.bin_off)[bin * kBinStride + zb.y + 1] - j0;
         }
@@ -2793,8 +2882,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
         __builtin_amdgcn_wave_barrier();
         if (len > 0) {
           const int q = n_live + lanes_below(live);
-          s_sl_j0[wv][q] = j0;
-          s_sl_pre[wv][q] = run + x - len;
+          s_sl_j0[FILL ? 0 : wv][q] = j0;
+          s_sl_pre[FILL ? 0 : wv][q] = run + x - len;
         }
         n_live += __popcll(live);
         run += __builtin_amdgcn_readfirstlane(__shfl(x, 63, 64));
@@ -2817,21 +2906,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
           // the slice of each lane's candidate: the slices starting before the round (jlo)
           // plus those starting at or below the lane in it (distinct starts, marked)
           const int c = c0 + lane;
-          s_mark[wv][lane] = 0;
+          s_mark[FILL ? 0 : wv][lane] = 0;
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
           if (jlo + lane < n_live) {
-            const int p = s_sl_pre[wv][jlo + lane] - c0;  // >= 0
-            if (p < 64) s_mark[wv][p] = 1;
+            const int p = s_sl_pre[FILL ? 0 : wv][jlo + lane] - c0;  // >= 0
+            if (p < 64) s_mark[FILL ? 0 : wv][p] = 1;
           }
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
-          const unsigned long long starts = __ballot(s_mark[wv][lane] != 0);
+          const unsigned long long starts = __ballot(s_mark[FILL ? 0 : wv][lane] != 0);
           active = c < run;
           if (active) {
             const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
             const int e = jlo - 1 + __popcll(starts & upto);
-            j = s_sl_j0[wv][e] + (c - s_sl_pre[wv][e]);
+            j = s_sl_j0[FILL ? 0 : wv][e] + (c - s_sl_pre[FILL ? 0 : wv][e]);
           }
           jlo += __popcll(starts);
           c0 += 64;
@@ -2843,7 +2932,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
           if (!last) {
             const int bin = wd * 32 + __builtin_ctz(bits);
             bits &= bits - 1u;
-            const int2 zb = s_zb[wv][bin / kPhiBins];
+            const int2 zb = s_zb[FILL ? 0 : wv][bin / kPhiBins];
             j_at = uload(w.bin_off + bin * kBinStride + zb.x);
             j_end = uload(w.bin_off + bin * kBinStride + zb.y + 1);
           }
@@ -2858,7 +2947,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
         keep = pt_first_anchor(sd, f, ModInfo{__float_as_int(f.w)});
       }
       const unsigned long long m = __ballot(keep);
-      if (keep) s_pq[wv][nq + lanes_below(m)] = j;
+      if (keep) s_pq[FILL ? 0 : wv][nq + lanes_below(m)] = j;
       nq += __popcll(m);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -2866,7 +2955,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
         const int n = nq < 64 ? nq : 64;
         if constexpr (decltype(want3)::value) n_pass3 = expand(std::integral_constant<int, 3>{}, n, n_pass3);
         if constexpr (decltype(want5)::value) n_pass5 = expand(std::integral_constant<int, 5>{}, n, n_pass5);
-        queue_pop64(s_pq[wv], nq - n);
+        queue_pop64(s_pq[FILL ? 0 : wv], nq - n);
         nq -= n;
       }
       if (last && nq == 0) break;
@@ -2880,83 +2969,79 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILL ? 4
       gp(w.pt5_cnt)[s] = n_pass5;
       if (n_pass3 > 0) atomicAdd(w.ts_p3 + (s >> w.sh_pt) * kSumStride, n_pass3);
       if (n_pass5 > 0) atomicAdd(w.ts_p5 + (s >> w.sh_pt) * kSumStride, n_pass5);
+      if (n_pass3 > g.tiles.pt3_cache) gp(w.ph_next)[4L * s] = spill3;
+      if (n_pass5 > g.tiles.pt5_cache) gp(w.ph_next)[4L * s + 1] = spill5;
     }
     return;
   }
-  auto fill = [&](auto kind) __attribute__((always_inline)) {
+  auto again = [&](auto kind) __attribute__((always_inline)) {
     constexpr int KO = decltype(kind)::value;
-    constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
-    const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;  // <= kCache
+    const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;
     const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
-    int *offs = KO == 3 ? w.pt3_off : w.pt5_off;
-    int base = pre;
-    for (int q = si - wv; q < si; ++q) base += uload(cnts + q);
-    const int expect = uload(cnts + s);
-    if (lane == 0) {
-      offs[s] = base;
-      if (s == w.n_seeds - 1) {
-        offs[s + 1] = base + expect;
-        put_total(w, base + expect, KO == 3 ? w.cap_pt3 : w.cap_pt5, KO == 3 ? C_RPT3 : C_RPT5,
-                  KO == 3 ? C_NPT3 : C_NPT5);
-      }
-    }
-    const bool cached = expect <= keep;
-    if (expect > pass_list && !cached) {
-      // rare: too many passing objects for the LDS list; ordered scan of all objects
-      const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
-      const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
-      for (int t0 = 0; t0 < n_obj; t0 += 64) {
-        const int t = t0 + lane;
-        bool pass = false;
-        float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
-          const float2 f = first[t];
-          if (seed_box(sd, f.x, f.y)) {
-            float4 P[KO];
-            ModInfo M[KO];
-            float kT, dkT;
-            load_object<KO>(w, g, t, P, M, &kT, &dkT);
-            pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+    const int s0 = ((int)blockIdx.x - 2 * nc) * 64;
+    const int cnt = s0 + lane < w.n_seeds ? gp(cnts)[s0 + lane] : 0;
+    for (unsigned long long m = __ballot(cnt > keep); m; m &= m - 1) {
+      const int q = __builtin_ctzll(m), expect = __builtin_amdgcn_readlane(cnt, q);
+      s = s0 + q;
+      sd = load_seed(w, s);
+      int base = wave_prefix(KO == 3 ? w.ts_p3 : w.ts_p5, w.sh_pt, cnts, 0, s);
+      if (expect > pass_list) {
+        const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
+        const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
+        for (int t0 = 0; t0 < n_obj; t0 += 64) {
+          const int t = t0 + lane;
+          bool pass = false;
+          float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
+            const float2 f = first[t];
+            if (seed_box(sd, f.x, f.y)) {
+              float4 P[KO];
+              ModInfo M[KO];
+              float kT, dkT;
+              load_object<KO>(w, g, t, P, M, &kT, &dkT);
+              pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+            }
           }
+          const unsigned long long mp = __ballot(pass);
+          if (pass) put_pt<KO>(w, base + lanes_below(mp), s, t, attr);
+          base += __popcll(mp);
         }
-        const unsigned long long m = __ballot(pass);
-        if (pass) put(kind, base + lanes_below(m), t, attr);
-        base += __popcll(m);
+        continue;
       }
-      return;
-    }
-    // the passing objects: what the count pass cached with their attributes, or searched again
-    int n = expect;
-    if (cached) {
-      for (int i = lane; i < expect; i += 64)
-        s_list[wv][i] = gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + i];
-    } else {
-      mark_bins();
-      search(std::integral_constant<bool, KO == 3>{}, std::integral_constant<bool, KO == 5>{});
-      n = KO == 3 ? n_pass3 : n_pass5;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // rank by object index (indices are distinct) and write in object order
-    for (int i = lane; i < n; i += 64) {
-      const int t = s_list[wv][i];
-      int rank = 0;
-      for (int q = 0; q < n; ++q) rank += s_list[wv][q] < t ? 1 : 0;
-      float4 attr;
-      if (cached) {
-        attr = gload(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)s * kCache + i);
+      const int spill = uload(w.ph_next + 4L * s + (KO == 5 ? 1 : 0));
+      int n = expect;
+      if (spill >= 0) {
+        constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
+        for (int i = lane; i < n; i += 64)
+          s_list[i] = i < keep ? gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + i]
+                               : gp(w.pt_spill)[(long)spill * kPassList + i];
       } else {
+        n_pass3 = n_pass5 = 0;
+        mark_bins();
+        search(std::integral_constant<bool, KO == 3>{}, std::integral_constant<bool, KO == 5>{});
+        n = KO == 3 ? n_pass3 : n_pass5;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int i = lane; i < n; i += 64) {
+        const int t = s_list[i];
+        int rank = 0;
+#pragma unroll 8
+        for (int r = 0; r < n; ++r) rank += s_list[r] < t ? 1 : 0;
+        float4 attr;
         float4 P[KO];
         ModInfo M[KO];
         float kT, dkT;
         load_object<KO>(w, g, t, P, M, &kT, &dkT);
         pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+        put_pt<KO>(w, base + rank, s, t, attr);
       }
-      put(kind, base + rank, t, attr);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   };
-  if (five) fill(std::integral_constant<int, 5>{});
-  else fill(std::integral_constant<int, 3>{});
+  again(std::integral_constant<int, 3>{});
+  again(std::integral_constant<int, 5>{});
 }
 
 template <int K>
@@ -3755,8 +3840,8 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
   run([&] {});  // pt3_scan
   run([&] {
     if (!seeds) return;
-    const unsigned n3 = seedwaves().x;
-    k_pt_binned<true><<<dim3(2 * n3, B), tb, 0, st>>>(wb, g, (int)n3);
+    const unsigned nc = gridwt((S + kPtSeeds - 1) / kPtSeeds).x, n_again = (unsigned)((S + 63) / 64);
+    k_pt_binned<true><<<dim3(2 * nc + n_again, B), tb, 0, st>>>(wb, g, (int)nc);
   });
   run([&] {});  // pt5_scan
   run([&] {});  // pt5_fill: with pt3_fill

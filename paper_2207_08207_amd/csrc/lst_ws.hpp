@@ -12,8 +12,8 @@ enum Ctr : int {
   C_NMD = 1, C_NLS, C_NT3, C_NT5, C_NPT3, C_NPT5, C_NTC, C_NTCHITS,   // built counts (clamped)
   C_RMD = 9, C_RLS, C_RT3, C_RT5, C_RPT3, C_RPT5,                      // required counts
   C_NT5KEEP = 15, C_NTC0 = 16, C_NTC1, C_NTC2, C_NTC3,                 // survivors, TCs per type
-  C_NOUTER = 20, C_NINC = 21, C_NPH = 22, C_NO3 = 23, C_NO5 = 24,      // scratch totals
-  C_NBIN = 25,
+  C_NINC = 21, C_NBIN = 25,      // scratch totals
+  C_NSPILL = 26,                 // seeds with more passing objects than the seed search caches
   C_NLSOVF = 27,                 // MDs with more segments than the count pass caches
   C_NEXTHITS = 28,               // hits of the extended track-candidate collection
   C_EXT = 29,                    // 1 once the track extensions of the event are written
@@ -192,6 +192,8 @@ struct Ws {
   int *ph_owner, *ph_head, *ph_next;
   // pixel triplets / quintuplets
   int *pt3_cnt, *pt3_off, *pt5_cnt, *pt5_off;
+  int *pt_spill;    // n_spill lists of kPassList objects, for seeds with more than those
+  int n_spill;
   int *pt3_cache, *pt5_cache;  // per seed: up to kPt3Cache / kPt5Cache passing objects found by the count pass
   float4 *pt3_cattr, *pt5_cattr;  // and their attributes
   int2 *pt3_so, *pt5_so;      // seed, object
