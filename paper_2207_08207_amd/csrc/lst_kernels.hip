@@ -376,7 +376,8 @@ constexpr int bin_reach(double D) {
 // key), with no global atomic: a two-level counting sort.
 //  1. k_hits_count: each block counts the hits of its tile of input hits per
 //     coarse bucket (key >> kFineBits) in LDS;
-//  2. k_hits_rows turns each bucket's counts into the hits of earlier tiles;
+//  2. k_hits_rows turns each bucket's counts into the hits of earlier tiles (the
+//     scatter does so itself for few tiles);
 //  3. k_hits_scatter: each wave places its 64 to 512 hits of the tile in input
 //     order, 64 at a time, after the waves before it; hits of one coarse bucket
 //     in a round find each other with ballots and take consecutive positions
@@ -551,8 +552,13 @@ __global__ __launch_bounds__(1024) void k_hits_rows(const Ws *__restrict__ wb, i
 // the round's hits of its bucket (match_value) places it.  The hit's
 // coordinates, input index and key within its bucket travel with it (one
 // 16-byte store), so the per-bucket sort reads them contiguously.
+// With few tiles (direct: at most kDirectTiles in the launch's largest event) every
+// block sums the tiles' counts for itself and there is no launch of k_hits_rows:
+// 4 us less on a tiny event (two tiles of 1,400 hits).  With the 130 tiles of a
+// PU50 event the blocks would read 80 MB for it.
+constexpr int kDirectTiles = 16;
 template <int NW, int R>
-__global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__ wb, int n_mod) {
+__global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__ wb, int n_mod, int direct) {
   extern __shared__ int s_hits[];  // nc positions, then NW rows of 16-bit counts, two a word
   __shared__ int s_wave[NW];
   constexpr int T = 64 * NW;
@@ -584,9 +590,21 @@ __global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__
   if (any_bad) atomicOr(&w.ctr[C_STATUS], (int)ST_BAD_HIT);
   // bucket starts: an exclusive scan of the bucket counts, kPer consecutive ones a thread
   constexpr int kPer = (kMaxCoarse + T - 1) / T;
-  int v[kPer], sum = 0;
+  int v[kPer], own[kPer], sum = 0;  // the bucket's hits, and those in earlier tiles
+  const int n_tiles = direct ? n_hit_tiles(w.n_hits, T * R) : 0;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) sum += v[i] = t * kPer + i < nc ? gp(w.coarse_cnt)[t * kPer + i] : 0;
+  for (int i = 0; i < kPer; ++i) {
+    const int c = t * kPer + i;
+    v[i] = own[i] = 0;
+    if (c < nc) {
+      if (!direct) v[i] = gp(w.coarse_cnt)[c];
+      for (int q = 0; q < n_tiles; ++q) {
+        if (q == tb) own[i] = v[i];
+        v[i] += gp(w.tile_hist)[(long)q * nc + c];
+      }
+    }
+    sum += v[i];
+  }
   const int inc = wave_inclusive(sum);
   if (lane == 63) s_wave[wv] = inc;
   __syncthreads();
@@ -596,7 +614,7 @@ __global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__
   for (int i = 0; i < kPer; ++i) {
     const int c = t * kPer + i;
     if (c < nc) {
-      s_base[c] = ex;
+      s_base[c] = ex + own[i];
       if (tb == 0) {
         gp(w.coarse_off)[c] = ex;
         if (c == nc - 1) gp(w.coarse_off)[nc] = ex + v[i];
@@ -622,7 +640,7 @@ __global__ __launch_bounds__(64 * NW) void k_hits_scatter(const Ws *__restrict__
       run += u;
     }
   }
-  if ((long)tb * (T * R) < w.n_hits)
+  if (!direct && (long)tb * (T * R) < w.n_hits)
     for (int c = t; c < nc; c += T) s_base[c] += gp(w.tile_hist)[(long)tb * nc + c];
   __syncthreads();
   unsigned short *s_run = reinterpret_cast<unsigned short *>(mine);
@@ -1653,9 +1671,13 @@ __device__ __forceinline__ int round_parent(int start, int n, int c0, int *mark,
 // the latency of its dependent gathers, and more resident waves hide more of
 // it (measured 9% faster than the 77-VGPR, six-wave build; the same for the
 // triplet and quintuplet searches made them slower).
+// direct (no seeds, MD capacity of at most kDirectMds): there is no launch of
+// k_ls_sums, the copying blocks sum the counts before theirs and their waves take
+// their own MDs with more segments than the cache: 4 us less on a tiny event.
+constexpr int kDirectMds = 8192;
 constexpr int kLsCopyMds = 16;
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_ls_fill(
-    const Ws *__restrict__ wb, DevGeom g, int n_copy) {
+    const Ws *__restrict__ wb, DevGeom g, int n_copy, int direct) {
   const Ws &w = wb[blockIdx.y];
   __shared__ int s_pre[kWaves][kMaxEdges + 1];  // running MD count before each edge
   __shared__ int s_first[kWaves][kMaxEdges];    // first MD of each linked module
@@ -1669,6 +1691,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
   const int n_md = uload(w.ctr + C_NMD);
   const int wv = wave_id(), lane = lane_id();
   const int wpb = blockDim.x >> 6;  // waves per block (a tuned launch may run fewer than kWaves)
+  const int sh = direct ? 30 : w.sh_ls;  // (no tile is before the first)
   if ((int)blockIdx.x < n_copy) {
     const int keep = g.tiles.ls_cache;
     int *s_seg = s_pre[wv], *s_off = s_first[wv], *s_mark = s_q[wv];  // 65 / 64 / 64 entries
@@ -1679,7 +1702,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       const int cnt = mine ? gp(w.ls_cnt)[a] : 0;
       int before = 0;  // the block's MDs on earlier waves
       for (int j = b0 + lane; j < min(a0, n_md); j += 64) before += gp(w.ls_cnt)[j];
-      const int off = block_prefix(w.ts_ls, w.sh_ls, w.ls_cnt, 0, b0, s_red) + wave_total(before) +
+      const int off = block_prefix(w.ts_ls, sh, w.ls_cnt, 0, b0, s_red) + wave_total(before) +
                       wave_inclusive(cnt) - cnt;
       if (mine) {
         gp(w.ls_off)[a] = off;
@@ -1730,7 +1753,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
-    return;
+    if (!direct) return;
   }
   auto process = [&](const int a) {
     const int ma = gp(w.md_mod)[a];
@@ -1774,7 +1797,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int total = run;
-    int out = wave_prefix(w.ts_ls, w.sh_ls, w.ls_cnt, 0, a);
+    int out = wave_prefix(w.ts_ls, sh, w.ls_cnt, 0, a);
     // the pair pre-test on the first n candidates of s_q (n <= 64); the passing ones join s_r
     int nr = 0;
     auto sift = [&](int n) {
@@ -1859,6 +1882,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
       nr -= n2;
     }
   };
+  if (direct) {  // those of the wave's own MDs
+    for (int a0 = ((int)blockIdx.x * wpb + wv) * kLsCopyMds; a0 < n_md; a0 += n_copy * wpb * kLsCopyMds) {
+      const bool more = lane < kLsCopyMds && a0 + lane < n_md && gp(w.ls_cnt)[a0 + lane] > g.tiles.ls_cache;
+      for (unsigned long long m = __ballot(more); m; m &= m - 1) process(a0 + __builtin_ctzll(m));
+    }
+    return;
+  }
   const int n_ovf = uload(w.ctr + C_NLSOVF);
   const int stride = ((int)gridDim.x - n_copy) * wpb;
   for (int k = ((int)blockIdx.x - n_copy) * wpb + wv; k < n_ovf; k += stride) process(uload(w.ls_ovf + k));
@@ -2516,6 +2546,49 @@ __global__ __launch_bounds__(kBlock) void k_t5_dedup(const Ws *__restrict__ wb) 
       }
       if (drop) gp(w.t5_keep)[t] = 0;
     }
+  }
+}
+
+// The same decision with every pair of T5s, one wave per T5 t and its lanes over
+// the others (at most 32 rounds), for capacities up to kPairsT5: no lists, so
+// three launches less (with the removal itself 16 -> 5 us on a tiny event of 179
+// T5s; the lists of a PU50 event, with ten times as many, take 21 us, and pairs
+// grow with the square).  The seed search's bins are scattered on further blocks.
+constexpr int kPairsT5 = 2048;
+__global__ __launch_bounds__(kBlock) void k_t5_pairs(const Ws *__restrict__ wb, DevGeom g, int n_main) {
+  const Ws &w = wb[blockIdx.y];
+  if ((int)blockIdx.x >= n_main) {
+    bin_scatter(w, g, (int)blockIdx.x - n_main, (int)gridDim.x - n_main);
+    return;
+  }
+  const int n = uload(w.ctr + C_NT5);
+  const int lane = lane_id(), wpb = blockDim.x >> 6;
+  for (int t = blockIdx.x * wpb + wave_id(); t < n; t += n_main * wpb) {
+    int mt[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) mt[j] = uload(w.t5_md + 5L * t + j);
+    const float st = __int_as_float(uload(reinterpret_cast<const int *>(w.t5_attr) + 8L * t + 1));
+    bool drop = false;
+    for (int u = lane; u < n; u += 64) {
+      const float su = gp(w.t5_attr)[8L * u + 1];
+      if (u == t || st < su) continue;
+      int shared = 0;
+#pragma unroll
+      for (int j = 0; j < 5; ++j) {
+        const int m = gp(w.t5_md)[5L * u + j];
+        shared += m == mt[0] || m == mt[1] || m == mt[2] || m == mt[3] || m == mt[4] ? 1 : 0;
+      }
+      if (shared < 2) continue;
+      bool better_u = su < st;
+      if (!better_u) {
+        int ht[10], hu[10];
+        t5_hits(w, t, ht);
+        t5_hits(w, u, hu);
+        better_u = better<10>(su, hu, st, ht);
+      }
+      drop |= better_u;
+    }
+    if (__ballot(drop) && lane == 0) gp(w.t5_keep)[t] = 0;
   }
 }
 
@@ -3774,10 +3847,11 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
       else k_hits_count<false, nw(), r()><<<d, T, n_co * sizeof(int), st>>>(Ws{}, wb, M, (int)hit_blocks);
     });
   });
-  run([&] { k_hits_rows<<<dim3((unsigned)((n_co + 31) / 32), B), 1024, 0, st>>>(wb, M, tile); });
+  const int direct = n_tiles <= kDirectTiles ? 1 : 0;
+  run([&] { if (!direct) k_hits_rows<<<dim3((unsigned)((n_co + 31) / 32), B), 1024, 0, st>>>(wb, M, tile); });
   run([&] {
     by_tile([&](auto nw, auto r) {
-      k_hits_scatter<nw(), r()><<<dim3(hit_blocks, B), 64 * nw(), lds_scatter, st>>>(wb, M);
+      k_hits_scatter<nw(), r()><<<dim3(hit_blocks, B), 64 * nw(), lds_scatter, st>>>(wb, M, direct);
     });
   });
   // the bucket sort and a1: MD
@@ -3793,15 +3867,17 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     const int lg = ls_group_for(g.tiles, B, b.cap_md);
     k_ls_count<<<gridwb((b.cap_md + lg - 1) / lg), tb, 0, st>>>(wb, g, lg);
   });
+  const bool ls_direct = !seeds && b.cap_md <= kDirectMds;
   run([&] {
+    if (ls_direct) return;
     const unsigned n_sum = (unsigned)std::min<long>(n_sum_tiles(b.cap_md), 256);
     const unsigned n_seed = seeds ? grid(S).x : 0;
     k_ls_sums<<<dim3(n_sum + n_seed, B), kBlock, 0, st>>>(wb, g.tiles.ls_cache, (int)n_sum);
   });
   run([&] {
     const unsigned n_copy = gridwt((b.cap_md + kLsCopyMds - 1) / kLsCopyMds).x;
-    const unsigned n_ovf = gridwt(std::min(b.cap_md, 4096)).x;  // the overflow MDs (428 on a PU200 event)
-    k_ls_fill<<<dim3(n_copy + n_ovf, B), tb, 0, st>>>(wb, g, (int)n_copy);
+    const unsigned n_ovf = ls_direct ? 0 : gridwt(std::min(b.cap_md, 4096)).x;  // the overflow MDs (428 on a PU200 event)
+    k_ls_fill<<<dim3(n_copy + n_ovf, B), tb, 0, st>>>(wb, g, (int)n_copy, ls_direct ? 1 : 0);
   });
   // a3: T3
   run([&] { k_t3<false><<<gridwt(b.cap_ls / kMinParents + 1), tb, 0, st>>>(wb, g); });
@@ -3821,14 +3897,21 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     const unsigned nq = seeds ? (kBinRows + rows - 1) / rows : 0;
     k_t5<true><<<dim3(d.x + nq, B), tb, 0, st>>>(wb, g, (int)d.x);
   });
-  // a5: T5 duplicate removal through per-MD incidence lists
+  // a5: T5 duplicate removal through per-MD incidence lists, or over all pairs of few
+  const bool pairs = b.cap_t5 <= kPairsT5;
   run([&] {
+    if (pairs) return;
     const unsigned n5 = grid(4L * b.cap_t5).x, nq = seeds ? grid(b.cap_md).x : 0;
     k_t5_inc<<<dim3(n5 + nq, B), kBlock, 0, st>>>(wb, g, (int)n5);
   });
-  run([&] { k_list_place<<<grid((b.cap_md + 1) / 2), kBlock, 0, st>>>(wb); });
-  run([&] { k_t5_inc_scatter<<<grid(5L * b.cap_t5), kBlock, 0, st>>>(wb); });
+  run([&] { if (!pairs) k_list_place<<<grid((b.cap_md + 1) / 2), kBlock, 0, st>>>(wb); });
+  run([&] { if (!pairs) k_t5_inc_scatter<<<grid(5L * b.cap_t5), kBlock, 0, st>>>(wb); });
   run([&] {
+    if (pairs) {
+      const unsigned n5 = gridwt(b.cap_t5).x, nq = seeds ? grid(b.cap_md).x : 0;
+      k_t5_pairs<<<dim3(n5 + nq, B), tb, 0, st>>>(wb, g, (int)n5);
+      return;
+    }
     const long blocks = (4L * b.cap_t5 + 63) / 64;  // 64 items a block
     k_t5_dedup<<<dim3(share_big((int)std::min(blocks, 1L << 24), tb), B), tb, 0, st>>>(wb);
   });

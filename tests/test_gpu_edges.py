@@ -206,3 +206,63 @@ def test_results_of_many_events(n, ext, lst, barrel, obarrel):
             compare_tc(r, oracle.run(obarrel, ev))
             _one.close()
         r.close()
+
+
+def _cut(ev, n):
+    return Event(x=ev.x[:n], y=ev.y[:n], z=ev.z[:n], module=ev.module[:n], sensor=ev.sensor[:n], sim=ev.sim[:n])
+
+
+# sixteen and seventeen hit tiles (the scatter's own sums, and those of a launch before it)
+@pytest.mark.parametrize("n_hits", [16384, 16385])
+def test_hits_at_the_direct_tile_limit(n_hits, lst, full, ofull):
+    ev = make_event("pu200", 31, pu=20.0)
+    assert ev.n_hits > 16385
+    ev = _cut(ev, n_hits)
+    print(f"[gpu] first {n_hits} hits", flush=True)
+    _same(lst.run_event(lst.Geometry(full), lst.upload_event(ev)), oracle.run(ofull, ev))
+
+
+def _with_capacity(lst, g, ev, **caps):
+    import torch
+    cap = lst.lst_default_capacity(ev.n_hits, ev.n_seeds)
+    for k, v in dict(dict(ls=65536, t3=65536, pt3=65536, pt5=65536), **caps).items():  # room in the other stages
+        setattr(cap, k, max(v, 1))
+    ws = lst.alloc_workspace(g, ev.n_hits, ev.n_seeds, cap)
+    st, h = lst.lst_build_event(g.handle, lst.upload_event(ev), ws, cap, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    return lst.EventResult(h, ws, st)
+
+
+# T5 duplicate removal over all pairs (capacities up to 2,048) and over lists, with hundreds of T5s at
+# one MD, seeded (the seed search's bins ride in both) and not
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("cap_t5", [2048, 2049])
+@pytest.mark.parametrize("seeded", [True, False])
+def test_t5_duplicates_at_the_pair_limit(seeded, cap_t5, block, lst, barrel, obarrel):
+    from dense import dense_event
+    ev = dense_event(barrel)
+    if not seeded:
+        ev = _cut(ev, ev.n_hits)
+    g = lst.Geometry(barrel)
+    g.set_launch_config({"t5_dedup": block})
+    o = oracle.run(obarrel, ev)
+    assert 500 < len(o.stage(oracle.ST_T5)[0]) <= 2048
+    print(f"[gpu] {len(o.stage(oracle.ST_T5)[0])} T5s, room for {cap_t5}", flush=True)
+    _same(_with_capacity(lst, g, ev, t5=cap_t5), o)
+
+
+# segments of unseeded events whose copying blocks sum the counts themselves (MD capacities up to
+# 8,192), with MDs past the cache
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("ls_cache", [32, 2, 0])
+@pytest.mark.parametrize("cap_md", [8192, 8193])
+def test_segments_at_the_direct_sum_limit(cap_md, ls_cache, block, lst, full, ofull):
+    ev = _cut(make_event("pu200", 32, pu=12.0), 22000)
+    g = lst.Geometry(full)
+    g.set_tile_config({"ls_cache": ls_cache})
+    g.set_launch_config({"ls_fill": block})
+    o = oracle.run(ofull, ev)
+    n_md = len(o.stage(0)[0])
+    assert 3000 < n_md <= 8192 and len(o.stage(1)[0]) > n_md / 4
+    print(f"[gpu] {n_md} MDs, {len(o.stage(1)[0])} segments", flush=True)
+    _same(_with_capacity(lst, g, ev, md=cap_md), o)
