@@ -340,7 +340,8 @@ lst_status lst_get_stage_counts(lst_event ev, int64_t *counts, int64_t *required
 lst_status lst_get_module_constants(lst_geometry geom, float *out);
 
 /* Live timing of one kernel launch site (for roofline measurement).  The
- * chain is a fixed sequence of launch sites, each launched once per event:
+ * chain is a fixed sequence of launch sites, each passed once per event (a site
+ * whose work rides in another's launch takes no time of its own):
  * lst_kernel_site_count() of them, named by lst_kernel_site_name(i) (NULL
  * for an invalid index).  lst_set_timed_site(i) makes every later enqueue in
  * the process bracket site i with two HIP events on the event's stream (-1 =
@@ -391,8 +392,8 @@ lst_status lst_autotune(lst_geometry geom, int32_t B, const lst_event_desc *evs,
  *     (4, 8 or 16);
  *   ls_group: inner MDs per wavefront of the segment count pass (1..16),
  *     whose selections share full wavefronts; 0 (the default) chooses per
- *     launch from its events and MD capacity (4 for one PU200-size event, 16
- *     for launches of 16 or more).
+ *     launch from its events and MD capacity (8 for one PU200-size event, 16
+ *     for launches of four or more).
  * lst_tile_range gives tile i's bounds; lst_get/set_tile_config read and
  * write all lst_tile_count() values at once (LST_E_INVALID and nothing changed
  * if one is out of range).  lst_autotune_tiles times the whole chain over the

@@ -1,13 +1,15 @@
 // gfx950 kernels of the Line Segment Tracking chain (arXiv:2207.08207).
 //
 // Every stage follows one pattern: count objects per parent (module, MD, LS,
-// T3, seed), exclusive-scan the counts on the device, then fill each parent's
-// objects at its scanned offset in a fixed order.  No global atomics decide
-// an output position, so the object arrays are identical run to run; the
-// only atomics are histogram counts and the scatter into per-MD / per-hit
-// incidence lists, whose consumers are order-independent.  Object counts
-// stay on the device: later kernels read them and stride over them, so the
-// whole chain is enqueued without a host round trip.
+// T3, seed), then fill each parent's objects at the prefix of the counts, which
+// the fill sums for itself from the count's tile sums, in a fixed order.  No
+// atomic decides an output position, so the object arrays are identical run to
+// run; the atomics that remain are sums, histogram counts, list places (per-MD
+// and per-hit lists, bins) and maxima, whose consumers are order-independent.
+// Object counts stay on the device: later kernels read them and stride over
+// them, so the whole chain is enqueued without a host round trip.  Work that no
+// launch waits for (clears, seeds, bins) rides on further blocks of launches
+// that are there anyway: a launch costs 4 to 5 us on one event.
 #include <hip/hip_fp16.h>
 
 #include <cstring>
@@ -196,10 +198,11 @@ static inline int grid_waves(long n, int block = kBlock) {
 
 // Waves per launch that grid-stride kernels share among the launch's events: eight
 // per wave slot of the chip (256 CUs x 32); the searches whose work is a large
-// fraction of their capacity (segments, triplets, quintuplets and their
-// duplicate removal, MDs) take four times that, since waves with more work
-// left than the others hide each other's latency (measured: two per slot made
-// the segment count 1.24x slower than eight).
+// fraction of their capacity (the segment count, the quintuplets' duplicate
+// removal) take four times that, since waves with more work left than the others
+// hide each other's latency (measured: two per slot made the segment count 1.24x
+// slower than eight; four times the blocks for the triplets and quintuplets of
+// eight PU200 events cost 20 us).
 constexpr long kLaunchWaves = 8L * 256 * 32;
 
 static inline int grid_for(long n, int block = kBlock) {
@@ -1657,8 +1660,9 @@ __device__ __forceinline__ int round_parent(int start, int n, int c0, int *mark,
 
 // Fill pass of the segment search.  Blocks [0, n_copy) write the segments of
 // the inner MDs whose partners the count pass cached: a wave takes kLsCopyMds
-// consecutive MDs, finds their offsets (wave_prefix) and strides over their
-// segments flattened, in candidate order, with the angles ls_pass reports.
+// consecutive MDs, finds their offsets (block_prefix) and strides over their
+// segments flattened, each at its rank by partner (the count finds a module's
+// partners in azimuth order), with the angles ls_pass reports.
 // The other blocks search again for the MDs with more segments than the cache
 // holds (listed by the count pass), one wave per inner MD a.  Its candidates
 // -- the MDs of every module linked to a's module, edge by edge -- are
@@ -3735,8 +3739,9 @@ __global__ __launch_bounds__(kBlock) void k_tc_ext_write(const Ws *__restrict__ 
 }
 
 // ------------------------------------------------------------- chain
-// Launch sites of the chain, in order; each is launched once per event.  One
-// of them can be bracketed by HIP events (KernelTimer) to time it live.
+// Launch sites of the chain, in order; each runs once per event, those whose
+// work rides in another site's launch without one of their own.  One of them can
+// be bracketed by HIP events (KernelTimer) to time it live.
 const char *const kSiteNames[] = {
     "fill_counters", "hits_count", "hits_scan", "hits_scatter", "bucket_sort",
     "md_count", "md_scan", "md_fill", "ls_count", "ls_scan", "ls_fill",
@@ -3753,7 +3758,9 @@ static_assert(sizeof(kSiteNames) / sizeof(kSiteNames[0]) <= kMaxSites, "launch-s
 
 // Sites whose kernels take any block of 64, 128 or 256 threads (grid-stride
 // loops over threads or waves, LDS sized for the largest block): the launch
-// shape the autotuner may choose.
+// shape the autotuner may choose.  (md_count, md_fill, pt5_fill and tc_pls, whose
+// work is in other launches or a block of fixed size, take a shape that nothing
+// reads.)
 static const char *const kTunableSites[] = {"md_count", "md_fill",  "ls_count", "ls_fill",  "t3_count",
                                             "t3_fill",  "t5_count", "t5_fill",  "t5_dedup", "pt_count",
                                             "pt3_fill", "pt5_fill", "tc_pt3",   "tc_t5",    "tc_pls",
