@@ -1031,7 +1031,7 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
       gp(w.md_mod)[at] = m0 + m;
       gp(w.inc_cnt)[at] = 0;
       gstore(w.md_pos, at, hi);
-      gp(w.inc_off)[at] = bin | atomicAdd(&s_az[bin], 1) << 9;
+      gp(w.inc_off)[at] = (int)((unsigned)bin | (unsigned)atomicAdd(&s_az[bin], 1) << 9);
       put_stub(w, g, at, md_stub(hi, hj, mi));
     };
     if (n <= keep && nup <= 0xffff) {
@@ -1062,7 +1062,8 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
   __syncthreads();
   const int last = min(first + s_at[kBucketMods], w.cap_md);
   for (int i = first + t; i < last; i += kSortThreads) {
-    const int v = gp(w.inc_off)[i], p = s_az[v & 511] + (v >> 9);
+    const unsigned v = (unsigned)gp(w.inc_off)[i];  // bin and place in it (below 2^23, the largest capacity)
+    const int p = s_az[v & 511u] + (int)(v >> 9);
     if (p < w.cap_md) gp(w.md_az)[p] = i;
   }
   if (t < kBucketMods && s_at[t + 1] > s_at[t])
