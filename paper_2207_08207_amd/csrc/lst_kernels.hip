@@ -2302,8 +2302,8 @@ __global__ __launch_bounds__(kBlock) void k_t5(const Ws *__restrict__ wb, DevGeo
       __builtin_amdgcn_wave_barrier();
     };
     int nq = 0;
-    int e = 0;  // parent of this lane's pair (pairs advance monotonically; the walk keeps registers
-                // low enough for five waves per SIMD)
+    int e = 0;  // parent of this lane's pair (pairs advance monotonically; the walk takes fewer
+                // registers than round_parent)
     for (int c0 = 0; c0 < total; c0 += 64) {
       const int c = c0 + lane;
       bool keep = false;
