@@ -2117,11 +2117,11 @@ __device__ __forceinline__ bool phiz_may_pass(const float4 &P, const float4 &Q, 
   return fabsf(t1 - t2) <= (tol * kMargin + kEps) * 1.00001f + 1e-5f * (fabsf(t1) + fabsf(t2));
 }
 
-// The triplets that start at MD m: (first, end).
+// The triplets that start at MD m: (first, end), both at most n_t3: past the
+// capacity the offsets run on, and t5_off has n_t3 + 1 entries.
 __device__ __forceinline__ int2 md_triplets(const Ws &w, int m, int n_ls, int n_t3) {
   const int l0 = min(gp(w.ls_off)[m], n_ls), l1 = min(gp(w.ls_off)[m + 1], n_ls);
-  const int lo = gp(w.t3_off)[l0], hi = min(gp(w.t3_off)[l1], n_t3);
-  return make_int2(lo, hi > lo ? hi : lo);
+  return make_int2(min(gp(w.t3_off)[l0], n_t3), min(gp(w.t3_off)[l1], n_t3));
 }
 // The quintuplets among the triplets [r.x, r.y).
 __device__ __forceinline__ int2 triplets_t5(const Ws &w, int2 r, int n_t5) {

@@ -1,0 +1,50 @@
+"""Calls at the limits of what an event may be -- capacities far below what is found, modules of
+unusual shape, hits far out -- object by object against the oracle (needs an MI355X)."""
+import numpy as np
+import pytest
+
+import oracle
+from lstgen import make_event
+
+from dense import dense_event
+from parity import compare_event, compare_tc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lst():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU is required for the gpu-marked tests")
+    import paper_2207_08207_amd as lst
+    lst.load_library()
+    return lst
+
+
+# the triplet capacity far below what is found, the quintuplets' duplicates removed over lists
+# (capacity above 2,048) and over pairs
+@pytest.mark.parametrize("cap_t5", [4096, 2048])
+@pytest.mark.parametrize("config", ["dense", "pu200_seeded", "pu200"])
+def test_triplet_capacity_overflow_reports_and_recovers(config, cap_t5, lst, barrel, obarrel, full, ofull):
+    import torch
+    geom, og = (barrel, obarrel) if config == "dense" else (full, ofull)
+    ev = dense_event(geom) if config == "dense" else make_event(config, 51, pu=20.0)
+    o = oracle.run(og, ev)
+    n_t3 = len(o.stage(oracle.ST_T3)[0])
+    g = lst.Geometry(geom)
+    cap = lst.lst_default_capacity(ev.n_hits, ev.n_seeds)
+    cap.t3, cap.t5 = 50, cap_t5
+    assert n_t3 > 20 * cap.t3
+    dev = lst.upload_event(ev)
+    ws = lst.alloc_workspace(g, ev.n_hits, ev.n_seeds, cap)
+    print(f"[gpu] {config}: {n_t3} triplets, room for {cap.t3}", flush=True)
+    st, h = lst.lst_build_event(g.handle, dev, ws, cap, torch.cuda.current_stream().cuda_stream)
+    assert st == lst.LST_E_CAPACITY
+    counts, req = lst.lst_get_stage_counts(h)
+    assert counts[2] == 50 and req[2] == n_t3
+    lst.lst_release_event(h)
+    r = lst.run_event(g, dev, cap=cap)  # grows and reruns
+    compare_event(r, o)
+    compare_tc(r, o)
+    r.close()
