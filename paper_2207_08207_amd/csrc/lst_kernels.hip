@@ -1140,8 +1140,9 @@ __device__ __forceinline__ float4 ls_inner(const float4 &A, float2 st, ModInfo m
 // cos D <= r_A, that bound is not taken.  An endcap A's check bounds st.y r_A
 // sin D / |dz|, with dz in the module's range.  The margins are those of
 // ls_stub_may_pass, and a further 1e-4 of the bound and 1e-5 in sine; rounding
-// stays below 1e-6 of both.  All bins for wide discs and windows, and for A far
-// from the module in azimuth.
+// stays below 1e-6 of both.  All bins for wide discs and windows, for A far
+// from the module in azimuth, and where the disc has no direction (its centre on
+// the beam line, or so far out that its distance overflows: sd and cd are NaN).
 __device__ __forceinline__ bool ls_azimuth_bins(const float4 &A, float2 st, const float4 &in, ModInfo ma, const LsLink &l,
                                                 ModInfo mb, float d0, int *b0, int *b1) {
   *b0 = 0;
@@ -1149,7 +1150,7 @@ __device__ __forceinline__ bool ls_azimuth_bins(const float4 &A, float2 st, cons
   // ls_window_bound and ls_module_may_pass, with the direction's products instead of the disc's
   const float wmax = l.rs < 0.0f ? 3.0e38f : (((l.ub - in.z) * l.rs + in.w) * kMargin + kEps) * 1.01f + 1e-6f;
   const float sd = (l.nx * A.y - l.ny * A.x) * in.x, cd = (l.nx * A.x + l.ny * A.y) * in.x;
-  if (!(l.c * fabsf(sd) - l.rho <= (wmax * (l.c + l.rho)) * 1.001f + 1e-4f)) return false;
+  if (l.c * fabsf(sd) - l.rho > (wmax * (l.c + l.rho)) * 1.001f + 1e-4f) return false;  // (no direction: kept)
   if (!(l.bins > 0.0f && wmax < 0.69f && cd > 0.5f)) return true;
   const float sw = wmax * 1.0001f + 1e-6f, cw = 0.9999f * __builtin_amdgcn_sqrtf(1.0f - sw * sw);
   const float e2 = (ma.endcap() ? ma.hlong() : ma.hphi()) + (mb.endcap() ? mb.hlong() : mb.hphi());
