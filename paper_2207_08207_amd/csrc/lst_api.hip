@@ -494,7 +494,10 @@ static void *pinned_get(size_t n) {
   void *q = nullptr;
   // every GPU may write there, and the host sees it once the chain has ended
   constexpr unsigned kFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
-  if (hipHostMalloc(&q, k < kPoolClasses ? (size_t)1 << k : n, kFlags) != hipSuccess) return nullptr;
+  if (hipHostMalloc(&q, k < kPoolClasses ? (size_t)1 << k : n, kFlags) != hipSuccess) {
+    drop(hipGetLastError());  // the caller decides whether that is an error: the launches after it must not report it
+    return nullptr;
+  }
   return q;
 }
 static void pinned_put(void *q, size_t n) {

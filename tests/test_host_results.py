@@ -1,0 +1,34 @@
+"""What the library's host code does with the buffers that results come back through, on a HIP
+runtime that lives in host memory (fake_hip.cpp) and refuses what the test says."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2207_08207_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("fake") / "fake_hip")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-D__HIP_PLATFORM_AMD__", "-D__align__(x)=",
+                    "-DHIP_SYMBOL(x)=(&x)", f"-I{rocm}/include", f"-I{CSRC}", "-x", "c++",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", exe, "-lpthread"], check=True)
+    return exe
+
+
+def run(exe, *args):
+    r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
+
+
+def test_candidates_of_a_batch(fake):
+    run(fake, "plain")
+
+
+def test_a_refused_result_buffer_is_no_error(fake):
+    """The candidates' pinned buffer is optional: the event is enqueued without it, and its results
+    are copied from the device."""
+    run(fake, "refused")
