@@ -13,6 +13,9 @@ size_t g_pinned = 0, g_pinned_max = 0, g_pinned_calls = 0;
 std::map<void *, size_t> g_host;
 std::set<hipStream_t> g_streams;
 bool g_record_fails = false;
+bool g_capturing = false;     // the one graph: a chain over these descriptors
+lst::Ws *g_graph_ws = nullptr;
+int g_graph_B = 0;
 int g_bad_stream_calls = 0, g_d2h = 0;
 hipError_t ret(hipError_t e) {
   if (e != hipSuccess) g_last = e;
@@ -63,10 +66,13 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   if (s && !g_streams.count(s)) ++g_bad_stream_calls;
   return hipSuccess;
 }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
-hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { *g = nullptr; return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { g_capturing = true; return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { g_capturing = false; *g = nullptr; return hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t *, hipGraph_t, hipGraphNode_t *, char *, size_t) { return hipSuccess; }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) {
+  lst::enqueue_chain(lst::DevGeom{}, g_graph_ws, g_graph_B, lst::Ws{}, nullptr, nullptr, nullptr, nullptr);
+  return hipSuccess;
+}
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
@@ -79,6 +85,11 @@ void launch_module_windows(const int *, const float *, const float *, const floa
                            hipStream_t) {}
 void launch_tc_export(const Ws *, int, int, int *, int *, int *, int *, hipStream_t) {}
 void enqueue_chain(const DevGeom &, Ws *d, int B, const Ws &, hipStream_t, const KernelTimer *, const int *, const Ws *value) {
+  if (g_capturing) {
+    g_graph_ws = d;
+    g_graph_B = B;
+    return;
+  }
   for (int i = 0; i < B; ++i) {
     if (value) d[i] = value[i];
     const Ws &w = d[i];
@@ -179,6 +190,9 @@ int refused() {
   g_refuse = 4096;
   CHECK(lst_plan_run(p, 1, &c.ev, nullptr, &e) == LST_OK);
   CHECK(hipGetLastError() == hipSuccess);
+  CHECK(lst_event_wait(e) == LST_OK);
+  g_refuse = SIZE_MAX;
+  CHECK(candidates_ok(e, 0));
   lst_release_event(e);
   lst_plan_release(p);
   free(ws);
