@@ -44,7 +44,7 @@ constexpr size_t kAlign = 256;
 // host memory: up to 1 MiB an event (a PU200 event takes 0.55) and 4 MiB a batch,
 // for batches of up to 64 events.
 constexpr int tc_room(int B) { return B > 64 ? 0 : (B <= 4 ? 262144 : 1048576 / B); }
-constexpr size_t kStageMax = 16u << 20;  // largest result copied through pinned memory
+constexpr size_t kStageMax = 8u << 20;  // largest result copied through pinned memory: the pool's largest class
 constexpr int kTupleW[7] = {2, 4, 6, 10, 1, 7, 11};
 constexpr int kAttrW[7] = {0, 2, 4, 8, 5, 3, 3};
 constexpr int64_t kMaxCap = 8000000;  // bounded by the two-level device scan (4096 x 2048)
@@ -463,6 +463,7 @@ static size_t batch_bytes(int n_mod, int B, const int32_t *nh, const int32_t *ns
 // kPoolPinnedMax bytes of buffers are kept, the rest is freed.  Nothing is
 // released at process exit.
 constexpr int kPoolClasses = 24;               // size classes 2^0 .. 2^23 bytes
+static_assert(kStageMax == (size_t)1 << (kPoolClasses - 1), "results are staged in the pool's buffers only");
 constexpr size_t kPoolPinnedMax = 64u << 20;
 struct HostPool {
   std::mutex mu;
@@ -875,17 +876,19 @@ lst_status lst_get_stage_counts(lst_event e, int64_t *counts, int64_t *required)
 }  // extern "C"
 
 namespace {
-// A device range in a pinned buffer of the pool.
+// A device range in a pinned buffer of the pool (buf stays NULL when the range is
+// larger than the pool's buffers or none is to be had: the caller then copies
+// without one).
 struct Staged {
   void *buf = nullptr;
   size_t bytes = 0;
   ~Staged() { pinned_put(buf, bytes); }
 };
 lst_status stage_copy(const void *src, size_t bytes, Staged *s) {
+  if (bytes > kStageMax) return LST_OK;
   s->bytes = bytes;
   s->buf = pinned_get(bytes);
-  if (!s->buf) return fail(LST_E_NOMEM, "pinned buffer for the results");
-  HIP_TRY(hipMemcpy(s->buf, src, bytes, hipMemcpyDeviceToHost));
+  if (s->buf) HIP_TRY(hipMemcpy(s->buf, src, bytes, hipMemcpyDeviceToHost));
   return LST_OK;
 }
 }  // namespace
@@ -909,7 +912,7 @@ lst_status lst_get_track_candidates(lst_event e, int32_t *n_tc, int32_t *n_hits_
   const int *src = nullptr;
   if (e->ctr()[lst::C_EXT] != 1 && w.h_tc && ints <= (size_t)w.h_tc_cap) {
     src = w.h_tc;
-  } else if (ints * sizeof(int) <= kStageMax) {
+  } else {
     const lst_status cs = stage_copy(w.tc_out, ints * sizeof(int), &s);
     if (cs != LST_OK) return cs;
     src = static_cast<const int *>(s.buf);
@@ -945,7 +948,7 @@ lst_status lst_get_extended_track_candidates(lst_event e, int32_t *n_tc, int32_t
   int *src = nullptr;
   if (w.h_tc && ints <= (size_t)w.h_tc_cap) {
     src = w.h_tc;
-  } else if (ints * sizeof(int) <= kStageMax) {
+  } else {
     const lst_status cs = stage_copy(w.ext_out, ints * sizeof(int), &s);
     if (cs != LST_OK) return cs;
     src = static_cast<int *>(s.buf);

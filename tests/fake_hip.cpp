@@ -198,10 +198,55 @@ int refused() {
   free(ws);
   return 0;
 }
+
+// no pinned buffer while the results are read
+int unstaged() {
+  lst_geometry g = geometry();
+  g_candidates = 60000;
+  Call c(g, 1, 500, 20);  // (made-up candidates: more than its result buffer holds)
+  lst_capacity cap{};
+  lst_default_capacity(500, 20, &cap);
+  cap.t5 = 70000;
+  size_t bytes = 0;
+  CHECK(lst_workspace_bytes(g, 500, 20, &cap, &bytes) == LST_OK);
+  void *ws = aligned_alloc(256, (bytes + 255) / 256 * 256);
+  lst_event e = nullptr;
+  CHECK(lst_enqueue_event(g, &c.ev, &cap, ws, bytes, nullptr, &e) == LST_OK);
+  CHECK(lst_event_wait(e) == LST_OK);
+  g_refuse = 0;
+  CHECK(candidates_ok(e, 0));
+  CHECK(g_d2h > 0 && hipGetLastError() == hipSuccess);
+  lst_release_event(e);
+  free(ws);
+  return 0;
+}
+
+// a result that no size class of the pool holds goes straight to the caller
+int unpooled() {
+  lst_geometry g = geometry();
+  g_candidates = 400000;  // 9.6 MB
+  lst_capacity cap{};
+  lst_default_capacity(500, 20, &cap);
+  cap.t5 = 400000;
+  size_t bytes = 0;
+  CHECK(lst_workspace_bytes(g, 500, 20, &cap, &bytes) == LST_OK);
+  Call c(g, 1, 500, 20);
+  void *ws = aligned_alloc(256, (bytes + 255) / 256 * 256);
+  lst_event e = nullptr;
+  CHECK(lst_enqueue_event(g, &c.ev, &cap, ws, bytes, nullptr, &e) == LST_OK);
+  CHECK(lst_event_wait(e) == LST_OK);
+  const size_t before = g_pinned_calls;
+  CHECK(candidates_ok(e, 0));
+  CHECK(g_pinned_calls == before);
+  lst_release_event(e);
+  free(ws);
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
-  const std::map<std::string, int (*)()> scenarios = {{"plain", plain}, {"refused", refused}};
+  const std::map<std::string, int (*)()> scenarios = {{"plain", plain}, {"refused", refused}, {"unstaged", unstaged},
+                                                          {"unpooled", unpooled}};
   const int rc = scenarios.at(argv[1])();
   if (rc == 0) printf("ok\n");
   return rc;

@@ -32,3 +32,10 @@ def test_a_refused_result_buffer_is_no_error(fake):
     """The candidates' pinned buffer is optional: the event is enqueued without it, and its results
     are copied from the device."""
     run(fake, "refused")
+
+
+@pytest.mark.parametrize("scenario", ["unstaged", "unpooled"])
+def test_results_without_a_pinned_buffer(scenario, fake):
+    """The getters copy straight into the caller's arrays when no pinned buffer is to be had, and when
+    the result is larger than any that the pool keeps."""
+    run(fake, scenario)
