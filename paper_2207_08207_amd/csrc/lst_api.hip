@@ -564,9 +564,8 @@ static void release_batch_ref(lst_batch_s *b) {
   if (--b->refs > 0) return;
   if (b->owner && *b->owner == b) *b->owner = nullptr;
   if (b->server) server_release_batch(b->server, b);
-  // the chain writes to the pinned buffers until it ends
-  if (b->failed) drop(hipStreamSynchronize(b->stream));
-  else if (!b->synced && b->done) drop(hipEventSynchronize(b->done));
+  // the chain writes to the pinned buffers until it ends (enqueue_failed has waited for a failed one)
+  if (!b->failed && !b->synced && b->done) drop(hipEventSynchronize(b->done));
   event_put(b->device, b->tbeg, true);
   event_put(b->device, b->tend, true);
   event_put(b->device, b->done, false);
@@ -574,6 +573,14 @@ static void release_batch_ref(lst_batch_s *b) {
   pinned_put(b->h_ws, sizeof(lst::Ws) * b->B);
   pinned_put(b->h_tc, sizeof(int) * tc_room(b->B) * b->B);
   delete b;
+}
+
+// A HIP call failed at the batch's enqueue.  What was launched before it still
+// writes to the batch's buffers: waited for here, since the stream may be gone
+// when the batch is released.
+static void enqueue_failed(lst_batch_s *b) {
+  b->failed = true;
+  drop(hipStreamSynchronize(b->stream));
 }
 
 static lst_status map_status(int st) {
@@ -679,7 +686,7 @@ static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *
     he = hipGetLastError();
   }
   if (he == hipSuccess) he = hipEventRecord(b->done, stream);
-  if (he != hipSuccess) b->failed = true;
+  if (he != hipSuccess) enqueue_failed(b);
   *out = b;
   if (he != hipSuccess) return fail(LST_E_DEVICE, std::string("enqueue: ") + hipGetErrorString(he));
   return LST_OK;
@@ -1185,7 +1192,7 @@ lst_status lst_plan_run(lst_plan p, int32_t n_events, const lst_event_desc *evs,
   hipError_t he = hipMemcpyAsync(p->base, b->h_ws, sizeof(lst::Ws) * p->B, hipMemcpyHostToDevice, b->stream);
   if (he == hipSuccess) he = hipGraphLaunch(p->exec, b->stream);
   if (he == hipSuccess) he = hipEventRecord(b->done, b->stream);
-  if (he != hipSuccess) b->failed = true;
+  if (he != hipSuccess) enqueue_failed(b);
   for (int i = 0; i < n_events; ++i) {
     auto *e = new (std::nothrow) lst_event_s();
     if (!e) {

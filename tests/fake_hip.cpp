@@ -16,7 +16,7 @@ bool g_record_fails = false;
 bool g_capturing = false;     // the one graph: a chain over these descriptors
 lst::Ws *g_graph_ws = nullptr;
 int g_graph_B = 0;
-int g_bad_stream_calls = 0, g_d2h = 0;
+int g_bad_stream_calls = 0, g_waits = 0, g_d2h = 0;
 hipError_t ret(hipError_t e) {
   if (e != hipSuccess) g_last = e;
   return e;
@@ -64,6 +64,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_
 hipError_t hipStreamDestroy(hipStream_t s) { g_streams.erase(s); free((void *)s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) {
   if (s && !g_streams.count(s)) ++g_bad_stream_calls;
+  else ++g_waits;
   return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { g_capturing = true; return hipSuccess; }
@@ -242,11 +243,30 @@ int unpooled() {
   free(ws);
   return 0;
 }
+
+// An enqueue that fails after its launches: the chain may still write to the pinned buffers, so they
+// are given back after a wait, and the stream, the program's own, may be gone by then.
+int failed() {
+  lst_geometry g = geometry();
+  Call c(g, 1, 500, 20);
+  hipStream_t st;
+  CHECK(hipStreamCreateWithFlags(&st, 0) == hipSuccess);
+  lst_event e = nullptr;
+  g_record_fails = true;
+  CHECK(lst_enqueue_event(g, &c.ev, nullptr, c.ws, c.bytes, st, &e) == LST_E_DEVICE && e);
+  g_record_fails = false;
+  CHECK(lst_event_wait(e) == LST_E_DEVICE);
+  const int at_enqueue = g_waits;
+  CHECK(hipStreamDestroy(st) == hipSuccess);
+  lst_release_event(e);
+  CHECK(g_bad_stream_calls == 0 && at_enqueue == 1);
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, int (*)()> scenarios = {{"plain", plain}, {"refused", refused}, {"unstaged", unstaged},
-                                                          {"unpooled", unpooled}};
+                                                          {"unpooled", unpooled}, {"failed", failed}};
   const int rc = scenarios.at(argv[1])();
   if (rc == 0) printf("ok\n");
   return rc;

@@ -39,3 +39,7 @@ def test_results_without_a_pinned_buffer(scenario, fake):
     """The getters copy straight into the caller's arrays when no pinned buffer is to be had, and when
     the result is larger than any that the pool keeps."""
     run(fake, scenario)
+
+
+def test_a_failed_event_outlives_its_stream(fake):
+    run(fake, "failed")
