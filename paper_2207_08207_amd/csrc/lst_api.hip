@@ -40,10 +40,20 @@ lst_status fail(lst_status s, const std::string &msg) { return fail(s, msg.c_str
   } while (0)
 
 constexpr size_t kAlign = 256;
-// Candidates' ints per event of a batch of B that the chain writes straight to
-// host memory: up to 1 MiB an event (a PU200 event takes 0.55) and 4 MiB a batch,
-// for batches of up to 64 events.
-constexpr int tc_room(int B) { return B > 64 ? 0 : (B <= 4 ? 262144 : 1048576 / B); }
+// Host memory that the chain writes an event's candidates to, in ints: about one
+// and a half times what PU50 to PU250 events take (36k to 180k ints with 133k to
+// 665k hits; 2k for 1,400 hits of a tiny one), at most 1 MiB and what its
+// capacities can fill.  A batch takes up to 8 MiB (eight PU250 events), with
+// smaller shares down to 0.6 of that; batches past it, batches of more than 64
+// events, and all while kResultsMax bytes are held by events not yet released, have
+// their results copied when they are read.
+constexpr long kRoomMax = 262144, kBatchRoomMax = 2097152;
+constexpr size_t kResultsMax = 64u << 20;
+constexpr int kRoomEvents = 64;
+static long tc_room(const lst::Ws &w, int ext) {
+  const long n = w.n_hits, need = std::min(n, 65536L) + std::max(n - 65536L, 0L) / 4 + 4L * w.n_seeds + 4096;
+  return (std::min(std::min(need, kRoomMax), (ext ? 26L : 16L) * w.cap_tc + 1) + 63) / 64 * 64;
+}
 constexpr size_t kStageMax = 8u << 20;  // largest result copied through pinned memory: the pool's largest class
 constexpr int kTupleW[7] = {2, 4, 6, 10, 1, 7, 11};
 constexpr int kAttrW[7] = {0, 2, 4, 8, 5, 3, 3};
@@ -102,7 +112,8 @@ struct lst_batch_s {
   hipEvent_t done = nullptr;
   lst::Ws *h_ws = nullptr;  // pinned: the descriptors uploaded to the header
   int *h_ctr = nullptr;     // pinned: the B x C_COUNT counters, written by the chain
-  int *h_tc = nullptr;      // pinned, B x tc_room(B) ints (or NULL): candidates of the events whose lists fit
+  int *h_tc = nullptr;      // pinned (or NULL): the candidates of the events whose lists fit, tc_room ints each
+  size_t h_tc_bytes = 0;
   std::atomic<int> refs{0};
   std::atomic<bool> synced{false};
   lst_server_s *server = nullptr;  // a server batch returns its workspace block here when freed
@@ -468,7 +479,7 @@ constexpr size_t kPoolPinnedMax = 64u << 20;
 struct HostPool {
   std::mutex mu;
   std::vector<void *> pinned[kPoolClasses];
-  size_t pinned_bytes = 0;
+  size_t pinned_bytes = 0, results_bytes = 0;
   std::unordered_map<int, std::vector<hipEvent_t>> sync_events, timing_events;
 };
 static HostPool &host_pool() {
@@ -515,6 +526,29 @@ static void pinned_put(void *q, size_t n) {
   }
   drop(hipHostFree(q));
 }
+// Buffers that results are written to: pinned ones of the pool, at most
+// kResultsMax bytes of them out at a time (NULL: none to be had).
+static void *results_get(size_t n) {
+  HostPool &P = host_pool();
+  const size_t bytes = (size_t)1 << size_class(n);
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    if (P.results_bytes + bytes > kResultsMax) return nullptr;
+    P.results_bytes += bytes;
+  }
+  void *q = pinned_get(n);
+  if (!q) {
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.results_bytes -= bytes;
+  }
+  return q;
+}
+static void results_put(void *q, size_t n) {
+  pinned_put(q, n);
+  HostPool &P = host_pool();
+  std::lock_guard<std::mutex> lk(P.mu);
+  P.results_bytes -= (size_t)1 << size_class(n);
+}
 static hipEvent_t event_get(int device, bool timing) {
   {
     HostPool &P = host_pool();
@@ -546,18 +580,32 @@ static bool batch_host_resources(lst_batch_s *b, int B) {
   if (hipGetDevice(&b->device) != hipSuccess) return false;
   b->h_ctr = static_cast<int *>(pinned_get(sizeof(int) * lst::C_COUNT * B));
   b->h_ws = static_cast<lst::Ws *>(pinned_get(sizeof(lst::Ws) * B));
-  if (tc_room(B) > 0) b->h_tc = static_cast<int *>(pinned_get(sizeof(int) * tc_room(B) * B));  // (optional)
   b->done = event_get(b->device, false);
   return b->h_ctr && b->h_ws && b->done;
 }
 
 static void server_release_batch(lst_server_s *s, lst_batch_s *b);
 
-// Where the chain of event i of the batch writes its results on the host.
-static void set_host_results(const lst_batch_s *b, int i, lst::Ws *w) {
-  w->h_ctr = b->h_ctr + (size_t)i * lst::C_COUNT;
-  w->h_tc = b->h_tc ? b->h_tc + (size_t)i * tc_room(b->B) : nullptr;
-  w->h_tc_cap = b->h_tc ? tc_room(b->B) : 0;
+// Where the chain of each of the batch's events (h_ws, laid out) writes its
+// results on the host.
+static void batch_results(lst_batch_s *b) {
+  const int ext = b->geom->g.ext;
+  long sum = 0;
+  for (int i = 0; i < b->B; ++i) sum += tc_room(b->h_ws[i], ext);
+  const double share = sum > kBatchRoomMax ? (double)kBatchRoomMax / (double)sum : 1.0;
+  if (b->B <= kRoomEvents && share >= 0.6) {
+    b->h_tc_bytes = sizeof(int) * (size_t)std::min(sum, kBatchRoomMax);
+    b->h_tc = static_cast<int *>(results_get(b->h_tc_bytes));
+  }
+  long at = 0;
+  for (int i = 0; i < b->B; ++i) {
+    lst::Ws &w = b->h_ws[i];
+    const long room = b->h_tc ? (long)(share * (double)tc_room(w, ext)) / 64 * 64 : 0;  // whole 256-byte lines
+    w.h_ctr = b->h_ctr + (size_t)i * lst::C_COUNT;
+    w.h_tc = room > 0 ? b->h_tc + at : nullptr;
+    w.h_tc_cap = (int)room;
+    at += room;
+  }
 }
 
 static void release_batch_ref(lst_batch_s *b) {
@@ -571,7 +619,7 @@ static void release_batch_ref(lst_batch_s *b) {
   event_put(b->device, b->done, false);
   pinned_put(b->h_ctr, sizeof(int) * lst::C_COUNT * b->B);
   pinned_put(b->h_ws, sizeof(lst::Ws) * b->B);
-  pinned_put(b->h_tc, sizeof(int) * tc_room(b->B) * b->B);
+  if (b->h_tc) results_put(b->h_tc, b->h_tc_bytes);
   delete b;
 }
 
@@ -660,7 +708,6 @@ static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *
                                  d_ctr + (size_t)i * lst::C_COUNT);
     w.x = ev.x; w.y = ev.y; w.z = ev.z; w.module = ev.module; w.sensor = ev.sensor;
     w.px = ev.px; w.py = ev.py; w.pz = ev.pz; w.q = ev.q; w.hits4 = ev.hits4;
-    set_host_results(b, i, &w);
     bound.n_hits = std::max(bound.n_hits, w.n_hits);
     bound.n_seeds = std::max(bound.n_seeds, w.n_seeds);
     bound.cap_md = std::max(bound.cap_md, w.cap_md);
@@ -671,6 +718,7 @@ static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *
     bound.cap_pt5 = std::max(bound.cap_pt5, w.cap_pt5);
     bound.cap_tc = std::max(bound.cap_tc, w.cap_tc);
   }
+  batch_results(b);
   lst::KernelTimer kt{-1, nullptr, nullptr};
   const int site = timed_site >= -1 ? timed_site : g_timed_site.load();
   if (site >= 0 && (b->tbeg = event_get(b->device, true)) && (b->tend = event_get(b->device, true))) {
@@ -1185,10 +1233,8 @@ lst_status lst_plan_run(lst_plan p, int32_t n_events, const lst_event_desc *evs,
     release_batch_ref(b);
     return fail(LST_E_DEVICE, "lst_plan_run: pinned buffers or event creation failed");
   }
-  for (int i = 0; i < p->B; ++i) {
-    plan_slot(p, i, i < n_events ? &evs[i] : nullptr, &b->h_ws[i]);
-    set_host_results(b, i, &b->h_ws[i]);
-  }
+  for (int i = 0; i < p->B; ++i) plan_slot(p, i, i < n_events ? &evs[i] : nullptr, &b->h_ws[i]);
+  batch_results(b);
   hipError_t he = hipMemcpyAsync(p->base, b->h_ws, sizeof(lst::Ws) * p->B, hipMemcpyHostToDevice, b->stream);
   if (he == hipSuccess) he = hipGraphLaunch(p->exec, b->stream);
   if (he == hipSuccess) he = hipEventRecord(b->done, b->stream);

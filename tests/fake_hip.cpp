@@ -262,11 +262,51 @@ int failed() {
   CHECK(g_bad_stream_calls == 0 && at_enqueue == 1);
   return 0;
 }
+
+// Host memory that held events take: little for small ones, bounded for many, and enough for the
+// batches that are meant to fit.
+int room() {
+  lst_geometry g = geometry();
+  {
+    Call c(g, 1, 1400, 0);
+    lst_event e = nullptr;
+    CHECK(lst_enqueue_event(g, &c.ev, nullptr, c.ws, c.bytes, nullptr, &e) == LST_OK);
+    CHECK(g_pinned <= 65536 && e->ws().h_tc && e->ws().h_tc_cap >= 4000);
+    lst_release_event(e);
+  }
+  for (int n : {1400, 530000}) {  // a thousand events held at once
+    Call c(g, 1, n, 0);
+    std::vector<lst_event> held(1000);
+    for (auto &e : held) CHECK(lst_enqueue_event(g, &c.ev, nullptr, c.ws, c.bytes, nullptr, &e) == LST_OK);
+    CHECK(g_pinned <= (n == 1400 ? 40u << 20 : 136u << 20));  // (64 MiB of freed ones may be kept)
+    CHECK(n != 530000 || (held[0]->ws().h_tc && !held[999]->ws().h_tc));
+    CHECK(lst_event_wait(held[0]) == LST_OK && candidates_ok(held[0], 0));
+    CHECK(lst_event_wait(held[999]) == LST_OK && candidates_ok(held[999], 0));
+    for (auto e : held) lst_release_event(e);
+  }
+  // ints that the candidates of PU200 events take: 144k
+  for (int B : {1, 8, 9, 32}) {
+    Call c(g, B, 530000, 8900);
+    std::vector<lst_event_desc> evs(B, c.ev);
+    std::vector<lst_event> e(B);
+    CHECK(lst_enqueue_batch(g, B, evs.data(), nullptr, c.ws, c.bytes, nullptr, e.data()) == LST_OK);
+    for (int i = 0; i < B; ++i) {
+      const lst::Ws &w = e[i]->ws();
+      CHECK(B == 32 ? !w.h_tc : w.h_tc && w.h_tc_cap >= 144000);
+      CHECK(i == 0 || !w.h_tc || w.h_tc >= e[i - 1]->ws().h_tc + e[i - 1]->ws().h_tc_cap);
+      CHECK(!w.h_tc || (size_t)(w.h_tc + w.h_tc_cap - e[i]->batch->h_tc) * sizeof(int) <= e[i]->batch->h_tc_bytes);
+      CHECK(lst_event_wait(e[i]) == LST_OK && candidates_ok(e[i], i));
+    }
+    for (auto x : e) lst_release_event(x);
+  }
+  CHECK(host_pool().results_bytes == 0);
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, int (*)()> scenarios = {{"plain", plain}, {"refused", refused}, {"unstaged", unstaged},
-                                                          {"unpooled", unpooled}, {"failed", failed}};
+                                                          {"unpooled", unpooled}, {"failed", failed}, {"room", room}};
   const int rc = scenarios.at(argv[1])();
   if (rc == 0) printf("ok\n");
   return rc;

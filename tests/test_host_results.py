@@ -43,3 +43,8 @@ def test_results_without_a_pinned_buffer(scenario, fake):
 
 def test_a_failed_event_outlives_its_stream(fake):
     run(fake, "failed")
+
+
+def test_host_memory_of_held_events(fake):
+    """Sized by the event, at most 64 MiB for all that are held, and room for eight PU200 events."""
+    run(fake, "room")
