@@ -2797,16 +2797,27 @@ __device__ __forceinline__ void pt_copy(const Ws &w, const DevGeom &g, int q, in
 // The seed search over the objects of the bins a seed's trajectory can reach.
 // The count: one wave per seed, both kinds on one mask; it counts the passing
 // objects and keeps up to pt3_cache / pt5_cache of them with their attributes.
-// A seed with more (up to 400 on dense events) writes the others' indices to one
-// of n_spill lists in global memory.
+// A seed with more of a kind (seven of eight PU200 events') is a task of the fill,
+// listed where its place among them says (pt_task); the first n_spill places have a
+// list in global memory for the others' indices.
 // The fill copies the kept ones (blocks [0, nc) the triplets, [nc, 2 nc) the
-// quintuplets); the first wave of each other block takes the seeds of its group
-// of 64 with more: their objects, from cache and list, or from a second search if
-// no list was left, are ranked by object index in LDS and written at the seed's
-// offset; a seed with more of them than the LDS list holds (tile pass_list <=
-// kPassList) takes an ordered scan over all objects instead.  (Searching again for
-// the seven such seeds of eight PU200 events made the fill 193 us.)  More than
-// max_slices marked bins are searched bin by bin.
+// quintuplets); the first waves of the other blocks share the tasks: a task's
+// objects, from cache and list, or from a second search without a list, are ranked
+// by object index in LDS and written at the seed's offset; with more of them than
+// the LDS list holds (tile pass_list <= kPassList) an ordered scan over all objects
+// is taken instead.  (Searching again for the seven made the fill 193 us.  With one
+// wave to each 64 consecutive seeds' tasks the fill of a PU200 event with nothing
+// cached took 1.53 ms, now 0.22, and with 16 triplets cached 117 us, now 41; that
+// of a PU400 event 8.7, now 8.1, which is one seed's scan.)  More than max_slices marked bins are searched bin by bin.
+// Tasks are counted in 16 lines by seed, since additions to one run one after
+// another (a PU200 event's count took 197 us with 17,800 tasks on one counter, 72
+// without); few seeds have one, so that the places stay below 4 n_seeds.
+__device__ __forceinline__ int pt_shards(const Ws &w) { return w.n_seeds >= 256 ? kTaskShards : 1; }
+__device__ __forceinline__ int pt_task(const Ws &w, int s) {  // called by one lane
+  const int n = pt_shards(w), q = s & (n - 1);
+  return atomicAdd(w.ts_task + q * kSumStride, 1) * n + q;
+}
+
 template <bool FILL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_pt_binned(const Ws *__restrict__ wb,
                                                                                               DevGeom g, int nc) {
@@ -2857,7 +2868,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
   };
   // entries of one kind (KO = 3: triplets, 5: quintuplets) that passed so far
   int n_pass3 = 0, n_pass5 = 0;
-  // the list that takes the seed's entries past the cache (-1: none yet, -2: none left)
+  // the seed's tasks (-1: none), whose lists take its entries past the cache
   int spill3 = -1, spill5 = -1;
   const int n_spill = w.n_spill;
   // the full selection on one object per active lane; passing ones are counted in ballot
@@ -2879,9 +2890,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     int &spill = KO == 3 ? spill3 : spill5;
     if (!FILL && n_pass + __popcll(m) > keep && spill == -1) {
       int v = 0;
-      if (lane == 0) v = atomicAdd(w.ctr + C_NSPILL, 1);
-      v = __builtin_amdgcn_readfirstlane(v);
-      spill = v < n_spill ? v : -2;
+      if (lane == 0) v = pt_task(w, s);
+      spill = __builtin_amdgcn_readfirstlane(v);
     }
     if (pass) {
       const int r = n_pass + lanes_below(m);
@@ -2891,7 +2901,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
         constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
         gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + r] = t;
         gstore(KO == 3 ? w.pt3_cattr : w.pt5_cattr, (long)s * kCache + r, attr);
-      } else if (spill >= 0 && r < kPassList) {
+      } else if (spill < n_spill && r < kPassList) {
         gp(w.pt_spill)[(long)spill * kPassList + r] = t;
       }
     }
@@ -3048,79 +3058,79 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
       gp(w.pt5_cnt)[s] = n_pass5;
       if (n_pass3 > 0) atomicAdd(w.ts_p3 + (s >> w.sh_pt) * kSumStride, n_pass3);
       if (n_pass5 > 0) atomicAdd(w.ts_p5 + (s >> w.sh_pt) * kSumStride, n_pass5);
-      if (n_pass3 > g.tiles.pt3_cache) gp(w.ph_next)[4L * s] = spill3;
-      if (n_pass5 > g.tiles.pt5_cache) gp(w.ph_next)[4L * s + 1] = spill5;
+      if (spill3 >= 0) gp(w.pt_tasks)[spill3] = 2 * s;
+      if (spill5 >= 0) gp(w.pt_tasks)[spill5] = 2 * s + 1;
     }
     return;
   }
-  auto again = [&](auto kind) __attribute__((always_inline)) {
+  auto again = [&](auto kind, int spill) __attribute__((always_inline)) {
     constexpr int KO = decltype(kind)::value;
     const int keep = KO == 3 ? g.tiles.pt3_cache : g.tiles.pt5_cache;
     const int *cnts = KO == 3 ? w.pt3_cnt : w.pt5_cnt;
-    const int s0 = ((int)blockIdx.x - 2 * nc) * 64;
-    const int cnt = s0 + lane < w.n_seeds ? gp(cnts)[s0 + lane] : 0;
-    for (unsigned long long m = __ballot(cnt > keep); m; m &= m - 1) {
-      const int q = __builtin_ctzll(m), expect = __builtin_amdgcn_readlane(cnt, q);
-      s = s0 + q;
-      sd = load_seed(w, s);
-      int base = wave_prefix(KO == 3 ? w.ts_p3 : w.ts_p5, w.sh_pt, cnts, 0, s);
-      if (expect > pass_list) {
-        const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
-        const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
-        for (int t0 = 0; t0 < n_obj; t0 += 64) {
-          const int t = t0 + lane;
-          bool pass = false;
-          float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
-            const float2 f = first[t];
-            if (seed_box(sd, f.x, f.y)) {
-              float4 P[KO];
-              ModInfo M[KO];
-              float kT, dkT;
-              load_object<KO>(w, g, t, P, M, &kT, &dkT);
-              pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-            }
+    const int expect = uload(cnts + s);
+    sd = load_seed(w, s);
+    int base = wave_prefix(KO == 3 ? w.ts_p3 : w.ts_p5, w.sh_pt, cnts, 0, s);
+    if (expect > pass_list) {
+      const float2 *first = KO == 3 ? w.t3_first : w.t5_first;
+      const int n_obj = KO == 3 ? w.ctr[C_NT3] : w.ctr[C_NT5];
+      for (int t0 = 0; t0 < n_obj; t0 += 64) {
+        const int t = t0 + lane;
+        bool pass = false;
+        float4 attr = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (t < n_obj && (KO == 3 || gp(w.t5_keep)[t])) {
+          const float2 f = first[t];
+          if (seed_box(sd, f.x, f.y)) {
+            float4 P[KO];
+            ModInfo M[KO];
+            float kT, dkT;
+            load_object<KO>(w, g, t, P, M, &kT, &dkT);
+            pass = pt_pass<KO>(sd, P, M, kT, dkT, &attr);
           }
-          const unsigned long long mp = __ballot(pass);
-          if (pass) put_pt<KO>(w, base + lanes_below(mp), s, t, attr);
-          base += __popcll(mp);
         }
-        continue;
+        const unsigned long long mp = __ballot(pass);
+        if (pass) put_pt<KO>(w, base + lanes_below(mp), s, t, attr);
+        base += __popcll(mp);
       }
-      const int spill = uload(w.ph_next + 4L * s + (KO == 5 ? 1 : 0));
-      int n = expect;
-      if (spill >= 0) {
-        constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
-        for (int i = lane; i < n; i += 64)
-          s_list[i] = i < keep ? gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + i]
-                               : gp(w.pt_spill)[(long)spill * kPassList + i];
-      } else {
-        n_pass3 = n_pass5 = 0;
-        mark_bins();
-        search(std::integral_constant<bool, KO == 3>{}, std::integral_constant<bool, KO == 5>{});
-        n = KO == 3 ? n_pass3 : n_pass5;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      for (int i = lane; i < n; i += 64) {
-        const int t = s_list[i];
-        int rank = 0;
-#pragma unroll 8
-        for (int r = 0; r < n; ++r) rank += s_list[r] < t ? 1 : 0;
-        float4 attr;
-        float4 P[KO];
-        ModInfo M[KO];
-        float kT, dkT;
-        load_object<KO>(w, g, t, P, M, &kT, &dkT);
-        pt_pass<KO>(sd, P, M, kT, dkT, &attr);
-        put_pt<KO>(w, base + rank, s, t, attr);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      return;
     }
+    int n = expect;
+    if (spill < n_spill) {
+      constexpr int kCache = KO == 3 ? kPt3Cache : kPt5Cache;
+      for (int i = lane; i < n; i += 64)
+        s_list[i] = i < keep ? gp(KO == 3 ? w.pt3_cache : w.pt5_cache)[(long)s * kCache + i]
+                             : gp(w.pt_spill)[(long)spill * kPassList + i];
+    } else {
+      n_pass3 = n_pass5 = 0;
+      mark_bins();
+      search(std::integral_constant<bool, KO == 3>{}, std::integral_constant<bool, KO == 5>{});
+      n = KO == 3 ? n_pass3 : n_pass5;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < n; i += 64) {
+      const int t = s_list[i];
+      int rank = 0;
+#pragma unroll 8
+      for (int r = 0; r < n; ++r) rank += s_list[r] < t ? 1 : 0;
+      float4 attr;
+      float4 P[KO];
+      ModInfo M[KO];
+      float kT, dkT;
+      load_object<KO>(w, g, t, P, M, &kT, &dkT);
+      pt_pass<KO>(sd, P, M, kT, dkT, &attr);
+      put_pt<KO>(w, base + rank, s, t, attr);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
-  again(std::integral_constant<int, 3>{});
-  again(std::integral_constant<int, 5>{});
+  const int shards = pt_shards(w), b = (int)blockIdx.x - 2 * nc, q = b & (shards - 1);
+  const int n_task = uload(w.ts_task + q * kSumStride), step = ((int)gridDim.x - 2 * nc) / shards;
+  for (int i = b / shards; i < n_task; i += step) {
+    const int spill = i * shards + q, task = uload(w.pt_tasks + spill);
+    s = task >> 1;
+    if (task & 1) again(std::integral_constant<int, 5>{}, spill);
+    else again(std::integral_constant<int, 3>{}, spill);
+  }
 }
 
 template <int K>
@@ -3932,7 +3942,9 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
   run([&] {});  // pt3_scan
   run([&] {
     if (!seeds) return;
-    const unsigned nc = gridwt((S + kPtSeeds - 1) / kPtSeeds).x, n_again = (unsigned)((S + 63) / 64);
+    // the tasks' blocks: whole rounds of the shards, about the chip's for the launch
+    const unsigned nc = gridwt((S + kPtSeeds - 1) / kPtSeeds).x;
+    const unsigned n_again = (unsigned)((std::min(2 * S, std::max(2048L / B, 64L)) + kTaskShards - 1) / kTaskShards) * kTaskShards;
     k_pt_binned<true><<<dim3(2 * nc + n_again, B), tb, 0, st>>>(wb, g, (int)nc);
   });
   run([&] {});  // pt5_scan

@@ -13,7 +13,6 @@ enum Ctr : int {
   C_RMD = 9, C_RLS, C_RT3, C_RT5, C_RPT3, C_RPT5,                      // required counts
   C_NT5KEEP = 15, C_NTC0 = 16, C_NTC1, C_NTC2, C_NTC3,                 // survivors, TCs per type
   C_NINC = 21, C_NBIN = 25,      // scratch totals
-  C_NSPILL = 26,                 // seeds with more passing objects than the seed search caches
   C_NLSOVF = 27,                 // MDs with more segments than the count pass caches
   C_NEXTHITS = 28,               // hits of the extended track-candidate collection
   C_EXT = 29,                    // 1 once the track extensions of the event are written
@@ -82,6 +81,7 @@ enum FillId : int { FL_CTR, FL_TS, FL_SEED_CNT, FL_SEED_TC, FL_PLS_NEAR, FL_BIN_
 // line the segment count of one event went from 0.119 to 0.165 ms).
 constexpr int kMaxSumTiles = 512;
 constexpr int kSumStride = 32;
+constexpr int kTaskShards = 16;  // lines that the seed search's tasks are counted in
 __host__ __device__ inline int tile_shift(long cap) {
   int s = 8;
   while ((cap >> s) >= kMaxSumTiles) ++s;
@@ -192,7 +192,9 @@ struct Ws {
   int *ph_owner, *ph_head, *ph_next;
   // pixel triplets / quintuplets
   int *pt3_cnt, *pt3_off, *pt5_cnt, *pt5_off;
-  int *pt_spill;    // n_spill lists of kPassList objects, for seeds with more than those
+  // seeds with more than those, per kind: the tasks of the fill (2 seed + kind), and n_spill
+  // lists of kPassList objects for the first of them
+  int *pt_tasks, *pt_spill;
   int n_spill;
   int *pt3_cache, *pt5_cache;  // per seed: up to kPt3Cache / kPt5Cache passing objects found by the count pass
   float4 *pt3_cattr, *pt5_cattr;  // and their attributes
@@ -236,6 +238,7 @@ struct Ws {
   // the count passes' sums per tile of parents (tile_shift) and, for triplets and
   // quintuplets, per wave (parent_shift)
   int *ts_ls, *ts_t3, *ts_t5, *ts_p3, *ts_p5;
+  int *ts_task;  // kTaskShards counts of tasks, likewise a line each
   int sh_ls, sh_t3, sh_t5, sh_pt;
   int *ws_t3, *ws_t5;
   // scan scratch and the job tables of the generic scan / clear kernels

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
-from lstgen import make_event
+from lstgen import make_event, make_single_track_event
 
 from dense import dense_event
 from parity import compare_event, compare_tc
@@ -45,6 +45,31 @@ def test_triplet_capacity_overflow_reports_and_recovers(config, cap_t5, lst, bar
     assert counts[2] == 50 and req[2] == n_t3
     lst.lst_release_event(h)
     r = lst.run_event(g, dev, cap=cap)  # grows and reruns
+    compare_event(r, o)
+    compare_tc(r, o)
+    r.close()
+
+
+# every seed past the caches: the fill's tasks counted in one line (fewer than 256 seeds) and in sixteen,
+# with lists for all and for a few of them
+@pytest.mark.parametrize("lists", [1000, 5])
+@pytest.mark.parametrize("n", [1, 17, 255, 256, 257])
+def test_seed_tasks_at_the_shard_limit(n, lists, lst, barrel, obarrel):
+    import torch
+    rng = np.random.default_rng(400 + n)
+    ev = make_single_track_event(barrel, np.exp(rng.uniform(np.log(0.9), np.log(20.0), n)), rng.uniform(-0.5, 0.5, n),
+                                 rng.uniform(0, 2 * np.pi, n), z0=rng.normal(0, 5, n),
+                                 q=np.where(rng.uniform(size=n) < 0.5, -1, 1), seeded=True, seed=n)
+    o = oracle.run(obarrel, ev)
+    g = lst.Geometry(barrel)
+    g.set_tile_config({"pt3_cache": 0, "pt5_cache": 0})
+    cap = lst.lst_default_capacity(ev.n_hits, ev.n_seeds)
+    cap.t5 = max(len(o.stage(oracle.ST_T5)[0]) + 1, (lists * 1024 + 9) // 10 if n > 200 or lists > 5 else 0)
+    ws = lst.alloc_workspace(g, ev.n_hits, ev.n_seeds, cap)
+    print(f"[gpu] {ev.n_seeds} seeds, {10 * cap.t5 // 1024} lists", flush=True)
+    st, h = lst.lst_build_event(g.handle, lst.upload_event(ev), ws, cap, torch.cuda.current_stream().cuda_stream)
+    assert st == lst.LST_OK
+    r = lst.EventResult(h, ws, st)
     compare_event(r, o)
     compare_tc(r, o)
     r.close()
