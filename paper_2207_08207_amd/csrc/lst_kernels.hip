@@ -741,18 +741,34 @@ __device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((
 // |u_j - u_i| = |sin(azimuth change)| / (cos cos) <= 5/4 W, up to rounding (each
 // u within 4e-7, W's test within 1e-6); bins are a little wider than twice that
 // bound (so a window touches two, whatever u inv rounds to) and wrap round (the
-// exact test decides, so sharing a bin only costs a test).  A module
-// with a hit outside that range (or nearly on the beam line, where products may
-// underflow), or a bucket with more hits than the lists hold, has every pair
-// tested.  A lower hit keeps up to kMdKeep partners, in order, for the fill.
+// exact test decides, so sharing a bin only costs a test).
+//
+// A module with a hit outside that range or a wide window (if one with more than
+// kMdWalk upper hits is among the bucket's), and every module of a bucket with more
+// hits than the lists hold, is listed again in a second pass, by direction
+// (md_bins), with the lists of such a bucket in the records of its upper hits, which
+// are read no more.  Modules with few hits, with one nearly on the beam line or far
+// out (where products may underflow or overflow) and with windows of more than about
+// a radian have every pair tested.
+//
+// A lower hit keeps up to kMdKeep partners, in order, for the fill; with more, in a
+// module of more than kMdWalk upper hits, all of them go to a list in global memory
+// (the segments' cache, not yet in use).
 // (Testing all pairs, 8.8M on a PU200 event for 138k MDs, took 25 + 27 us to
 // count and 24 + 14 us to fill for one event, 318 us for eight; the kernel is
 // bound by the chain of its steps in the densest bucket, hence few passes over
-// the hits.)
+// the hits.  Without the second listing and the lists of partners, 6 x 1,000 and 24 x
+// 1,000 hits a sensor on modules of a whole and of a quarter of the azimuth took
+// 2.21 and 6.47 ms here and 0.06 and 3.06 in the fill, now 0.24 and 0.80, 0.06 and
+// 0.21; a PU400 event, whose densest bucket has 8,500 hits, 0.60 ms, now 0.12.)
+// At most 80 scalar registers (72 and the reserved ones): with 80 and those a SIMD
+// held seven waves, so a CU three of these blocks instead of four, and eight PU50
+// events took 78 us instead of 71.
 constexpr int kSortWaves = 8, kSortThreads = 64 * kSortWaves;
 constexpr int kBucketMods = kFineKeys / 2;
 constexpr int kMdBins = 64;    // per module
 constexpr int kMdList = 8192;  // hits of a bucket that the lists can hold
+constexpr int kMdWalk = 64;    // upper hits that the fill tests again one after another
 static_assert((kMdBins & (kMdBins - 1)) == 0, "bins wrap round by a mask");
 
 // The module of the bucket's q-th lower hit (modules' lower hits before: lpre[0..kBucketMods]).
@@ -763,6 +779,53 @@ __device__ __forceinline__ int lower_module(const int *lpre, int q) {
     if (lpre[m + s] <= q) m += s;
   return m;
 }
+// Direction of (x, y) from the beam line: non-decreasing in the azimuth from -pi to
+// pi, from -2 to 2, with a slope of at most 1 (a half to 1).
+__device__ __forceinline__ float direction(float x, float y) {
+  const float t = y * frcp(fabsf(x) + fabsf(y));
+  return x >= 0.0f ? t : (y >= 0.0f ? 2.0f - t : -2.0f - t);
+}
+// Bins of the whole circle for pairs with |sin of the azimuth change| <= W and a
+// positive cosine (up to rounding, 3e-7): (d, bins per unit of direction, bins) with d
+// at least the change of direction and a bin at least 2.1 d wide, so that what a
+// lower hit of direction p pairs with is in the bins of p - d and p + d.  No bins
+// (0) for windows that would leave fewer than four.  Up to 65,536 bins, d's 4e-6
+// is more than the rounding of their edges.
+__device__ __forceinline__ float3 md_bins(float W) {
+  const float c2 = 1.0f - W * W;
+  if (!(W >= 0.0f && c2 > 0.1f)) return make_float3(0.f, 0.f, 0.f);
+  const float d = W * frsq(c2) * 1.0001f + 4e-6f;
+  const float n = fminf(floorf((4.0f / 2.1f) / d), 65536.0f);
+  return n >= 4.0f ? make_float3(d, 0.25f * n, n) : make_float3(0.f, 0.f, 0.f);
+}
+__device__ __forceinline__ int md_bin(float p, const float3 &b) {
+  const float v = floorf((p + 2.0f) * b.y);
+  return (int)(v < 0.0f ? v + b.z : (v >= b.z ? v - b.z : v));
+}
+// The first kMdKeep partners of a lower hit, ascending, and how many there are.
+struct MdKept {
+  unsigned kept[kMdKeep];
+  int n = 0;
+  __device__ __forceinline__ MdKept() {
+#pragma unroll
+    for (int i = 0; i < kMdKeep; ++i) kept[i] = 0xffffu;
+  }
+  __device__ __forceinline__ void take(int j) {
+    ++n;
+    unsigned v = (unsigned)min(j, 0xffff);
+#pragma unroll
+    for (int i = 0; i < kMdKeep; ++i) {
+      const unsigned lo = min(kept[i], v);
+      v = max(kept[i], v);
+      kept[i] = lo;
+    }
+  }
+  __device__ __forceinline__ int4 packed() const {
+    return make_int4((int)(kept[0] | kept[1] << 16), (int)(kept[2] | kept[3] << 16), (int)(kept[4] | kept[5] << 16), n);
+  }
+};
+// Whether a lower hit's partners, n of nup upper hits, go to a list.
+__device__ __forceinline__ bool md_listed(int n, int nup) { return n > kMdKeep && nup > kMdWalk && nup <= 0xffff; }
 // lpre from key0, by the first wave.
 __device__ __forceinline__ void lower_prefix(const int *key0, int *lpre) {
   const int lane = lane_id();
@@ -771,12 +834,15 @@ __device__ __forceinline__ void lower_prefix(const int *key0, int *lpre) {
   if (lane <= kBucketMods) lpre[lane] = x - n;
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict__ wb, DevGeom g) {
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) void k_bucket_md(const Ws *__restrict__ wb, DevGeom g) {
   __shared__ int s_cnt[kSortWaves][kFineKeys];
   __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1];
   __shared__ int s_head[kBucketMods * kMdBins];  // per (module, bin): its first upper (position in the bucket), -1: none
   __shared__ unsigned short s_next[kMdList];     // per hit of the bucket: the next upper of its bin
-  __shared__ int s_ref[kBucketMods], s_odd[kBucketMods], s_nmd[kBucketMods];
+  __shared__ int s_ref[kBucketMods], s_nmd[kBucketMods];
+  // how a module is searched: 0 by u; 1 (a hit outside u's range, a wide window) by direction if one of
+  // them has more than kMdWalk upper hits (s_any), else all pairs; 2 or 3 all pairs
+  __shared__ int s_odd[kBucketMods], s_any, s_more;
   __shared__ float4 s_mod[kBucketMods];          // per module: reference direction x, y, window in u, bins per unit of u
   __shared__ int s_x0[kBucketMods], s_x1[kBucketMods], s_y0[kBucketMods], s_y1[kBucketMods];
   const Ws &w = wb[blockIdx.y];
@@ -800,6 +866,7 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
     s_x1[t] = s_y1[t] = (int)0x80000000;
     s_odd[t] = s_nmd[t] = 0;
   }
+  if (t == 0) s_any = s_more = 0;
   __syncthreads();
   for (int j = a + lane; j < b; j += 64) {
     const int f = tag_fine(gload(w.hcp, j).w);
@@ -835,15 +902,13 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
     const float4 h = gload(w.hcp, s_ref[lane]);
     const float d = gload(g.win, m0 + lane).x * 1.27f + 4e-6f;
     s_mod[lane] = make_float4(h.x, h.y, d, 0.47f / d);
-    const float r = sqrtf(h.x * h.x + h.y * h.y);
-    if (!(r >= 1e-3f && r <= 1e6f && d < 0.25f)) s_odd[lane] = 1;
   }
   __syncthreads();
   // u of a hit of module m; false outside the range that the bins cover
   auto u_of = [&](const float4 &mod, const float4 &h, float *u) {
     const float dot = mod.x * h.x + mod.y * h.y, cr = mod.x * h.y - mod.y * h.x;
     *u = cr * frcp(dot);
-    return h.w >= 1e-3f && h.w <= 1e6f && dot > 0.0f && fabsf(cr) <= 0.5f * dot;
+    return dot > 0.0f && fabsf(cr) <= 0.5f * dot;
   };
   auto bin_of = [](float u, float inv) { return (int)floorf(u * inv) & (kMdBins - 1); };
   for (int r0 = a; r0 < b; r0 += 64) {
@@ -862,8 +927,11 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
       if (s_ref[m] >= 0) {  // the module has lower hits
         const float4 mod = s_mod[m];
         float u;
-        if (!u_of(mod, hr, &u)) {
-          s_odd[m] = 1;
+        if (!(hr.w >= 1e-3f && hr.w <= 1e6f)) {
+          atomicOr(&s_odd[m], 2);
+        } else if (!u_of(mod, hr, &u) || !(mod.z < 0.25f)) {
+          atomicOr(&s_odd[m], 1);
+          if (s_key0[2 * m + 2] - s_key0[2 * m + 1] > kMdWalk) s_any = 1;
         } else if (f & 1) {
           const int i = pos - j0;
           if (i < kMdList) s_next[i] = (unsigned short)atomicExch(&s_head[m * kMdBins + bin_of(u, mod.w)], i);
@@ -883,30 +951,49 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-  // ---- the MD search
   const bool fits = L <= kMdList;
+  const bool again = !fits || __builtin_amdgcn_readfirstlane(s_any);
+  if (again) {  // (the whole block) modules that are listed by direction
+    if (t < kBucketMods && s_ref[t] >= 0) {
+      int mode = s_odd[t];
+      if (mode == 0 && !fits) mode = 1;
+      if (mode == 1) {
+        const float3 b = md_bins(gload(g.win, m0 + t).x);
+        s_mod[t] = make_float4(b.x, b.y, b.z, 0.0f);
+        if (b.z == 0.0f) mode = 2;
+      }
+      s_odd[t] = mode;
+    }
+    __syncthreads();
+    for (int i = t; i < kBucketMods * kMdBins; i += kSortThreads)
+      if (s_odd[i / kMdBins] == 1) s_head[i] = -1;
+    __syncthreads();
+    for (int p = j0 + t; p < j1; p += kSortThreads) {
+      int f = 0;  // its key
+#pragma unroll
+      for (int q = kFineKeys / 2; q > 0; q >>= 1)
+        if (s_key0[f + q] <= p) f += q;
+      const int m = f >> 1;
+      if (!(f & 1) || s_odd[m] != 1 || s_ref[m] < 0) continue;
+      const float4 h = gload(w.hpos, p);
+      const int b = md_bin(direction(h.x, h.y), make_float3(s_mod[m].x, s_mod[m].y, s_mod[m].z));
+      const int old = atomicExch(&s_head[m * kMdBins + (b & (kMdBins - 1))], p - j0);
+      if (fits) s_next[p - j0] = (unsigned short)old;
+      else gp(reinterpret_cast<int *>(w.hcp + p))[0] = old;
+    }
+    __syncthreads();
+  }
+  // ---- the MD search
+  static_assert(kMdKeep == 6 && kMdList <= 0x8000, "packed in three words; list ends are negative");
   const int n_lower = s_lpre[kBucketMods];
-  for (int q = t; q < n_lower; q += kSortThreads) {
+  for (int q = t; q < n_lower && !again; q += kSortThreads) {
     const int m = lower_module(s_lpre, q);
     const int p = s_key0[2 * m] + (q - s_lpre[m]), up0 = s_key0[2 * m + 1], nup = s_key0[2 * m + 2] - up0;
-    unsigned kept[kMdKeep];
-#pragma unroll
-    for (int i = 0; i < kMdKeep; ++i) kept[i] = 0xffffu;
-    int n = 0;
-    auto take = [&](int j) {  // into the kept ones, ascending
-      ++n;
-      unsigned v = (unsigned)min(j, 0xffff);
-#pragma unroll
-      for (int i = 0; i < kMdKeep; ++i) {
-        const unsigned lo = min(kept[i], v);
-        v = max(kept[i], v);
-        kept[i] = lo;
-      }
-    };
+    MdKept r;
     if (nup > 0) {
       const float4 hi = gload(w.hpos, p), win = gload(g.win, m0 + m);
       const ModInfo mi{gp(g.info)[m0 + m]};
-      if (fits && !s_odd[m]) {
+      if (!s_odd[m]) {
         const float4 mod = s_mod[m];
         float u;
         u_of(mod, hi, &u);
@@ -926,19 +1013,112 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
             k = rest;
             rest = -1;
           }
-          if (md_pass(hi, hj, win, mi)) take(j);
+          if (md_pass(hi, hj, win, mi)) r.take(j);
         }
       } else {
         for (int j = 0; j < nup; ++j)
-          if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) take(j);
+          if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) r.take(j);
       }
     }
-    static_assert(kMdKeep == 6 && kMdList <= 0x8000, "packed in three words; list ends are negative");
-    gstore(reinterpret_cast<int4 *>(w.hcp), p,
-           make_int4((int)(kept[0] | kept[1] << 16), (int)(kept[2] | kept[3] << 16), (int)(kept[4] | kept[5] << 16), n));
-    if (n > 0) atomicAdd(&s_nmd[m], n);
+    if (md_listed(r.n, nup)) s_more = 1;
+    gstore(reinterpret_cast<int4 *>(w.hcp), p, r.packed());
+    if (r.n > 0) atomicAdd(&s_nmd[m], r.n);
   }
   __syncthreads();
+  // the same with modules listed by direction, and the lists of the lower hits with many partners
+  if (again || __builtin_amdgcn_readfirstlane(s_more)) {  // (the whole block)
+    for (int q0 = 0; q0 < n_lower; q0 += kSortThreads) {
+      const int q = q0 + t;
+      int m = 0, p = 0, up0 = 0, nup = 0;
+      int h0 = -1, h1 = -1;  // the lists of the two bins
+      bool listed = true, mine = q < n_lower;
+      if (mine) {
+        m = lower_module(s_lpre, q);
+        p = s_key0[2 * m] + (q - s_lpre[m]);
+        up0 = s_key0[2 * m + 1];
+        nup = s_key0[2 * m + 2] - up0;
+        if (!again) mine = md_listed(gload(reinterpret_cast<const int4 *>(w.hcp), p).w, nup);
+      }
+      float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), win = hi;
+      ModInfo mi{0};
+      if (mine && nup > 0) {
+        hi = gload(w.hpos, p);
+        win = gload(g.win, m0 + m);
+        mi.bits = gp(g.info)[m0 + m];
+        const int mode = s_odd[m];
+        const float4 mod = s_mod[m];
+        int b0 = 0, b1 = 0;
+        if (mode == 0) {
+          float u;
+          u_of(mod, hi, &u);
+          b0 = bin_of(u - mod.z, mod.w);
+          b1 = bin_of(u + mod.z, mod.w);
+        } else if (mode == 1 && again) {
+          const float d = direction(hi.x, hi.y);
+          const float3 b = make_float3(mod.x, mod.y, mod.z);
+          b0 = md_bin(d - b.x, b) & (kMdBins - 1);
+          b1 = md_bin(d + b.x, b) & (kMdBins - 1);
+        } else {
+          listed = false;
+        }
+        if (listed) {
+          h0 = s_head[m * kMdBins + b0];
+          h1 = b1 != b0 ? s_head[m * kMdBins + b1] : -1;
+        }
+      }
+      // the first pass counts; more of them fill a list, kMdKeep partners each, of those from `from` on
+      int from = 0, all = 0, k = 0, list = -1;
+      for (bool first = true; __ballot(mine); first = false) {
+        MdKept r;
+        if (mine && listed) {
+          int i = h0, rest = h1;
+          if (i < 0) {
+            i = rest;
+            rest = -1;
+          }
+          while (i >= 0) {
+            const float4 hj = gload(w.hpos, j0 + i);
+            const int j = j0 + i - up0;
+            i = fits ? (int)(short)s_next[i] : gp(reinterpret_cast<const int *>(w.hcp + j0 + i))[0];
+            if (i < 0) {
+              i = rest;
+              rest = -1;
+            }
+            if (j >= from && md_pass(hi, hj, win, mi)) r.take(j);
+          }
+        } else if (mine) {
+          for (int j = from; j < nup && (first || r.n < kMdKeep); ++j)
+            if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) r.take(j);
+        }
+        if (first) {
+          if (again && mine && r.n > 0) atomicAdd(&s_nmd[m], r.n);
+          all = mine && md_listed(r.n, nup) ? r.n : 0;
+          const int x = wave_inclusive(all), sum = __builtin_amdgcn_readlane(x, 63);
+          int at = 0;
+          if (sum > 0 && lane == 63) at = atomicAdd(w.ctr + C_NMDLIST, sum);
+          at = __builtin_amdgcn_readlane(at, 63) + x - all;
+          if (all > 0 && at >= 0 && at + (long)all <= (long)kLsCache * w.cap_md) list = at;
+          if (mine) {
+            int4 rec = r.packed();
+            if (all > 0) rec.x = list;  // (-1: the fill tests again)
+            gstore(reinterpret_cast<int4 *>(w.hcp), p, rec);
+          }
+          // the bins again for each pass, or all passes once through the module, whichever tests fewer
+          listed = listed && (long)all * all < 8L * nup;
+        }
+        mine = mine && list >= 0;
+        if (mine) {
+#pragma unroll
+          for (int i = 0; i < kMdKeep; ++i)
+            if (i < all - k) gp(w.ls_cache)[(long)list + k + i] = (int)r.kept[i];
+          k += kMdKeep;
+          from = (int)r.kept[kMdKeep - 1] + 1;
+          mine = k < all;
+        }
+      }
+    }
+    __syncthreads();
+  }
   if (t < kBucketMods && m0 + t < n_mod) {
     gp(w.md_cnt)[m0 + t] = s_nmd[t];
     if (s_nmd[t] > 0)
@@ -954,7 +1134,7 @@ __global__ __launch_bounds__(kSortThreads) void k_bucket_md(const Ws *__restrict
 // The MDs of a coarse bucket, in row-major (lower, upper) order per module: the
 // offset of each of the bucket's lower hits is the MDs of the buckets before
 // (summed here) plus a scan over the lower hits before it.  Partners that the
-// search did not keep are searched again.
+// search did not keep come from its list, or are searched again.
 __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__ wb, DevGeom g) {
   __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1], s_red[kSortWaves];
   __shared__ int s_at[kBucketMods + 1];  // the modules' first MDs, from the bucket's first
@@ -1038,6 +1218,11 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
       for (int i = 0; i < n; ++i) {
         const int word = i < 2 ? r.x : (i < 4 ? r.y : r.z);
         const int j = (word >> (16 * (i & 1))) & 0xffff;
+        put(pos + i, j, gload(w.hpos, up0 + j));
+      }
+    } else if (md_listed(n, nup) && r.x >= 0 && keep == kMdKeep) {
+      for (int i = 0; i < n; ++i) {
+        const int j = min(gp(w.ls_cache)[r.x + i], nup - 1);
         put(pos + i, j, gload(w.hpos, up0 + j));
       }
     } else {

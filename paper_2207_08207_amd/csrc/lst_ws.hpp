@@ -13,6 +13,7 @@ enum Ctr : int {
   C_RMD = 9, C_RLS, C_RT3, C_RT5, C_RPT3, C_RPT5,                      // required counts
   C_NT5KEEP = 15, C_NTC0 = 16, C_NTC1, C_NTC2, C_NTC3,                 // survivors, TCs per type
   C_NINC = 21, C_NBIN = 25,      // scratch totals
+  C_NMDLIST = 26,                // entries of the mini-doublet search's lists
   C_NLSOVF = 27,                 // MDs with more segments than the count pass caches
   C_NEXTHITS = 28,               // hits of the extended track-candidate collection
   C_EXT = 29,                    // 1 once the track extensions of the event are written

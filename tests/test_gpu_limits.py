@@ -5,9 +5,11 @@ import pytest
 
 import oracle
 from lstgen import make_event, make_single_track_event
+from lstgen.events import make_tiny_event
 
 from dense import dense_event
 from parity import compare_event, compare_tc
+from wide_modules import merge_event, sector_geometry
 
 pytestmark = pytest.mark.gpu
 
@@ -70,6 +72,43 @@ def test_seed_tasks_at_the_shard_limit(n, lists, lst, barrel, obarrel):
     st, h = lst.lst_build_event(g.handle, lst.upload_event(ev), ws, cap, torch.cuda.current_stream().cuda_stream)
     assert st == lst.LST_OK
     r = lst.EventResult(h, ws, st)
+    compare_event(r, o)
+    compare_tc(r, o)
+    r.close()
+
+
+# few wide modules: hits outside the range of the bins by u, listed by direction, in LDS and (more than
+# 8,192 hits a bucket) in global memory; windows wide enough for lists of partners; all pairs tested
+@pytest.mark.parametrize("nphi,nz,n,bound,md_cache", [(1, 1, 60, 0.1, 32), (1, 1, 800, 0.1, 32), (4, 1, 300, 0.1, 32),
+                                                      (4, 1, 1500, 0.1, 32), (4, 1, 300, 0.1, 3), (4, 1, 200, 3.6, 32),
+                                                      (2, 1, 120, 10.0, 32), (8, 4, 1500, 0.1, 32)])
+def test_wide_modules(nphi, nz, n, bound, md_cache, lst, barrel):
+    geom, new = sector_geometry(barrel, nphi, nz)
+    rng = np.random.default_rng(n)
+    ev = make_single_track_event(barrel, np.exp(rng.uniform(np.log(0.8), np.log(50.0), n)), rng.uniform(-0.5, 0.5, n),
+                                 rng.uniform(0, 2 * np.pi, n), z0=rng.normal(0, 5, n),
+                                 q=np.where(rng.uniform(size=n) < 0.5, -1, 1), smear=True, seed=n, n_noise=50)
+    ev = merge_event(ev, new)
+    g, og = lst.Geometry(geom), oracle.OracleGeometry(geom, d0_max=bound)
+    g.set_tile_config({"md_cache": md_cache})
+    g.set_impact_bound(bound)
+    o = oracle.run(og, ev)
+    print(f"[gpu] {geom.n_modules} modules, {ev.n_hits} hits, {o.count(0)} mini-doublets", flush=True)
+    r = lst.run_event(g, lst.upload_event(ev))
+    compare_event(r, o)
+    compare_tc(r, o)
+    r.close()
+
+
+# a lower hit on the beam line's side of 10 um and one 20 km out: every pair of their modules tested
+def test_hits_near_the_beam_line_and_far_out(lst, barrel, obarrel):
+    ev = make_tiny_event(4, n_tracks=60, n_noise=40)
+    m = [int(k) for k in np.argsort(np.bincount(ev.module[ev.module >= 0]))[-3:]]
+    for k, x in zip(m, (1e-5, 2e6, 0.0)):
+        i = np.nonzero((ev.module == k) & (ev.sensor == 0))[0][0]
+        ev.x[i], ev.y[i] = x, 0.0
+    r = lst.run_event(lst.Geometry(barrel), lst.upload_event(ev))
+    o = oracle.run(obarrel, ev)
     compare_event(r, o)
     compare_tc(r, o)
     r.close()
