@@ -367,6 +367,8 @@ lst_status lst_get_site_time(lst_event ev, float *ms);
  *    reps times per choice of each tunable site in turn, timing that site with
  *    HIP events on `stream`, keeps the fastest choice per site and returns in
  *    site_ms (optional) the best time of each tuned site (-1 for the others).
+ *    md_count, md_fill, pt5_fill and tc_pls, whose work rides in launches of a
+ *    fixed shape, keep theirs and are timed with it.
  *    It waits for the device; on any error the previous shapes are restored.
  *    Not to be called while other calls use the same geometry. */
 lst_status lst_get_launch_config(lst_geometry geom, int32_t n, int32_t *site_block);

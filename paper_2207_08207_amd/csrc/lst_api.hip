@@ -1708,8 +1708,10 @@ lst_status lst_autotune(lst_geometry g, int32_t B, const lst_event_desc *evs, co
     if (!lst::site_tunable(site)) continue;
     float best = 3.0e38f;
     int best_b = g->site_block[site];
+    const bool shaped = lst::site_shaped(site);
     for (int c : choices) {
-      g->site_block[site] = c;
+      if (!shaped && c != choices[0]) break;  // nothing to choose: timed as it is
+      if (shaped) g->site_block[site] = c;
       float tmin = 3.0e38f;
       for (int r = 0; r < reps; ++r) {
         float ms = 0.0f;
@@ -1719,7 +1721,7 @@ lst_status lst_autotune(lst_geometry g, int32_t B, const lst_event_desc *evs, co
       }
       if (tmin < best) {
         best = tmin;
-        best_b = c;
+        if (shaped) best_b = c;
       }
     }
     g->site_block[site] = best_b;
@@ -1737,7 +1739,7 @@ struct TileSpec {
   int n_choices;
 };
 const TileSpec kTileSpecs[] = {
-    {"md_cache", 0, lst::kMdCache, {0, 16, lst::kMdCache}, 3},
+    {"md_cache", 0, lst::kMdCache, {0, lst::kMdKeep / 2, lst::kMdCache}, 3},  // (from kMdKeep on all the same)
     {"ls_cache", 0, lst::kLsCache, {8, 16, lst::kLsCache}, 3},
     {"t3_cache", 0, lst::kT3Cache, {0, 1, 2}, 3},
     {"t5_cache", 0, lst::kT5Cache, {0, 1, 2}, 3},

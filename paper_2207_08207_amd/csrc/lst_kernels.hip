@@ -3956,8 +3956,8 @@ static_assert(sizeof(kSiteNames) / sizeof(kSiteNames[0]) <= kMaxSites, "launch-s
 // Sites whose kernels take any block of 64, 128 or 256 threads (grid-stride
 // loops over threads or waves, LDS sized for the largest block): the launch
 // shape the autotuner may choose.  (md_count, md_fill, pt5_fill and tc_pls, whose
-// work is in other launches or a block of fixed size, take a shape that nothing
-// reads.)
+// work is in other launches or a block of fixed size, take a shape, as in files
+// that were saved when they read it, and have none to choose.)
 static const char *const kTunableSites[] = {"md_count", "md_fill",  "ls_count", "ls_fill",  "t3_count",
                                             "t3_fill",  "t5_count", "t5_fill",  "t5_dedup", "pt_count",
                                             "pt3_fill", "pt5_fill", "tc_pt3",   "tc_t5",    "tc_pls",
@@ -3968,6 +3968,13 @@ bool site_tunable(int site) {
   for (const char *n : kTunableSites)
     if (std::strcmp(n, kSiteNames[site]) == 0) return true;
   return false;
+}
+
+bool site_shaped(int site) {
+  if (!site_tunable(site)) return false;
+  for (const char *n : {"md_count", "md_fill", "pt5_fill", "tc_pls"})
+    if (std::strcmp(n, kSiteNames[site]) == 0) return false;
+  return true;
 }
 
 // Inner MDs per wave of the segment count pass: the tile when set, else the

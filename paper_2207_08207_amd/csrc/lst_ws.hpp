@@ -278,6 +278,7 @@ extern const int kNumSites;
 constexpr int kMaxSites = 64;
 // True for the launch sites that take a block of 64, 128 or 256 threads.
 bool site_tunable(int site);
+bool site_shaped(int site);  // and its launch reads the shape
 // Enqueues the whole chain for B events whose descriptors are d_ws[0..B) in
 // device memory; `bound` holds, field by field, the largest sizes and
 // capacities of the batch (it sets the launch grids).  site_block (kMaxSites

@@ -23,6 +23,7 @@ hipError_t ret(hipError_t e) {
 }
 // what the made-up chain finds: candidates of four hits each, per event
 int g_candidates = 10;
+int g_chains = 0;
 }  // namespace
 
 hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
@@ -79,13 +80,15 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
 
 namespace lst {
-const char *const kSiteNames[] = {"whole"};
-const int kNumSites = 1;
-bool site_tunable(int) { return false; }
+const char *const kSiteNames[] = {"fixed", "shaped", "unshaped"};
+const int kNumSites = 3;
+bool site_tunable(int s) { return s > 0; }
+bool site_shaped(int s) { return s == 1; }
 void launch_module_windows(const int *, const float *, const float *, const float *, const float *, int, double, float4 *,
                            hipStream_t) {}
 void launch_tc_export(const Ws *, int, int, int *, int *, int *, int *, hipStream_t) {}
 void enqueue_chain(const DevGeom &, Ws *d, int B, const Ws &, hipStream_t, const KernelTimer *, const int *, const Ws *value) {
+  ++g_chains;
   if (g_capturing) {
     g_graph_ws = d;
     g_graph_B = B;
@@ -302,11 +305,25 @@ int room() {
   CHECK(host_pool().results_bytes == 0);
   return 0;
 }
+
+// A site whose launch reads no shape is timed as it is.
+int tune() {
+  lst_geometry g = geometry();
+  Call c(g, 1, 500, 20);
+  int32_t shape[3] = {0, 64, 128};
+  CHECK(lst_set_launch_config(g, 3, shape) == LST_OK);
+  float ms[3];
+  CHECK(lst_autotune(g, 1, &c.ev, nullptr, c.ws, c.bytes, nullptr, 2, ms) == LST_OK);
+  CHECK(ms[0] == -1.0f && ms[1] > 0.0f && ms[2] > 0.0f);
+  CHECK(g_chains == 3 * 2 + 2);
+  CHECK(lst_get_launch_config(g, 3, shape) == LST_OK && shape[0] == 0 && shape[2] == 128);
+  return 0;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, int (*)()> scenarios = {{"plain", plain}, {"refused", refused}, {"unstaged", unstaged},
-                                                          {"unpooled", unpooled}, {"failed", failed}, {"room", room}};
+                                                          {"unpooled", unpooled}, {"failed", failed}, {"room", room}, {"tune", tune}};
   const int rc = scenarios.at(argv[1])();
   if (rc == 0) printf("ok\n");
   return rc;

@@ -48,3 +48,7 @@ def test_a_failed_event_outlives_its_stream(fake):
 def test_host_memory_of_held_events(fake):
     """Sized by the event, at most 64 MiB for all that are held, and room for eight PU200 events."""
     run(fake, "room")
+
+
+def test_the_autotuner_skips_sites_without_a_shape(fake):
+    run(fake, "tune")
