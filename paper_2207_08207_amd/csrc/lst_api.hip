@@ -202,6 +202,8 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.inc_b0 = reinterpret_cast<int *>(t.md_bin + md);
   static_assert(5 * sizeof(int4) <= 26 * sizeof(int), "the other MDs of the lists' T5s, per quintuplet");
   t.inc_mds = reinterpret_cast<int4 *>(t.ext_out);  // 20 t5 <= 26 tc
+  static_assert(kTaskShards * kSumStride <= kSeedKeys, "a line each");
+  t.ts_task = t.seed_cnt;  // read last by the segment sums, cleared again beside the quintuplet count
   t.pt_tasks = t.ph_next;  // 2 S and a few <= 4 S; the lists of pixel hits are read last by the pLS duplicate removal
   t.pt_spill = reinterpret_cast<int *>(t.inc_list);  // read last by the T5 duplicate removal
   t.n_spill = (int)(10 * t5 / kPassList);
@@ -212,10 +214,10 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   t.seed_key = t.tc_md; t.seed_slot = t.tc_md + S;          // 2 S <= 5 tc
   // the tile sums, one after another (cleared together)
   const long nl = n_sum_tiles(md), n3 = n_sum_tiles(ls), n5 = n_sum_tiles(t3), np = n_sum_tiles(S);
-  const long n_ts = (nl + n3 + n5 + 2 * np + kTaskShards) * kSumStride;
+  const long n_ts = (nl + n3 + n5 + 2 * np) * kSumStride;
   t.ts_ls = I(n_ts);
   t.ts_t3 = t.ts_ls + nl * kSumStride; t.ts_t5 = t.ts_t3 + n3 * kSumStride;
-  t.ts_p3 = t.ts_t5 + n5 * kSumStride; t.ts_p5 = t.ts_p3 + np * kSumStride; t.ts_task = t.ts_p5 + np * kSumStride;
+  t.ts_p3 = t.ts_t5 + n5 * kSumStride; t.ts_p5 = t.ts_p3 + np * kSumStride;
   t.sh_ls = tile_shift(md); t.sh_t3 = tile_shift(ls); t.sh_t5 = tile_shift(t3); t.sh_pt = tile_shift(S);
 #undef I
 #undef F

@@ -2323,6 +2323,7 @@ __device__ __forceinline__ int2 triplets_t5(const Ws &w, int2 r, int n_t5) {
 // blocks, q = 0, 1, ... of nq.
 __device__ __forceinline__ void bin_count(const Ws &w, int q, int nq) {
   if (w.n_seeds == 0) return;
+  if (q == 0 && threadIdx.x < kTaskShards) gp(w.ts_task)[threadIdx.x * kSumStride] = 0;  // (the seed search's tasks)
   const int n = uload(w.ctr + C_NMD), n_ls = uload(w.ctr + C_NLS), n_t3 = uload(w.ctr + C_NT3);
   for (int m = q * blockDim.x + threadIdx.x; m < n; m += nq * blockDim.x) {
     const int2 r = md_triplets(w, m, n_ls, n_t3);
@@ -3308,6 +3309,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
+  if (w.n_seeds == 0) return;  // (an event without seeds beside others: its counts are not cleared)
   const int shards = pt_shards(w), b = (int)blockIdx.x - 2 * nc, q = b & (shards - 1);
   const int n_task = uload(w.ts_task + q * kSumStride), step = ((int)gridDim.x - 2 * nc) / shards;
   for (int i = b / shards; i < n_task; i += step) {
