@@ -232,9 +232,6 @@ size_t workspace_layout(int n_mod, int n_hits, int n_seeds, const Caps &c, Ws *w
   if (w && base) {
     const long S = n_seeds;  // the jobs follow the event's own sizes
     int *ct = t.ctr;
-    auto sj = [&](int id, const int *in, int *out, const int *n_dev, long n_fix, long n_cap, int *req, int *clamped,
-                  long cap) { t.scans[id] = ScanJob{in, out, n_dev, (int)n_fix, (int)n_cap, req, clamped, (int)cap}; };
-    sj(SC_EXT, t.ext_cnt, t.ext_off, ct + C_NTC, 0, p5 + p3 + t5 + S, ct + C_NEXTHITS, nullptr, 0);
     const auto fj = [&](int id, int *p, long n, int stride = 1) { t.fills[id] = FillJob{p, (int)n, stride}; };
     fj(FL_CTR, ct, C_COUNT);
     fj(FL_TS, t.ts_ls, n_ts / kSumStride, kSumStride);
@@ -658,13 +655,14 @@ lst_status lst_workspace_bytes(lst_geometry g, int32_t n_hits, int32_t n_seeds, 
   return lst_batch_workspace_bytes(g, 1, &n_hits, &n_seeds, cap, bytes);
 }
 
-// The hit bucketing scans one count per (coarse bucket, tile of input hits):
-// an event must keep that within one device scan on this geometry.
+// The hit bucketing keeps one count per (coarse bucket, tile of input hits): an
+// event's stay below what a device scan takes, in tiles of kScanTileHits, the limit
+// that callers know from when they were scanned.
 static lst_status check_bucketing(lst_geometry g, int64_t n_hits) {
   const int64_t items = (int64_t)lst::n_coarse(g->g.n_mod) * lst::n_hit_tiles(n_hits, lst::kScanTileHits);
   if (items > kMaxTc) {
     char msg[200];
-    snprintf(msg, sizeof(msg), "%lld hits: above what the hit bucketing scans on a detector of %d modules",
+    snprintf(msg, sizeof(msg), "%lld hits: above what the hit bucketing counts on a detector of %d modules",
              (long long)n_hits, g->g.n_mod);
     return fail(LST_E_INVALID, msg);
   }
@@ -683,9 +681,10 @@ static lst_status check_event_desc(const lst_event_desc &ev) {
   return LST_OK;
 }
 
-// Lays out B events in the workspace at `base` (batch_bytes() bytes), uploads
-// their descriptors and enqueues the chain and the counter read-back on
-// `stream`.  The returned batch holds one reference per event.
+// Lays out B events in the workspace at `base` (batch_bytes() bytes) and enqueues
+// the chain on `stream`, after a copy of their descriptors (one event's goes with the
+// first launch); its last launch writes the counters, and the candidates that fit, to
+// the batch's host buffers.  The returned batch holds one reference per event.
 static lst_status enqueue_batch_at(lst_geometry g, int B, const lst_event_desc *evs, const std::vector<lst::Caps> &caps,
                                    char *base, hipStream_t stream, lst_batch_s **out, int timed_site = -2) {
   *out = nullptr;

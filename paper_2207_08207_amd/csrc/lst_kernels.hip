@@ -90,8 +90,6 @@ __device__ __forceinline__ int block_sum(int v, int *s_red) {
   return t;
 }
 
-__device__ __forceinline__ int dev_count(const int *p, int fallback) { return p ? *p : fallback; }
-
 // ------------------------------------------------------------------ start
 // On further blocks (q of nq) of the chain's first launch: clears what later
 // launches count into, empties the lists of the pixel hits that seeds use and
@@ -115,14 +113,13 @@ __device__ __forceinline__ void start_blocks(const Ws &w, int q, int nq) {
 }
 
 // ------------------------------------------------------------------ scan
-// Exclusive scan of in[0..n) into out[0..n], out[n] = total; n = *n_dev (or
-// n_fix).  Two passes: tile sums, then each tile's scan offset by the sum of
-// the tiles before it.
-__global__ void k_scan_reduce(const Ws *__restrict__ wb, int job) {
+// Exclusive scan of the extended candidates' hit counts, out[n] = total.  Two
+// passes: tile sums, then each tile's scan offset by the sum of the tiles before
+// it.
+__global__ void k_scan_reduce(const Ws *__restrict__ wb) {
   __shared__ int s_red[kWaves];
   const Ws &w = wb[blockIdx.y];
-  const ScanJob &J = w.scans[job];
-  const int n = dev_count(J.n_dev, J.n_fix);
+  const int n = uload(w.ctr + C_NTC);
   // tiles 0 .. n / kScanTile (the last one may be empty), strided over the grid
   for (long t = blockIdx.x; t * kScanTile <= n; t += gridDim.x) {
     const long base = t * kScanTile;
@@ -130,23 +127,21 @@ __global__ void k_scan_reduce(const Ws *__restrict__ wb, int job) {
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
       const long i = base + (long)k * kBlock + threadIdx.x;
-      if (i < n) v += J.in[i];
+      if (i < n) v += gp(w.ext_cnt)[i];
     }
     v = block_sum(v, s_red);
     if (threadIdx.x == 0) w.scan_tmp[t] = v;
   }
 }
 
-// Each tile adds the tile sums before it (at most a few hundred for the
-// chain's counts) to its own exclusive scan; the tile holding index n writes
-// out[n] and the totals.  (Two launches per scan instead of a third,
+// Each tile adds the tile sums before it (at most a few hundred) to its own
+// exclusive scan; the tile holding index n writes out[n] and the total.  (Two launches per scan instead of a third,
 // single-block pass over the tile sums.)  Both passes stride over the tiles,
 // so the grid need not cover the capacity.
-__global__ void k_scan_apply(const Ws *__restrict__ wb, int job) {
+__global__ void k_scan_apply(const Ws *__restrict__ wb) {
   __shared__ int s_wave[kWaves], s_red[kWaves];
   const Ws &w = wb[blockIdx.y];
-  const ScanJob &J = w.scans[job];
-  const int n = dev_count(J.n_dev, J.n_fix);
+  const int n = uload(w.ctr + C_NTC);
   for (long t = blockIdx.x; t * kScanTile <= n; t += gridDim.x) {
     const long base = t * kScanTile;
     int pre = 0;
@@ -155,7 +150,7 @@ __global__ void k_scan_apply(const Ws *__restrict__ wb, int job) {
     // the tile in kScanItems rounds of kBlock consecutive items
     for (int k = 0; k < kScanItems; ++k) {
       const long i = base + (long)k * kBlock + threadIdx.x;
-      const int v = (i < n) ? J.in[i] : 0;
+      const int v = (i < n) ? gp(w.ext_cnt)[i] : 0;
       // inclusive scan within the wave
       int x = v;
       for (int o = 1; o < 64; o <<= 1) {
@@ -171,18 +166,11 @@ __global__ void k_scan_apply(const Ws *__restrict__ wb, int job) {
         wbs += (q < (int)(threadIdx.x >> 6)) ? c : 0;
         tot += c;
       }
-      if (i <= n) J.out[i] = run + wbs + x - v;  // out[n] = total
+      if (i <= n) gp(w.ext_off)[i] = run + wbs + x - v;  // [n] = total
       __syncthreads();
       run += tot;
     }
-    if (base + kScanTile > n && threadIdx.x == 0) {
-      const int tot = run;  // every item of the later tiles is past n
-      if (J.tot_req) *J.tot_req = tot;
-      if (J.tot_clamped) {
-        *J.tot_clamped = tot < J.cap ? tot : J.cap;
-        if (tot > J.cap) atomicOr(w.ctr + C_STATUS, (int)ST_CAPACITY);
-      }
-    }
+    if (base + kScanTile > n && threadIdx.x == 0) w.ctr[C_NEXTHITS] = run;  // every item of the later tiles is past n
   }
 }
 
@@ -212,14 +200,14 @@ static inline int grid_for(long n, int block = kBlock) {
   return (int)g;
 }
 
-// Scan job `job` of every event of the batch; n_cap bounds the item count.
-static void scan(const Ws *wb, int B, int job, long n_cap, hipStream_t st) {
+// The scan in every event of the batch; n_cap bounds the item count.
+static void scan(const Ws *wb, int B, long n_cap, hipStream_t st) {
   // tiles covering n_cap + 1 outputs (capacities are checked on the host so that every scan's
   // count stays below kMaxScanBlocks tiles), at most an equal share of kLaunchWaves per event
   const long share = std::max(64L, kLaunchWaves / B / kWaves);
   const int nb = (int)std::min<long>(std::min<long>((n_cap + kScanTile) / kScanTile, kMaxScanBlocks), share);
-  k_scan_reduce<<<dim3(nb, B), kBlock, 0, st>>>(wb, job);
-  k_scan_apply<<<dim3(nb, B), kBlock, 0, st>>>(wb, job);
+  k_scan_reduce<<<dim3(nb, B), kBlock, 0, st>>>(wb);
+  k_scan_apply<<<dim3(nb, B), kBlock, 0, st>>>(wb);
 }
 
 // ------------------------------------------------- offsets inside a fill pass
@@ -4173,7 +4161,7 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     else if (c == 16) k_tc_ext<16><<<gridwt((b.cap_tc + 15) / 16), tb, 0, st>>>(wb, g);
     else k_tc_ext<8><<<gridwt((b.cap_tc + 7) / 8), tb, 0, st>>>(wb, g);
   });
-  run([&] { if (g.ext) scan(wb, B, SC_EXT, b.cap_tc, st); });
+  run([&] { if (g.ext) scan(wb, B, b.cap_tc, st); });
   run([&] { if (g.ext) k_tc_ext_write<<<grid(b.cap_tc), kBlock, 0, st>>>(wb); });
   if (whole) (void)hipEventRecord(kt->end, st);
 }

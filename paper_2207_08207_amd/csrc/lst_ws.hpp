@@ -53,20 +53,6 @@ struct DevGeom {
   Tiles tiles;
 };
 
-// One exclusive scan of the chain: out[0..n] = scan of in[0..n), n = *n_dev
-// (or n_fix); the total goes to *tot_req and, clamped to cap (overflow
-// flagged), to *tot_clamped.  n_cap bounds n for the launch grid.
-struct ScanJob {
-  const int *in;
-  int *out;
-  const int *n_dev;
-  int n_fix, n_cap;
-  int *tot_req, *tot_clamped;
-  int cap;
-};
-enum ScanId : int {
-  SC_EXT, SC_COUNT
-};
 // One array cleared to zero at the start of the chain: n entries, `stride` ints apart.
 struct FillJob {
   int *p;
@@ -101,7 +87,7 @@ constexpr int kMdCache = 32;  // largest md_cache tile
 constexpr int kMdKeep = 6;    // partners per lower hit the MD search keeps
 constexpr int kT3Cache = 2;   // triplets per parent segment whose candidate the T3 count pass keeps
 constexpr int kT5Cache = 2;   // quintuplets per parent triplet whose candidate the T5 count pass keeps
-constexpr int kPt3Cache = 256;  // pT3 per seed (PU200 maximum ~190)
+constexpr int kPt3Cache = 256;  // pT3 per seed (most PU200 events' largest is below, about one seed an event has more)
 constexpr int kPt5Cache = 16;   // pT5 per seed
 // Hit bucketing: block tiles of kHitTile to 4 kHitTile input hits; (module,
 // sensor) keys in coarse buckets of kFineKeys consecutive keys (at most
@@ -242,9 +228,8 @@ struct Ws {
   int *ts_task;  // kTaskShards counts of tasks, likewise a line each
   int sh_ls, sh_t3, sh_t5, sh_pt;
   int *ws_t3, *ws_t5;
-  // scan scratch and the job tables of the generic scan / clear kernels
+  // scan scratch and the table of the clears
   int *scan_tmp;
-  ScanJob scans[SC_COUNT];
   FillJob fills[FL_COUNT];
 };
 
