@@ -747,8 +747,10 @@ __device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((
 // bound by the chain of its steps in the densest bucket, hence few passes over
 // the hits.  Without the second listing and the lists of partners, 6 x 1,000 and 24 x
 // 1,000 hits a sensor on modules of a whole and of a quarter of the azimuth took
-// 2.21 and 6.47 ms here and 0.06 and 3.06 in the fill, now 0.24 and 0.80, 0.06 and
-// 0.21; a PU400 event, whose densest bucket has 8,500 hits, 0.60 ms, now 0.12.)
+// 2.21 and 6.47 ms here and 0.06 and 3.06 in the fill, now 0.23 and 0.77, 0.06 and
+// 0.32; a PU400 event, whose densest bucket has 8,500 hits, 0.60 ms, now 0.14; 3,000
+// hits a sensor on one module, each with five partners, 0.92 and 6.00, now 2.00 and
+// 1.10.)
 // At most 80 scalar registers (72 and the reserved ones): with 80 and those a SIMD
 // held seven waves, so a CU three of these blocks instead of four, and eight PU50
 // events took 78 us instead of 71.
@@ -1017,7 +1019,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
   if (again || __builtin_amdgcn_readfirstlane(s_more)) {  // (the whole block)
     for (int q0 = 0; q0 < n_lower; q0 += kSortThreads) {
       const int q = q0 + t;
-      int m = 0, p = 0, up0 = 0, nup = 0;
+      int m = 0, p = 0, up0 = 0, nup = 0, n = 0;
       int h0 = -1, h1 = -1;  // the lists of the two bins
       bool listed = true, mine = q < n_lower;
       if (mine) {
@@ -1025,7 +1027,10 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
         p = s_key0[2 * m] + (q - s_lpre[m]);
         up0 = s_key0[2 * m + 1];
         nup = s_key0[2 * m + 2] - up0;
-        if (!again) mine = md_listed(gload(reinterpret_cast<const int4 *>(w.hcp), p).w, nup);
+        if (!again) {
+          n = gload(reinterpret_cast<const int4 *>(w.hcp), p).w;
+          mine = md_listed(n, nup);
+        }
       }
       float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), win = hi;
       ModInfo mi{0};
@@ -1054,10 +1059,28 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
           h1 = b1 != b0 ? s_head[m * kMdBins + b1] : -1;
         }
       }
-      // the first pass counts; more of them fill a list, kMdKeep partners each, of those from `from` on
-      int from = 0, all = 0, k = 0, list = -1;
-      for (bool first = true; __ballot(mine); first = false) {
+      // the first pass counts (again: no search has), the second fills the list
+      int list = -1, k = 0;
+      for (int pass = again ? 0 : 1; pass < 2; ++pass) {
+        if (pass == 1) {
+          const int all = mine && md_listed(n, nup) ? n : 0, x = wave_inclusive(all), sum = __builtin_amdgcn_readlane(x, 63);
+          if (sum == 0) break;
+          int at = 0;
+          if (lane == 63) at = atomicAdd(w.ctr + C_NMDLIST, sum);
+          at = __builtin_amdgcn_readlane(at, 63) + x - all;
+          mine = all > 0;
+          if (mine && at >= 0 && at + (long)all <= (long)kLsCache * w.cap_md) list = at;
+          // in any order from the bins, if the fill ranks them with fewer steps than one pass over
+          // the module takes, which finds them in order
+          listed = listed && (long)all * all <= 4L * nup;
+          if (mine) gstore(reinterpret_cast<int4 *>(w.hcp), p, make_int4(list, listed ? 0 : 1, 0, n));  // (-1: the fill tests again)
+          mine = list >= 0;
+        }
         MdKept r;
+        auto take = [&](int j) {
+          if (pass == 0) r.take(j);
+          else if (k < n) gp(w.ls_cache)[(long)list + k++] = j;
+        };
         if (mine && listed) {
           int i = h0, rest = h1;
           if (i < 0) {
@@ -1072,36 +1095,16 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
               i = rest;
               rest = -1;
             }
-            if (j >= from && md_pass(hi, hj, win, mi)) r.take(j);
+            if (md_pass(hi, hj, win, mi)) take(j);
           }
         } else if (mine) {
-          for (int j = from; j < nup && (first || r.n < kMdKeep); ++j)
-            if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) r.take(j);
+          for (int j = 0; j < nup; ++j)
+            if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) take(j);
         }
-        if (first) {
-          if (again && mine && r.n > 0) atomicAdd(&s_nmd[m], r.n);
-          all = mine && md_listed(r.n, nup) ? r.n : 0;
-          const int x = wave_inclusive(all), sum = __builtin_amdgcn_readlane(x, 63);
-          int at = 0;
-          if (sum > 0 && lane == 63) at = atomicAdd(w.ctr + C_NMDLIST, sum);
-          at = __builtin_amdgcn_readlane(at, 63) + x - all;
-          if (all > 0 && at >= 0 && at + (long)all <= (long)kLsCache * w.cap_md) list = at;
-          if (mine) {
-            int4 rec = r.packed();
-            if (all > 0) rec.x = list;  // (-1: the fill tests again)
-            gstore(reinterpret_cast<int4 *>(w.hcp), p, rec);
-          }
-          // the bins again for each pass, or all passes once through the module, whichever tests fewer
-          listed = listed && (long)all * all < 8L * nup;
-        }
-        mine = mine && list >= 0;
-        if (mine) {
-#pragma unroll
-          for (int i = 0; i < kMdKeep; ++i)
-            if (i < all - k) gp(w.ls_cache)[(long)list + k + i] = (int)r.kept[i];
-          k += kMdKeep;
-          from = (int)r.kept[kMdKeep - 1] + 1;
-          mine = k < all;
+        if (pass == 0 && mine) {
+          n = r.n;
+          gstore(reinterpret_cast<int4 *>(w.hcp), p, r.packed());
+          if (n > 0) atomicAdd(&s_nmd[m], n);
         }
       }
     }
@@ -1209,9 +1212,17 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
         put(pos + i, j, gload(w.hpos, up0 + j));
       }
     } else if (md_listed(n, nup) && r.x >= 0 && keep == kMdKeep) {
+      const auto list = gp(w.ls_cache) + r.x;
       for (int i = 0; i < n; ++i) {
-        const int j = min(gp(w.ls_cache)[r.x + i], nup - 1);
-        put(pos + i, j, gload(w.hpos, up0 + j));
+        const int j = list[i];
+        int at = i;
+        if (r.y == 0) {  // (in any order: its place is its rank)
+          at = 0;
+#pragma unroll 8
+          for (int k = 0; k < n; ++k) at += list[k] < j ? 1 : 0;
+        }
+        const int jj = min(max(j, 0), nup - 1);  // (lists overlap only if their count overflowed: the event is refused)
+        put(pos + at, jj, gload(w.hpos, up0 + jj));
       }
     } else {
       const float4 win = gload(g.win, m0 + m);

@@ -112,3 +112,39 @@ def test_hits_near_the_beam_line_and_far_out(lst, barrel, obarrel):
     compare_event(r, o)
     compare_tc(r, o)
     r.close()
+
+
+# lower hits with more than six partners among many upper hits: lists in any order, ranked by the fill;
+# lists in order from a pass over the module (more partners than twice the root of its upper hits); at most
+# 64 upper hits, tested again; beside a bucket that is searched by u, and one listed by direction
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("n_upper,spread", [(300, 0.05), (200, 0.001), (64, 0.02), (63, 0.004)])
+def test_lists_of_partners(n_upper, spread, wide, lst, barrel):
+    geom, new = sector_geometry(barrel, 4, 1) if wide else (barrel, np.arange(barrel.n_modules))
+    ev = merge_event(make_tiny_event(6, n_tracks=80, n_noise=30), new)
+    og = oracle.OracleGeometry(geom)
+    pair = oracle.run(og, ev, last=0).stage(0)[0][0]  # the hits are spread about one mini-doublet's
+    m = int(ev.module[pair[0]])
+    rng = np.random.default_rng(n_upper)
+    add = {k: [getattr(ev, k)] for k in ("x", "y", "z", "module", "sensor", "sim")}
+    for sensor, n in ((0, 40), (1, n_upper)):
+        i = pair[sensor]
+        a = rng.uniform(-spread, spread, n)
+        add["x"].append(np.cos(a) * ev.x[i] - np.sin(a) * ev.y[i])
+        add["y"].append(np.sin(a) * ev.x[i] + np.cos(a) * ev.y[i])
+        add["z"].append(ev.z[i] + rng.uniform(-1e-3, 1e-3, n))
+        add["module"].append(np.full(n, m))
+        add["sensor"].append(np.full(n, sensor))
+        add["sim"].append(np.full(n, -1))
+    for k, v in add.items():
+        setattr(ev, k, np.concatenate(v).astype(v[0].dtype))
+    partners = np.bincount(oracle.run(og, ev, last=0).stage(0)[0][:, 0])
+    print(f"[gpu] module {m}: up to {partners.max()} partners of {n_upper}", flush=True)
+    assert (partners > 6).sum() > 25
+    cap = lst.lst_default_capacity(ev.n_hits, ev.n_seeds)
+    cap.md = cap.ls = cap.t3 = 400000
+    r = lst.run_event(lst.Geometry(geom), lst.upload_event(ev), cap=cap)
+    o = oracle.run(og, ev)
+    compare_event(r, o)
+    compare_tc(r, o)
+    r.close()
