@@ -731,26 +731,30 @@ __device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((
 // bound (so a window touches two, whatever u inv rounds to) and wrap round (the
 // exact test decides, so sharing a bin only costs a test).
 //
-// A module with a hit outside that range or a wide window (if one with more than
-// kMdWalk upper hits is among the bucket's), and every module of a bucket with more
-// hits than the lists hold, is listed again in a second pass, by direction
-// (md_bins), with the lists of such a bucket in the records of its upper hits, which
-// are read no more.  Modules with few hits, with one nearly on the beam line or far
-// out (where products may underflow or overflow) and with windows of more than about
-// a radian have every pair tested.
+// A module with a hit outside that range (or nearly on the beam line, where products
+// may underflow, or far out) or a wide window, or a bucket with more hits than the
+// lists hold, has every pair tested, and the fill tests a lower hit's again if it has
+// more than kMdKeep partners (they are kept in order).  That is too slow for
+// detectors of few, wide modules, so in launches with many hits a module
+// (CROWDED, kCrowdedHits):
+//  - modules with a hit outside the range of u (if one with more than kMdWalk upper
+//    hits is among the bucket's), and all of a bucket with more hits than the lists
+//    hold, are listed again in a second pass, by direction (md_bins), with the lists of
+//    such a bucket in the records of its upper hits, which are read no more; only those
+//    with few hits, with one near the beam line or far out and with windows of more
+//    than about a radian have every pair tested;
+//  - lower hits with more than kMdKeep partners in a module of more than kMdWalk upper
+//    hits have all of them written to a list in global memory (the segments' cache,
+//    not yet in use).
 //
-// A lower hit keeps up to kMdKeep partners, in order, for the fill; with more, in a
-// module of more than kMdWalk upper hits, all of them go to a list in global memory
-// (the segments' cache, not yet in use).
 // (Testing all pairs, 8.8M on a PU200 event for 138k MDs, took 25 + 27 us to
 // count and 24 + 14 us to fill for one event, 318 us for eight; the kernel is
 // bound by the chain of its steps in the densest bucket, hence few passes over
-// the hits.  Without the second listing and the lists of partners, 6 x 1,000 and 24 x
-// 1,000 hits a sensor on modules of a whole and of a quarter of the azimuth took
-// 2.21 and 6.47 ms here and 0.06 and 3.06 in the fill, now 0.23 and 0.77, 0.06 and
-// 0.32; a PU400 event, whose densest bucket has 8,500 hits, 0.60 ms, now 0.14; 3,000
-// hits a sensor on one module, each with five partners, 0.92 and 6.00, now 2.00 and
-// 1.10.)
+// the hits.  Crowded, 6 x 1,000 and 24 x 1,000 hits a sensor on modules of a whole and
+// of a quarter of the azimuth take 0.23 and 0.77 ms here and 0.06 and 0.32 in the fill,
+// else 2.21, 6.47, 0.06 and 3.06.  With 64 hits a module or fewer, PU400's 55
+// among them, the plain form is the faster one or close: 1 to 2 us on one event,
+// whose densest bucket's chain is longer with the other's checks.)
 // At most 80 scalar registers (72 and the reserved ones): with 80 and those a SIMD
 // held seven waves, so a CU three of these blocks instead of four, and eight PU50
 // events took 78 us instead of 71.
@@ -759,6 +763,7 @@ constexpr int kBucketMods = kFineKeys / 2;
 constexpr int kMdBins = 64;    // per module
 constexpr int kMdList = 8192;  // hits of a bucket that the lists can hold
 constexpr int kMdWalk = 64;    // upper hits that the fill tests again one after another
+constexpr long kCrowdedHits = 64;  // hits a module, of the launch's largest event
 static_assert((kMdBins & (kMdBins - 1)) == 0, "bins wrap round by a mask");
 
 // The module of the bucket's q-th lower hit (modules' lower hits before: lpre[0..kBucketMods]).
@@ -824,14 +829,16 @@ __device__ __forceinline__ void lower_prefix(const int *key0, int *lpre) {
   if (lane <= kBucketMods) lpre[lane] = x - n;
 }
 
-__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) void k_bucket_md(const Ws *__restrict__ wb, DevGeom g) {
+template <bool CROWDED>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) void k_bucket_md(const Ws *__restrict__ wb,
+                                                                                                DevGeom g) {
   __shared__ int s_cnt[kSortWaves][kFineKeys];
   __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1];
   __shared__ int s_head[kBucketMods * kMdBins];  // per (module, bin): its first upper (position in the bucket), -1: none
   __shared__ unsigned short s_next[kMdList];     // per hit of the bucket: the next upper of its bin
   __shared__ int s_ref[kBucketMods], s_nmd[kBucketMods];
-  // how a module is searched: 0 by u; 1 (a hit outside u's range, a wide window) by direction if one of
-  // them has more than kMdWalk upper hits (s_any), else all pairs; 2 or 3 all pairs
+  // how a module is searched: 0 by u; 1 (a hit outside u's range, a wide window) all pairs, or by
+  // direction (CROWDED, and one of them has more than kMdWalk upper hits: s_any); 2 or 3 all pairs
   __shared__ int s_odd[kBucketMods], s_any, s_more;
   __shared__ float4 s_mod[kBucketMods];          // per module: reference direction x, y, window in u, bins per unit of u
   __shared__ int s_x0[kBucketMods], s_x1[kBucketMods], s_y0[kBucketMods], s_y1[kBucketMods];
@@ -856,7 +863,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
     s_x1[t] = s_y1[t] = (int)0x80000000;
     s_odd[t] = s_nmd[t] = 0;
   }
-  if (t == 0) s_any = s_more = 0;
+  if (CROWDED && t == 0) s_any = s_more = 0;
   __syncthreads();
   for (int j = a + lane; j < b; j += 64) {
     const int f = tag_fine(gload(w.hcp, j).w);
@@ -892,13 +899,14 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
     const float4 h = gload(w.hcp, s_ref[lane]);
     const float d = gload(g.win, m0 + lane).x * 1.27f + 4e-6f;
     s_mod[lane] = make_float4(h.x, h.y, d, 0.47f / d);
+    if (!CROWDED && !(d < 0.25f)) s_odd[lane] = 1;
   }
   __syncthreads();
   // u of a hit of module m; false outside the range that the bins cover
   auto u_of = [&](const float4 &mod, const float4 &h, float *u) {
     const float dot = mod.x * h.x + mod.y * h.y, cr = mod.x * h.y - mod.y * h.x;
     *u = cr * frcp(dot);
-    return dot > 0.0f && fabsf(cr) <= 0.5f * dot;
+    return (CROWDED || (h.w >= 1e-3f && h.w <= 1e6f)) && dot > 0.0f && fabsf(cr) <= 0.5f * dot;
   };
   auto bin_of = [](float u, float inv) { return (int)floorf(u * inv) & (kMdBins - 1); };
   for (int r0 = a; r0 < b; r0 += 64) {
@@ -917,9 +925,11 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
       if (s_ref[m] >= 0) {  // the module has lower hits
         const float4 mod = s_mod[m];
         float u;
-        if (!(hr.w >= 1e-3f && hr.w <= 1e6f)) {
+        if (CROWDED && !(hr.w >= 1e-3f && hr.w <= 1e6f)) {
           atomicOr(&s_odd[m], 2);
-        } else if (!u_of(mod, hr, &u) || !(mod.z < 0.25f)) {
+        } else if (!CROWDED && !u_of(mod, hr, &u)) {
+          s_odd[m] = 1;
+        } else if (CROWDED && (!u_of(mod, hr, &u) || !(mod.z < 0.25f))) {
           atomicOr(&s_odd[m], 1);
           if (s_key0[2 * m + 2] - s_key0[2 * m + 1] > kMdWalk) s_any = 1;
         } else if (f & 1) {
@@ -942,7 +952,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
   }
   __syncthreads();
   const bool fits = L <= kMdList;
-  const bool again = !fits || __builtin_amdgcn_readfirstlane(s_any);
+  const bool again = CROWDED && (!fits || __builtin_amdgcn_readfirstlane(s_any));
   if (again) {  // (the whole block) modules that are listed by direction
     if (t < kBucketMods && s_ref[t] >= 0) {
       int mode = s_odd[t];
@@ -983,7 +993,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
     if (nup > 0) {
       const float4 hi = gload(w.hpos, p), win = gload(g.win, m0 + m);
       const ModInfo mi{gp(g.info)[m0 + m]};
-      if (!s_odd[m]) {
+      if ((CROWDED || fits) && !s_odd[m]) {
         const float4 mod = s_mod[m];
         float u;
         u_of(mod, hi, &u);
@@ -1010,13 +1020,13 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
           if (md_pass(hi, gload(w.hpos, up0 + j), win, mi)) r.take(j);
       }
     }
-    if (md_listed(r.n, nup)) s_more = 1;
+    if (CROWDED && md_listed(r.n, nup)) s_more = 1;
     gstore(reinterpret_cast<int4 *>(w.hcp), p, r.packed());
     if (r.n > 0) atomicAdd(&s_nmd[m], r.n);
   }
   __syncthreads();
   // the same with modules listed by direction, and the lists of the lower hits with many partners
-  if (again || __builtin_amdgcn_readfirstlane(s_more)) {  // (the whole block)
+  if (CROWDED && (again || __builtin_amdgcn_readfirstlane(s_more))) {  // (the whole block)
     for (int q0 = 0; q0 < n_lower; q0 += kSortThreads) {
       const int q = q0 + t;
       int m = 0, p = 0, up0 = 0, nup = 0, n = 0;
@@ -1126,6 +1136,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
 // offset of each of the bucket's lower hits is the MDs of the buckets before
 // (summed here) plus a scan over the lower hits before it.  Partners that the
 // search did not keep come from its list, or are searched again.
+template <bool CROWDED>
 __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__ wb, DevGeom g) {
   __shared__ int s_key0[kFineKeys + 1], s_lpre[kBucketMods + 1], s_red[kSortWaves];
   __shared__ int s_at[kBucketMods + 1];  // the modules' first MDs, from the bucket's first
@@ -1211,7 +1222,7 @@ __global__ __launch_bounds__(kSortThreads) void k_md_fill(const Ws *__restrict__
         const int j = (word >> (16 * (i & 1))) & 0xffff;
         put(pos + i, j, gload(w.hpos, up0 + j));
       }
-    } else if (md_listed(n, nup) && r.x >= 0 && keep == kMdKeep) {
+    } else if (CROWDED && md_listed(n, nup) && r.x >= 0 && keep == kMdKeep) {
       const auto list = gp(w.ls_cache) + r.x;
       for (int i = 0; i < n; ++i) {
         const int j = list[i];
@@ -4067,13 +4078,19 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
     });
   });
   // the bucket sort and a1: MD
+  const bool crowded = N > kCrowdedHits * M;
   // (with the seeds in further blocks)
   run([&] {
     const unsigned n_seed = (unsigned)std::min((S + kSortThreads - 1) / kSortThreads, 4096L);
-    k_bucket_md<<<dim3((unsigned)n_co + n_seed, B), kSortThreads, 0, st>>>(wb, g);
+    const dim3 d((unsigned)n_co + n_seed, B);
+    if (crowded) k_bucket_md<true><<<d, kSortThreads, 0, st>>>(wb, g);
+    else k_bucket_md<false><<<d, kSortThreads, 0, st>>>(wb, g);
   });
   for (int q = 0; q < 2; ++q) run([&] {});  // md_count, md_scan: with bucket_sort, md_fill
-  run([&] { k_md_fill<<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g); });
+  run([&] {
+    if (crowded) k_md_fill<true><<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g);
+    else k_md_fill<false><<<dim3((unsigned)n_co, B), kSortThreads, 0, st>>>(wb, g);
+  });
   // a2: LS
   run([&] {
     const int lg = ls_group_for(g.tiles, B, b.cap_md);
