@@ -42,17 +42,21 @@ lst_status fail(lst_status s, const std::string &msg) { return fail(s, msg.c_str
 constexpr size_t kAlign = 256;
 // Host memory that the chain writes an event's candidates to, in ints: about one
 // and a half times what PU50 to PU250 events take (36k to 180k ints with 133k to
-// 665k hits; 2k for 1,400 hits of a tiny one), at most 1 MiB and what its
-// capacities can fill.  A batch takes up to 8 MiB (eight PU250 events), with
-// smaller shares down to 0.6 of that; batches past it, batches of more than 64
-// events, and all while kResultsMax bytes are held by events not yet released, have
-// their results copied when they are read.
-constexpr long kRoomMax = 262144, kBatchRoomMax = 2097152;
+// 665k hits; 2k for 1,400 hits of a tiny one), at most what its capacities can fill
+// and an event's share of 4 MiB a batch, 1 MiB.  An event that is likely to need
+// more (PU200 in batches of eight), batches of more than 64 events, and all while
+// kResultsMax bytes are held by events not yet released, have their results copied
+// when they are read: written by the chain, the candidates of eight large events take
+// 95 us of its stream instead of 29 (4.5 MB over PCIe), which cost a saturated server
+// 5% (64 requests 10.5 -> 11.0 ms), where the copies run beside other streams' chains.
+constexpr long kRoomMax = 262144, kBatchRoomMax = 1048576;
 constexpr size_t kResultsMax = 64u << 20;
 constexpr int kRoomEvents = 64;
-static long tc_room(const lst::Ws &w, int ext) {
-  const long n = w.n_hits, need = std::min(n, 65536L) + std::max(n - 65536L, 0L) / 4 + 4L * w.n_seeds + 4096;
-  return (std::min(std::min(need, kRoomMax), (ext ? 26L : 16L) * w.cap_tc + 1) + 63) / 64 * 64;
+static long tc_room(const lst::Ws &w, int B, int ext) {
+  const long n = w.n_hits, fill = (ext ? 26L : 16L) * w.cap_tc + 1;
+  const long need = std::min(fill, std::min(n, 65536L) + std::max(n - 65536L, 0L) / 4 + 4L * w.n_seeds + 4096);
+  const long most = B > kRoomEvents ? 0 : std::min(kRoomMax, kBatchRoomMax / B);
+  return most < need * 6 / 10 ? 0 : (std::min(need, most) + 63) / 64 * 64;  // whole 256-byte lines
 }
 constexpr size_t kStageMax = 8u << 20;  // largest result copied through pinned memory: the pool's largest class
 constexpr int kTupleW[7] = {2, 4, 6, 10, 1, 7, 11};
@@ -591,16 +595,15 @@ static void server_release_batch(lst_server_s *s, lst_batch_s *b);
 static void batch_results(lst_batch_s *b) {
   const int ext = b->geom->g.ext;
   long sum = 0;
-  for (int i = 0; i < b->B; ++i) sum += tc_room(b->h_ws[i], ext);
-  const double share = sum > kBatchRoomMax ? (double)kBatchRoomMax / (double)sum : 1.0;
-  if (b->B <= kRoomEvents && share >= 0.6) {
-    b->h_tc_bytes = sizeof(int) * (size_t)std::min(sum, kBatchRoomMax);
+  for (int i = 0; i < b->B; ++i) sum += tc_room(b->h_ws[i], b->B, ext);
+  if (sum > 0) {
+    b->h_tc_bytes = sizeof(int) * (size_t)sum;
     b->h_tc = static_cast<int *>(results_get(b->h_tc_bytes));
   }
   long at = 0;
   for (int i = 0; i < b->B; ++i) {
     lst::Ws &w = b->h_ws[i];
-    const long room = b->h_tc ? (long)(share * (double)tc_room(w, ext)) / 64 * 64 : 0;  // whole 256-byte lines
+    const long room = b->h_tc ? tc_room(w, b->B, ext) : 0;
     w.h_ctr = b->h_ctr + (size_t)i * lst::C_COUNT;
     w.h_tc = room > 0 ? b->h_tc + at : nullptr;
     w.h_tc_cap = (int)room;

@@ -46,7 +46,7 @@ def test_a_failed_event_outlives_its_stream(fake):
 
 
 def test_host_memory_of_held_events(fake):
-    """Sized by the event, at most 64 MiB for all that are held, and room for eight PU200 events."""
+    """Sized by the event, at most 64 MiB for all that are held, room for four PU200 events, none for more."""
     run(fake, "room")
 
 
