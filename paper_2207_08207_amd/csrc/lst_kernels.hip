@@ -899,7 +899,8 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) 
     const float4 h = gload(w.hcp, s_ref[lane]);
     const float d = gload(g.win, m0 + lane).x * 1.27f + 4e-6f;
     s_mod[lane] = make_float4(h.x, h.y, d, 0.47f / d);
-    if (!CROWDED && !(d < 0.25f)) s_odd[lane] = 1;
+    const float r = sqrtf(h.x * h.x + h.y * h.y);
+    if (!CROWDED && !(r >= 1e-3f && r <= 1e6f && d < 0.25f)) s_odd[lane] = 1;
   }
   __syncthreads();
   // u of a hit of module m; false outside the range that the bins cover
@@ -3003,7 +3004,7 @@ __device__ __forceinline__ void pt_copy(const Ws &w, const DevGeom &g, int q, in
 // the LDS list holds (tile pass_list <= kPassList) an ordered scan over all objects
 // is taken instead.  (Searching again for the seven made the fill 193 us.  With one
 // wave to each 64 consecutive seeds' tasks the fill of a PU200 event with nothing
-// cached took 1.53 ms, now 0.22, and with 16 triplets cached 117 us, now 41; that
+// cached took 1.53 ms, now 0.29, and with 16 triplets cached 117 us, now 50; that
 // of a PU400 event 8.7, now 8.1, which is one seed's scan.)  More than max_slices marked bins are searched bin by bin.
 // Tasks are counted in 16 lines by seed, since additions to one run one after
 // another (a PU200 event's count took 197 us with 17,800 tasks on one counter, 72
@@ -4152,9 +4153,11 @@ void enqueue_chain(const DevGeom &g, Ws *wb, int B, const Ws &b, hipStream_t st,
   run([&] {});  // pt3_scan
   run([&] {
     if (!seeds) return;
-    // the tasks' blocks: whole rounds of the shards, about the chip's for the launch
+    // the tasks' blocks: whole rounds of the shards, three a CU for the launch (with eight a
+    // PU200 event with nothing cached takes 0.21 ms, but eight PU10 events, without a task,
+    // 0.5 us longer)
     const unsigned nc = gridwt((S + kPtSeeds - 1) / kPtSeeds).x;
-    const unsigned n_again = (unsigned)((std::min(2 * S, std::max(2048L / B, 64L)) + kTaskShards - 1) / kTaskShards) * kTaskShards;
+    const unsigned n_again = (unsigned)((std::min(2 * S, std::max(768L / B, 64L)) + kTaskShards - 1) / kTaskShards) * kTaskShards;
     k_pt_binned<true><<<dim3(2 * nc + n_again, B), tb, 0, st>>>(wb, g, (int)nc);
   });
   run([&] {});  // pt5_scan
