@@ -135,9 +135,9 @@ __global__ void k_scan_reduce(const Ws *__restrict__ wb) {
 }
 
 // Each tile adds the tile sums before it (at most a few hundred) to its own
-// exclusive scan; the tile holding index n writes out[n] and the total.  (Two launches per scan instead of a third,
-// single-block pass over the tile sums.)  Both passes stride over the tiles,
-// so the grid need not cover the capacity.
+// exclusive scan; the tile holding index n writes out[n] and the total.  (Two
+// launches instead of a third, single-block pass over the tile sums.)  Both passes
+// stride over the tiles, so the grid need not cover the capacity.
 __global__ void k_scan_apply(const Ws *__restrict__ wb) {
   __shared__ int s_wave[kWaves], s_red[kWaves];
   const Ws &w = wb[blockIdx.y];
@@ -752,9 +752,10 @@ __device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((
 // bound by the chain of its steps in the densest bucket, hence few passes over
 // the hits.  Crowded, 6 x 1,000 and 24 x 1,000 hits a sensor on modules of a whole and
 // of a quarter of the azimuth take 0.23 and 0.77 ms here and 0.06 and 0.32 in the fill,
-// else 2.21, 6.47, 0.06 and 3.06.  With 64 hits a module or fewer, PU400's 55
-// among them, the plain form is the faster one or close: 1 to 2 us on one event,
-// whose densest bucket's chain is longer with the other's checks.)
+// else 2.21, 6.47, 0.06 and 3.06.  The line, 48 hits a module: with 55, PU400, the
+// densest bucket has 8,500 hits, and the crowded form takes 0.14 ms instead of 0.60;
+// below about 50 every bucket's hits fit the lists, and its checks only lengthen the
+// densest bucket's chain, by 1 to 2 us.)
 // At most 80 scalar registers (72 and the reserved ones): with 80 and those a SIMD
 // held seven waves, so a CU three of these blocks instead of four, and eight PU50
 // events took 78 us instead of 71.
@@ -763,7 +764,7 @@ constexpr int kBucketMods = kFineKeys / 2;
 constexpr int kMdBins = 64;    // per module
 constexpr int kMdList = 8192;  // hits of a bucket that the lists can hold
 constexpr int kMdWalk = 64;    // upper hits that the fill tests again one after another
-constexpr long kCrowdedHits = 64;  // hits a module, of the launch's largest event
+constexpr long kCrowdedHits = 48;  // hits a module, of the launch's largest event
 static_assert((kMdBins & (kMdBins - 1)) == 0, "bins wrap round by a mask");
 
 // The module of the bucket's q-th lower hit (modules' lower hits before: lpre[0..kBucketMods]).

@@ -115,7 +115,7 @@ def test_hits_near_the_beam_line_and_far_out(lst, barrel, obarrel):
 
 
 # lower hits with more than six partners among many upper hits.  On 5,736 modules all are tested again;
-# on 24, crowded (more than 64 hits a module): lists in any order, ranked by the fill, and in order from a
+# on 24, crowded (more than 48 hits a module): lists in any order, ranked by the fill, and in order from a
 # pass over the module (more partners than twice the root of its upper hits)
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n_upper,spread", [(300, 0.05), (200, 0.001), (64, 0.02), (63, 0.004)])
@@ -141,7 +141,7 @@ def test_lists_of_partners(n_upper, spread, wide, lst, barrel):
     partners = np.bincount(oracle.run(og, ev, last=0).stage(0)[0][:, 0])
     print(f"[gpu] module {m}: up to {partners.max()} partners of {n_upper}", flush=True)
     assert (partners > 6).sum() > 25
-    assert (ev.n_hits > 64 * geom.n_modules) == wide
+    assert (ev.n_hits > 48 * geom.n_modules) == wide
     cap = lst.lst_default_capacity(ev.n_hits, ev.n_seeds)
     cap.md = cap.ls = cap.t3 = 400000
     r = lst.run_event(lst.Geometry(geom), lst.upload_event(ev), cap=cap)
